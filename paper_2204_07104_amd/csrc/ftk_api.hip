@@ -402,12 +402,12 @@ int launch_grad_mfma16(ftk_ctx* c, float lambda_A, float lr_A, int pass = -1) {
     }
 }
 
-template <int N, int P, int WAVES, bool X4, bool ROWS, int MODE = kSyncPass>
-int launch_tiled_npwxr(ftk_ctx* c, const TiledArgs& g) {
-    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(grad_tiled_kernel<N, P, WAVES, X4, ROWS, MODE>), c->max_lds)) return rc;
+template <int N, int P, int WAVES, bool ROWS, int MODE = kSyncPass>
+int launch_tiled_npwr(ftk_ctx* c, const TiledArgs& g) {
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(grad_tiled_kernel<N, P, WAVES, ROWS, MODE>), c->max_lds)) return rc;
     if (c->prepare_only) return FTK_OK;
     Bracket t(c, FTK_K_GRAD);
-    hipLaunchKernelGGL((grad_tiled_kernel<N, P, WAVES, X4, ROWS, MODE>), dim3(c->mfma_grid), dim3(WAVES * 64), c->tiled_lds_bytes,
+    hipLaunchKernelGGL((grad_tiled_kernel<N, P, WAVES, ROWS, MODE>), dim3(c->mfma_grid), dim3(WAVES * 64), c->tiled_lds_bytes,
                        c->stream, g);
     FTK_HIP(c, hipGetLastError());
     return FTK_OK;
@@ -422,19 +422,17 @@ template <int N, int P, int WAVES>
 int launch_tiled_npw(ftk_ctx* c, const TiledArgs& g, int pass) {
     if (pass == kFactorPhase || pass == kCorePhase) {
         if (!tiled_modewise_ok(c)) return fail(c, FTK_EUNSUPPORTED, "the mode-by-mode order is not built for the rows form of the tiled kernel");
-        if (c->tiled_x4)
-            return pass == kFactorPhase ? launch_tiled_npwxr<N, P, WAVES, true, false, kFactorPhase>(c, g)
-                                        : launch_tiled_npwxr<N, P, WAVES, true, false, kCorePhase>(c, g);
-        return pass == kFactorPhase ? launch_tiled_npwxr<N, P, WAVES, false, false, kFactorPhase>(c, g)
-                                    : launch_tiled_npwxr<N, P, WAVES, false, false, kCorePhase>(c, g);
+        return pass == kFactorPhase ? launch_tiled_npwr<N, P, WAVES, false, kFactorPhase>(c, g)
+                                    : launch_tiled_npwr<N, P, WAVES, false, kCorePhase>(c, g);
     }
-    // the rows form is built for rows fetched 16 bytes per lane (every J_n a multiple of four) only
     if (c->rows) {
+        // list entries are written 16 bytes apart: every J_n a multiple of four
+        if (!c->tiled_x4) return fail(c, FTK_EUNSUPPORTED, "rows needs every J_n to be a multiple of 4");
         // the row owners' table (up to 64 KB, dynamic) sits next to 4 KB of static LDS
         if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(rows_apply_kernel), 65536)) return rc;
-        return c->tiled_x4 ? launch_tiled_npwxr<N, P, WAVES, true, true>(c, g) : fail(c, FTK_EUNSUPPORTED, "rows needs every J_n to be a multiple of 4");
+        return launch_tiled_npwr<N, P, WAVES, true>(c, g);
     }
-    return c->tiled_x4 ? launch_tiled_npwxr<N, P, WAVES, true, false>(c, g) : launch_tiled_npwxr<N, P, WAVES, false, false>(c, g);
+    return launch_tiled_npwr<N, P, WAVES, false>(c, g);
 }
 
 template <int N>
@@ -576,7 +574,7 @@ template <int N, int P, bool X4>
 int launch_errors_tiled_npx(ftk_ctx* c, const Coo& coo, long long nnz) {
     const long long groups = (nnz + 63) / 64;
     const int grid = blocks_for(groups, 4, c->num_cu * 8);
-    const size_t lds = 4 * ((size_t)N * 256 * P * P + 4 * (size_t)tiled_wave_scratch(N, P));
+    const size_t lds = 4 * ((size_t)N * 256 * P * P + 4 * (size_t)tiled_errors_scratch(N));
     TiledModeBytes mode_bytes = {};
     for (int n = 0; n < N; ++n) mode_bytes.v[n] = (unsigned int)(c->dims[n] * c->L.J[n] * 4);
     // the kernel also has 64 bytes of static LDS

@@ -1,21 +1,26 @@
 // Matrix-core gradient and evaluation kernels for general shapes: any order N <= 8 (N <= 10 at P = 1), any J_n <= 16 P,
 // any R <= 16 P with P in {1, 2, 4} (ranks are zero-padded to 16 P).  Same method as the J = R = 16
 // kernel (see ftk_kernels_mfma16.hpp for the operand layouts), with every 16 P x 16 P contraction
-// cut into P x P blocks of v_mfma_f32_16x16x4_f32 and the core factors B^(n) (and their
-// transposes) held in LDS instead of registers:
+// cut into P x P blocks of 16 x 16 and the core factors B^(n) held in LDS instead of registers:
 //
 //   projections    C^T[rb] [r x sample]   = sum_jb  B^T[rb][jb] . a^T[jb]
 //   A gradient     -e GS[jb] [sample x j] = sum_rb  (-e W)[rb] . B^T[rb][jb]
 //   core gradient  GB[jb][rb] [j x r]    += a^T[jb] . (-e W)[rb]            (contracts the tile's samples)
 //   top rows       TOP[jb] [row x j]     += ONEHOT [row x sample] . GRAD[jb] [sample x j]
 //
+// Above rank 16 the contractions run on the bf16 matrix instructions with operands cut into three parts (ftk_split.hpp),
+// which leaves the vector ALU to everything else; what bounds the pass is then the latency of its LDS trips and product
+// chains with two waves per SIMD (one at P = 4), and the float atomics (about 20e9 64-byte requests per second for the
+// whole chip, whatever the address).  J = R = 32, 4e6 samples per step, frequent rows: 872 us with fp32 instructions,
+// 803 us now; J_n <= 30, R = 22, order 4, 2.5e5 samples: 147 and 136 us; J = R = 64, 1e6 samples: 773 and 760 us.  The error
+// of the parameters against 64 bits is 0.6 to 1.0 times what it was.  At P = 1 the fp32 instructions stay: a tile has four of
+// them per product, and the parts of up to ten modes do not fit the registers (order 10, J = R = 4: 679 us against 537).
+//
 // One wave owns 64 sampled entries at a time (four tiles of 16), draws their positions with Philox
 // in registers and parks the records in a private LDS buffer (two of them, used in turn, so the
 // rows of a group's first tile can be requested while the group before it is still being worked
-// on).  The factor rows of a tile are requested one tile ahead.  Where every J_n is a multiple of
-// four (X4) a lane fetches 16 bytes of its sample's row, which is the operand layout of the
-// projections, and the other layout comes from an LDS transpose; otherwise lanes fetch single
-// floats in the layout of the gradient and the transpose runs the other way.
+// on).  The factor rows of a tile are requested one tile ahead, 16 bytes per lane: the operand layout of the
+// projections.  The other layout comes out of LDS.
 // Factor-row gradients take the same three routes as in the J = R = 16 kernel: rows 0..15 of a
 // mode through the one-hot product, rows [16, K_n) into a table per workgroup, all other rows
 // through float atomics.  The atomic is issued by every lane for every element, without a test: an
@@ -48,6 +53,7 @@
 #include <stdint.h>
 
 #include "ftk_kernels_mfma16.hpp"
+#include "ftk_split.hpp"
 
 namespace ftk {
 
@@ -106,6 +112,7 @@ __host__ __device__ constexpr int rows_entry_words(int J) { return (J + 1 + 3) &
 
 // one parked group of 64 samples, in words.  Evaluation pass: [order][64] row numbers | [64] values.
 __host__ __device__ constexpr int tiled_park_words(int order) { return (order + 1) * 64; }
+__host__ __device__ constexpr int tiled_errors_scratch(int order) { return 2 * tiled_park_words(order) + kTransposeFloats; }
 // Gradient pass: [order][64] byte offsets of the rows inside their modes (for the gathers) | [order][64] route words
 // (where the row's gradient goes, decided once per sample when the group is parked) | [64] values
 __host__ __device__ constexpr int tiled_grad_park_words(int order) { return (2 * order + 1) * 64; }
@@ -117,18 +124,25 @@ __host__ __device__ constexpr int tiled_grad_park_words(int order) { return (2 *
 // Every word is a multiple of four (the atomic's address has to be aligned even where it is out of range) and below
 // 0xc0000000 (the marker 2^30 of a padded column is added to it and must not wrap).
 constexpr unsigned int kRouteTable = 0x40000000u, kRouteOneHot = 0x80000000u, kRouteNone = kRouteOneHot | (0xffu << 2);
+constexpr unsigned int kRowSlack = 64;   // bytes behind a mode's last row that may be read (padding of the parameter allocation)
 constexpr unsigned int kRouteList = 0xa0000000u, kRouteListMask = 0xe0000000u;   // list areas stay below 2^29 bytes
 // ROWS: behind the ordinary layout, LDS holds three arrays of n_buckets words (rounded up to a multiple of
 // four): list counters | first words | capacities; then per wave and parked group one word, "a list was full"
 __host__ __device__ constexpr size_t tiled_rows_lds_words(int order, int waves, int n_buckets) {
     return (size_t)3 * ((n_buckets + 3) & ~3) + (size_t)waves * 2;
 }
-// per wave: two parked groups, the transpose buffer, and 4 x 16 P words nobody reads (see `sink`)
+// Core factors in LDS: the three bf16 parts of every 16 x 16 block of the zero-padded B^(n), block (n, part, jb, rb) at
+// ((3 n + part) P + jb) P + rb (see ftk_split.hpp): read straight they are operands of the A gradient, transposed of the
+// projections.
+// (P = 1: the fp32 values twice, in the operand order of both products, see operand_slot)
+__host__ __device__ constexpr int tiled_core_bytes(int order, int P) { return P == 1 ? order * 2048 : 3 * order * P * P * kSplitBlockBytes; }
+// per wave, in words: two parked groups, three blocks in which tiles change their layout, and (P <= 2) 4 x 16 P words
+// nobody reads (see `sink`)
 __host__ __device__ constexpr int tiled_wave_scratch(int order, int P) {
-    return 2 * tiled_grad_park_words(order) + kTransposeFloats + 64 * P;
+    return 2 * tiled_grad_park_words(order) + 3 * kSplitBlockBytes / 4 + (P < 4 ? 64 * P : 0);
 }
 __host__ __device__ constexpr size_t tiled_lds_floats(int order, int P, int waves, int H) {
-    return (size_t)2 * order * 256 * P * P + (size_t)H * 16 * P + (size_t)waves * tiled_wave_scratch(order, P);
+    return (size_t)tiled_core_bytes(order, P) / 4 + (size_t)H * 16 * P + (size_t)waves * tiled_wave_scratch(order, P);
 }
 
 // MODE (see process_group in ftk_kernels_mfma16.hpp): kSyncPass serves the synchronous and the fused in-place step
@@ -137,7 +151,7 @@ __host__ __device__ constexpr size_t tiled_lds_floats(int order, int P, int wave
 // before it left them, adds the row's change to A (scatter as in the in-place step) and advances the samples'
 // projections of that mode by the change, c^(n) += delta B^(n) (P x P more products); the core phase takes only the core
 // gradient, at the rows the factor phase left.
-template <int N, int P, int WAVES, bool X4, bool ROWS, int MODE = kSyncPass>
+template <int N, int P, int WAVES, bool ROWS, int MODE = kSyncPass>
 __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     static_assert(MODE == kSyncPass || ((MODE == kFactorPhase || MODE == kCorePhase) && !ROWS), "the passes of the printed order keep no lists");
     extern __shared__ float lds[];
@@ -150,15 +164,17 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     constexpr bool LDS_TABLE = P < 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g4 = lane >> 4;
-    float* Bl = lds;                                 // B^(n) (zero padded) as operands of the projections, see operand_slot
-    float* Bt = Bl + N * D * D;                      // its transpose as operands of the A gradient
-    float* hot = Bt + N * D * D;                     // [H][D]
+    lds_char* core = (lds_char*)lds;                 // B^(n), see tiled_core_bytes
+    float* hot = lds + tiled_core_bytes(N, P) / 4;   // [H][D]
     float* wave_lds = hot + (size_t)g.H * D + wave * tiled_wave_scratch(N, P);
-    // two parked groups (see tiled_grad_park_words); tbuf [16][20]
-    float* tbuf = wave_lds + 2 * tiled_grad_park_words(N);
+    // two parked groups (see tiled_grad_park_words), then the three blocks of `turn`
+    lds_char* turn = (lds_char*)(wave_lds + 2 * tiled_grad_park_words(N));
+    // where this lane's part of a block is: straight, and as the address it names for a transposed read
+    const int straight = split_slot(c, g4), transposed = split_slot(4 * g4 + (c >> 2), c & 3);
+    const SplitConst sc = split_const();
     // Table updates are issued for every element; those of samples that take another route aim at a
     // row of their own that nobody reads (one per 16-lane group, so they never collide).
-    float* sink = tbuf + kTransposeFloats;
+    float* sink = wave_lds + 2 * tiled_grad_park_words(N) + 3 * kSplitBlockBytes / 4;
     const unsigned int sink_addr = lds_address(sink + g4 * D), hot_addr = lds_address(hot);
     const unsigned int sink_rel = sink_addr - hot_addr;          // beyond every row of the table
     const unsigned int top_key = kRouteOneHot | ((unsigned int)c << 2);   // the route word of row c of the one-hot product
@@ -166,16 +182,28 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     // checked by the host) or to itself it stays beyond the end of the buffer as an unsigned offset.
     constexpr unsigned int kDropped = 0x40000000u;
 
-    for (int q = tid; q < N * D * D; q += THREADS) {
-        const int n = q / (D * D), rem = q - n * D * D, j = rem / D, r = rem - j * D;
-        const float b = (j < g.J[n] && r < g.R) ? g.B[g.B_off[n] + j * g.R + r] : 0.0f;
-        Bl[operand_slot<P>(n, j, r)] = b;
-        // the factor every row gradient carries (1, or -lr_A in in-place mode) rides in the operand of the A-gradient
-        // products, the only place Bt is used: -e GS comes out of the matrix cores already scaled
-        Bt[operand_slot<P>(n, r, j)] = g.scale * b;
+    float* Bl = lds;                                 // P = 1: B^(n) (zero padded) as operands of the projections, see operand_slot
+    float* Bt = Bl + N * D * D;                      // and its transpose as operands of the A gradient
+    float* tbuf = reinterpret_cast<float*>(wave_lds + 2 * tiled_grad_park_words(N));   // P = 1: [16][20], in the place of `turn`
+    for (int q = tid; q < N * D * D / 4; q += THREADS) {
+        const int n = q / (D * D / 4), rem = q - n * (D * D / 4), j = rem / (D / 4), r = 4 * (rem - j * (D / 4));
+        floatx4 b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = (j < g.J[n] && r + i < g.R) ? g.B[g.B_off[n] + j * g.R + r + i] : 0.0f;
+        if constexpr (P == 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                Bl[operand_slot<P>(n, j, r + i)] = b[i];
+                Bt[operand_slot<P>(n, r + i, j)] = b[i];
+            }
+            continue;
+        }
+        store_block(core + ((3 * n * P + (j >> 4)) * P + (r >> 4)) * kSplitBlockBytes + split_slot(j & 15, (r & 15) >> 2),
+                    P * P * kSplitBlockBytes, split(b, sc));
     }
     for (int q = tid; q < g.H * D; q += THREADS) hot[q] = 0.0f;
-    for (int q = lane; q < 4 * D; q += 64) sink[q] = __builtin_inff();
+    if constexpr (LDS_TABLE)
+        for (int q = lane; q < 4 * D; q += 64) sink[q] = __builtin_inff();
     // ROWS: list counters, bucket info and the parked entry words behind everything else
     const int nb4 = (g.n_buckets + 3) & ~3;
     unsigned int* list_count = reinterpret_cast<unsigned int*>(hot + (size_t)g.H * D + WAVES * tiled_wave_scratch(N, P));
@@ -206,7 +234,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     __amdgpu_buffer_rsrc_t rsrc_A[N], rsrc_dA[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.mode_bytes[n]);
+        rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.mode_bytes[n] + kRowSlack);
         rsrc_dA[n] = make_rsrc(g.dA + g.A_off[n], LDS_TABLE ? g.mode_bytes[n] : g.dA_bytes[n]);
     }
     // ROWS: this workgroup's list area (the host keeps list_words below 2^27, so byte offsets stay below 2^29)
@@ -214,7 +242,6 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
         make_rsrc(ROWS ? (const void*)(g.lists + (size_t)blockIdx.x * g.list_words) : (const void*)g.A, ROWS ? g.list_words * 4u : 0u);
 
     const long long M = g.M;
-    const float lambda_scaled = g.lambda_A * g.scale;
     // Every wave takes a contiguous share of Psi made of whole tiles: the launch's ceil(M / 16) tiles go evenly to the
     // workgroups (the host has done that division), a workgroup's tiles evenly to its four SIMDs, so that the work
     // differs by one tile at most, where whole groups of 64 dealt round-robin leave up to four tiles between the waves.
@@ -288,7 +315,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             const int row = (int)flat[n];
-            in_mode[n] = act ? (unsigned int)(row * g.J[n] * 4) : g.mode_bytes[n];
+            in_mode[n] = act ? (unsigned int)(row * g.J[n] * 4) : g.mode_bytes[n] + kRowSlack;
             if (!act)
                 route[n] = kRouteNone;
             else if (list_word[n] != 0u)
@@ -329,40 +356,72 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
         }
         park[2 * N * 64 + slot] = act ? __uint_as_float(flat[N]) : 0.0f;
     };
-    // Request the factor rows of tile `sub` of a parked group whose first sample is number `first`.
-    //   X4: rows[n][jb] = components 16 jb + 4g .. +3 of the row of sample c           (layout X)
-    //  !X4: rows[n][jb][v] = component 16 jb + c of the row of sample 4g + v            (layout Y)
-    // Components past J_n and samples past the end of Psi read as zero (out-of-range offset).
+    // Request the factor rows of tile `sub` of a parked group: rows[n][jb] = components 16 jb + 4g .. +3 of the row of
+    // sample c.  Columns in blocks of four past J_n and samples past the end of Psi read as zero (out-of-range offset).
+    // Where J_n is no multiple of four the last block runs into the row behind (16-byte loads of a buffer need 4-byte
+    // alignment only; behind a mode's last row there are kRowSlack bytes of padding): those columns meet rows of B^(n)
+    // that are zero, and what they bring about in padded columns of sums is never read.
     auto gather_rows = [&](const float* park, int sub, floatx4 (&rows)[N][P]) {
         const int* in_mode = reinterpret_cast<const int*>(park);   // byte offsets of the rows; the end of the mode for no sample
-        if constexpr (X4) {
 #pragma unroll
-            for (int n = 0; n < N; ++n) {
-                const int row_off = in_mode[n * 64 + sub * 16 + c];
+        for (int n = 0; n < N; ++n) {
+            const int row_off = in_mode[n * 64 + sub * 16 + c];
 #pragma unroll
-                for (int jb = 0; jb < P; ++jb) {
-                    const int col = 16 * jb + 4 * g4;
-                    const int off = col < g.J[n] ? row_off + col * 4 : (int)g.mode_bytes[n];
-                    rows[n][jb] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], off, 0, 0));
-                }
-            }
-        } else {
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                const int4 r = *reinterpret_cast<const int4*>(in_mode + n * 64 + sub * 16 + 4 * g4);
-                const int rr[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-                for (int jb = 0; jb < P; ++jb) {
-                    const int col = 16 * jb + c;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int off = col < g.J[n] ? rr[v] + col * 4 : (int)g.mode_bytes[n];
-                        rows[n][jb][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc_A[n], off, 0, 0));
-                    }
-                }
+            for (int jb = 0; jb < P; ++jb) {
+                const int col = 16 * jb + 4 * g4;
+                const int off = col < g.J[n] ? row_off + col * 4 : (int)(g.mode_bytes[n] + kRowSlack);
+                rows[n][jb] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], off, 0, 0));
             }
         }
     };
+
+    // the all-one diagonal as a bf16 operand: column c of rows 4g .. 4g+3
+    shortx4 diagonal;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) diagonal[i] = 4 * g4 + i == c ? (short)0x3f80 : (short)0;
+    const bf16x8 diagonal2 = pair_up(diagonal, diagonal), diagonal_high = pair_up(shortx4{0, 0, 0, 0}, diagonal);
+    // block `half` of an operand of two blocks in the other layout: lane (c, g) puts in four values of row c and gets out
+    // four of column c
+    auto turn_in = [&](const bf16x8 (&x)[3], int half) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) store_part(turn + straight + q * kSplitBlockBytes, half == 0 ? low_half(x[q]) : high_half(x[q]));
+        lds_wave_sync();
+    };
+    auto turn_block = [&](const bf16x8 (&x)[3], int half) {
+        turn_in(x, half);
+        const Split y = transposed_block(turn + transposed, kSplitBlockBytes);
+        lds_wave_sync();
+        return y;
+    };
+    auto turn_pairs = [&](const bf16x8 (&x)[3], int half) {
+        turn_in(x, half);
+        const SplitPairs y = transposed_pairs(turn + transposed, kSplitBlockBytes);
+        lds_wave_sync();
+        return y;
+    };
+    auto core_block = [&](int n, int jb, int rb) { return core + ((3 * n * P + jb) * P + rb) * kSplitBlockBytes; };
+    // Operands of one step of a P x P grid of products: part `part` (0 h, 1 m, 2 l) of two neighbouring blocks of the
+    // contracted index (blocks 2 kc, 2 kc + 1), for all P blocks of the other one.  For the projections the contracted index
+    // is j, read transposed; for the A gradient it is r, read straight.
+    auto project_operands = [&](int n, int part, int kc, bf16x8 (&op)[P]) {
+#pragma unroll
+        for (int rb = 0; rb < P; ++rb)
+            op[rb] = pair_up(lds_transposed(core_block(n, 2 * kc, rb) + part * (P * P * kSplitBlockBytes) + transposed),
+                             lds_transposed(core_block(n, 2 * kc + 1, rb) + part * (P * P * kSplitBlockBytes) + transposed));
+    };
+    auto gradient_operands = [&](int n, int part, int kc, bf16x8 (&op)[P]) {
+#pragma unroll
+        for (int jb = 0; jb < P; ++jb)
+            op[jb] = pair_up(lds_straight(core_block(n, jb, 2 * kc) + part * (P * P * kSplitBlockBytes) + straight),
+                             lds_straight(core_block(n, jb, 2 * kc + 1) + part * (P * P * kSplitBlockBytes) + straight));
+    };
+    // Steps of one grid run over the parts l, m, h of the core factor (small terms first) and the pairs of blocks; their
+    // operands are read kAhead steps before the products that use them (the barrier keeps LDS reads where they stand).
+    // A tile's core gradient is summed from zero and then added (see ftk_split.hpp) -- but at P = 4 the 192 sums live in
+    // the half of the register file that the vector ALU does not reach, and go on in the matrix instructions.
+    constexpr bool kFreshSums = P == 2;
+    constexpr int KC = P > 1 ? P / 2 : 1, kSteps = 3 * KC, kAhead = P == 2 ? 2 : 1;
+    auto hold_reads = [&]() { __builtin_amdgcn_sched_barrier(0x6); };
 
     uint4 rec[W4];
     int group = 0;
@@ -388,10 +447,10 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
 
 #pragma unroll 1
         for (int sub = 0; sub < tiles; ++sub) {
-            // Request the next tile's rows (past the last group every lane is past the end of Psi and
-            // nothing is read).  X4: into the registers of this tile's rows as soon as the projections
-            // have consumed them; otherwise those registers stay in use as the gradient's layout, and
-            // the request goes out at the top of the tile into registers of its own.
+            // Request the next tile's rows (past the last group every lane is past the end of Psi and nothing is read).
+            // P = 1: into registers of their own, early.  Above, where the registers are taken: into those of this tile's
+            // rows, once the last mode's gradients have begun; every mode's rows are cut into parts twice (kept parts instead
+            // cost 50 spilled registers at P = 2: 1 010 us against 803).
             auto request_next = [&](floatx4 (&rows)[N][P]) {
                 if (sub < 3) {
                     gather_rows(park, sub + 1, rows);
@@ -404,84 +463,54 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     gather_rows(park_next, 0, rows);
                 }
             };
-            floatx4 nxt[X4 ? 1 : N][X4 ? 1 : P];
-            if constexpr (!X4) request_next(nxt);
+            floatx4 nxt[P == 1 ? N : 1][P];
+            if constexpr (P == 1) request_next(nxt);
 
             const float x = sval[sub * 16 + c];
-            // both layouts of the tile's rows: aX[k] = component 16 jb + 4g + k of sample c (only used
-            // by the projections), aY[n][jb][v] = component 16 jb + c of sample 4g + v
-            float aY[N][P][4];
             // projections (layout X): s[n][rb][v] = c^(n)_{r = 16 rb + 4g + v} of sample c
-            // The core-factor operands of a block of products are read from LDS one block ahead of the
-            // products that use them (the scheduling barrier keeps the reads where they are written).
-            // (Not for P = 4, where the registers are all taken: there each block reads its own.)
-            constexpr bool AHEAD = P < 4;
             floatx4 s[N][P];
-            float4 bop[P];
-            if constexpr (AHEAD) {
 #pragma unroll
-                for (int rb = 0; rb < P; ++rb) bop[rb] = *reinterpret_cast<const float4*>(Bl + rb * 256 + lane * 4);
-            }
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
+            for (int n = 0; n < N; ++n)
 #pragma unroll
                 for (int rb = 0; rb < P; ++rb) s[n][rb] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            float aY[P == 1 ? N : 1][4];   // P = 1: the rows in layout Y, component c of samples 4g .. 4g+3
+            if constexpr (P == 1) {
+                float4 ahead = *reinterpret_cast<const float4*>(Bl + lane * 4);
 #pragma unroll
-                for (int jb = 0; jb < P; ++jb) {
-                    float4 bcur[P];
-                    if constexpr (AHEAD) {
+                for (int n = 0; n < N; ++n) {
+                    const float4 bcur = ahead;
+                    if (n + 1 < N) ahead = *reinterpret_cast<const float4*>(Bl + (n + 1) * 256 + lane * 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    *reinterpret_cast<float4*>(tbuf + c * 20 + 4 * g4) = make_float4(cur[n][0][0], cur[n][0][1], cur[n][0][2], cur[n][0][3]);
+                    lds_wave_sync();
 #pragma unroll
-                        for (int rb = 0; rb < P; ++rb) bcur[rb] = bop[rb];
-                        if (n * P + jb + 1 < N * P) {
+                    for (int v = 0; v < 4; ++v) aY[n][v] = tbuf[(4 * g4 + v) * 20 + c];
+                    lds_wave_sync();
+                    const float bk[4] = {bcur.x, bcur.y, bcur.z, bcur.w};
 #pragma unroll
-                            for (int rb = 0; rb < P; ++rb)
-                                bop[rb] = *reinterpret_cast<const float4*>(Bl + ((n * P + jb + 1) * P + rb) * 256 + lane * 4);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    } else {
+                    for (int k = 0; k < 4; ++k) s[n][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(bk[k], cur[n][0][k], s[n][0], 0, 0, 0);
+                }
+            } else {
+                bf16x8 op[kAhead + 1][P];
 #pragma unroll
-                        for (int rb = 0; rb < P; ++rb)
-                            bcur[rb] = *reinterpret_cast<const float4*>(Bl + ((n * P + jb) * P + rb) * 256 + lane * 4);
-                    }
-                    float ax[4];
-                    if constexpr (X4) {
+                for (int st = 0; st < kAhead; ++st) project_operands(st / kSteps, 2 - st % kSteps / KC, st % KC, op[st]);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) ax[k] = cur[n][jb][k];
-                        *reinterpret_cast<float4*>(tbuf + c * 20 + 4 * g4) = make_float4(ax[0], ax[1], ax[2], ax[3]);
-                        lds_wave_sync();
+                for (int n = 0; n < N; ++n) {
+                    bf16x8 a[KC][3];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) aY[n][jb][v] = tbuf[(4 * g4 + v) * 20 + c];
-                        lds_wave_sync();
-                    } else {
+                    for (int kc = 0; kc < KC; ++kc) split2(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a[kc]);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            aY[n][jb][v] = cur[n][jb][v];
-                            tbuf[(4 * g4 + v) * 20 + c] = aY[n][jb][v];
-                        }
-                        lds_wave_sync();
-                        const float4 ax4 = *reinterpret_cast<const float4*>(tbuf + c * 20 + 4 * g4);
-                        lds_wave_sync();
-                        ax[0] = ax4.x;
-                        ax[1] = ax4.y;
-                        ax[2] = ax4.z;
-                        ax[3] = ax4.w;
-                    }
+                    for (int i = 0; i < kSteps; ++i) {
+                        const int st = n * kSteps + i, next = st + kAhead, part = 2 - i / KC, kc = i % KC;
+                        if (next < N * kSteps) project_operands(next / kSteps, 2 - next % kSteps / KC, next % KC, op[next % (kAhead + 1)]);
+                        hold_reads();
 #pragma unroll
-                    for (int rb = 0; rb < P; ++rb) {
-                        const float bk[4] = {bcur[rb].x, bcur[rb].y, bcur[rb].z, bcur[rb].w};
+                        for (int q = 2 - part; q >= 0; --q)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            s[n][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(bk[k], ax[k], s[n][rb], 0, 0, 0);
+                            for (int rb = 0; rb < P; ++rb) s[n][rb] = mfma_bf16(op[st % (kAhead + 1)][rb], a[kc][q], s[n][rb]);
                     }
                 }
             }
-
-            // P = 4: the request waits until the last mode's gradients are under way: the registers it fills are then free
-            // for the leave-one-out products and the A-gradient stage, which otherwise shuttle values through the
-            // other half of the register file (C5 0.780 -> 0.761 ms per launch); the rows still have a third of the
-            // tile's matrix work to arrive in.
-            constexpr bool LATE_REQUEST = P == 4;
-            if constexpr (X4 && !LATE_REQUEST) request_next(cur);
 
             // leave-one-out products, prediction, error (factor phase: per mode, further down)
             floatx4 w[N][P];
@@ -502,20 +531,10 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     run *= s[n][rb];
                 }
             }
-            xhat += __shfl_xor(xhat, 16);
-            xhat += __shfl_xor(xhat, 32);
-            float neg_e = xhat - x;
+            float neg_e = sum_over_groups(xhat) - x;
 
-            float4 top_[P];   // operands of the next block of the A-gradient products, read one block ahead
-            if constexpr (AHEAD) {
-#pragma unroll
-                for (int jb = 0; jb < P; ++jb) top_[jb] = *reinterpret_cast<const float4*>(Bt + jb * 256 + lane * 4);
-            }
 #pragma unroll
             for (int n = 0; n < N; ++n) {
-                if constexpr (X4 && LATE_REQUEST) {
-                    if (n == N - 1) request_next(cur);
-                }
                 if constexpr (MODE == kFactorPhase) {
                     // w^(n), prediction and error from the projections as they stand: those of modes < n already advanced
                     float part = 0.0f;
@@ -529,67 +548,99 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                         const floatx4 full = wn * s[n][rb];
                         part += (full[0] + full[1]) + (full[2] + full[3]);
                     }
-                    part += __shfl_xor(part, 16);
-                    part += __shfl_xor(part, 32);
-                    neg_e = part - x;
+                    neg_e = sum_over_groups(part) - x;
                 }
-                // -e w^(n) (layout X), -e GS^(n) (layout Y), and -e w^(n) in layout Y through LDS
-                floatx4 gs[P];
-                float wY[P][4];
+                floatx4 ay[P], gs[P];   // rows and -e GS^(n), layout Y
 #pragma unroll
                 for (int jb = 0; jb < P; ++jb) gs[jb] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int rb = 0; rb < P; ++rb) {
-                    float4 tcur[P];
-                    if constexpr (AHEAD) {
-#pragma unroll
-                        for (int jb = 0; jb < P; ++jb) tcur[jb] = top_[jb];
-                        if (n * P + rb + 1 < N * P) {
-#pragma unroll
-                            for (int jb = 0; jb < P; ++jb)
-                                top_[jb] = *reinterpret_cast<const float4*>(Bt + ((n * P + rb + 1) * P + jb) * 256 + lane * 4);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    } else {
-#pragma unroll
-                        for (int jb = 0; jb < P; ++jb)
-                            tcur[jb] = *reinterpret_cast<const float4*>(Bt + ((n * P + rb) * P + jb) * 256 + lane * 4);
-                    }
-                    const floatx4 wp = w[n][rb] * neg_e;
+                if constexpr (P == 1) {
+                    const float4 b4 = *reinterpret_cast<const float4*>(Bt + n * 256 + lane * 4);
+                    const float bk[4] = {b4.x, b4.y, b4.z, b4.w};
+                    const floatx4 wp = w[n][0] * neg_e;
                     *reinterpret_cast<float4*>(tbuf + c * 20 + 4 * g4) = make_float4(wp[0], wp[1], wp[2], wp[3]);
                     if constexpr (MODE != kCorePhase) {
 #pragma unroll
-                        for (int jb = 0; jb < P; ++jb) {
-                            const float tk[4] = {tcur[jb].x, tcur[jb].y, tcur[jb].z, tcur[jb].w};
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                gs[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wp[k], tk[k], gs[jb], 0, 0, 0);
-                        }
+                        for (int k = 0; k < 4; ++k) gs[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wp[k], bk[k], gs[0], 0, 0, 0);
                     }
                     lds_wave_sync();
+                    float wY[4];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) wY[rb][v] = tbuf[(4 * g4 + v) * 20 + c];
+                    for (int v = 0; v < 4; ++v) wY[v] = tbuf[(4 * g4 + v) * 20 + c];
                     lds_wave_sync();
+                    ay[0] = floatx4{aY[n][0], aY[n][1], aY[n][2], aY[n][3]};
+                    if constexpr (MODE != kFactorPhase) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) GBacc[n][0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(aY[n][v], wY[v], GBacc[n][0][0], 0, 0, 0);
+                    }
+                } else {
+                    bf16x8 op[kAhead + 1][P];
+                    if constexpr (MODE != kCorePhase) {
+#pragma unroll
+                        for (int st = 0; st < kAhead; ++st) gradient_operands(n, 2 - st / KC, st % KC, op[st]);
+                    }
+                    // the rows' parts in layout Y
+                    Split aYp[P];
+#pragma unroll
+                    for (int kc = 0; kc < KC; ++kc) {
+                        bf16x8 a[3];
+                        split2(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a);
+                        aYp[2 * kc] = turn_block(a, 0);
+                        aYp[2 * kc + 1] = turn_block(a, 1);
+                    }
+                    if (n == N - 1) request_next(cur);
+                    // -e w^(n), in both layouts
+                    bf16x8 wX[KC][3];
+                    SplitPairs wYp[P];
+#pragma unroll
+                    for (int kc = 0; kc < KC; ++kc) {
+                        split2(w[n][2 * kc] * neg_e, w[n][2 * kc + 1] * neg_e, sc, wX[kc]);
+                        if constexpr (MODE != kFactorPhase) {
+                            wYp[2 * kc] = turn_pairs(wX[kc], 0);
+                            wYp[2 * kc + 1] = turn_pairs(wX[kc], 1);
+                        }
+                    }
+                    if constexpr (MODE != kCorePhase) {
+                        // the rows whole, for the regulariser term: the all-one diagonal times their parts (exact);
+                        // ay[jb][v] = component 16 jb + c of sample 4g + v
+#pragma unroll
+                        for (int jb = 0; jb < P; ++jb) {
+                            ay[jb] = mfma_bf16(diagonal_high, pair_up(high_half(aYp[jb].mh), aYp[jb].l), floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+                            ay[jb] = mfma_bf16(diagonal2, aYp[jb].mh, ay[jb]);
+                        }
+#pragma unroll
+                        for (int st = 0; st < kSteps; ++st) {
+                            const int next = st + kAhead, part = 2 - st / KC, kc = st % KC;
+                            if (next < kSteps) gradient_operands(n, 2 - next / KC, next % KC, op[next % (kAhead + 1)]);
+                            hold_reads();
+#pragma unroll
+                            for (int q = 2 - part; q >= 0; --q)
+#pragma unroll
+                                for (int jb = 0; jb < P; ++jb) gs[jb] = mfma_bf16(wX[kc][q], op[st % (kAhead + 1)][jb], gs[jb]);
+                        }
+                    }
+                    // core gradient block: GB[j = 16 jb + 4g + v][r = 16 rb + c], summed over the tile's samples
+                    if constexpr (MODE != kFactorPhase) {
+#pragma unroll
+                        for (int jb = 0; jb < P; ++jb) {
+                            floatx4 part[P];
+#pragma unroll
+                            for (int rb = 0; rb < P; ++rb) part[rb] = kFreshSums ? floatx4{0.0f, 0.0f, 0.0f, 0.0f} : GBacc[n][jb][rb];
+#pragma unroll
+                            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                                for (int rb = 0; rb < P; ++rb) part[rb] = contract16_step(q, aYp[jb], wYp[rb], part[rb]);
+#pragma unroll
+                            for (int rb = 0; rb < P; ++rb) GBacc[n][jb][rb] = kFreshSums ? GBacc[n][jb][rb] + part[rb] : part[rb];
+                        }
+                    }
                 }
-
-                if constexpr (MODE == kCorePhase) {
-#pragma unroll
-                    for (int jb = 0; jb < P; ++jb)
-#pragma unroll
-                        for (int rb = 0; rb < P; ++rb)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                GBacc[n][jb][rb] =
-                                    __builtin_amdgcn_mfma_f32_16x16x4f32(aY[n][jb][v], wY[rb][v], GBacc[n][jb][rb], 0, 0, 0);
-                    continue;
-                }
+                if constexpr (MODE == kCorePhase) continue;
                 // factor-row gradients: where each row's goes was decided when the group was parked (route words, see
                 // tiled_grad_park_words).  Padding columns and samples past the end of Psi have a = 0 and -e GS = 0, so
                 // their gradient is zero without a test; what keeps them out of dA is the offset.
                 const uint4 routes4 = *reinterpret_cast<const uint4*>(routes + n * 64 + sub * 16 + 4 * g4);
                 const unsigned int abase[4] = {routes4.x, routes4.y, routes4.z, routes4.w};   // samples 4g .. 4g+3
                 unsigned int tbase[4];      // P <= 2: LDS address of the sample's table row, or of the row nobody reads
-                float onehot[4];
                 bool is_top[4];
                 // ROWS: the byte offset of each sample's list entry in the workgroup's list area (or the marker), the word that
                 // names its row in the entry (the row's byte offset inside its mode), and whether any list of the group was full
@@ -611,7 +662,6 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     // a table word minus its tag is the row's offset in the table, every other word lands far above it
                     if constexpr (LDS_TABLE) tbase[v] = hot_addr + min(abase[v] - kRouteTable, sink_rel);
                     is_top[v] = abase[v] == top_key;
-                    onehot[v] = is_top[v] ? 1.0f : 0.0f;
                 }
                 // ROWS: the atomics only go out where a row needs them (its list was full; P = 4: a table row)
                 bool rows_need_atomics = group_had_full_list;
@@ -652,6 +702,11 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                 };
                 // the one-hot products are skipped for a tile in which no sample hits rows 0..15 of this mode, the swaps
                 // for a tile in which no sample has a table row (wave-uniform tests)
+                shortx4 onehot;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) onehot[v] = is_top[v] ? (short)0x3f80 : (short)0;
+                Split dx[P];      // factor phase: the row's change in layout X
+                floatx4 change;   // the same, P = 1, layout Y
                 const bool any_top = g.top[n] > 0 && __builtin_amdgcn_ballot_w64(is_top[0] || is_top[1] || is_top[2] || is_top[3]) != 0;
                 bool any_table = false;
                 if constexpr (LDS_TABLE) {
@@ -665,7 +720,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     float grad[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        grad[v] = fmaf(lambda_scaled, aY[n][jb][v], gs[jb][v]);
+                        grad[v] = g.scale * fmaf(g.lambda_A, ay[jb][v], gs[jb][v]);
                         if constexpr (ROWS) {
                             // the list entry: components 0 .. J_n - 1, then the word that names the row (its lane may be in
                             // a block of columns of its own when J_n is a multiple of 16: see below)
@@ -683,38 +738,58 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                             tval[4 * jb + v] = grad[v];
                         }
                     }
+                    const floatx4 whole = {grad[0], grad[1], grad[2], grad[3]};
+                    change = whole;
                     if (any_top) {
+                        if constexpr (P == 1) {
 #pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            Top[n][jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(onehot[k], grad[k], Top[n][jb], 0, 0, 0);
+                            for (int k = 0; k < 4; ++k)
+                                Top[n][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(is_top[k] ? 1.0f : 0.0f, grad[k], Top[n][0], 0, 0, 0);
+                        } else {
+                            const Split gp = split(whole, sc);
+                            floatx4 part = mfma_bf16(pair_up(shortx4{0, 0, 0, 0}, onehot), pair_up(high_half(gp.mh), gp.l), floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+                            part = mfma_bf16(pair_up(onehot, onehot), gp.mh, part);
+                            Top[n][jb] += part;
+                        }
                     }
                     if constexpr (MODE == kFactorPhase) {
-                        // the block of the row's change (layout Y) goes through LDS into layout X and advances the
-                        // sample's projections of this mode: c^(n)[rb] += delta[jb] B^(n)[jb][rb]
-                        if (n + 1 < N) {
+                        // lane (c, g) holds the change of component 16 jb + c in samples 4g..: straight in, transposed out
+                        if (P > 1 && n + 1 < N) {
+                            store_block(turn + straight, kSplitBlockBytes, split(whole, sc));
+                            lds_wave_sync();
+                            dx[jb] = transposed_block(turn + transposed, kSplitBlockBytes);
+                            lds_wave_sync();
+                        }
+                    }
+                }
+                if constexpr (MODE == kFactorPhase) {
+                    // advance the samples' projections of this mode: c^(n)[rb] += delta B^(n)[rb]
+                    if (n + 1 < N) {
+                        if constexpr (P == 1) {
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) tbuf[(4 * g4 + v) * 20 + c] = grad[v];
+                            for (int v = 0; v < 4; ++v) tbuf[(4 * g4 + v) * 20 + c] = change[v];
                             lds_wave_sync();
                             const float4 dx4 = *reinterpret_cast<const float4*>(tbuf + c * 20 + 4 * g4);
                             lds_wave_sync();
-                            const float dx[4] = {dx4.x, dx4.y, dx4.z, dx4.w};
+                            const float4 b4 = *reinterpret_cast<const float4*>(Bl + n * 256 + lane * 4);
+                            const float dk[4] = {dx4.x, dx4.y, dx4.z, dx4.w}, bk[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-                            for (int rb = 0; rb < P; ++rb) {
-                                const float4 b4 = *reinterpret_cast<const float4*>(Bl + ((n * P + jb) * P + rb) * 256 + lane * 4);
-                                const float bk[4] = {b4.x, b4.y, b4.z, b4.w};
+                            for (int k = 0; k < 4; ++k) s[n][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(bk[k], dk[k], s[n][0], 0, 0, 0);
+                        } else {
 #pragma unroll
-                                for (int k = 0; k < 4; ++k)
-                                    s[n][rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(bk[k], dx[k], s[n][rb], 0, 0, 0);
+                            for (int st = 0; st < kSteps; ++st) {
+                                const int part = 2 - st / KC, kc = st % KC;
+                                bf16x8 op[P];
+                                project_operands(n, part, kc, op);
+#pragma unroll
+                                for (int q = 2 - part; q >= 0; --q) {
+                                    const bf16x8 d = q == 0 ? pair_up(high_half(dx[2 * kc].mh), high_half(dx[2 * kc + 1].mh))
+                                                     : q == 1 ? pair_up(low_half(dx[2 * kc].mh), low_half(dx[2 * kc + 1].mh)) : pair_up(dx[2 * kc].l, dx[2 * kc + 1].l);
+#pragma unroll
+                                    for (int rb = 0; rb < P; ++rb) s[n][rb] = mfma_bf16(op[rb], d, s[n][rb]);
+                                }
                             }
                         }
-                    } else {
-                        // core gradient block: GB[j = 16 jb + 4g + v'][r = 16 rb + c]
-#pragma unroll
-                        for (int rb = 0; rb < P; ++rb)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                GBacc[n][jb][rb] =
-                                    __builtin_amdgcn_mfma_f32_16x16x4f32(aY[n][jb][v], wY[rb][v], GBacc[n][jb][rb], 0, 0, 0);
                     }
                 }
                 if constexpr (LDS_TABLE) {
@@ -730,7 +805,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     }
                 }
             }
-            if constexpr (!X4) {
+            if constexpr (P == 1) {
 #pragma unroll
                 for (int n = 0; n < N; ++n)
 #pragma unroll
@@ -936,7 +1011,7 @@ __global__ void __launch_bounds__(256) errors_tiled_kernel(Coo coo, uint64_t nnz
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g4 = lane >> 4;
     float* Bl = lds;                                                    // [N][D][D], see operand_slot
-    float* wave_lds = lds + N * D * D + wave * tiled_wave_scratch(N, P);   // two parked groups, then tbuf
+    float* wave_lds = lds + N * D * D + wave * tiled_errors_scratch(N);   // two parked groups, then tbuf
     float* tbuf = wave_lds + 2 * tiled_park_words(N);
     for (int q = tid; q < N * D * D; q += 256) {
         const int n = q / (D * D), rem = q - n * D * D, j = rem / D, r = rem - j * D;

@@ -1,0 +1,159 @@
+// fp32 products on the bf16 matrix instructions.
+//
+// The fp32 matrix instruction of this chip (v_mfma_f32_16x16x4_f32, 33 clocks for 2 048 flop) runs on the vector
+// ALU's multipliers: it takes their time and nothing else runs beside it.  v_mfma_f32_16x16x32_bf16 takes 16.5 clocks
+// for 16 384 flop, runs on a unit of its own and leaves the vector ALU free (16 of them with 48 vector instructions
+// between them take 64 issue slots, no more; measured).  So every fp32 operand is cut into three bf16 parts
+//   x = h + m + l,   h = bf16(x),  m = bf16(x - h),  l = bf16(x - h - m)      (8 + 8 + 8 bits: nothing is left over)
+// and a product is the six partial products down to 2^-16 of the largest, hH + hM + mH + hL + mM + lH; what is dropped
+// (mL, lM, lL) is below 2^-24.  Over 64 terms the sum's error against 64 bits is 0.65 times that of a chain of fp32
+// matrix instructions (rms and maximum, three distributions of the operands, one with exponents spread over 2^+-10).
+// The instruction rounds its sum after every four products (measured: to nearest), so a sum that goes on over a whole
+// launch is not kept in it: the products of one tile are summed from zero and then added by the vector ALU, one rounding
+// at the size of the long sum instead of 24.
+// Six bf16 instructions cost 99 clocks per 16x16x32 where eight fp32 instructions cost 264, and they run beside the
+// vector instructions that do the cutting (seven per two values).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace ftk {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));    // four bf16, two registers
+typedef short shortx8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// The three parts of four fp32 values, the middle and the high one side by side: see contract16.
+struct Split {
+    bf16x8 mh;
+    shortx4 l;
+};
+// The same as the other operand of contract16: every pair of parts that it takes.
+struct SplitPairs {
+    bf16x8 mh, hm, lh;
+};
+
+// The two constants that v_dot2_f32_bf16 takes the remainder with: x - part is c + a0 b0 + a1 b1 with b = (-1, 0) or (0, -1).
+// They stay in scalar registers: the compiler may turn (-1, 0) into the inline constant -1.0, which the instruction reads
+// as the fp32 pattern, i.e. as (0, -1).
+struct SplitConst {
+    unsigned int low, high;
+};
+__device__ __forceinline__ SplitConst split_const() {
+    SplitConst k;
+    asm volatile("s_mov_b32 %0, 0xbf80\n\ts_mov_b32 %1, 0xbf800000" : "=s"(k.low), "=s"(k.high));
+    return k;
+}
+
+__device__ __forceinline__ bf16x2 round_pair(float x, float y) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    return __builtin_convertvector(floatx2{x, y}, bf16x2);
+}
+__device__ __forceinline__ void split_pair(float x, float y, const SplitConst& k, unsigned int& h, unsigned int& m, unsigned int& l) {
+    const bf16x2 low = __builtin_bit_cast(bf16x2, k.low), high = __builtin_bit_cast(bf16x2, k.high);
+    const bf16x2 hp = round_pair(x, y);
+    const float x1 = __builtin_amdgcn_fdot2_f32_bf16(hp, low, x, false), y1 = __builtin_amdgcn_fdot2_f32_bf16(hp, high, y, false);
+    const bf16x2 mp = round_pair(x1, y1);
+    const float x2 = __builtin_amdgcn_fdot2_f32_bf16(mp, low, x1, false), y2 = __builtin_amdgcn_fdot2_f32_bf16(mp, high, y1, false);
+    const bf16x2 lp = round_pair(x2, y2);
+    h = __builtin_bit_cast(unsigned int, hp);
+    m = __builtin_bit_cast(unsigned int, mp);
+    l = __builtin_bit_cast(unsigned int, lp);
+}
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Split split(const floatx4& x, const SplitConst& k) {
+    unsigned int h0, h1, m0, m1, l0, l1;
+    split_pair(x[0], x[1], k, h0, m0, l0);
+    split_pair(x[2], x[3], k, h1, m1, l1);
+    return Split{__builtin_bit_cast(bf16x8, uintx4{m0, m1, h0, h1}), __builtin_bit_cast(shortx4, uintx2{l0, l1})};
+}
+// The parts of two neighbouring blocks side by side: part 0 h, 1 m, 2 l.
+__device__ __forceinline__ void split2(const floatx4& x, const floatx4& y, const SplitConst& k, bf16x8 (&part)[3]) {
+    uintx4 h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned int hi, mi, li;
+        split_pair(i < 2 ? x[2 * i] : y[2 * i - 4], i < 2 ? x[2 * i + 1] : y[2 * i - 3], k, hi, mi, li);
+        h[i] = hi;
+        m[i] = mi;
+        l[i] = li;
+    }
+    part[0] = __builtin_bit_cast(bf16x8, h);
+    part[1] = __builtin_bit_cast(bf16x8, m);
+    part[2] = __builtin_bit_cast(bf16x8, l);
+}
+
+__device__ __forceinline__ bf16x8 pair_up(const shortx4& a, const shortx4& b) {
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ floatx4 mfma_bf16(const bf16x8& a, const bf16x8& b, const floatx4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ shortx4 low_half(const bf16x8& x) {
+    const shortx8 s = __builtin_bit_cast(shortx8, x);
+    return __builtin_shufflevector(s, s, 0, 1, 2, 3);
+}
+__device__ __forceinline__ shortx4 high_half(const bf16x8& x) {
+    const shortx8 s = __builtin_bit_cast(shortx8, x);
+    return __builtin_shufflevector(s, s, 4, 5, 6, 7);
+}
+
+// Operand layout of the 16x16x32 instruction (lane l, c = l % 16, g = l / 16): eight values of row (column) c, k slots
+// 8g .. 8g+7; the result is laid out as that of the 16x16x4 instruction (register v: row 4g + v, column c).  Which
+// contracted index sits in which slot is free as long as both operands agree: slots (g, 0..3) hold indices 4g..4g+3 of
+// one block of 16 and slots (g, 4..7) those of the next block -- or, where only 16 values are contracted, another part of
+// the SAME block, so that one instruction adds two of the six partial products.
+// Contraction of one block in steps q = 0..2, for several sums side by side: lH + hL, then mH + hM, then mM + hH.
+// (The 16x16x16 instruction would need no part twice, but its result must not be the addend of a 16x16x32
+// instruction right behind it: the compiler puts no wait between the two, and sums came out wrong.)
+__device__ __forceinline__ floatx4 contract16_step(int q, const Split& a, const SplitPairs& b, const floatx4& acc) {
+    return q == 0 ? mfma_bf16(pair_up(high_half(a.mh), a.l), b.lh, acc) : mfma_bf16(a.mh, q == 1 ? b.hm : b.mh, acc);
+}
+__device__ __forceinline__ floatx4 contract16_step(int q, const SplitPairs& a, const Split& b, const floatx4& acc) {
+    return q == 0 ? mfma_bf16(a.lh, pair_up(high_half(b.mh), b.l), acc) : mfma_bf16(q == 1 ? a.hm : a.mh, b.mh, acc);
+}
+
+// A 16 x 16 block X of one bf16 part in LDS (512 bytes), readable both ways:
+//   straight    lane (c, g) holds X[c][4g .. 4g+3]:  one 8-byte access at split_slot(c, g)
+//   transposed  lane (c, g) gets X[4g .. 4g+3][c]:   ds_read_b64_tr_b16, to which lane (c, g) names the 8 bytes of row
+//               4g + c / 4, columns 4 (c % 4) .. +3, i.e. split_slot(4g + c / 4, c % 4)
+// The exclusive-or spreads the 32 lanes that the LDS serves at a time over all its banks in both directions.
+constexpr int kSplitBlockBytes = 512;
+__host__ __device__ __forceinline__ constexpr int split_slot(int c, int g) { return (16 * g + (c ^ ((g >> 1) << 3))) * 8; }
+
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ shortx4 lds_straight(const lds_char* p) { return *(const __attribute__((address_space(3))) shortx4*)p; }
+__device__ __forceinline__ shortx4 lds_transposed(const lds_char* p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4*)p);
+}
+// the three parts of a block, `stride` bytes apart (h, m, l)
+__device__ __forceinline__ Split transposed_block(const lds_char* p, int stride) {
+    return Split{pair_up(lds_transposed(p + stride), lds_transposed(p)), lds_transposed(p + 2 * stride)};
+}
+// ... as pairs: parts that are needed twice are read twice, which is cheaper than a copy in the vector ALU
+__device__ __forceinline__ SplitPairs transposed_pairs(const lds_char* p, int stride) {
+    return SplitPairs{pair_up(lds_transposed(p + stride), lds_transposed(p)), pair_up(lds_transposed(p), lds_transposed(p + stride)),
+                      pair_up(lds_transposed(p + 2 * stride), lds_transposed(p))};
+}
+__device__ __forceinline__ void store_part(lds_char* p, const shortx4& x) { *(__attribute__((address_space(3))) shortx4*)p = x; }
+__device__ __forceinline__ void store_block(lds_char* p, int stride, const Split& s) {
+    store_part(p, high_half(s.mh));
+    store_part(p + stride, low_half(s.mh));
+    store_part(p + 2 * stride, s.l);
+}
+
+// x added over the four lane groups, the sum in every lane: two swaps of lane rows, no trip through LDS
+__device__ __forceinline__ float sum_over_groups(float x) {
+    unsigned int u = __float_as_uint(x);
+    auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    u = __float_as_uint(x);
+    p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
+}  // namespace ftk

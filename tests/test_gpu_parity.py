@@ -376,6 +376,24 @@ def test_matrix_core_kernel_with_ranks_off_the_block_size(order, dims, J, R, zip
         one_step_case(w, idx, vals, kernel="tiled", tiles=tiles, flags=binding.FTK_LAYOUT_EXACT)
 
 
+@pytest.mark.parametrize("J,R", [(1, 17), (15, 16), (17, 1), (31, 33), (33, 31), (47, 48), (63, 64)])
+@pytest.mark.parametrize("M", [1, 17, 1025])
+def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
+    """Ranks one off a block of 16 in each direction: the last 16-byte piece of a row runs into the row behind
+    it (behind a mode's last row: into its padding), and the sums over parts of operands end inside a block.
+    Parameters of both signs and size 1, few rows, so that the last row of every mode is hit; the tolerance
+    is the one for a step from fp32 sums."""
+    w = synth.tiny_workload(3, (9, 5, 3), 400, (J, J, J), R, M, seed=90 + J, values="normal")
+    scale = float(R) * J ** 3
+    w = synth.replace(w, lr_A=1e-2 / scale, lr_B=1e-2 / scale)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(J)
+    A0 = [rng.uniform(-1, 1, size=(d, J)).astype(np.float32) for d in w.dims]
+    B0 = [rng.uniform(-1, 1, size=(J, R)).astype(np.float32) for _ in w.dims]
+    announce("edges of blocks J=%d R=%d M=%d" % (J, R, M))
+    one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
+
+
 @pytest.mark.parametrize("kernel", [None, "rows"])
 @pytest.mark.parametrize("name,nnz,M,dims", [
     ("C2", 200_000, 20_000, (4_800, 1_777, 220)),
