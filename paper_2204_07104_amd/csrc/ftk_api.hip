@@ -19,6 +19,7 @@
 #include "ftk_kernels_generic.hpp"
 #include "ftk_kernels_mfma16.hpp"
 #include "ftk_kernels_tiled.hpp"
+#include "ftk_kernels_errors.hpp"
 #define FTK_INSTANCES_EXTERN
 #include "ftk_instances.hpp"   // the matrix-core kernel instances are compiled in translation units of their own
 
@@ -63,7 +64,9 @@ struct ftk_ctx {
     float* d_dA = nullptr;
     float* d_B = nullptr;
     float* d_GB = nullptr;
-    double* d_sums = nullptr;
+    double* h_sums = nullptr; // pinned: one pair of error sums per workgroup of an evaluation pass, written by the kernel itself
+    double* d_sums = nullptr; // the same memory as the device names it
+    float* d_S = nullptr;     // projected rows of the evaluation pass (made at its first use, see launch_errors)
     unsigned int* d_flag = nullptr;
 
     uint32_t* d_pos = nullptr;
@@ -138,6 +141,7 @@ struct ftk_ctx {
     bool timing = false;
     bool no_events = false;   // set while ftk_sgd_step_noalloc enqueues: no event is created even if timing is on
     bool prepare_only = false;   // the launch functions stop after raising the kernel's LDS limit
+    int error_grid = 0;          // workgroups of the evaluation pass in the stream
     TimingSlot slots[FTK_K_COUNT];
     std::vector<const void*> lds_limit_raised;   // kernels whose dynamic-LDS limit this context has raised
 
@@ -560,10 +564,17 @@ int ensure_batch(ftk_ctx* c) {
     return FTK_OK;
 }
 
+// Workgroups of an evaluation pass: each leaves one pair of sums in h_sums, which the host adds up (adds to one address
+// from all workgroups take 41 ns each: 0.17 ms for 4 096 of them).
+constexpr int kErrorBlocksPerCu = 8;
+int error_blocks(ftk_ctx* c, long long work, int per_block) {
+    return c->error_grid = blocks_for(work, per_block, c->num_cu * kErrorBlocksPerCu);
+}
+
 template <int N>
 void launch_errors_mfma16_n(ftk_ctx* c, const Coo& coo, long long nnz) {
     const long long groups = (nnz + 63) / 64;
-    const int grid = blocks_for(groups, 4, c->num_cu * 8);
+    const int grid = error_blocks(c, groups, 4);
     ModeBytes row_bytes = {};
     for (int n = 0; n < N; ++n) row_bytes.v[n] = (unsigned int)(c->dims[n] * 64);
     hipLaunchKernelGGL(errors_mfma16_kernel<N>, dim3(grid), dim3(256), 0, c->stream, coo, (uint64_t)nnz,
@@ -573,7 +584,7 @@ void launch_errors_mfma16_n(ftk_ctx* c, const Coo& coo, long long nnz) {
 template <int N, int P, bool X4>
 int launch_errors_tiled_npx(ftk_ctx* c, const Coo& coo, long long nnz) {
     const long long groups = (nnz + 63) / 64;
-    const int grid = blocks_for(groups, 4, c->num_cu * 8);
+    const int grid = error_blocks(c, groups, 4);
     const size_t lds = 4 * ((size_t)N * 256 * P * P + 4 * (size_t)tiled_errors_scratch(N));
     TiledModeBytes mode_bytes = {};
     for (int n = 0; n < N; ++n) mode_bytes.v[n] = (unsigned int)(c->dims[n] * c->L.J[n] * 4);
@@ -594,10 +605,85 @@ int launch_errors_tiled_n(ftk_ctx* c, const Coo& coo, long long nnz) {
     }
 }
 
+template <int N>
+void launch_errors_rows_n(ftk_ctx* c, const Coo& coo, long long nnz, const ErrorRows& s) {
+    const dim3 grid(error_blocks(c, (nnz + 63) / 64, 4)), threads(256);
+    if (s.Rs <= 4) hipLaunchKernelGGL((errors_rows_kernel<N, 1>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+    else if (s.Rs <= 8) hipLaunchKernelGGL((errors_rows_kernel<N, 2>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+    else if (s.Rs <= 16) hipLaunchKernelGGL((errors_rows_kernel<N, 4>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+    else if (s.Rs <= 32) hipLaunchKernelGGL((errors_rows_kernel<N, 8>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+    else hipLaunchKernelGGL((errors_rows_kernel<N, 16>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+}
+
+// The pass over projected rows (ftk_kernels_errors.hpp), where the shape allows it and it pays; `done` says whether it ran.
+int launch_errors_rows(ftk_ctx* c, const Coo& coo, long long nnz, bool* done) {
+    *done = false;
+    ErrorRows s = {};
+    s.Rs = (c->R_user + 3) & ~3;
+    long long rows = 0;
+    int row_floats = 0;
+    for (int n = 0; n < c->order; ++n) {
+        if (c->J_user[n] > kProjectMaxRank || c->R_user > kProjectMaxRank) return FTK_OK;
+        rows += c->dims[n];
+        row_floats += c->L.J[n];
+    }
+    // Projecting the rows costs a pass over the factors, so the set has to be large against them, the more so the less a
+    // projection costs per entry (J = R = 16, 500 000 rows: 1e6 entries 85 us that way and this, 1e8 1 852 and 1 430 us;
+    // J = R = 32, 1.6e6 rows: 2e6 entries 149 us per entry, 263 us by rows, 2.5e8 12.7 and 4.4 ms; J = R = 64: 18.7 and
+    // 3.3 ms).  A gathered row of S must not be longer than a row of A where the gathering is all there is (order 6,
+    // J = 8, R = 16, 2e8 entries: 16.5 ms per entry, 19.5 ms by rows), and not twice as long where the products count
+    // (J = 18, 30, 9, 25, R = 22, 5e6 entries: 516 us per entry, 176 us by rows).
+    const bool narrow = s.Rs <= 16;
+    if (nnz * c->order < (narrow ? 24 : 6) * rows || c->order * s.Rs > (narrow ? 1 : 2) * row_floats) return FTK_OK;
+    if (!c->d_S && hipMalloc(&c->d_S, (size_t)rows * s.Rs * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();   // no room: the passes that need none
+        c->d_S = nullptr;
+        return FTK_OK;
+    }
+    ProjectArgs p = {};
+    p.order = c->order;
+    p.R = c->R_user;
+    p.stride_B = c->L.R;
+    p.Rs = s.Rs;
+    float* S = c->d_S;
+    const int per_block = 256 / (s.Rs / 4) * kProjectRows;
+    for (int n = 0; n < c->order; ++n) {
+        s.S[n] = S;
+        p.A[n] = c->d_A + c->L.A_off[n];
+        p.B[n] = c->d_B + c->L.B_off[n];
+        p.S[n] = S;
+        p.rows[n] = c->dims[n];
+        p.J[n] = c->J_user[n];
+        p.stride_A[n] = c->L.J[n];
+        p.block0[n + 1] = p.block0[n] + blocks_for(c->dims[n], per_block, c->num_cu * 8);
+        S += c->dims[n] * s.Rs;
+    }
+    hipLaunchKernelGGL(project_rows_kernel, dim3(p.block0[c->order]), dim3(256), 0, c->stream, p);
+    FTK_HIP(c, hipGetLastError());
+    switch (c->order) {
+        case 1: launch_errors_rows_n<1>(c, coo, nnz, s); break;
+        case 2: launch_errors_rows_n<2>(c, coo, nnz, s); break;
+        case 3: launch_errors_rows_n<3>(c, coo, nnz, s); break;
+        case 4: launch_errors_rows_n<4>(c, coo, nnz, s); break;
+        case 5: launch_errors_rows_n<5>(c, coo, nnz, s); break;
+        case 6: launch_errors_rows_n<6>(c, coo, nnz, s); break;
+        case 7: launch_errors_rows_n<7>(c, coo, nnz, s); break;
+        case 8: launch_errors_rows_n<8>(c, coo, nnz, s); break;
+        case 9: launch_errors_rows_n<9>(c, coo, nnz, s); break;
+        default: launch_errors_rows_n<10>(c, coo, nnz, s); break;
+    }
+    *done = true;
+    return FTK_OK;
+}
+
 // Sums of squared and absolute errors over `nnz` packed records (internal row numbers).
 int launch_errors(ftk_ctx* c, Coo coo, long long nnz, double* host_sums) {
-    FTK_HIP(c, hipMemsetAsync(c->d_sums, 0, 2 * sizeof(double), c->stream));
-    if (c->variant == V_MFMA16 && c->rec_words == 4 * ((c->order + 1 + 3) / 4)) {
+    bool done = false;
+    if (c->variant != V_GENERIC)
+        if (const int rc = launch_errors_rows(c, coo, nnz, &done)) return rc;
+    if (done) {
+        // (queued above)
+    } else if (c->variant == V_MFMA16 && c->rec_words == 4 * ((c->order + 1 + 3) / 4)) {
         switch (c->order) {
             case 1: launch_errors_mfma16_n<1>(c, coo, nnz); break;
             case 2: launch_errors_mfma16_n<2>(c, coo, nnz); break;
@@ -628,13 +714,17 @@ int launch_errors(ftk_ctx* c, Coo coo, long long nnz, double* host_sums) {
     } else {
         const int b_in_lds = (size_t)c->L.B_total * 4 <= 65536 - 256;
         const size_t lds = b_in_lds ? (size_t)c->L.B_total * 4 : 0;
-        const int grid = blocks_for(nnz, 256, c->num_cu * 8);
+        const int grid = error_blocks(c, nnz, 256);
         hipLaunchKernelGGL(errors_generic_kernel, dim3(grid), dim3(256), lds, c->stream, coo, c->L, (uint64_t)nnz,
                            (const float*)c->d_A, (const float*)c->d_B, b_in_lds, c->d_sums);
     }
     FTK_HIP(c, hipGetLastError());
-    FTK_HIP(c, hipMemcpyAsync(host_sums, c->d_sums, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     FTK_HIP(c, hipStreamSynchronize(c->stream));
+    host_sums[0] = host_sums[1] = 0.0;
+    for (int b = 0; b < c->error_grid; ++b) {
+        host_sums[0] += c->h_sums[2 * b + 0];
+        host_sums[1] += c->h_sums[2 * b + 1];
+    }
     return FTK_OK;
 }
 
@@ -645,11 +735,12 @@ void release(ftk_ctx* c) {
     for (int n = 0; n < kMaxOrder; ++n)
         if (c->d_new_of_old[n]) hipFree(c->d_new_of_old[n]);
     if (c->d_arena) c->d_A = c->d_dA = nullptr;   // parts of the arena
-    void* ptrs[] = {c->d_arena, c->d_rec, c->d_rec_tiles, c->d_stage, c->d_A, c->d_dA, c->d_B, c->d_GB, c->d_sums, c->d_flag,
+    void* ptrs[] = {c->d_arena, c->d_rec, c->d_rec_tiles, c->d_stage, c->d_A, c->d_dA, c->d_B, c->d_GB, c->d_S, c->d_flag,
                     c->d_pos, c->d_bidx, c->d_bval, c->d_hot_partial, c->d_gb_partial, c->d_lists, c->d_list_fill,
                     c->d_bucket_info, c->d_bucket_rows, c->d_overflow};
     for (void* p : ptrs)
         if (p) hipFree(p);
+    if (c->h_sums) hipHostFree(c->h_sums);
     delete c;
 }
 
@@ -975,7 +1066,8 @@ int create_impl(ftk_ctx* c, const int64_t* dims, const int32_t* const* idx, cons
     FTK_HIP(c, hipMalloc(&c->d_B, (size_t)c->L.B_total * sizeof(float)));
     FTK_HIP(c, hipMalloc(&c->d_GB, (size_t)c->L.B_total * sizeof(float)));
     FTK_HIP(c, hipMalloc(&c->d_stage, (size_t)stage * sizeof(float)));
-    FTK_HIP(c, hipMalloc(&c->d_sums, 2 * sizeof(double)));
+    FTK_HIP(c, hipHostMalloc((void**)&c->h_sums, (size_t)c->num_cu * kErrorBlocksPerCu * 2 * sizeof(double), hipHostMallocDefault));
+    FTK_HIP(c, hipHostGetDevicePointer((void**)&c->d_sums, c->h_sums, 0));
     FTK_HIP(c, hipMemset(c->d_A, 0, (size_t)c->A_total * sizeof(float)));
     FTK_HIP(c, hipMemset(c->d_dA, 0, (size_t)c->A_total * sizeof(float)));
     FTK_HIP(c, hipMemset(c->d_B, 0, (size_t)c->L.B_total * sizeof(float)));

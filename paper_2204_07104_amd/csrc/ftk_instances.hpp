@@ -4,6 +4,7 @@
 #pragma once
 #include "ftk_kernels_mfma16.hpp"
 #include "ftk_kernels_tiled.hpp"
+#include "ftk_kernels_errors.hpp"
 
 // J_n = R = 16 kernel, order N: both sampling rules x the four passes, and the evaluation pass
 #define FTK_MFMA16_INSTANCES(X, XE, N)                                                    \
@@ -20,6 +21,10 @@
 // orders 9 and 10 (the end of the paper's order sweep): ranks up to 16 only
 #define FTK_TILED_INSTANCES_HIGH(X, XE, N) FTK_TILED_INSTANCES_P(X, XE, N, 1, 8)
 
+// evaluation pass over projected rows, order N: 1, 2, 4, 8 or 16 lanes per entry
+#define FTK_ROWS_INSTANCES(X, N) X(N, 1) X(N, 2) X(N, 4) X(N, 8) X(N, 16)
+
+#define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_GRAD_MFMA16(N, T, M) template __global__ void ftk::grad_mfma16_kernel<N, T, M>(ftk::Mfma16Args);
 #define FTK_ERRORS_MFMA16(N) \
     template __global__ void ftk::errors_mfma16_kernel<N>(ftk::Coo, uint64_t, const float*, const float*, ftk::Layout, ftk::ModeBytes, double*);
@@ -44,4 +49,8 @@
 #define FTK_X_GT(N, P, W, R, M) extern FTK_GRAD_TILED(N, P, W, R, M)
 #define FTK_X_ET(N, P, X4) extern FTK_ERRORS_TILED(N, P, X4)
 FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
+#define FTK_X_ER(N, G) extern FTK_ERRORS_ROWS(N, G)
+FTK_ROWS_INSTANCES(FTK_X_ER, 1) FTK_ROWS_INSTANCES(FTK_X_ER, 2) FTK_ROWS_INSTANCES(FTK_X_ER, 3) FTK_ROWS_INSTANCES(FTK_X_ER, 4)
+FTK_ROWS_INSTANCES(FTK_X_ER, 5) FTK_ROWS_INSTANCES(FTK_X_ER, 6) FTK_ROWS_INSTANCES(FTK_X_ER, 7) FTK_ROWS_INSTANCES(FTK_X_ER, 8)
+FTK_ROWS_INSTANCES(FTK_X_ER, 9) FTK_ROWS_INSTANCES(FTK_X_ER, 10)
 #endif

@@ -249,7 +249,7 @@ __global__ void factor_phase_generic_kernel(GradArgs g, float* A_rw, float lr_A)
 __global__ void __launch_bounds__(256) errors_generic_kernel(Coo coo, Layout L, uint64_t nnz,
                                                              const float* __restrict__ A,
                                                              const float* __restrict__ B, int b_in_lds,
-                                                             double* __restrict__ sums /* [2]: sse, sae */) {
+                                                             double* __restrict__ sums /* [gridDim.x][2]: sse, sae */) {
     extern __shared__ float lds[];
     __shared__ double red[2][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -291,8 +291,8 @@ __global__ void __launch_bounds__(256) errors_generic_kernel(Coo coo, Layout L, 
             a += red[0][w];
             b += red[1][w];
         }
-        atomicAdd(sums + 0, a);
-        atomicAdd(sums + 1, b);
+        sums[2 * blockIdx.x + 0] = a;
+        sums[2 * blockIdx.x + 1] = b;
     }
 }
 

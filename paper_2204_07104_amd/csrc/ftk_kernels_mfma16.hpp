@@ -783,7 +783,7 @@ struct ModeBytes {
 template <int N>
 __global__ void __launch_bounds__(256) errors_mfma16_kernel(Coo coo, uint64_t nnz, const float* __restrict__ A,
                                                             const float* __restrict__ B, Layout L, ModeBytes row_bytes,
-                                                            double* __restrict__ sums /* [2]: sse, sae */) {
+                                                            double* __restrict__ sums /* [gridDim.x][2]: sse, sae */) {
     typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
     constexpr int W4 = (N + 1 + 3) / 4;
     __shared__ int sidx_all[4][(N + 1) * 64];   // per wave: [N][64] row byte offsets | [64] values
@@ -864,8 +864,8 @@ __global__ void __launch_bounds__(256) errors_mfma16_kernel(Coo coo, uint64_t nn
     }
     __syncthreads();
     if (tid == 0) {
-        atomicAdd(sums + 0, (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]));
-        atomicAdd(sums + 1, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+        sums[2 * blockIdx.x + 0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+        sums[2 * blockIdx.x + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     }
 }
 

@@ -1003,7 +1003,7 @@ struct TiledModeBytes {
 template <int N, int P, bool X4>
 __global__ void __launch_bounds__(256) errors_tiled_kernel(Coo coo, uint64_t nnz, const float* __restrict__ A,
                                                            const float* __restrict__ B, Layout L, TiledModeBytes mode_bytes,
-                                                           double* __restrict__ sums /* [2]: sse, sae */) {
+                                                           double* __restrict__ sums /* [gridDim.x][2]: sse, sae */) {
     extern __shared__ float lds[];
     constexpr int W4 = (N + 1 + 3) / 4;
     constexpr int D = 16 * P;
@@ -1197,8 +1197,8 @@ __global__ void __launch_bounds__(256) errors_tiled_kernel(Coo coo, uint64_t nnz
     }
     __syncthreads();
     if (tid == 0) {
-        atomicAdd(sums + 0, (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]));
-        atomicAdd(sums + 1, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
+        sums[2 * blockIdx.x + 0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+        sums[2 * blockIdx.x + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     }
 }
 

@@ -612,6 +612,29 @@ def test_rmse_and_mae_match_oracle():
         assert ma == pytest.approx(want_ma, rel=1e-5)
 
 
+@pytest.mark.parametrize("order", [1, 2, 3, 6, 7, 10])
+@pytest.mark.parametrize("J,R", [(3, 1), (5, 4), (9, 8), (16, 15), (20, 17), (33, 32), (47, 48), (64, 64)])
+@pytest.mark.parametrize("n_eval", [64, 4099])
+def test_errors_over_projected_rows(order, J, R, n_eval):
+    """The evaluation pass that projects the rows first: 1 to 16 lanes per entry with and without idle columns, every
+    order, a ragged last group.  Errors are about 1e-7 of a prediction each (fp32 products of `order` projections), so the
+    two measures over a set of residuals of their own size agree with the oracle's to a few 1e-6."""
+    if max(J, R) > (64 if order <= 3 else 32 if order <= 7 else 16):
+        pytest.skip("no matrix-core kernel at this order and rank, so no evaluation over projected rows")
+    dims = (11, 4, 7, 3, 5, 2, 6, 3, 2, 4)[:order]
+    w = synth.tiny_workload(order, dims, n_eval, (J,) * order, R, 16, seed=3 + order, values="normal")
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(order)
+    A = [rng.uniform(-1, 1, size=(d, J)).astype(np.float32) for d in dims]
+    B = [(rng.uniform(-1, 1, size=(J, R)) / np.sqrt(J)).astype(np.float32) for _ in dims]
+    announce("projected rows order=%d J=%d R=%d n=%d" % (order, J, R, n_eval))
+    with binding.FastTucker(dims, idx, vals, w.J, R, 1) as ft:
+        ft.ftk_set_factors(A, B)
+        got = (ft.ftk_rmse(), ft.ftk_mae())
+    assert got[0] == pytest.approx(oracle.rmse(dims, idx, vals, A, B), rel=5e-6)
+    assert got[1] == pytest.approx(oracle.errors(dims, idx, vals, A, B)[1], rel=5e-6)
+
+
 @pytest.mark.parametrize("order,dims,J,R", [
     (3, (700, 500, 90), (16, 16, 16), 16),      # matrix-core kernel for J = R = 16
     (3, (300, 200, 50), (24, 40, 9), 20),       # tiled kernel, padded ranks
