@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <numeric>
 #include <cstdarg>
 #include <cstdio>
@@ -11,6 +12,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <utility>
 #include <limits>
 #include <vector>
@@ -59,7 +61,12 @@ struct ftk_ctx {
     uint32_t* d_rec = nullptr;               // the tensor: one record per stored entry (see struct Coo)
     int rec_words = 4;
     int32_t* d_new_of_old[kMaxOrder] = {};   // internal row number of every caller row
-    float* d_stage = nullptr;                // staging for ftk_get/set_factors (largest I_n * J_n floats)
+    char* h_ring = nullptr;                  // pinned chunks that parameters and held-out sets pass through (see ring_setup)
+    char* d_ring = nullptr;                  // the same memory as the device names it
+    size_t ring_chunk = 0;                   // bytes of one chunk
+    hipEvent_t ring_event[4] = {};
+    uint32_t* d_held_out = nullptr;          // records of the held-out set being evaluated, kept up to kHeldOutKeep bytes
+    size_t held_out_bytes = 0;
     float* d_A = nullptr;
     float* d_dA = nullptr;
     float* d_B = nullptr;
@@ -211,6 +218,114 @@ float* scratch_address(const ftk_ctx* c) {
     if (c->device < 0 || c->device >= kMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     return g_scratch_ptr[c->device];
+}
+
+// ---- data between the caller's pageable memory and the GPU ----
+// It goes through a ring of pinned chunks that kernels read or write directly over the bus, while threads copy the chunks
+// before or after.  One thread copies about 10 GB/s, less where the caller's pages are touched for the first time, and the
+// bus takes several times that; so a transfer of T MB gets T threads, up to eight (a thread costs 20 us to start).
+// Factors of 208 MB out: 20.9 ms by pageable copies (and a device copy of each matrix), 7.0 ms this way, 12.1 ms with chunks
+// of 1 MB; 32 MB 2.2 and 0.9 ms; 77 KB, where one launch and one wait replace three, 0.33 and 0.03 ms.  A held-out set of
+// 330 000 entries in host arrays: 483 and 225 us for the whole evaluation.
+constexpr int kRingDepth = 4;
+constexpr size_t kRingChunkMin = 64 << 10, kRingChunkMax = 4 << 20;
+constexpr int kCopyThreads = 8;
+
+// A ring that suits a transfer of `bytes`; returns the number of threads to copy with (0: failed, c->err says why).
+int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
+    size_t chunk = kRingChunkMin;
+    while (chunk < kRingChunkMax && chunk * 16 < bytes) chunk *= 2;   // (a large ring takes long to pin: 0.15 ms per MB)
+    if (c->ring_chunk < chunk) {
+        FTK_HIP(c, hipStreamSynchronize(c->stream));
+        if (c->h_ring) hipHostFree(c->h_ring);
+        c->h_ring = nullptr;
+        c->ring_chunk = 0;
+        FTK_HIP(c, hipHostMalloc((void**)&c->h_ring, chunk * kRingDepth, hipHostMallocDefault));
+        FTK_HIP(c, hipHostGetDevicePointer((void**)&c->d_ring, c->h_ring, 0));
+        c->ring_chunk = chunk;
+        for (hipEvent_t& e : c->ring_event)
+            if (!e) FTK_HIP(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    }
+    const int cpus = (int)std::thread::hardware_concurrency();
+    *threads = (int)std::max<size_t>(1, std::min<size_t>(bytes >> 20, (size_t)std::min(kCopyThreads, cpus > 1 ? cpus / 2 : 1)));
+    return FTK_OK;
+}
+
+// Runs work(part, parts) on `parts` threads each time step() is called; step() returns when all have.
+template <class Work>
+class CopyTeam {
+public:
+    CopyTeam(int parts, Work work) : work_(work) {
+        for (int t = 1; t < parts; ++t) {
+            try {
+                team_.emplace_back([this, t] { follow(t); });
+            } catch (...) {   // no more threads: the ones there are share the work
+                break;
+            }
+        }
+        parts_ = (int)team_.size() + 1;
+        go_.store(0, std::memory_order_release);
+    }
+    ~CopyTeam() {
+        go_.store(-1, std::memory_order_release);
+        for (std::thread& t : team_) t.join();
+    }
+    CopyTeam(const CopyTeam&) = delete;
+    CopyTeam& operator=(const CopyTeam&) = delete;
+    void step(long long item) {
+        item_ = item;
+        go_.store(++steps_, std::memory_order_release);
+        work_(item, 0, parts_);
+        while (finished_.load(std::memory_order_acquire) != steps_ * (long long)team_.size()) std::this_thread::yield();
+    }
+
+private:
+    void follow(int part) {
+        for (long long seen = 0;;) {
+            long long now;
+            while ((now = go_.load(std::memory_order_acquire)) == seen || now == -2) std::this_thread::yield();
+            if (now == -1) return;
+            seen = now;
+            work_(item_, part, parts_);
+            finished_.fetch_add(1, std::memory_order_release);
+        }
+    }
+    Work work_;
+    std::vector<std::thread> team_;
+    int parts_ = 1;
+    long long item_ = 0, steps_ = 0;
+    std::atomic<long long> go_{-2}, finished_{0};   // -2: the team is still being put together, -1: over
+};
+
+// Chunks 0 .. n - 1 to the device: copy(chunk, part, parts) fills its place in the ring, launch(chunk) queues what reads it.
+template <class Copy, class Launch>
+int ring_in(ftk_ctx* c, long long n, int threads, Copy copy, Launch launch) {
+    CopyTeam<Copy> team(n > 0 ? threads : 1, copy);
+    for (long long k = 0; k < n; ++k) {
+        if (k >= kRingDepth) FTK_HIP(c, hipEventSynchronize(c->ring_event[k % kRingDepth]));
+        team.step(k);
+        launch(k);
+        FTK_HIP(c, hipGetLastError());
+        FTK_HIP(c, hipEventRecord(c->ring_event[k % kRingDepth], c->stream));
+    }
+    return FTK_OK;
+}
+
+// Chunks 0 .. n - 1 from the device: launch(chunk) queues what writes its place in the ring, copy(chunk, part, parts) empties it.
+template <class Copy, class Launch>
+int ring_out(ftk_ctx* c, long long n, int threads, Copy copy, Launch launch) {
+    CopyTeam<Copy> team(n > 0 ? threads : 1, copy);
+    long long queued = 0;
+    for (long long k = 0; k < n; ++k) {
+        for (; queued < n && queued < k + kRingDepth; ++queued) {
+            launch(queued);
+            FTK_HIP(c, hipGetLastError());
+            FTK_HIP(c, hipEventRecord(c->ring_event[queued % kRingDepth], c->stream));
+        }
+        FTK_HIP(c, hipEventSynchronize(c->ring_event[k % kRingDepth]));
+        team.step(k);
+    }
+    return FTK_OK;
 }
 
 // Raise a kernel's dynamic-LDS limit to the device maximum, once per context and kernel (the limit is
@@ -735,12 +850,15 @@ void release(ftk_ctx* c) {
     for (int n = 0; n < kMaxOrder; ++n)
         if (c->d_new_of_old[n]) hipFree(c->d_new_of_old[n]);
     if (c->d_arena) c->d_A = c->d_dA = nullptr;   // parts of the arena
-    void* ptrs[] = {c->d_arena, c->d_rec, c->d_rec_tiles, c->d_stage, c->d_A, c->d_dA, c->d_B, c->d_GB, c->d_S, c->d_flag,
+    void* ptrs[] = {c->d_arena, c->d_rec, c->d_rec_tiles, c->d_held_out, c->d_A, c->d_dA, c->d_B, c->d_GB, c->d_S, c->d_flag,
                     c->d_pos, c->d_bidx, c->d_bval, c->d_hot_partial, c->d_gb_partial, c->d_lists, c->d_list_fill,
                     c->d_bucket_info, c->d_bucket_rows, c->d_overflow};
     for (void* p : ptrs)
         if (p) hipFree(p);
     if (c->h_sums) hipHostFree(c->h_sums);
+    if (c->h_ring) hipHostFree(c->h_ring);
+    for (hipEvent_t e : c->ring_event)
+        if (e) hipEventDestroy(e);
     delete c;
 }
 
@@ -944,14 +1062,13 @@ int create_impl(ftk_ctx* c, const int64_t* dims, const int32_t* const* idx, cons
     if (c->max_lds < 65536) c->max_lds = 65536;
 
     // packed parameter layout: every mode starts on a 256-byte boundary
-    long long a_off = 0, stage = 0;
+    long long a_off = 0;
     int b_off = 0;
     for (int n = 0; n < N; ++n) {
         c->L.A_off[n] = a_off;
         c->L.B_off[n] = b_off;
         a_off += ((dims[n] * c->L.J[n] + 16 + 63) / 64) * 64;   // >= 16 floats of slack after every mode
         b_off += c->L.J[n] * c->L.R;
-        stage = std::max(stage, (long long)dims[n] * c->J_user[n]);
     }
     c->A_total = a_off;
     c->L.B_total = b_off;
@@ -983,7 +1100,7 @@ int create_impl(ftk_ctx* c, const int64_t* dims, const int32_t* const* idx, cons
     const hipMemcpyKind kind = (flags & FTK_PTRS_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     const int scan_blocks = blocks_for(c->nnz, 256, c->num_cu * 8);
     c->rec_words = record_words(N);
-    FTK_HIP(c, hipMalloc(&c->d_flag, sizeof(unsigned int)));
+    FTK_HIP(c, hipMalloc(&c->d_flag, kMaxOrder * sizeof(unsigned int)));
     FTK_HIP(c, hipMalloc(&c->d_rec, (size_t)c->nnz * c->rec_words * sizeof(uint32_t)));
     if (c->rec_words != N + 1) FTK_HIP(c, hipMemset(c->d_rec, 0, (size_t)c->nnz * c->rec_words * sizeof(uint32_t)));
     uint32_t* d_col = nullptr;        // one caller column at a time
@@ -1065,7 +1182,6 @@ int create_impl(ftk_ctx* c, const int64_t* dims, const int32_t* const* idx, cons
     }
     FTK_HIP(c, hipMalloc(&c->d_B, (size_t)c->L.B_total * sizeof(float)));
     FTK_HIP(c, hipMalloc(&c->d_GB, (size_t)c->L.B_total * sizeof(float)));
-    FTK_HIP(c, hipMalloc(&c->d_stage, (size_t)stage * sizeof(float)));
     FTK_HIP(c, hipHostMalloc((void**)&c->h_sums, (size_t)c->num_cu * kErrorBlocksPerCu * 2 * sizeof(double), hipHostMallocDefault));
     FTK_HIP(c, hipHostGetDevicePointer((void**)&c->d_sums, c->h_sums, 0));
     FTK_HIP(c, hipMemset(c->d_A, 0, (size_t)c->A_total * sizeof(float)));
@@ -1475,6 +1591,80 @@ int ftk_mae(ftk_ctx* c, double* out) {
     return FTK_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// A held-out set in host memory: its columns go through the ring, where one kernel checks, renumbers and packs them.  The
+// records' memory is kept for the next call unless it is large.
+constexpr size_t kHeldOutKeep = (size_t)64 << 20;
+int evaluate_host(ftk_ctx* c, int64_t n_eval, const int32_t* const* idx, const float* vals, double* rmse_out, double* mae_out) {
+    const int N = c->order;
+    const size_t bytes = (size_t)n_eval * c->rec_words * sizeof(uint32_t);
+    if (c->held_out_bytes < bytes) {
+        FTK_HIP(c, hipStreamSynchronize(c->stream));
+        if (c->d_held_out) hipFree(c->d_held_out);
+        c->d_held_out = nullptr;
+        c->held_out_bytes = 0;
+        FTK_HIP(c, hipMalloc(&c->d_held_out, bytes));
+        c->held_out_bytes = bytes;
+    }
+    struct GiveBack {
+        ftk_ctx* c;
+        ~GiveBack() {
+            if (c->held_out_bytes <= kHeldOutKeep) return;
+            hipStreamSynchronize(c->stream);
+            hipFree(c->d_held_out);
+            c->d_held_out = nullptr;
+            c->held_out_bytes = 0;
+        }
+    } give_back{c};
+    int threads = 1;
+    const size_t entry = (size_t)(N + 1) * sizeof(uint32_t);
+    if (const int rc = ring_setup(c, (size_t)n_eval * entry, &threads)) return rc;
+    HeldOutArgs p = {};
+    p.order = N;
+    p.words = c->rec_words;
+    for (int n = 0; n < N; ++n) {
+        p.new_of_old[n] = c->d_new_of_old[n];
+        p.dims[n] = (int32_t)c->dims[n];
+    }
+    FTK_HIP(c, hipMemsetAsync(c->d_flag, 0, kMaxOrder * sizeof(unsigned int), c->stream));
+    const long long chunk = (long long)(c->ring_chunk / entry), n_chunks = (n_eval + chunk - 1) / chunk;
+    auto place = [&](char* ring, long long k) { return reinterpret_cast<uint32_t*>(ring + (size_t)(k % kRingDepth) * c->ring_chunk); };
+    auto copy = [&](long long k, int part, int parts) {
+        const long long first = k * chunk, count = std::min<long long>(chunk, n_eval - first);
+        const long long lo = count * part / parts, hi = count * (part + 1) / parts;
+        for (int n = 0; n <= N; ++n)
+            memcpy(place(c->h_ring, k) + n * count + lo, (n < N ? (const uint32_t*)idx[n] : (const uint32_t*)vals) + first + lo,
+                   (size_t)(hi - lo) * sizeof(uint32_t));
+    };
+    auto launch = [&](long long k) {
+        const long long first = k * chunk, count = std::min<long long>(chunk, n_eval - first);
+        hipLaunchKernelGGL(pack_held_out_kernel, dim3(blocks_for(count, 256, c->num_cu * 8)), dim3(256), 0, c->stream, p,
+                           (const uint32_t*)place(c->d_ring, k), count, c->d_held_out + first * c->rec_words, c->d_flag);
+    };
+    try {
+        if (const int rc = ring_in(c, n_chunks, threads, copy, launch)) return rc;
+    } catch (...) {
+        return fail(c, FTK_ENOMEM, "host allocation failed");
+    }
+    // (entries out of range read row 0: the errors over them are taken before the count is looked at, and dropped)
+    double s[2] = {0.0, 0.0};
+    if (const int rc = launch_errors(c, Coo{c->d_held_out, c->rec_words}, n_eval, s)) return rc;
+    unsigned int bad[kMaxOrder] = {};
+    FTK_HIP(c, hipMemcpy(bad, c->d_flag, sizeof bad, hipMemcpyDeviceToHost));
+    for (int n = 0; n < N; ++n)
+        if (bad[n]) return fail(c, FTK_EINVAL, "idx[%d] holds %u entries outside [0, %lld)", n, bad[n], (long long)c->dims[n]);
+    if (rmse_out) *rmse_out = sqrt(s[0] / (double)n_eval);
+    if (mae_out) *mae_out = s[1] / (double)n_eval;
+    return FTK_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int ftk_evaluate(ftk_ctx* c, int64_t n_eval, const int32_t* const* idx, const float* vals, uint32_t flags,
                  double* rmse_out, double* mae_out) {
     if (!c) return FTK_EINVAL;
@@ -1485,7 +1675,8 @@ int ftk_evaluate(ftk_ctx* c, int64_t n_eval, const int32_t* const* idx, const fl
     const int N = c->order;
     for (int n = 0; n < N; ++n)
         if (!idx[n]) return fail(c, FTK_EINVAL, "idx[%d] is NULL", n);
-    const hipMemcpyKind kind = (flags & FTK_PTRS_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+    if (!(flags & FTK_PTRS_DEVICE)) return evaluate_host(c, n_eval, idx, vals, rmse_out, mae_out);
+    const hipMemcpyKind kind = hipMemcpyDeviceToDevice;
     uint32_t* d_rec = nullptr;
     uint32_t* d_col = nullptr;
     struct Guard {
@@ -1534,48 +1725,86 @@ double ftk_step_size(double alpha, double beta, int64_t t) {
     return alpha / denom;
 }
 
-int ftk_get_factors(ftk_ctx* c, float* const* A_out, float* const* B_out) {
-    if (!c) return FTK_EINVAL;
-    if (const int rc_dev = check_device(c)) return rc_dev;
-    for (int n = 0; n < c->order; ++n) {
-        if (A_out && A_out[n]) {
-            const long long na = c->dims[n] * c->J_user[n];
-            hipLaunchKernelGGL(permute_rows_kernel, dim3(blocks_for(na, 256, c->num_cu * 8)), dim3(256), 0, c->stream,
-                               (const float*)(c->d_A + c->L.A_off[n]), c->d_stage, (const int32_t*)c->d_new_of_old[n],
-                               (long long)c->dims[n], c->J_user[n], c->L.J[n], 0);
-            FTK_HIP(c, hipGetLastError());
-            FTK_HIP(c, hipMemcpyAsync(A_out[n], c->d_stage, (size_t)na * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-            FTK_HIP(c, hipStreamSynchronize(c->stream));
-        }
-        if (B_out && B_out[n])   // J_n rows of R floats out of rows of (padded) L.R floats
-            FTK_HIP(c, hipMemcpy2DAsync(B_out[n], (size_t)c->R_user * sizeof(float), c->d_B + c->L.B_off[n],
-                                        (size_t)c->L.R * sizeof(float), (size_t)c->R_user * sizeof(float),
-                                        (size_t)c->J_user[n], hipMemcpyDeviceToHost, c->stream));
+}  // extern "C"
+
+namespace {
+
+// The matrices that `A`, `B` name (NULL entries skipped), one after the other.
+template <class F>
+ParamSegments param_segments(const ftk_ctx* c, F* const* A, F* const* B, F** host) {
+    ParamSegments p = {};
+    for (int t = 0; t < 2 * c->order; ++t) {
+        const bool core = t >= c->order;
+        const int n = core ? t - c->order : t;
+        F* const* from = core ? B : A;
+        if (!from || !from[n]) continue;
+        const int k = p.count++;
+        host[k] = from[n];
+        p.base[k] = core ? c->d_B + c->L.B_off[n] : c->d_A + c->L.A_off[n];
+        p.new_of_old[k] = core ? nullptr : c->d_new_of_old[n];
+        p.cols[k] = core ? c->R_user : c->J_user[n];
+        p.stride[k] = core ? c->L.R : c->L.J[n];
+        p.begin[k + 1] = p.begin[k] + (core ? (long long)c->J_user[n] * c->R_user : (long long)c->dims[n] * c->J_user[n]);
+    }
+    return p;
+}
+
+// memcpy of floats [lo, hi) of the caller's sequence to or from `ring`, which holds them from float `first` on
+template <bool IN, class F>
+void copy_params(const ParamSegments& p, F* const* host, float* ring, long long first, long long lo, long long hi) {
+    for (int k = 0; k < p.count; ++k) {
+        const long long a = std::max(lo, p.begin[k]), b = std::min(hi, p.begin[k + 1]);
+        if (a >= b) continue;
+        if constexpr (IN)
+            memcpy(ring + (a - first), host[k] + (a - p.begin[k]), (size_t)(b - a) * sizeof(float));
+        else
+            memcpy(host[k] + (a - p.begin[k]), ring + (a - first), (size_t)(b - a) * sizeof(float));
+    }
+}
+
+// All of the caller's matrices in (IN) or out, in chunks of the ring.
+template <bool IN, class F>
+int move_params(ftk_ctx* c, F* const* A, F* const* B) {
+    F* host[2 * kMaxOrder] = {};
+    const ParamSegments p = param_segments(c, A, B, host);
+    const long long total = p.begin[p.count];
+    if (total == 0) return FTK_OK;
+    int threads = 1;
+    if (const int rc = ring_setup(c, (size_t)total * sizeof(float), &threads)) return rc;
+    const long long chunk = (long long)(c->ring_chunk / sizeof(float)), n = (total + chunk - 1) / chunk;
+    auto place = [&](char* ring, long long k) { return reinterpret_cast<float*>(ring + (size_t)(k % kRingDepth) * c->ring_chunk); };
+    auto copy = [&](long long k, int part, int parts) {
+        const long long first = k * chunk, count = std::min(chunk, total - first);
+        copy_params<IN>(p, host, place(c->h_ring, k), first, first + count * part / parts, first + count * (part + 1) / parts);
+    };
+    auto launch = [&](long long k) {
+        const long long first = k * chunk, count = std::min(chunk, total - first);
+        hipLaunchKernelGGL(move_params_kernel<IN>, dim3(blocks_for(count, 256, c->num_cu * 8)), dim3(256), 0, c->stream, p, place(c->d_ring, k), first, count);
+    };
+    try {
+        const int rc = IN ? ring_in(c, n, threads, copy, launch) : ring_out(c, n, threads, copy, launch);
+        if (rc != FTK_OK) return rc;
+    } catch (...) {
+        return fail(c, FTK_ENOMEM, "host allocation failed");
     }
     FTK_HIP(c, hipStreamSynchronize(c->stream));
     return FTK_OK;
 }
 
+}  // namespace
+
+extern "C" {
+
+int ftk_get_factors(ftk_ctx* c, float* const* A_out, float* const* B_out) {
+    if (!c) return FTK_EINVAL;
+    if (const int rc_dev = check_device(c)) return rc_dev;
+    return move_params<false>(c, A_out, B_out);
+}
+
 int ftk_set_factors(ftk_ctx* c, const float* const* A_in, const float* const* B_in) {
     if (!c) return FTK_EINVAL;
     if (const int rc_dev = check_device(c)) return rc_dev;
-    for (int n = 0; n < c->order; ++n) {
-        if (A_in && A_in[n]) {
-            const long long na = c->dims[n] * c->J_user[n];
-            FTK_HIP(c, hipMemcpyAsync(c->d_stage, A_in[n], (size_t)na * sizeof(float), hipMemcpyHostToDevice, c->stream));
-            hipLaunchKernelGGL(permute_rows_kernel, dim3(blocks_for(na, 256, c->num_cu * 8)), dim3(256), 0, c->stream,
-                               (const float*)c->d_stage, c->d_A + c->L.A_off[n], (const int32_t*)c->d_new_of_old[n],
-                               (long long)c->dims[n], c->J_user[n], c->L.J[n], 1);
-            FTK_HIP(c, hipGetLastError());
-            FTK_HIP(c, hipStreamSynchronize(c->stream));
-        }
-        if (B_in && B_in[n])
-            FTK_HIP(c, hipMemcpy2DAsync(c->d_B + c->L.B_off[n], (size_t)c->L.R * sizeof(float), B_in[n],
-                                        (size_t)c->R_user * sizeof(float), (size_t)c->R_user * sizeof(float),
-                                        (size_t)c->J_user[n], hipMemcpyHostToDevice, c->stream));
-    }
-    FTK_HIP(c, hipStreamSynchronize(c->stream));
-    return FTK_OK;
+    return move_params<true>(c, A_in, B_in);
 }
 
 int ftk_set_sampling(ftk_ctx* c, int rule) {

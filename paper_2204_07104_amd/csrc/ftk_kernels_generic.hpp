@@ -376,24 +376,56 @@ __global__ void __launch_bounds__(256) reorder_records_kernel(const uint32_t* __
     }
 }
 
-// Parameter rows between the caller's numbering and the internal one:
-// to_internal:  dst[new_of_old[i]][:] = src[i][:]      from_internal:  dst[i][:] = src[new_of_old[i]][:]
-// Rows between the caller's numbering (J floats per row) and the library's (renumbered, `stride`
-// floats per row, padding untouched).
-__global__ void __launch_bounds__(256) permute_rows_kernel(const float* __restrict__ src, float* __restrict__ dst,
-                                                           const int32_t* __restrict__ new_of_old, long long rows,
-                                                           int J, int stride, int to_internal) {
-    const long long total = rows * J;
-    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (long long)gridDim.x * blockDim.x) {
-        const long long i = q / J;
-        const int j = (int)(q - i * J);
-        const long long m = new_of_old[i];
-        if (to_internal)
-            dst[m * stride + j] = src[q];
+// Parameters between the caller's layout (all matrices one after the other, row-major, J or R floats per row) and the
+// library's (rows renumbered, `stride` floats per row, padding untouched), for floats [first, first + count) of the
+// caller's; `io` is pinned host memory that holds just these.  The transfer over the bus is the kernel's own reads or
+// writes of it, so nothing is staged in device memory.
+struct ParamSegments {
+    float* base[2 * kMaxOrder];
+    const int32_t* new_of_old[2 * kMaxOrder];   // NULL: rows in the caller's order
+    int cols[2 * kMaxOrder], stride[2 * kMaxOrder];
+    long long begin[2 * kMaxOrder + 1];         // first float of each matrix in the caller's sequence
+    int count;
+};
+template <bool TO_INTERNAL>
+__global__ void __launch_bounds__(256) move_params_kernel(ParamSegments p, float* __restrict__ io, long long first, long long count) {
+    for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < count; q += (long long)gridDim.x * blockDim.x) {
+        const long long f = first + q;
+        int s = 0;
+        while (s + 1 < p.count && f >= p.begin[s + 1]) ++s;
+        const unsigned long long e = (unsigned long long)(f - p.begin[s]);
+        const unsigned int cols = (unsigned int)p.cols[s];
+        // (a 64-bit division is many times the price of a 32-bit one)
+        const unsigned long long i = e >> 32 ? e / cols : (unsigned int)e / cols;
+        const unsigned int j = (unsigned int)(e - i * cols);
+        const long long m = p.new_of_old[s] ? p.new_of_old[s][i] : (long long)i;
+        float* x = p.base[s] + m * p.stride[s] + j;
+        if (TO_INTERNAL)
+            *x = io[q];
         else
-            dst[q] = src[m * stride + j];
+            io[q] = *x;
     }
+}
+
+// Records of a held-out set out of its columns in pinned host memory: column n of `count` entries at columns + n * count.
+// Row numbers are checked and go through the renumbering; bad[n] counts those out of range (which read row 0 then).
+struct HeldOutArgs {
+    const int32_t* new_of_old[kMaxOrder];
+    int32_t dims[kMaxOrder];
+    int order, words;
+};
+__global__ void __launch_bounds__(256) pack_held_out_kernel(HeldOutArgs p, const uint32_t* __restrict__ columns, long long count,
+                                                            uint32_t* __restrict__ rec, unsigned int* __restrict__ bad) {
+    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += (long long)gridDim.x * blockDim.x)
+        for (int w = 0; w < p.words; ++w) {
+            uint32_t v = w <= p.order ? columns[w * count + e] : 0u;
+            if (w < p.order) {
+                const bool ok = v < (uint32_t)p.dims[w];   // a negative number is a large unsigned one
+                if (!ok) atomicAdd(bad + w, 1u);
+                v = ok ? (uint32_t)p.new_of_old[w][v] : 0u;
+            }
+            rec[e * p.words + w] = v;
+        }
 }
 
 __global__ void __launch_bounds__(256) init_factor_kernel(float* __restrict__ out, long long rows, int J, int stride,

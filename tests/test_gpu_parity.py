@@ -612,6 +612,30 @@ def test_rmse_and_mae_match_oracle():
         assert ma == pytest.approx(want_ma, rel=1e-5)
 
 
+@pytest.mark.parametrize("dims,J,R", [
+    ((1, 1), (1, 1), 1),
+    ((4_097, 3, 259), (5, 16, 8), 9),             # one chunk of the ring, odd row lengths
+    ((70_001, 311), (61, 33), 40),                # several chunks and threads, chunk ends inside a row
+    ((300_007, 11, 2), (64, 7, 3), 5),            # more chunks than the ring holds
+])
+@pytest.mark.parametrize("flags", [0, binding.FTK_LAYOUT_EXACT])
+def test_factors_in_and_out_are_the_same_bits(dims, J, R, flags):
+    """Parameters through the pinned ring, whole and one matrix at a time: every float comes back as it went in."""
+    rng = np.random.default_rng(7)
+    idx = [rng.integers(0, d, 2_000).astype(np.int32) for d in dims]
+    A = [rng.standard_normal((d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [rng.standard_normal((j, R)).astype(np.float32) for j in J]
+    announce("factors in and out %r J=%r" % (dims, J))
+    with binding.FastTucker(dims, idx, rng.standard_normal(2_000).astype(np.float32), J, R, 1, flags=flags) as ft:
+        ft.ftk_set_factors(A, B)
+        for x, y in zip(A + B, sum(ft.ftk_get_factors(), [])):
+            assert np.array_equal(x, y)
+        ft.ftk_set_factors(None, [-b for b in B])
+        ft.ftk_set_factors([2 * a for a in A], None)
+        for x, y in zip([2 * a for a in A] + [-b for b in B], sum(ft.ftk_get_factors(), [])):
+            assert np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("order", [1, 2, 3, 6, 7, 10])
 @pytest.mark.parametrize("J,R", [(3, 1), (5, 4), (9, 8), (16, 15), (20, 17), (33, 32), (47, 48), (64, 64)])
 @pytest.mark.parametrize("n_eval", [64, 4099])
