@@ -22,6 +22,7 @@
 #include "ftk_kernels_mfma16.hpp"
 #include "ftk_kernels_tiled.hpp"
 #include "ftk_kernels_errors.hpp"
+#include "ftk_kernels_owners.hpp"
 #define FTK_INSTANCES_EXTERN
 #include "ftk_instances.hpp"   // the matrix-core kernel instances are compiled in translation units of their own
 
@@ -142,6 +143,20 @@ struct ftk_ctx {
     uint2* d_bucket_info = nullptr;
     int4* d_bucket_rows = nullptr;
     unsigned int* d_overflow = nullptr;
+    // Synchronous step by row owners in the space of the projections (ftk_kernels_owners.hpp)
+    bool auto_kernel = true;         // the kernel variant is the library's choice
+    bool own = false;                // for the current |Psi|
+    long long own_for_M = -1;
+    int own_buckets = 0, own_lists = 0, own_core_floats = 0;
+    unsigned int own_rows_per_bucket[kMaxOrder] = {}, own_bucket0[kMaxOrder + 1] = {}, own_cap[kMaxOrder] = {}, own_place0[kMaxOrder] = {};
+    unsigned int own_places = 0;
+    size_t own_append_lds = 0, own_lds = 0;
+    float* d_own_values = nullptr;
+    unsigned short* d_own_ids = nullptr;
+    unsigned int* d_own_fill = nullptr;
+    float* d_own_core = nullptr;
+    unsigned int* d_own_overflow = nullptr;
+    size_t own_value_floats = 0, own_fill_words = 0, own_core_total = 0;
     float* use_hot_partial = nullptr; // the partial tables of the step being enqueued: the two above, or the
     float* use_gb_partial = nullptr;  // library's static scratch array (ftk_sgd_step_noalloc)
 
@@ -720,6 +735,31 @@ int launch_errors_tiled_n(ftk_ctx* c, const Coo& coo, long long nnz) {
     }
 }
 
+// S^(n) = A^(n) B^(n) of all modes into d_S; S[n] receives where mode n starts.
+int launch_project(ftk_ctx* c, int Rs, const float** S_out) {
+    ProjectArgs p = {};
+    p.order = c->order;
+    p.R = c->R_user;
+    p.stride_B = c->L.R;
+    p.Rs = Rs;
+    float* S = c->d_S;
+    const int per_block = 256 / (Rs / 4) * kProjectRows;
+    for (int n = 0; n < c->order; ++n) {
+        S_out[n] = S;
+        p.A[n] = c->d_A + c->L.A_off[n];
+        p.B[n] = c->d_B + c->L.B_off[n];
+        p.S[n] = S;
+        p.rows[n] = c->dims[n];
+        p.J[n] = c->J_user[n];
+        p.stride_A[n] = c->L.J[n];
+        p.block0[n + 1] = p.block0[n] + blocks_for(c->dims[n], per_block, c->num_cu * 8);
+        S += c->dims[n] * Rs;
+    }
+    hipLaunchKernelGGL(project_rows_kernel, dim3(p.block0[c->order]), dim3(256), 0, c->stream, p);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
+
 template <int N>
 void launch_errors_rows_n(ftk_ctx* c, const Coo& coo, long long nnz, const ErrorRows& s) {
     const dim3 grid(error_blocks(c, (nnz + 63) / 64, 4)), threads(256);
@@ -755,26 +795,7 @@ int launch_errors_rows(ftk_ctx* c, const Coo& coo, long long nnz, bool* done) {
         c->d_S = nullptr;
         return FTK_OK;
     }
-    ProjectArgs p = {};
-    p.order = c->order;
-    p.R = c->R_user;
-    p.stride_B = c->L.R;
-    p.Rs = s.Rs;
-    float* S = c->d_S;
-    const int per_block = 256 / (s.Rs / 4) * kProjectRows;
-    for (int n = 0; n < c->order; ++n) {
-        s.S[n] = S;
-        p.A[n] = c->d_A + c->L.A_off[n];
-        p.B[n] = c->d_B + c->L.B_off[n];
-        p.S[n] = S;
-        p.rows[n] = c->dims[n];
-        p.J[n] = c->J_user[n];
-        p.stride_A[n] = c->L.J[n];
-        p.block0[n + 1] = p.block0[n] + blocks_for(c->dims[n], per_block, c->num_cu * 8);
-        S += c->dims[n] * s.Rs;
-    }
-    hipLaunchKernelGGL(project_rows_kernel, dim3(p.block0[c->order]), dim3(256), 0, c->stream, p);
-    FTK_HIP(c, hipGetLastError());
+    if (const int rc = launch_project(c, s.Rs, s.S)) return rc;
     switch (c->order) {
         case 1: launch_errors_rows_n<1>(c, coo, nnz, s); break;
         case 2: launch_errors_rows_n<2>(c, coo, nnz, s); break;
@@ -852,7 +873,8 @@ void release(ftk_ctx* c) {
     if (c->d_arena) c->d_A = c->d_dA = nullptr;   // parts of the arena
     void* ptrs[] = {c->d_arena, c->d_rec, c->d_rec_tiles, c->d_held_out, c->d_A, c->d_dA, c->d_B, c->d_GB, c->d_S, c->d_flag,
                     c->d_pos, c->d_bidx, c->d_bval, c->d_hot_partial, c->d_gb_partial, c->d_lists, c->d_list_fill,
-                    c->d_bucket_info, c->d_bucket_rows, c->d_overflow};
+                    c->d_bucket_info, c->d_bucket_rows, c->d_overflow, c->d_own_values, c->d_own_ids, c->d_own_fill, c->d_own_core,
+                    c->d_own_overflow};
     for (void* p : ptrs)
         if (p) hipFree(p);
     if (c->h_sums) hipHostFree(c->h_sums);
@@ -1047,6 +1069,247 @@ int plan_rows(ftk_ctx* c, long long n_samples) {
     c->rows_list_words = (unsigned int)std::max<unsigned long long>(words, 1);
     c->rows_apply_lds = std::max<size_t>(lds_cells, 1) * sizeof(float);
     c->tiled_lds_bytes += 4 * tiled_rows_lds_words(N, c->tiled_waves, c->rows_n_buckets);
+    return FTK_OK;
+}
+
+// When the row owners are the faster way.  Per step, owners against the atomic kernels (modes hit evenly):
+//   order 10, R = 4, 10 000 rows per mode: 2e4 samples 51 / 43 us, 5e4 54 / 62, 1e5 62 / 85, 1e6 244 / 537
+//   order 4, R = 4: 5e4 samples 45 / 28 us, 3e5 73 / 82;  order 7, R = 8: 1e5 73 / 67, 3e5 128 / 137
+//   order 3, R = 8, 180 000 rows: 3e5 76 / 70, 1e6 153 / 176;  order 6, R = 4: 1e6 175 / 324
+//   order 6, R = 16: 2e6 689 / 625 (an entry is 64 bytes, written and read once: no gain over an atomic)
+//   order 3, R = 8, 6 000 rows: 1e6 236 / 137 (few rows in a bucket: lanes meet on them and repeat their swaps)
+constexpr int kOwnersRank = 8;                  // R
+constexpr double kOwnersEntries4 = 9e5, kOwnersEntries8 = 2e6;   // samples x modes, for R <= 4 and above
+constexpr double kOwnersCold = 0.5;             // share of the row updates that no on-chip table takes
+constexpr double kOwnersRows = 0.5;             // rows of all modes against samples x modes
+constexpr long long kOwnersBucketRows = 48;     // least rows in a bucket
+
+// Whether the synchronous step over n_samples samples goes by row owners, with what buckets and lists, and their memory.
+// Not an error if not: the other kernels do every step.
+void plan_owners(ftk_ctx* c, long long n_samples) {
+    c->own = false;
+    const int N = c->order, Rs = (c->R_user + 3) & ~3;
+    if (!c->auto_kernel || c->variant == V_GENERIC || N < 2 || c->R_user > kOwnersRank) return;
+    long long rows_total = 0;
+    double cold = 0.0;
+    for (int n = 0; n < N; ++n) {
+        if (c->J_user[n] > kProjectMaxRank || c->dims[n] >= (1LL << 24)) return;
+        rows_total += c->dims[n];
+        double on_chip = 0.0;
+        for (int r = 0; r < c->hot_K[n]; ++r) on_chip += (double)c->sorted_counts[n][r];
+        cold += 1.0 - on_chip / (double)c->nnz;
+    }
+    const double entries = (double)n_samples * N;
+    if (cold < kOwnersCold * N || entries < (Rs <= 4 ? kOwnersEntries4 : kOwnersEntries8) || (double)rows_total > kOwnersRows * entries) return;
+    // Buckets: as many as two workgroups per CU own at once, or a multiple of that, with their sums in half of a CU's LDS.  Every
+    // mode has one entry per sample, so the modes get the same number of buckets, but for those whose rows need more.
+    const long long most_rows = std::min<long long>(65535, ((long long)c->max_lds / 8 - c->num_cu) / (Rs + 1));
+    int n_buckets = 0;
+    for (int m = 1;; ++m) {
+        const long long target = 2LL * c->num_cu * m;
+        if (target > kOwnersMaxBuckets) return;
+        long long nb[kMaxOrder], left = target;
+        for (int n = 0; n < N; ++n) left -= nb[n] = (c->dims[n] + most_rows - 1) / most_rows;
+        if (left < 0) continue;
+        for (bool given = true; given && left > 0;) {   // one more to the modes that have the fewest
+            given = false;
+            long long fewest = target;
+            for (int n = 0; n < N; ++n)
+                if (nb[n] < c->dims[n]) fewest = std::min(fewest, nb[n]);
+            for (int n = 0; n < N && left > 0; ++n)
+                if (nb[n] == fewest && nb[n] < c->dims[n]) {
+                    nb[n] += 1;
+                    left -= 1;
+                    given = true;
+                }
+        }
+        n_buckets = 0;
+        for (int n = 0; n < N; ++n) {
+            const long long per = (c->dims[n] + nb[n] - 1) / nb[n];
+            if (per < kOwnersBucketRows) return;
+            c->own_rows_per_bucket[n] = (unsigned int)per;
+            c->own_bucket0[n] = (unsigned int)n_buckets;
+            n_buckets += (int)((c->dims[n] + per - 1) / per);
+        }
+        for (int n = N; n <= kMaxOrder; ++n) c->own_bucket0[n] = (unsigned int)n_buckets;
+        break;
+    }
+    // the fullest bucket of every mode (rows are numbered by descending frequency: its first)
+    double share[kMaxOrder] = {}, fullest = 0.0;
+    for (int n = 0; n < N; ++n) {
+        for (unsigned int r = 0; r < c->own_rows_per_bucket[n] && r < (unsigned int)c->dims[n]; ++r) share[n] += (double)c->sorted_counts[n][r];
+        share[n] /= (double)c->nnz;
+        fullest = std::max(fullest, share[n]);
+    }
+    if (fullest * n_buckets > 1.6 * N) return;   // uneven: the owner of the fullest bucket would work on alone
+    // one workgroup of the appending pass per CU, but no more than give every wave 64 samples: a bucket has a list in each
+    int lists = (int)std::max<long long>(1, std::min<long long>(c->num_cu, (n_samples + kAppendThreads - 1) / kAppendThreads));
+    unsigned long long places = 0;
+    for (;; lists += c->num_cu) {
+        if (lists > 8 * c->num_cu) return;
+        places = 0;
+        for (int n = 0; n < N; ++n) {
+            const double expect = share[n] * (double)n_samples / lists;
+            c->own_cap[n] = (unsigned int)std::ceil(expect + 4.0 * std::sqrt(expect) + 8.0);
+            c->own_place0[n] = (unsigned int)places;
+            places += (unsigned long long)c->own_cap[n] * ((n + 1 < N ? c->own_bucket0[n + 1] : (unsigned int)n_buckets) - c->own_bucket0[n]);
+        }
+        places = (places + 1) & ~1ull;
+        if (4ull * n_buckets + 2 * places <= (unsigned long long)c->max_lds) break;
+    }
+    c->own_places = (unsigned int)places;
+    c->own_buckets = n_buckets;
+    c->own_lists = lists;
+    c->own_append_lds = 4 * (size_t)n_buckets + 2 * places;
+    c->own_lds = (size_t)kOwnThreads * Rs * sizeof(float);
+    c->own_core_floats = 0;
+    for (int n = 0; n < N; ++n) {
+        c->own_lds = std::max(c->own_lds, ((size_t)c->own_rows_per_bucket[n] * (Rs + 1) + lists) * sizeof(float));
+        c->own_core_floats = std::max(c->own_core_floats, c->J_user[n] * c->R_user);
+    }
+    // memory
+    const size_t values = (size_t)lists * places * Rs, fill = (size_t)lists * n_buckets, core = (size_t)n_buckets * c->own_core_floats;
+    if (!c->d_S || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return;
+        }
+        size_t free_bytes = 0, all_bytes = 0;
+        if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes) return;
+        hipStreamSynchronize(c->stream);
+        auto grow = [&](auto*& ptr, size_t& have, size_t want) {
+            if (ptr && have >= want) return true;
+            if (ptr) hipFree(ptr);
+            ptr = nullptr;
+            have = 0;
+            if (hipMalloc((void**)&ptr, want * sizeof(*ptr)) != hipSuccess) {
+                (void)hipGetLastError();
+                ptr = nullptr;
+                return false;
+            }
+            have = want;
+            return true;
+        };
+        size_t ids_have = c->d_own_ids ? c->own_value_floats / Rs : 0, one = c->d_own_overflow ? 1 : 0, s_have = c->d_S ? (size_t)rows_total * Rs : 0;
+        const bool ok = grow(c->d_own_ids, ids_have, values / Rs) && grow(c->d_own_values, c->own_value_floats, values) &&
+                        grow(c->d_own_fill, c->own_fill_words, fill) && grow(c->d_own_core, c->own_core_total, core) &&
+                        grow(c->d_S, s_have, (size_t)rows_total * Rs);
+        if (!ok) return;
+        if (!one) {
+            if (!grow(c->d_own_overflow, one, 1)) return;
+            if (hipMemset(c->d_own_overflow, 0, sizeof(unsigned int)) != hipSuccess) return;
+        }
+    }
+    c->own = true;
+}
+
+template <int N, int G>
+int launch_append_ng(ftk_ctx* c, const AppendArgs& g) {
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(append_lists_kernel<N, G>), c->max_lds)) return rc;
+    hipLaunchKernelGGL((append_lists_kernel<N, G>), dim3(c->own_lists), dim3(kAppendThreads), c->own_append_lds, c->stream, g);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
+template <int N>
+int launch_append_n(ftk_ctx* c, const AppendArgs& g) {
+    return g.Rs <= 4 ? launch_append_ng<N, 1>(c, g) : launch_append_ng<N, 2>(c, g);
+}
+template <int G>
+int launch_own_g(ftk_ctx* c, const OwnArgs& g) {
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(own_rows_kernel<G>), c->max_lds)) return rc;
+    hipLaunchKernelGGL(own_rows_kernel<G>, dim3(c->own_buckets), dim3(kOwnThreads), c->own_lds, c->stream, g);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
+
+// One synchronous step by row owners.
+int step_owners(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, float lambda_B) {
+    const int N = c->order;
+    AppendArgs a = {};
+    a.coo = sampled_records(c);
+    a.rule = sample_rule(c);
+    a.seed = c->sample_seed;
+    a.M = c->n_samples;
+    a.Rs = (c->R_user + 3) & ~3;
+    a.places = c->own_places;
+    a.n_buckets = c->own_buckets;
+    a.values = c->d_own_values;
+    a.ids = c->d_own_ids;
+    a.fill = c->d_own_fill;
+    a.A = c->d_A;
+    a.B = c->d_B;
+    a.dA = c->d_dA;
+    a.GB = c->d_GB;
+    a.R = c->R_user;
+    a.stride_B = c->L.R;
+    a.lambda_A = lambda_A;
+    a.overflow = c->d_own_overflow;
+    OwnArgs o = {};
+    o.values = c->d_own_values;
+    o.ids = c->d_own_ids;
+    o.fill = c->d_own_fill;
+    o.order = N;
+    o.Rs = a.Rs;
+    o.R = c->R_user;
+    o.stride_B = c->L.R;
+    o.lists = c->own_lists;
+    o.places = c->own_places;
+    o.A = c->d_A;
+    o.dA = c->d_dA;
+    o.B = c->d_B;
+    o.core = c->d_own_core;
+    o.core_floats = c->own_core_floats;
+    o.overflow = c->d_own_overflow;
+    o.lr_A = lr_A;
+    o.lambda_A = lambda_A;
+    FinishArgs f = {};
+    f.core = c->d_own_core;
+    f.core_floats = c->own_core_floats;
+    f.order = N;
+    f.R = c->R_user;
+    f.stride_B = c->L.R;
+    f.B = c->d_B;
+    f.GB = c->d_GB;
+    f.overflow = c->d_own_overflow;
+    f.lr_B = lr_B;
+    f.lambda_B = lambda_B;
+    f.inv_M = 1.0f / (float)c->n_samples;
+    for (int n = 0; n < N; ++n) {
+        a.rows_per_bucket[n] = o.rows_per_bucket[n] = c->own_rows_per_bucket[n];
+        a.inv_rows_per_bucket[n] = 1.0f / (float)c->own_rows_per_bucket[n];
+        a.bucket0[n] = c->own_bucket0[n];
+        a.cap[n] = o.cap[n] = c->own_cap[n];
+        a.place0[n] = o.place0[n] = c->own_place0[n];
+        a.A_off[n] = o.A_off[n] = c->L.A_off[n];
+        a.B_off[n] = o.B_off[n] = f.B_off[n] = c->L.B_off[n];
+        a.J[n] = o.J[n] = c->L.J[n];
+        o.J_user[n] = f.J[n] = c->J_user[n];
+        o.rows[n] = c->dims[n];
+    }
+    for (int n = 0; n <= kMaxOrder; ++n) o.bucket0[n] = f.bucket0[n] = c->own_bucket0[n];
+    {
+        Bracket t(c, FTK_K_GRAD);
+        if (const int rc = launch_project(c, a.Rs, a.S)) return rc;
+        int rc;
+        switch (N) {
+            case 2: rc = launch_append_n<2>(c, a); break;
+            case 3: rc = launch_append_n<3>(c, a); break;
+            case 4: rc = launch_append_n<4>(c, a); break;
+            case 5: rc = launch_append_n<5>(c, a); break;
+            case 6: rc = launch_append_n<6>(c, a); break;
+            case 7: rc = launch_append_n<7>(c, a); break;
+            case 8: rc = launch_append_n<8>(c, a); break;
+            case 9: rc = launch_append_n<9>(c, a); break;
+            default: rc = launch_append_n<10>(c, a); break;
+        }
+        if (rc != FTK_OK) return rc;
+    }
+    Bracket t(c, FTK_K_APPLY);
+    if (const int rc = a.Rs <= 4 ? launch_own_g<1>(c, o) : launch_own_g<2>(c, o)) return rc;
+    const int per_mode = (c->own_core_floats + 63) / 64;
+    hipLaunchKernelGGL(finish_core_kernel, dim3(per_mode * N), dim3(256), 0, c->stream, f, per_mode);
+    FTK_HIP(c, hipGetLastError());
     return FTK_OK;
 }
 
@@ -1345,6 +1608,11 @@ int ftk_sample(ftk_ctx* c, uint64_t seed, int64_t n_samples) {
             return rc;
         }
     }
+    if (c->own_for_M != n_samples) {
+        c->own_for_M = n_samples;
+        c->own = false;
+        if (check_device(c) == FTK_OK) plan_owners(c, n_samples);
+    }
     return FTK_OK;
 }
 
@@ -1372,6 +1640,7 @@ int ftk_sgd_step(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, float lambd
     if (!c) return FTK_EINVAL;
     if (const int rc_dev = check_device(c)) return rc_dev;
     if (c->n_samples < 1) return fail(c, FTK_ESTATE, "ftk_sgd_step before ftk_sample");
+    if (c->own && c->mode == FTK_SYNC) return step_owners(c, lr_A, lr_B, lambda_A, lambda_B);
     c->use_hot_partial = c->d_hot_partial;
     c->use_gb_partial = c->d_gb_partial;
     return step_impl(c, lr_A, lr_B, lambda_A, lambda_B);
@@ -1831,6 +2100,8 @@ int ftk_set_sampling(ftk_ctx* c, int rule) {
     }
     if (rule != c->sampling) c->batch_valid = false;
     c->sampling = rule;
+    c->own = false;
+    c->own_for_M = -1;
     if (c->variant != V_GENERIC)
         if (const int rc = pick_hot_rows(c, std::max<long long>(c->n_samples, 1))) return rc;
     return prepare_variant(c);
@@ -1905,7 +2176,10 @@ int ftk_set_kernel(ftk_ctx* c, const char* name) {
     if (!name) return fail(c, FTK_EINVAL, "name is NULL");
     if (const int rc_dev = check_device(c)) return rc_dev;
     // the accumulators of both variants are clean between steps, so switching is always safe
-    if (!strcmp(name, "auto"))
+    c->auto_kernel = !strcmp(name, "auto");
+    c->own = false;
+    c->own_for_M = -1;   // planned again with the next ftk_sample
+    if (c->auto_kernel)
         name = (c->mfma16_ok && (c->order <= 5 || !c->tiled_ok)) ? "mfma16" : c->tiled_ok ? "tiled" : c->mfma16_ok ? "mfma16" : "generic";
     if (!strcmp(name, "rows") || !strcmp(name, "rows:tight")) {
         if (!c->rows_ok)

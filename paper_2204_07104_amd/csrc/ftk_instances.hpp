@@ -5,6 +5,7 @@
 #include "ftk_kernels_mfma16.hpp"
 #include "ftk_kernels_tiled.hpp"
 #include "ftk_kernels_errors.hpp"
+#include "ftk_kernels_owners.hpp"
 
 // J_n = R = 16 kernel, order N: both sampling rules x the four passes, and the evaluation pass
 #define FTK_MFMA16_INSTANCES(X, XE, N)                                                    \
@@ -24,6 +25,10 @@
 // evaluation pass over projected rows, order N: 1, 2, 4, 8 or 16 lanes per entry
 #define FTK_ROWS_INSTANCES(X, N) X(N, 1) X(N, 2) X(N, 4) X(N, 8) X(N, 16)
 
+// row owners, order N >= 2: 1 or 2 lanes per sample
+#define FTK_APPEND_INSTANCES(X, N) X(N, 1) X(N, 2)
+
+#define FTK_APPEND(N, G) template __global__ void ftk::append_lists_kernel<N, G>(ftk::AppendArgs);
 #define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_GRAD_MFMA16(N, T, M) template __global__ void ftk::grad_mfma16_kernel<N, T, M>(ftk::Mfma16Args);
 #define FTK_ERRORS_MFMA16(N) \
@@ -53,4 +58,8 @@ FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
 FTK_ROWS_INSTANCES(FTK_X_ER, 1) FTK_ROWS_INSTANCES(FTK_X_ER, 2) FTK_ROWS_INSTANCES(FTK_X_ER, 3) FTK_ROWS_INSTANCES(FTK_X_ER, 4)
 FTK_ROWS_INSTANCES(FTK_X_ER, 5) FTK_ROWS_INSTANCES(FTK_X_ER, 6) FTK_ROWS_INSTANCES(FTK_X_ER, 7) FTK_ROWS_INSTANCES(FTK_X_ER, 8)
 FTK_ROWS_INSTANCES(FTK_X_ER, 9) FTK_ROWS_INSTANCES(FTK_X_ER, 10)
+#define FTK_X_AP(N, G) extern FTK_APPEND(N, G)
+FTK_APPEND_INSTANCES(FTK_X_AP, 2) FTK_APPEND_INSTANCES(FTK_X_AP, 3) FTK_APPEND_INSTANCES(FTK_X_AP, 4)
+FTK_APPEND_INSTANCES(FTK_X_AP, 5) FTK_APPEND_INSTANCES(FTK_X_AP, 6) FTK_APPEND_INSTANCES(FTK_X_AP, 7)
+FTK_APPEND_INSTANCES(FTK_X_AP, 8) FTK_APPEND_INSTANCES(FTK_X_AP, 9) FTK_APPEND_INSTANCES(FTK_X_AP, 10)
 #endif

@@ -612,6 +612,46 @@ def test_rmse_and_mae_match_oracle():
         assert ma == pytest.approx(want_ma, rel=1e-5)
 
 
+OWNER_CASES = [
+    # order, rows per mode, J, R, stored entries, |Psi|: modes hit evenly, enough samples x modes, ranks up to 8
+    (10, (10_000,) * 10, (4,) * 10, 4, 400_000, 100_001),
+    (2, (60_013, 40_009), (9, 3), 1, 300_000, 460_001),            # one column in use out of four, a ragged last group
+    (3, (30_011, 70_001, 26_000), (16, 5, 64), 7, 500_000, 700_003),   # idle columns, one row of B per thread group of 64
+    (7, (9_001, 8_000, 12_007, 6_500, 9_999, 7_000, 8_192), (8, 3, 8, 8, 1, 8, 12), 8, 300_000, 300_007),
+]
+
+
+@pytest.mark.parametrize("order,dims,J,R,nnz,M", OWNER_CASES)
+@pytest.mark.parametrize("tiles", [False, True])
+def test_step_by_row_owners(order, dims, J, R, nnz, M, tiles):
+    """Large sample sets over evenly hit modes at small ranks: the step sums R numbers per row and sample in lists and
+    applies B and A per row.  Every parameter against the oracle's step, then a step on the kernel with atomics (set by
+    name), which finds the accumulators as it needs them, and one on the owners again.  Under the tile
+    rule every run of 64 entries is drawn many times, so that lists fill up and rows take the fallback."""
+    announce("row owners order=%d J=%r R=%d M=%d%s" % (order, J, R, M, ", tiles" if tiles else ""))
+    w = synth.tiny_workload(order, dims, 6_400 if tiles else nnz, J, R, M, seed=50 + order, values="normal")
+    # an element moves by many tolerances: hits x |GS| x e
+    w = synth.replace(w, lr_A=0.2 * 6_400 / M if tiles else 0.005, lr_B=0.1, lambda_A=0.05, lambda_B=0.02)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(order)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
+    draw = oracle.sample_positions_tiles if tiles else oracle.sample_positions
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_set_factors(A, B)
+        if tiles:
+            ft.ftk_set_sampling(binding.FTK_SAMPLE_TILES)
+        for t, kernel in enumerate(("auto", "tiled", "auto")):
+            ft.ftk_set_kernel(kernel)
+            ft.ftk_sample(900 + t, M)
+            ft.ftk_sgd_step(w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
+            oracle.sgd_step_sync(dims, idx, vals, A, B, draw(900 + t, M, w.nnz), w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
+            gA, gB = ft.ftk_get_factors()
+            assert_params_close(gA, A, "A, step %d" % t)
+            assert_params_close(gB, B, "B, step %d" % t)
+            A, B = gA, gB      # the next step is compared from where this one ended: one step's bound for each
+
+
 @pytest.mark.parametrize("dims,J,R", [
     ((1, 1), (1, 1), 1),
     ((4_097, 3, 259), (5, 16, 8), 9),             # one chunk of the ring, odd row lengths
