@@ -249,7 +249,7 @@ constexpr int kCopyThreads = 8;
 // A ring that suits a transfer of `bytes`; returns the number of threads to copy with (0: failed, c->err says why).
 int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
     size_t chunk = kRingChunkMin;
-    while (chunk < kRingChunkMax && chunk * 16 < bytes) chunk *= 2;   // (a large ring takes long to pin: 0.15 ms per MB)
+    while (chunk < kRingChunkMax && chunk * 8 < bytes) chunk *= 2;   // (a large ring takes long to pin: 0.15 ms per MB)
     if (c->ring_chunk < chunk) {
         FTK_HIP(c, hipStreamSynchronize(c->stream));
         if (c->h_ring) hipHostFree(c->h_ring);
@@ -735,6 +735,11 @@ int launch_errors_tiled_n(ftk_ctx* c, const Coo& coo, long long nnz) {
     }
 }
 
+// The most frequent rows in LDS (plan_hot_errors): from four in ten gathers on, where a table row is used 20 times by its
+// workgroup.  1e8 entries of two skewed modes and one of 2 200 rows: R = 16 1 430 -> 934 us, R = 8 1 258 -> 616 us; wider
+// rows are better left to the caches (R = 32, 2.5e8 entries: 4.35 ms and 4.69 with tables; R = 64, 1e8: 3.28 and 5.68).
+constexpr double kErrorHotShare = 0.4, kErrorHotReuse = 20.0;
+
 // S^(n) = A^(n) B^(n) of all modes into d_S; S[n] receives where mode n starts.
 int launch_project(ftk_ctx* c, int Rs, const float** S_out) {
     ProjectArgs p = {};
@@ -760,14 +765,56 @@ int launch_project(ftk_ctx* c, int Rs, const float** S_out) {
     return FTK_OK;
 }
 
+template <int N, int G>
+int launch_errors_rows_ng(ftk_ctx* c, const Coo& coo, long long nnz, const ErrorRows& s, bool hot) {
+    if constexpr (G <= 4) {
+        if (hot) {
+            if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(errors_rows_kernel<N, G, true>), c->max_lds - 1024)) return rc;
+            c->error_grid = c->num_cu;
+            hipLaunchKernelGGL((errors_rows_kernel<N, G, true>), dim3(c->error_grid), dim3(kErrorHotThreads),
+                               ((size_t)s.hot_rows * s.Rs + error_hot_floats(N)) * sizeof(float), c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+            FTK_HIP(c, hipGetLastError());
+            return FTK_OK;
+        }
+    }
+    const dim3 grid(error_blocks(c, (nnz + 63) / 64, 4));
+    hipLaunchKernelGGL((errors_rows_kernel<N, G, false>), grid, dim3(256), 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
 template <int N>
-void launch_errors_rows_n(ftk_ctx* c, const Coo& coo, long long nnz, const ErrorRows& s) {
-    const dim3 grid(error_blocks(c, (nnz + 63) / 64, 4)), threads(256);
-    if (s.Rs <= 4) hipLaunchKernelGGL((errors_rows_kernel<N, 1>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
-    else if (s.Rs <= 8) hipLaunchKernelGGL((errors_rows_kernel<N, 2>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
-    else if (s.Rs <= 16) hipLaunchKernelGGL((errors_rows_kernel<N, 4>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
-    else if (s.Rs <= 32) hipLaunchKernelGGL((errors_rows_kernel<N, 8>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
-    else hipLaunchKernelGGL((errors_rows_kernel<N, 16>), grid, threads, 0, c->stream, coo, (uint64_t)nnz, s, c->d_sums);
+int launch_errors_rows_n(ftk_ctx* c, const Coo& coo, long long nnz, const ErrorRows& s, bool hot) {
+    return s.Rs <= 4 ? launch_errors_rows_ng<N, 1>(c, coo, nnz, s, hot) : s.Rs <= 8 ? launch_errors_rows_ng<N, 2>(c, coo, nnz, s, hot)
+           : s.Rs <= 16 ? launch_errors_rows_ng<N, 4>(c, coo, nnz, s, hot) : s.Rs <= 32 ? launch_errors_rows_ng<N, 8>(c, coo, nnz, s, hot)
+                                                                             : launch_errors_rows_ng<N, 16>(c, coo, nnz, s, hot);
+}
+
+// The most frequent rows that the LDS of a CU holds (most frequent first over all modes), where they serve enough of the
+// gathers and the set is large enough to pay for filling the tables.
+bool plan_hot_errors(const ftk_ctx* c, long long nnz, ErrorRows& s) {
+    const long long most = ((long long)(c->max_lds - 2048) / 4 - error_hot_floats(c->order)) / s.Rs;
+    if (most < 16 || s.Rs > 16) return false;
+    double served = 0.0;
+    for (int n = 0; n < c->order; ++n) {
+        s.K[n] = 0;
+        if ((unsigned long long)c->dims[n] * s.Rs * 4 >= 0xffffff00ull) return false;
+        s.bytes[n] = (unsigned int)(c->dims[n] * s.Rs * 4);
+    }
+    long long taken = 0;
+    for (; taken < most; ++taken) {
+        int best = -1;
+        for (int n = 0; n < c->order; ++n)
+            if (s.K[n] < c->dims[n] && (best < 0 || c->sorted_counts[n][s.K[n]] > c->sorted_counts[best][s.K[best]])) best = n;
+        if (best < 0) break;
+        served += (double)c->sorted_counts[best][s.K[best]];
+        s.K[best] += 1;
+    }
+    s.hot_rows = 0;
+    for (int n = 0; n < c->order; ++n) {
+        s.hot0[n] = s.hot_rows;
+        s.hot_rows += s.K[n];
+    }
+    return served >= kErrorHotShare * (double)c->nnz * c->order && (double)nnz * c->order >= kErrorHotReuse * (double)taken * c->num_cu;
 }
 
 // The pass over projected rows (ftk_kernels_errors.hpp), where the shape allows it and it pays; `done` says whether it ran.
@@ -796,20 +843,22 @@ int launch_errors_rows(ftk_ctx* c, const Coo& coo, long long nnz, bool* done) {
         return FTK_OK;
     }
     if (const int rc = launch_project(c, s.Rs, s.S)) return rc;
+    const bool hot = plan_hot_errors(c, nnz, s);
+    int rc = FTK_OK;
     switch (c->order) {
-        case 1: launch_errors_rows_n<1>(c, coo, nnz, s); break;
-        case 2: launch_errors_rows_n<2>(c, coo, nnz, s); break;
-        case 3: launch_errors_rows_n<3>(c, coo, nnz, s); break;
-        case 4: launch_errors_rows_n<4>(c, coo, nnz, s); break;
-        case 5: launch_errors_rows_n<5>(c, coo, nnz, s); break;
-        case 6: launch_errors_rows_n<6>(c, coo, nnz, s); break;
-        case 7: launch_errors_rows_n<7>(c, coo, nnz, s); break;
-        case 8: launch_errors_rows_n<8>(c, coo, nnz, s); break;
-        case 9: launch_errors_rows_n<9>(c, coo, nnz, s); break;
-        default: launch_errors_rows_n<10>(c, coo, nnz, s); break;
+        case 1: rc = launch_errors_rows_n<1>(c, coo, nnz, s, hot); break;
+        case 2: rc = launch_errors_rows_n<2>(c, coo, nnz, s, hot); break;
+        case 3: rc = launch_errors_rows_n<3>(c, coo, nnz, s, hot); break;
+        case 4: rc = launch_errors_rows_n<4>(c, coo, nnz, s, hot); break;
+        case 5: rc = launch_errors_rows_n<5>(c, coo, nnz, s, hot); break;
+        case 6: rc = launch_errors_rows_n<6>(c, coo, nnz, s, hot); break;
+        case 7: rc = launch_errors_rows_n<7>(c, coo, nnz, s, hot); break;
+        case 8: rc = launch_errors_rows_n<8>(c, coo, nnz, s, hot); break;
+        case 9: rc = launch_errors_rows_n<9>(c, coo, nnz, s, hot); break;
+        default: rc = launch_errors_rows_n<10>(c, coo, nnz, s, hot); break;
     }
-    *done = true;
-    return FTK_OK;
+    *done = rc == FTK_OK;
+    return rc;
 }
 
 // Sums of squared and absolute errors over `nnz` packed records (internal row numbers).

@@ -13,6 +13,7 @@ FTK_TILED_INSTANCES(FTK_GRAD_TILED, FTK_ERRORS_TILED, FTK_INST_ORDER)
 FTK_TILED_INSTANCES_HIGH(FTK_GRAD_TILED, FTK_ERRORS_TILED, FTK_INST_ORDER)
 #endif
 FTK_ROWS_INSTANCES(FTK_ERRORS_ROWS, FTK_INST_ORDER)
+FTK_HOT_INSTANCES(FTK_ERRORS_HOT, FTK_INST_ORDER)
 #if FTK_INST_ORDER >= 2
 FTK_APPEND_INSTANCES(FTK_APPEND, FTK_INST_ORDER)
 #endif

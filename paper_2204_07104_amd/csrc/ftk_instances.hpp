@@ -24,12 +24,14 @@
 
 // evaluation pass over projected rows, order N: 1, 2, 4, 8 or 16 lanes per entry
 #define FTK_ROWS_INSTANCES(X, N) X(N, 1) X(N, 2) X(N, 4) X(N, 8) X(N, 16)
+#define FTK_HOT_INSTANCES(X, N) X(N, 1) X(N, 2) X(N, 4)   // with the frequent rows in LDS
 
 // row owners, order N >= 2: 1 or 2 lanes per sample
 #define FTK_APPEND_INSTANCES(X, N) X(N, 1) X(N, 2)
 
 #define FTK_APPEND(N, G) template __global__ void ftk::append_lists_kernel<N, G>(ftk::AppendArgs);
-#define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
+#define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G, false>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
+#define FTK_ERRORS_HOT(N, G) template __global__ void ftk::errors_rows_kernel<N, G, true>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_GRAD_MFMA16(N, T, M) template __global__ void ftk::grad_mfma16_kernel<N, T, M>(ftk::Mfma16Args);
 #define FTK_ERRORS_MFMA16(N) \
     template __global__ void ftk::errors_mfma16_kernel<N>(ftk::Coo, uint64_t, const float*, const float*, ftk::Layout, ftk::ModeBytes, double*);
@@ -55,6 +57,10 @@
 #define FTK_X_ET(N, P, X4) extern FTK_ERRORS_TILED(N, P, X4)
 FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
 #define FTK_X_ER(N, G) extern FTK_ERRORS_ROWS(N, G)
+#define FTK_X_EH(N, G) extern FTK_ERRORS_HOT(N, G)
+FTK_HOT_INSTANCES(FTK_X_EH, 1) FTK_HOT_INSTANCES(FTK_X_EH, 2) FTK_HOT_INSTANCES(FTK_X_EH, 3) FTK_HOT_INSTANCES(FTK_X_EH, 4)
+FTK_HOT_INSTANCES(FTK_X_EH, 5) FTK_HOT_INSTANCES(FTK_X_EH, 6) FTK_HOT_INSTANCES(FTK_X_EH, 7) FTK_HOT_INSTANCES(FTK_X_EH, 8)
+FTK_HOT_INSTANCES(FTK_X_EH, 9) FTK_HOT_INSTANCES(FTK_X_EH, 10)
 FTK_ROWS_INSTANCES(FTK_X_ER, 1) FTK_ROWS_INSTANCES(FTK_X_ER, 2) FTK_ROWS_INSTANCES(FTK_X_ER, 3) FTK_ROWS_INSTANCES(FTK_X_ER, 4)
 FTK_ROWS_INSTANCES(FTK_X_ER, 5) FTK_ROWS_INSTANCES(FTK_X_ER, 6) FTK_ROWS_INSTANCES(FTK_X_ER, 7) FTK_ROWS_INSTANCES(FTK_X_ER, 8)
 FTK_ROWS_INSTANCES(FTK_X_ER, 9) FTK_ROWS_INSTANCES(FTK_X_ER, 10)

@@ -4,8 +4,9 @@
 // once, S^(n) = A^(n) B^(n) (project_rows_kernel, one streaming pass over A), and an entry then only gathers N rows of S
 // and multiplies them, x^ = sum_r prod_n S^(n)[i_n, r].  No matrix instruction and no exchange between layouts is left
 // per entry; what bounds the pass is the gathering of N rows of 4 R bytes per entry out of the L2 and last-level caches.
-// At order 3 with J = R = 16 (1e8 entries) that is 1.2 ns per row and CU, where rows that sit in L2 take 1.0; what the
-// passes with a projection per entry take stands at the dispatch (launch_errors_rows).
+// At order 3 with J = R = 16 (1e8 entries) that is 1.2 ns per row and CU, where rows that sit in L2 take 1.0, so rows that
+// are short and often asked for are kept in LDS (HOT: 1 430 -> 934 us); what the passes with a projection per entry take
+// stands at the dispatch (launch_errors_rows).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -30,7 +31,13 @@ struct ProjectArgs {
 struct ErrorRows {
     const float* S[kMaxOrder];
     int Rs;          // floats per row of S, a multiple of four
+    // HOT: rows [0, K[n]) of S, the most frequent ones, are kept in LDS (table row hot0[n] on); bytes[n] is the size of S^(n)
+    int K[kMaxOrder], hot0[kMaxOrder], hot_rows;
+    unsigned int bytes[kMaxOrder];
 };
+constexpr int kErrorHotThreads = 1024;
+// floats of LDS next to the table: a row of zeros and what the waves park
+__host__ __device__ constexpr int error_hot_floats(int order) { return 64 + kErrorHotThreads / 64 * (order + 1) * 64; }
 
 #ifndef FTK_TEMPLATE_KERNELS_ONLY
 // S[i][0..Rs) = A[i][:] B for every mode (columns R .. Rs - 1 zero), Rs = R rounded up to four.  A thread makes four columns of
@@ -112,22 +119,40 @@ __device__ __forceinline__ float group_sum(float x) {
 
 // G lanes work on one entry (four columns each, 4 G >= Rs), a wave on 64 / G entries at a time and on 64 in turn; all
 // rows of kDepth such turns are asked for before the first is used.
-template <int N, int G>
-__global__ void __launch_bounds__(256) errors_rows_kernel(Coo coo, uint64_t nnz, ErrorRows s, double* __restrict__ sums /* [gridDim.x][2]: sse, sae */) {
+// HOT: one workgroup per CU with the most frequent rows in LDS.  Every row is asked for twice, from LDS and from memory; the
+// one that is not meant aims at the row of zeros or past the end of the buffer, where the request is dropped, and the two
+// are added.
+template <int N, int G, bool HOT>
+__global__ void __launch_bounds__(HOT ? kErrorHotThreads : 256) errors_rows_kernel(Coo coo, uint64_t nnz, ErrorRows s, double* __restrict__ sums /* [gridDim.x][2]: sse, sae */) {
     constexpr int W4 = (N + 1 + 3) / 4, E = 64 / G;
     constexpr int kDepth = N * G <= 12 ? G : N <= 3 ? (G < 4 ? G : 4) : N <= 6 ? (G < 2 ? G : 2) : 1;
-    __shared__ int parked_all[4][(N + 1) * 64];   // per wave: [N][64] row numbers | [64] values
-    __shared__ double red[2][4];
+    constexpr int THREADS = HOT ? kErrorHotThreads : 256, WAVES = THREADS / 64;
+    __shared__ int parked_all[HOT ? 1 : WAVES][(N + 1) * 64];   // per wave: [N][64] row numbers | [64] values
+    __shared__ double red[2][WAVES];
+    extern __shared__ float error_lds[];   // HOT: table [hot_rows][Rs] | 64 zeros | parked_all
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane % G, who = lane / G;
-    int* parked = parked_all[wave];
+    int* parked = HOT ? reinterpret_cast<int*>(error_lds + (size_t)s.hot_rows * s.Rs + 64) + wave * ((N + 1) * 64) : parked_all[HOT ? 0 : wave];
+    const float* zeros = error_lds + (size_t)s.hot_rows * s.Rs;
+    __amdgpu_buffer_rsrc_t rsrc[N];
+    if constexpr (HOT) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            rsrc[n] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s.S[n]), 0, s.bytes[n], 0x00020000);
+            const float4* from = reinterpret_cast<const float4*>(s.S[n]);
+            float4* to = reinterpret_cast<float4*>(error_lds + (size_t)s.hot0[n] * s.Rs);
+            for (int q = tid; q < s.K[n] * (s.Rs / 4); q += THREADS) to[q] = from[q];
+        }
+        if (tid < 64) error_lds[(size_t)s.hot_rows * s.Rs + tid] = 0.0f;
+        __syncthreads();
+    }
     const bool column = 4 * sub < s.Rs;
     const int col = column ? 4 * sub : 0;
     const uint4* rec4 = reinterpret_cast<const uint4*>(coo.rec);
-    const uint64_t n_groups = (nnz + 63) / 64, stride = (uint64_t)gridDim.x * 4;
+    const uint64_t n_groups = (nnz + 63) / 64, stride = (uint64_t)gridDim.x * WAVES;
     double sse = 0.0, sae = 0.0;
     uint4 rec[W4];
-    uint64_t group = (uint64_t)blockIdx.x * 4 + wave;
+    uint64_t group = (uint64_t)blockIdx.x * WAVES + wave;
     auto load = [&](uint64_t g) {
         const uint64_t p = g * 64 + lane;
 #pragma unroll
@@ -157,7 +182,17 @@ __global__ void __launch_bounds__(256) errors_rows_kernel(Coo coo, uint64_t nnz,
 #pragma unroll
                 for (int n = 0; n < N; ++n) {
                     const uint32_t row = (uint32_t)parked[n * 64 + (t0 + u) * E + who];
-                    v[u][n] = *reinterpret_cast<const float4*>(s.S[n] + (uint64_t)row * (uint32_t)s.Rs + col);
+                    if constexpr (HOT) {
+                        typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+                        const bool hot = row < (uint32_t)s.K[n];
+                        const uint32_t at = row * (uint32_t)s.Rs + (uint32_t)col;
+                        const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc[n], hot ? (int)0xfffffff0u : (int)(at * 4u), 0, 0);
+                        const float4 h = *reinterpret_cast<const float4*>(hot ? error_lds + (uint32_t)(s.hot0[n] * s.Rs) + at : zeros);
+                        v[u][n] = make_float4(__uint_as_float(q[0]) + h.x, __uint_as_float(q[1]) + h.y, __uint_as_float(q[2]) + h.z,
+                                              __uint_as_float(q[3]) + h.w);
+                    } else {
+                        v[u][n] = *reinterpret_cast<const float4*>(s.S[n] + (uint64_t)row * (uint32_t)s.Rs + col);
+                    }
                 }
 #pragma unroll
             for (int u = 0; u < kDepth; ++u) {
@@ -188,8 +223,13 @@ __global__ void __launch_bounds__(256) errors_rows_kernel(Coo coo, uint64_t nnz,
     }
     __syncthreads();
     if (tid == 0) {
-        sums[2 * blockIdx.x + 0] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        sums[2 * blockIdx.x + 1] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+        double a = 0.0, b = 0.0;
+        for (int w = 0; w < WAVES; ++w) {
+            a += red[0][w];
+            b += red[1][w];
+        }
+        sums[2 * blockIdx.x + 0] = a;
+        sums[2 * blockIdx.x + 1] = b;
     }
 }
 

@@ -363,8 +363,19 @@ __global__ void __launch_bounds__(256) finish_core_kernel(FinishArgs g, int bloc
     const int n = (int)blockIdx.x / blocks_per_mode, q = ((int)blockIdx.x - n * blocks_per_mode) * 64 + ((int)threadIdx.x & 63), part = (int)threadIdx.x >> 6;
     const int count = g.J[n] * g.R;
     float sum = 0.0f;
-    if (q < count)
-        for (unsigned int b = g.bucket0[n] + part; b < g.bucket0[n + 1]; b += 4) sum += g.core[(size_t)b * g.core_floats + q];
+    if (q < count) {
+        // eight loads in flight: a mode has up to some hundred buckets
+        const float* src = g.core + q;
+        unsigned int b = g.bucket0[n] + part;
+        const unsigned int end = g.bucket0[n + 1];
+        for (; b + 28 < end; b += 32) {
+            float t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(b + 4 * u) * g.core_floats];
+            sum += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        }
+        for (; b < end; b += 4) sum += src[(size_t)b * g.core_floats];
+    }
     red[part][threadIdx.x & 63] = sum;
     __syncthreads();
     if (part == 0 && q < count) {

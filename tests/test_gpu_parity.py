@@ -676,6 +676,28 @@ def test_factors_in_and_out_are_the_same_bits(dims, J, R, flags):
             assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("dims,zipf,J,R,nnz", [
+    ((61, 7, 40), (None, None, None), 9, 3, 200_003),              # every row in LDS, one lane per entry
+    ((50, 30, 20, 9, 8, 7, 6), (None,) * 7, 5, 7, 150_001),        # order 7, two lanes, an idle column
+    ((70_001, 4_000, 90), (1.2, 1.1, None), 16, 16, 4_200_001),    # more rows than LDS holds: rows from both places
+])
+def test_errors_with_frequent_rows_in_lds(dims, zipf, J, R, nnz):
+    """The evaluation pass that keeps the most frequent projected rows in LDS, against the oracle (bound: see
+    test_errors_over_projected_rows)."""
+    N = len(dims)
+    w = synth.tiny_workload(N, dims, nnz, (J,) * N, R, 16, seed=5, values="normal", zipf=zipf)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(N)
+    A = [rng.uniform(-1, 1, size=(d, J)).astype(np.float32) for d in dims]
+    B = [(rng.uniform(-1, 1, size=(J, R)) / np.sqrt(J)).astype(np.float32) for _ in dims]
+    announce("frequent rows in LDS dims=%r R=%d" % (dims, R))
+    with binding.FastTucker(dims, idx, vals, w.J, R, 1) as ft:
+        ft.ftk_set_factors(A, B)
+        got = (ft.ftk_rmse(), ft.ftk_mae())
+    assert got[0] == pytest.approx(oracle.rmse(dims, idx, vals, A, B), rel=5e-6)
+    assert got[1] == pytest.approx(oracle.errors(dims, idx, vals, A, B)[1], rel=5e-6)
+
+
 @pytest.mark.parametrize("order", [1, 2, 3, 6, 7, 10])
 @pytest.mark.parametrize("J,R", [(3, 1), (5, 4), (9, 8), (16, 15), (20, 17), (33, 32), (47, 48), (64, 64)])
 @pytest.mark.parametrize("n_eval", [64, 4099])
