@@ -965,11 +965,11 @@ int pick_hot_rows(ftk_ctx* c, long long n_samples) {
     }
     c->hot_H_max = (int)std::max(1LL, budget_bytes / row_bytes);
     const int H = (int)std::min<long long>(c->hot_H_max, rows_total);
-    // A table row saves its workgroup one global atomic per hit (~12 ns of a per-CU unit that is the
-    // kernel's bottleneck) and costs one 64-byte store and one read at the end of the step: worth
+    // A table row saves its workgroup one global atomic per hit (~12 ns per CU at the 20.5e9 a second that
+    // the chip retires: the kernel's bottleneck) and costs one 64-byte store and one read at the end of the step: worth
     // it from a fraction of an expected hit per workgroup and step.
     double min_count = 0.25 * (double)c->mfma_grid * (double)c->nnz / (double)std::max<long long>(n_samples, 1);
-    // Ranks above 32: the pass is bound by matrix-instruction issue and the atomic unit has room, so the
+    // Ranks above 32: one wave per SIMD, bound by its latency; the atomics have room, so the
     // table rows are added by atomics as well (to per-workgroup tables in global memory, see the kernel)
     // and save no atomic.  What they are for is to keep a frequent row from queueing on ONE address across
     // all workgroups: float atomics on one address retire at ~41 ns each, so a row is worth a table row
@@ -1133,6 +1133,13 @@ constexpr double kOwnersCold = 0.5;             // share of the row updates that
 constexpr double kOwnersRows = 0.5;             // rows of all modes against samples x modes
 constexpr long long kOwnersBucketRows = 48;     // least rows in a bucket
 
+bool stream_capturing(ftk_ctx* c) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Whether the synchronous step over n_samples samples goes by row owners, with what buckets and lists, and their memory.
 // Not an error if not: the other kernels do every step.
 void plan_owners(ftk_ctx* c, long long n_samples) {
@@ -1218,12 +1225,9 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
     }
     // memory
     const size_t values = (size_t)lists * places * Rs, fill = (size_t)lists * n_buckets, core = (size_t)n_buckets * c->own_core_floats;
-    if (!c->d_S || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
-        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(c->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return;
-        }
+    // (a growth that failed half way leaves a part missing, which is made here another time)
+    if (!c->d_S || !c->d_own_ids || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
+        if (stream_capturing(c)) return;
         size_t free_bytes = 0, all_bytes = 0;
         if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes) return;
         hipStreamSynchronize(c->stream);
@@ -1247,7 +1251,12 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
         if (!ok) return;
         if (!one) {
             if (!grow(c->d_own_overflow, one, 1)) return;
-            if (hipMemset(c->d_own_overflow, 0, sizeof(unsigned int)) != hipSuccess) return;
+            hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<float*>(c->d_own_overflow), 1LL);
+            if (hipGetLastError() != hipSuccess) {
+                hipFree(c->d_own_overflow);
+                c->d_own_overflow = nullptr;
+                return;
+            }
         }
     }
     c->own = true;
@@ -1689,7 +1698,9 @@ int ftk_sgd_step(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, float lambd
     if (!c) return FTK_EINVAL;
     if (const int rc_dev = check_device(c)) return rc_dev;
     if (c->n_samples < 1) return fail(c, FTK_ESTATE, "ftk_sgd_step before ftk_sample");
-    if (c->own && c->mode == FTK_SYNC) return step_owners(c, lr_A, lr_B, lambda_A, lambda_B);
+    // A captured step keeps to buffers that live as long as the context: a larger Psi replaces the owners' lists, and a graph
+    // recorded before would go on using the old ones.
+    if (c->own && c->mode == FTK_SYNC && !stream_capturing(c)) return step_owners(c, lr_A, lr_B, lambda_A, lambda_B);
     c->use_hot_partial = c->d_hot_partial;
     c->use_gb_partial = c->d_gb_partial;
     return step_impl(c, lr_A, lr_B, lambda_A, lambda_B);

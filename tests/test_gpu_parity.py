@@ -652,6 +652,41 @@ def test_step_by_row_owners(order, dims, J, R, nnz, M, tiles):
             A, B = gA, gB      # the next step is compared from where this one ended: one step's bound for each
 
 
+def test_a_captured_step_outlives_the_owners_lists():
+    """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
+    replaced their lists: each replay against the oracle's step."""
+    import torch
+    dims, J, R, M = (60_013, 40_009), (5, 8), 8, 1_100_001
+    announce("captured step, M=%d" % M)
+    w = synth.tiny_workload(2, dims, 300_000, J, R, M, seed=3, values="normal")
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(2)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
+    rates = (0.002, 0.1, 0.05, 0.02)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_set_stream(stream.cuda_stream)
+        ft.ftk_sample(77, M)
+        ft.ftk_sgd_step(*rates)
+        with torch.cuda.graph(graph, stream=stream):
+            ft.ftk_sgd_step(*rates)
+        ft.ftk_sample(78, 3 * M)
+        ft.ftk_sgd_step(*rates)
+        ft.ftk_set_factors(A, B)
+        pos = oracle.sample_positions(77, M, w.nnz)
+        for t in range(3):
+            with torch.cuda.stream(stream):
+                graph.replay()
+            gA, gB = ft.ftk_get_factors()
+            oracle.sgd_step_sync(dims, idx, vals, A, B, pos, *rates)
+            assert_params_close(gA, A, "A, replay %d" % t)
+            assert_params_close(gB, B, "B, replay %d" % t)
+            A, B = gA, gB
+        stream.synchronize()
+        ft.ftk_set_stream(None)
+
+
 @pytest.mark.parametrize("dims,J,R", [
     ((1, 1), (1, 1), 1),
     ((4_097, 3, 259), (5, 16, 8), 9),             # one chunk of the ring, odd row lengths
