@@ -116,7 +116,7 @@ struct ftk_ctx {
     int mfma_grid = 0;                // workgroups of the persistent gradient kernels for the current |Psi|
     int mfma_grid_max = 0;            // what the partial tables are sized for (one workgroup per CU)
     size_t mfma_lds_bytes = 0;
-    float* d_hot_partial = nullptr;   // [mfma_grid][hot_H][16]
+    float* d_hot_partial = nullptr;   // [mfma_grid][hot_H][table_width]
     // Ranks above 32 (tiled kernel, P = 4): A, dA and the workgroups' tables of the frequent rows are ONE allocation
     // (d_A its start), because there the table rows are added by the same buffer atomics as the rows of dA (or of A,
     // in-place mode) and must be within reach of the same 32-bit offsets.  The tables are zero between steps.
@@ -482,6 +482,17 @@ int launch_mfma16_nt(ftk_ctx* c, const Mfma16Args& g, int pass) {
     }
 }
 
+// Floats in a row of the workgroups' tables.  The J = R = 16 kernel also serves ranks up to 16 in rows padded with zeros; its
+// tables leave the padding out, so that they hold two or four times as many rows and fewer leave the CU as atomics.
+// J = R = 8 (order 3): 3e5 samples over 6 000 rows 54.4 -> 42.1 us per step (a row of 64 bytes left 1.86 of three updates to
+// the atomics, 1.2 now), 1e6 samples of 1e8 entries 110 -> 106 us.
+int table_width(const ftk_ctx* c) {
+    if (c->variant == V_TILED) return 16 * c->tiled_P;
+    int J = 0;
+    for (int n = 0; n < c->order; ++n) J = std::max(J, (int)c->J_user[n]);
+    return J <= 4 ? 4 : J <= 8 ? 8 : 16;
+}
+
 template <int N>
 int launch_mfma16_n(ftk_ctx* c, const Mfma16Args& g, int pass) {
     return c->sampling == FTK_SAMPLE_TILES ? launch_mfma16_nt<N, true>(c, g, pass) : launch_mfma16_nt<N, false>(c, g, pass);
@@ -518,6 +529,7 @@ int launch_grad_mfma16(ftk_ctx* c, float lambda_A, float lr_A, int pass = -1) {
     }
     g.all_bytes = (unsigned int)(c->A_total * 4);
     g.H = c->hot_H;
+    g.width = table_width(c);
     g.hot_partial = c->use_hot_partial;
     g.gb_partial = c->use_gb_partial;
     g.lambda_A = lambda_A;
@@ -961,7 +973,7 @@ int pick_hot_rows(ftk_ctx* c, long long n_samples) {
         row_bytes = 64LL * c->tiled_P;
     } else {
         budget_bytes = (long long)c->max_lds - 4LL * (kMfmaWaves * mfma16_wave_scratch(N) + N * 256 + kSinkRows * 16) - 1024;
-        row_bytes = 64;
+        row_bytes = 4LL * table_width(c);
     }
     c->hot_H_max = (int)std::max(1LL, budget_bytes / row_bytes);
     const int H = (int)std::min<long long>(c->hot_H_max, rows_total);
@@ -1058,7 +1070,7 @@ int pick_hot_rows(ftk_ctx* c, long long n_samples) {
         }
     }
     c->hot_H = std::max(off, 1);
-    c->mfma_lds_bytes = 4 * ((size_t)(c->hot_H + kSinkRows) * 16 + kMfmaWaves * mfma16_wave_scratch(N) + N * 256);
+    c->mfma_lds_bytes = 4 * ((size_t)c->hot_H * table_width(c) + kSinkRows * 16 + kMfmaWaves * mfma16_wave_scratch(N) + N * 256);
     c->tiled_lds_bytes = 4 * tiled_lds_floats(N, c->tiled_P, c->tiled_waves, c->hot_H);
     c->hot_for_M = n_samples;
     if (c->variant == V_TILED && c->rows) return plan_rows(c, n_samples);
@@ -1721,7 +1733,7 @@ int ftk_sgd_step_noalloc(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, flo
     // the partial tables of this step: [grid][H][row floats], then [grid x parts][B_total]
     const bool tiled = c->variant == V_TILED;
     // (ranks above 32: the tables of the frequent rows sit behind dA, allocated with it)
-    const size_t hot_floats = wide_tables(c) ? 0 : (((size_t)c->mfma_grid * c->hot_H * (tiled ? 16 * c->tiled_P : 16)) + 63) / 64 * 64;
+    const size_t hot_floats = wide_tables(c) ? 0 : (((size_t)c->mfma_grid * c->hot_H * table_width(c)) + 63) / 64 * 64;
     const size_t gb_floats = (size_t)c->mfma_grid * c->L.B_total;
     const size_t need = (hot_floats + gb_floats) * sizeof(float);
     if (need > kScratchBytes)
@@ -1754,7 +1766,7 @@ int launch_apply_parts(ftk_ctx* c, bool hot, bool core, float lr_A, float lr_B, 
         p.hot_partial = p.hot_clear ? c->d_wide_tables : c->use_hot_partial;
         p.hot_parts = c->mfma_grid;
         p.H = c->hot_H;
-        p.J = c->variant == V_TILED ? 16 * c->tiled_P : 16;
+        p.J = table_width(c);
         p.hot_blocks = (c->hot_H * p.J + 63) / 64;
         p.order = c->order;
         for (int n = 0; n < kMaxOrder; ++n) {
@@ -1844,7 +1856,7 @@ int step_impl(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, float lambda_B
             p.hot_partial = p.hot_clear ? c->d_wide_tables : c->use_hot_partial;
             p.hot_parts = c->mfma_grid;
             p.H = c->hot_H;
-            p.J = tiled ? 16 * c->tiled_P : 16;
+            p.J = table_width(c);
             p.hot_blocks = (c->hot_H * p.J + 63) / 64;
             p.order = c->order;
             for (int n = 0; n < kMaxOrder; ++n) {

@@ -91,7 +91,8 @@ struct Mfma16Args {
     int top[kMfma16MaxOrder];       // 16 if K[n] >= 16 (rows 0..15 go through the one-hot matrix product), else 0
     int hot_off[kMfma16MaxOrder];   // first LDS table row of mode n
     int H;                    // rows in the LDS table (>= sum K[n])
-    float* hot_partial;       // [gridDim.x][H][16]
+    int width;                // floats in a row of the table: 4, 8 or 16, no fewer than the caller's J_n (see table_width)
+    float* hot_partial;       // [gridDim.x][H][width]
     float* gb_partial;        // [gridDim.x][N * 256]
     unsigned int row_bytes[kMfma16MaxOrder];   // I_n * 64: size of mode n's rows in A and dA
     unsigned int all_bytes;              // size of the whole packed A (and dA), below 2^31 - 64
@@ -186,7 +187,7 @@ __device__ __forceinline__ void gather_rows(const __amdgpu_buffer_rsrc_t (&rsrc_
 constexpr int kSyncPass = 0, kInPlacePass = 1, kFactorPhase = 2, kCorePhase = 3;
 
 template <int N, int MODE>
-__device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>& st, unsigned int hot_addr,
+__device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>& st, unsigned int cell_base, unsigned int cell_mask,
                                               unsigned int top_key, const unsigned int* scur, const unsigned int* snxt,
                                               float* tbuf, int c, int g4, int n_tiles) {
     __amdgpu_buffer_rsrc_t rsrc_A[N];
@@ -360,9 +361,9 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         //     fetched again through the tile's two compacted lists, four rows per instruction:
         //     rows of the workgroup's LDS table by compare-and-swap float adds, the rest by global
         //     float atomics.
-        // A global float atomic instruction costs this chip the same ~110 clocks of a per-CU unit
-        // whether one or all four of its 16-lane rows are in range, so the lists matter: without
-        // them nearly every instruction of every (mode, quarter) would carry at least one such row.
+        // The whole chip retires 20.5e9 float-atomic requests of up to 64 bytes a second, and an atomic
+        // instruction takes a CU the same time whether one or all four of its 16-lane rows are in range, so the
+        // lists matter: without them nearly every instruction of every (mode, quarter) would carry such a row.
         if constexpr (MODE == kCorePhase) {
             // core gradient only: GB[j = 4g+v'][r = c] += sum_samples a_j (-e w_r)
 #pragma unroll
@@ -425,7 +426,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 val[i] = tbuf[(e[i] >> 20) * 20u + (unsigned int)c];
-                cl[i] = hot_addr + (e[i] & 0xfffffu) + c4;
+                cl[i] = cell_base + (e[i] & cell_mask);
                 sn[i] = *(lds_u32*)(uintptr_t)cl[i];
             }
             swap4(first, val, cl, sn);
@@ -474,7 +475,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             // the table cells of the first batch are read while the matrix core is busy below
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                cell[i] = hot_addr + (et[i] & 0xfffffu) + c4;
+                cell[i] = cell_base + (et[i] & cell_mask);
                 seen[i] = *(lds_u32*)(uintptr_t)cell[i];
             }
 #pragma unroll
@@ -532,10 +533,10 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
     const int c = lane & 15, g4 = lane >> 4;
     float* hot = lds;
-    float* wave_lds = lds + (size_t)(g.H + kSinkRows) * 16 + wave * mfma16_wave_scratch(N);
+    float* wave_lds = lds + (size_t)(g.H * g.width + kSinkRows * 16) + wave * mfma16_wave_scratch(N);
     unsigned int* sbuf = reinterpret_cast<unsigned int*>(wave_lds);   // two parked groups
     float* tbuf = wave_lds + 2 * kGroupWords;                          // [N][16][20]
-    float* gbred = lds + (size_t)(g.H + kSinkRows) * 16 + kMfmaWaves * mfma16_wave_scratch(N);
+    float* gbred = lds + (size_t)(g.H * g.width + kSinkRows * 16) + kMfmaWaves * mfma16_wave_scratch(N);
 
     WaveState<N> st;
 #pragma unroll
@@ -555,6 +556,10 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     const long long M = g.M;
     const uint4* rec4 = reinterpret_cast<const uint4*>(g.coo.rec);
     const unsigned int hot_addr = lds_address(hot);
+    // Where this lane's column of a listed table row lies: cell_base + (entry & cell_mask).  A table row holds g.width
+    // floats; lanes of the columns behind them carry zeros and aim at the quarter's row of +inf, whatever the entry.
+    const unsigned int sink_addr = hot_addr + (unsigned int)(g.H * g.width) * 4u, cell_mask = c < g.width ? 0xfffffu : 0u;
+    const unsigned int cell_base = (c < g.width ? hot_addr : sink_addr + (unsigned int)g4 * 64u) + (unsigned int)c * 4u;
     // row word of "row c, one of the 16 most frequent" (kept opaque so that the match below is one compare)
     unsigned int top_key = (2u << kRouteShift) + (unsigned int)c * 64u;
     asm volatile("" : "+v"(top_key));
@@ -644,7 +649,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         // every list position starts out unused: lane (tile, quarter q, j) clears positions [q][j], [q][j+4], ...
         {
             const int q = (lane >> 2) & 3, j = lane & 3;
-            const unsigned int unused_cell = (unsigned int)(g.H + q) * 64u;   // a row of +inf, one per quarter
+            const unsigned int unused_cell = (unsigned int)(g.H * g.width + q * 16) * 4u;   // a row of +inf, one per quarter
 #pragma unroll
             for (int i = 0; i < 4 * N; i += 4) {
                 atomic_list[q * (4 * N) + j + i] = kNoAtomic;
@@ -670,7 +675,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             }
             if (to_table) {
                 const int p = n_table + __popcll(table_lanes & lanes_below);
-                table_list[(p & 3) * (4 * N) + (p >> 2)] = (slot << 20) | ((unsigned int)(g.hot_off[n] + row) * 64u);
+                table_list[(p & 3) * (4 * N) + (p >> 2)] = (slot << 20) | ((unsigned int)((g.hot_off[n] + row) * g.width) * 4u);
             }
             n_atomic += __popcll(atomic_lanes & tile_lanes);
             n_table += __popcll(table_lanes & tile_lanes);
@@ -689,8 +694,8 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         load_record(0, rec0);
         load_record(1, rec);
     }
-    for (int q = tid; q < g.H * 4; q += kMfmaThreads) reinterpret_cast<float4*>(hot)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int q = tid; q < kSinkRows * 16; q += kMfmaThreads) hot[g.H * 16 + q] = __uint_as_float(0x7f800000u);
+    for (int q = tid; q < g.H * (g.width / 4); q += kMfmaThreads) reinterpret_cast<float4*>(hot)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int q = tid; q < kSinkRows * 16; q += kMfmaThreads) hot[g.H * g.width + q] = __uint_as_float(0x7f800000u);
     for (int q = tid; q < N * 256; q += kMfmaThreads) gbred[q] = 0.0f;
     __syncthreads();
     if (has_turns) {
@@ -713,7 +718,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             park_record(t + 1, rec, snxt);
             load_record(t + 2, rec);
             lds_wave_sync();
-            process_group<N, MODE>(g, st, hot_addr, top_key, scur, snxt, tbuf, c, g4, tiles_of(t));
+            process_group<N, MODE>(g, st, cell_base, cell_mask, top_key, scur, snxt, tbuf, c, g4, tiles_of(t));
         };
         // From order 4 on the first turn is peeled off the loop: the loop proper is then entered with the same sequence
         // of outstanding memory operations as its own back edge, and the compiler's wait counts in the steady state
@@ -741,8 +746,8 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         for (int n = 0; n < N; ++n)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = g.top[n] > 0 ? g.hot_off[n] + 4 * g4 + v : g.H + v;
-                cell[8 * n + v] = hot_addr + (unsigned int)(row * 16 + c) * 4u;
+                cell[8 * n + v] = g.top[n] > 0 && c < g.width ? hot_addr + (unsigned int)((g.hot_off[n] + 4 * g4 + v) * g.width + c) * 4u
+                                                              : sink_addr + (unsigned int)(v * 16 + c) * 4u;
                 val[8 * n + v] = st.Top[n][v];
                 cell[8 * n + 4 + v] = lds_address(gbred + n * 256 + (4 * g4 + v) * 16 + c);
                 val[8 * n + 4 + v] = st.GBacc[n][v];
@@ -764,8 +769,8 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     __syncthreads();
     float* gb_out = g.gb_partial + (size_t)blockIdx.x * (N * 256);
     for (int q = tid; q < N * 256; q += kMfmaThreads) gb_out[q] = gbred[q];
-    float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * 16;
-    for (int q = tid; q < g.H * 4; q += kMfmaThreads) reinterpret_cast<float4*>(hot_out)[q] = reinterpret_cast<const float4*>(hot)[q];
+    float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * g.width;
+    for (int q = tid; q < g.H * (g.width / 4); q += kMfmaThreads) reinterpret_cast<float4*>(hot_out)[q] = reinterpret_cast<const float4*>(hot)[q];
 }
 
 // ---------------------------------------------------------------------------------------------

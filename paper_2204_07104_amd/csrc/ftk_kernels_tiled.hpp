@@ -30,7 +30,7 @@
 //           atomic instructions, and every row summed on chip is an atomic request less;
 //   P = 4   in global memory, in the same allocation as the accumulator, and its rows are added by
 //           the very atomics that are issued anyway (another offset, nothing else): this shape is
-//           bound by instruction issue with one wave per SIMD, the atomic unit has room, and what a
+//           bound by the latency of one wave per SIMD, the atomics have room, and what a
 //           table row is for is to keep the most frequent rows from queueing on one address across
 //           all workgroups.
 // The core gradient lives in matrix-core accumulators for the whole kernel, is summed over the

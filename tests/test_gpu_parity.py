@@ -652,6 +652,38 @@ def test_step_by_row_owners(order, dims, J, R, nnz, M, tiles):
             A, B = gA, gB      # the next step is compared from where this one ended: one step's bound for each
 
 
+@pytest.mark.parametrize("dims,zipf,J,R", [
+    ((3_001, 701, 90), (None, 1.2, None), (4, 3, 1), 4),                        # table rows of 4 floats
+    ((5_003, 640), (1.1, None), (8, 5), 6),                                    # of 8
+    ((410, 301, 205, 97, 2_503), (None, None, None, 1.1, None), (2, 8, 7, 3, 8), 8),   # of 8, the form without values read ahead
+    ((3_001, 701, 90), (None, 1.2, None), (9, 3, 1), 4),                        # of 16
+])
+def test_table_rows_of_the_callers_width(dims, zipf, J, R):
+    """The J = R = 16 kernel on padded ranks: its tables hold rows of 4, 8 or 16 floats.  Every parameter against the oracle's
+    step.  A row collects up to n = 2e4 gradients of size |g| < 5 in fp32: lr n 2^-24 |g| = 6e-7, inside the bound's 1e-6."""
+    N, M = len(dims), 60_013
+    announce("table rows of the caller's width dims=%r J=%r" % (dims, J))
+    w = synth.tiny_workload(N, dims, 200_003, J, R, M, seed=8, values="normal", zipf=zipf)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(N)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) / np.sqrt(j)).astype(np.float32) for j in J]
+    rates = (1e-4, 0.1, 0.05, 0.02)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "mfma16"
+        ft.ftk_set_factors(A, B)
+        for t, step in enumerate((ft.ftk_sgd_step, ft.ftk_sgd_step_noalloc)):
+            ft.ftk_sample(31 + t, M)
+            K, top = ft.ftk_get_table_rows()
+            assert sum(K) > 150 and max(top) == 16      # rows of the table and of the one-hot product
+            step(*rates)
+            oracle.sgd_step_sync(dims, idx, vals, A, B, oracle.sample_positions(31 + t, M, w.nnz), *rates)
+            gA, gB = ft.ftk_get_factors()
+            assert_params_close(gA, A, "A, step %d" % t)
+            assert_params_close(gB, B, "B, step %d" % t)
+            A, B = gA, gB
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
