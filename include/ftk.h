@@ -110,6 +110,9 @@ void ftk_destroy(ftk_ctx* ctx);
  *   u = w0 | w1 << 32  for even k,   w2 | w3 << 32  for odd k
  *   p_k = floor(u * nnz / 2^64)
  * Psi stays valid until the next ftk_sample.  1 <= n_samples < 2^31.
+ * A changed n_samples plans the step anew; where "auto" then takes row owners (see ftk_set_kernel) this allocates
+ * their lists and workspace on the device, kept for the context's life.  While the stream is being captured, or where memory is
+ * short, nothing is allocated and the step runs without them.
  */
 int ftk_sample(ftk_ctx* ctx, uint64_t seed, int64_t n_samples);
 
@@ -187,7 +190,8 @@ int ftk_mae(ftk_ctx* ctx, double* out);
  * arrays as for ftk_create), vals: fp32[n_eval]; host memory, or device memory if flags has
  * FTK_PTRS_DEVICE.  Borrowed for the duration of the call only.  Either output may be NULL.
  * The set is copied to the device, checked and evaluated in one streaming pass; errors are summed
- * in double.  Waits for the stream.  FTK_EINVAL: n_eval outside 1..2^32-1, NULL idx / vals, an
+ * in double.  The context keeps the workspaces of its first evaluation (the projected rows A^(n) B^(n)).
+ * Waits for the stream.  FTK_EINVAL: n_eval outside 1..2^32-1, NULL idx / vals, an
  * index outside [0, I_n), unknown flag bits.  FTK_ENOMEM / FTK_EDEVICE as for ftk_create.
  */
 int ftk_evaluate(ftk_ctx* ctx, int64_t n_eval, const int32_t* const* idx, const float* vals, uint32_t flags,
@@ -272,6 +276,9 @@ int ftk_get_timing(ftk_ctx* ctx, int which, double* total_ms, int64_t* launches,
  *              buckets; allocates the lists (sized from |Psi| and the rows' frequencies) on the device.
  *              "rows:tight" is the same with lists of half the expected length, so that many rows take the
  *              fallback (a full list sends the row through a float atomic after all): for tests.
+ * With "auto" in force, ftk_sgd_step in FTK_SYNC mode at R <= 8 lets row owners do the whole step where Psi is large and its
+ * hits are spread evenly over the rows: gradients are summed per row in the space of the projections, without atomics.
+ * ftk_kernel_name and ftk_get_table_rows keep reporting the variant and tables that the other steps of the context use.
  * All of them compute the same step (same Psi, same formulas); they differ in speed only.
  * ftk_kernel_name: the variant in use (static string, never NULL).
  */
