@@ -485,7 +485,7 @@ int launch_mfma16_nt(ftk_ctx* c, const Mfma16Args& g, int pass) {
 // Floats in a row of the workgroups' tables.  The J = R = 16 kernel also serves ranks up to 16 in rows padded with zeros; its
 // tables leave the padding out, so that they hold two or four times as many rows and fewer leave the CU as atomics.
 // J = R = 8 (order 3): 3e5 samples over 6 000 rows 54.4 -> 42.1 us per step (a row of 64 bytes left 1.86 of three updates to
-// the atomics, 1.2 now), 1e6 samples of 1e8 entries 110 -> 106 us.
+// the atomics, 1.14 now), 1e6 samples of 1e8 entries 110 -> 106 us.
 int table_width(const ftk_ctx* c) {
     if (c->variant == V_TILED) return 16 * c->tiled_P;
     int J = 0;
