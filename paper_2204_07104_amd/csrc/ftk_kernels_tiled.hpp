@@ -421,6 +421,10 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     // the half of the register file that the vector ALU does not reach, and go on in the matrix instructions.
     constexpr bool kFreshSums = P == 2;
     constexpr int KC = P > 1 ? P / 2 : 1, kSteps = 3 * KC, kAhead = P == 2 ? 2 : 1;
+    // -e is taken with its sign turned in odd waves (P > 1): what the bf16 instructions cut off towards -inf then goes the other
+    // way there, and drops out where the waves are summed (see ftk_split.hpp).
+    const unsigned int sign = P > 1 ? (unsigned int)__builtin_amdgcn_readfirstlane(wave & 1) << 31 : 0u;
+    auto turned = [&](float v) { return __uint_as_float(__float_as_uint(v) ^ sign); };
     auto hold_reads = [&]() { __builtin_amdgcn_sched_barrier(0x6); };
 
     uint4 rec[W4];
@@ -531,7 +535,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     run *= s[n][rb];
                 }
             }
-            float neg_e = sum_over_groups(xhat) - x;
+            float neg_e = turned(sum_over_groups(xhat) - x);
 
 #pragma unroll
             for (int n = 0; n < N; ++n) {
@@ -548,7 +552,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                         const floatx4 full = wn * s[n][rb];
                         part += (full[0] + full[1]) + (full[2] + full[3]);
                     }
-                    neg_e = sum_over_groups(part) - x;
+                    neg_e = turned(sum_over_groups(part) - x);
                 }
                 floatx4 ay[P], gs[P];   // rows and -e GS^(n), layout Y
 #pragma unroll
@@ -720,7 +724,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     float grad[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        grad[v] = g.scale * fmaf(g.lambda_A, ay[jb][v], gs[jb][v]);
+                        grad[v] = turned(g.scale) * fmaf(turned(g.lambda_A), ay[jb][v], gs[jb][v]);
                         if constexpr (ROWS) {
                             // the list entry: components 0 .. J_n - 1, then the word that names the row (its lane may be in
                             // a block of columns of its own when J_n is a multiple of 16: see below)
@@ -840,7 +844,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             float* cell = gb_sum + ((size_t)n * D + 16 * jb + 4 * g4 + v) * D + 16 * rb + c;
-                            *cell = turn == 0 ? GBacc[n][jb][rb][v] : *cell + GBacc[n][jb][rb][v];
+                            *cell = turn == 0 ? GBacc[n][jb][rb][v] : fmaf(turned(1.0f), GBacc[n][jb][rb][v], *cell);   // (wave 0 turns none)
                         }
         }
         __syncthreads();

@@ -394,6 +394,42 @@ def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
     one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
 
 
+@pytest.mark.parametrize("J,R", [(32, 32), (18, 25), (64, 64), (40, 48)])
+def test_core_gradient_of_a_long_psi_is_as_precise_as_fp32_sums(J, R):
+    """The core gradient by itself (lr_A = 0), 1e6 samples whose contributions have both signs, against 64 bits.  With fp32
+    matrix instructions a wave's sum is rounded four times a tile, 61 tiles a wave at most: 2^-25 sqrt(244) = 4.7e-7 of the sum
+    for roundings that are independent; 6e-7 leaves the sums over the waves their part.  Roundings that all lean one way show as
+    a mean: the errors of n elements with no common part have one of std / sqrt(n)."""
+    dims, nnz, M = (4_000, 3_000, 2_000), 2_000_000, 1_000_003
+    announce("core gradient of a long Psi J=%d R=%d" % (J, R))
+    rng = np.random.default_rng(J)
+    idx = [rng.integers(0, d, nnz).astype(np.int32) for d in dims]
+    vals = rng.standard_normal(nnz).astype(np.float32)
+    A = [rng.uniform(-1, 1, size=(d, J)).astype(np.float32) for d in dims]
+    B = [(rng.uniform(-1, 1, size=(J, R)) / J).astype(np.float32) for _ in dims]
+    with binding.FastTucker(dims, idx, vals, (J,) * 3, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "tiled"
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(5, M)
+        ft.ftk_sgd_step(0.0, float(M), 0.0, 0.0)      # B - M (GB / M)
+        got = ft.ftk_get_factors()[1]
+    pos = oracle.sample_positions(5, M, nnz)
+    A64, B64 = [a.astype(np.float64) for a in A], [b.astype(np.float64) for b in B]
+    proj = [a @ b for a, b in zip(A64, B64)]
+    GB = [np.zeros((J, R)) for _ in dims]
+    for lo in range(0, M, 1 << 16):
+        rows = [i[pos[lo:lo + (1 << 16)]] for i in idx]
+        c = [s[r] for s, r in zip(proj, rows)]
+        minus_e = ((c[0] * c[1] * c[2]).sum(1) - vals[pos[lo:lo + (1 << 16)]])[:, None]
+        for n, (k, m) in enumerate(((1, 2), (0, 2), (0, 1))):
+            GB[n] += A64[n][rows[n]].T @ (c[k] * c[m] * minus_e)
+    err = np.concatenate([((b - g) - want).ravel() for b, g, want in zip(B64, got, GB)])
+    size = np.sqrt(np.mean(np.concatenate([g.ravel() for g in GB]) ** 2))
+    print("[case] relative error %.2e, mean %.1f standard errors" % (np.sqrt(np.mean(err ** 2)) / size, err.mean() / err.std() * np.sqrt(err.size)), flush=True)
+    assert np.sqrt(np.mean(err ** 2)) <= 6e-7 * size
+    assert abs(err.mean()) <= 6 * err.std() / np.sqrt(err.size)
+
+
 @pytest.mark.parametrize("kernel", [None, "rows"])
 @pytest.mark.parametrize("name,nnz,M,dims", [
     ("C2", 200_000, 20_000, (4_800, 1_777, 220)),
