@@ -101,7 +101,7 @@ struct ftk_ctx {
     bool tiled_ok = false;    // general matrix-core kernel: J_n, R <= 64
     int tiled_P = 1;          // ranks padded to 16 * tiled_P
     int tiled_waves = 8;
-    bool tiled_x4 = false;    // every J_n is a multiple of four: rows are fetched 16 bytes per lane
+    bool tiled_x4 = false;    // every J_n is a multiple of four: no 16-byte piece of a row runs past its end
     size_t tiled_lds_bytes = 0;
     int sampling = FTK_SAMPLE_ENTRIES;
     uint32_t* d_rec_tiles = nullptr;   // the records in the order of the tile-sampling rule (built on first use)
@@ -548,12 +548,12 @@ int launch_grad_mfma16(ftk_ctx* c, float lambda_A, float lr_A, int pass = -1) {
     }
 }
 
-template <int N, int P, int WAVES, bool ROWS, int MODE = kSyncPass>
-int launch_tiled_npwr(ftk_ctx* c, const TiledArgs& g) {
-    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(grad_tiled_kernel<N, P, WAVES, ROWS, MODE>), c->max_lds)) return rc;
+template <int N, int P, int WAVES, bool X4, bool ROWS, int MODE = kSyncPass>
+int launch_tiled_npwxr(ftk_ctx* c, const TiledArgs& g) {
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(grad_tiled_kernel<N, P, WAVES, X4, ROWS, MODE>), c->max_lds)) return rc;
     if (c->prepare_only) return FTK_OK;
     Bracket t(c, FTK_K_GRAD);
-    hipLaunchKernelGGL((grad_tiled_kernel<N, P, WAVES, ROWS, MODE>), dim3(c->mfma_grid), dim3(WAVES * 64), c->tiled_lds_bytes,
+    hipLaunchKernelGGL((grad_tiled_kernel<N, P, WAVES, X4, ROWS, MODE>), dim3(c->mfma_grid), dim3(WAVES * 64), c->tiled_lds_bytes,
                        c->stream, g);
     FTK_HIP(c, hipGetLastError());
     return FTK_OK;
@@ -568,17 +568,20 @@ template <int N, int P, int WAVES>
 int launch_tiled_npw(ftk_ctx* c, const TiledArgs& g, int pass) {
     if (pass == kFactorPhase || pass == kCorePhase) {
         if (!tiled_modewise_ok(c)) return fail(c, FTK_EUNSUPPORTED, "the mode-by-mode order is not built for the rows form of the tiled kernel");
-        return pass == kFactorPhase ? launch_tiled_npwr<N, P, WAVES, false, kFactorPhase>(c, g)
-                                    : launch_tiled_npwr<N, P, WAVES, false, kCorePhase>(c, g);
+        if (c->tiled_x4)
+            return pass == kFactorPhase ? launch_tiled_npwxr<N, P, WAVES, true, false, kFactorPhase>(c, g)
+                                        : launch_tiled_npwxr<N, P, WAVES, true, false, kCorePhase>(c, g);
+        return pass == kFactorPhase ? launch_tiled_npwxr<N, P, WAVES, false, false, kFactorPhase>(c, g)
+                                    : launch_tiled_npwxr<N, P, WAVES, false, false, kCorePhase>(c, g);
     }
     if (c->rows) {
         // list entries are written 16 bytes apart: every J_n a multiple of four
         if (!c->tiled_x4) return fail(c, FTK_EUNSUPPORTED, "rows needs every J_n to be a multiple of 4");
         // the row owners' table (up to 64 KB, dynamic) sits next to 4 KB of static LDS
         if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(rows_apply_kernel), 65536)) return rc;
-        return launch_tiled_npwr<N, P, WAVES, true>(c, g);
+        return launch_tiled_npwxr<N, P, WAVES, true, true>(c, g);
     }
-    return launch_tiled_npwr<N, P, WAVES, false>(c, g);
+    return c->tiled_x4 ? launch_tiled_npwxr<N, P, WAVES, true, false>(c, g) : launch_tiled_npwxr<N, P, WAVES, false, false>(c, g);
 }
 
 template <int N>

@@ -394,6 +394,38 @@ def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
     one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
 
 
+@pytest.mark.parametrize("J,R", [((5, 9, 7), 6), ((18, 30, 9), 22), ((35, 33, 50), 40)])
+@pytest.mark.parametrize("mode", [binding.FTK_SYNC, binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE])
+def test_a_row_that_no_sample_touches_may_hold_anything(J, R, mode):
+    """A row of no stored entry (the last one in the library's own order) is not finite, next to rows that are sampled: with
+    rows whose length is no multiple of four a 16-byte load of the neighbour reads into it.  Nothing else may see it; in the
+    synchronous mode the step is the oracle's."""
+    dims, M = (41, 23, 12), 4_099
+    announce("untouched row with inf and NaN J=%r mode=%d" % (J, mode))
+    w = synth.tiny_workload(3, [d - 1 for d in dims], 3_000, J, R, M, seed=17, values="normal")
+    w = synth.replace(w, lr_A=1e-5, lr_B=1e-4)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(R)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) / j).astype(np.float32) for j in J]
+    for a in A:
+        a[-1] = np.where(np.arange(a.shape[1]) % 2 == 0, np.nan, np.inf)
+    with binding.FastTucker(dims, idx, vals, J, R, 1, flags=binding.FTK_LAYOUT_EXACT) as ft:
+        ft.ftk_set_kernel("tiled")
+        ft.ftk_set_mode(mode)
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(3, M)
+        ft.ftk_sgd_step(w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
+        gA, gB = ft.ftk_get_factors()
+    for got, a in zip(gA, A):
+        assert np.array_equal(got[-1], a[-1], equal_nan=True)
+    assert all(np.isfinite(got[:-1]).all() for got in gA) and all(np.isfinite(b).all() for b in gB)
+    if mode == binding.FTK_SYNC:
+        oracle.sgd_step_sync(dims, idx, vals, A, B, oracle.sample_positions(3, M, w.nnz), w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
+        assert_params_close([a[:-1] for a in gA], [a[:-1] for a in A], "A")
+        assert_params_close(gB, B, "B")
+
+
 @pytest.mark.parametrize("J,R", [(32, 32), (18, 25), (64, 64), (40, 48)])
 def test_core_gradient_of_a_long_psi_is_as_precise_as_fp32_sums(J, R):
     """The core gradient by itself (lr_A = 0), 1e6 samples whose contributions have both signs, against 64 bits.  With fp32
