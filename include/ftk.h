@@ -298,6 +298,15 @@ const char* ftk_kernel_name(const ftk_ctx* ctx);
  */
 int ftk_get_table_rows(ftk_ctx* ctx, int32_t* K_out, int32_t* top_out);
 
+/*
+ * Whether row owners do the synchronous step over the Psi in force (see ftk_set_kernel), and what that has come to so far.
+ *   planned   1 if an ftk_sgd_step now (FTK_SYNC, outside stream capture) is done by row owners, else 0
+ *   bytes     device memory the context holds for the owners' lists and sums
+ *   spilled   row updates since ftk_create that found the list of their bucket full and went through float atomics
+ * Any output may be NULL; with `spilled` the call waits for the stream.  For tests and tuning.
+ */
+int ftk_get_row_owners(ftk_ctx* ctx, int32_t* planned, int64_t* bytes, int64_t* spilled);
+
 /* Message for the most recent failure on this context (ctx == NULL: of ftk_create on this thread). */
 const char* ftk_last_error(const ftk_ctx* ctx);
 

@@ -30,7 +30,7 @@ SYMBOLS = [
     "ftk_create", "ftk_destroy", "ftk_sample", "ftk_get_samples", "ftk_sgd_step", "ftk_sgd_step_noalloc", "ftk_rmse", "ftk_mae",
     "ftk_evaluate", "ftk_step_size", "ftk_set_sampling",
     "ftk_get_factors", "ftk_set_factors", "ftk_set_mode", "ftk_set_stream", "ftk_set_timing",
-    "ftk_get_timing", "ftk_set_kernel", "ftk_kernel_name", "ftk_get_table_rows", "ftk_last_error",
+    "ftk_get_timing", "ftk_set_kernel", "ftk_kernel_name", "ftk_get_table_rows", "ftk_get_row_owners", "ftk_last_error",
 ]
 
 
@@ -117,6 +117,8 @@ def load():
     L.ftk_kernel_name.restype = C.c_char_p
     L.ftk_get_table_rows.argtypes = [vp, vp, vp]
     L.ftk_get_table_rows.restype = C.c_int
+    L.ftk_get_row_owners.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
+    L.ftk_get_row_owners.restype = C.c_int
     L.ftk_last_error.argtypes = [vp]
     L.ftk_last_error.restype = C.c_char_p
     _lib = L
@@ -304,3 +306,10 @@ class FastTucker:
         top = np.zeros(self.order, dtype=np.int32)
         self._check(self._L.ftk_get_table_rows(self._ctx, K.ctypes.data, top.ctypes.data))
         return K, top
+
+    def ftk_get_row_owners(self) -> Tuple[bool, int, int]:
+        """(planned, bytes, spilled): whether row owners do the synchronous step over the current Psi, the memory held for
+        their lists, and how many row updates found a full list so far."""
+        planned, held, spilled = C.c_int32(0), C.c_int64(0), C.c_int64(0)
+        self._check(self._L.ftk_get_row_owners(self._ctx, C.byref(planned), C.byref(held), C.byref(spilled)))
+        return bool(planned.value), held.value, spilled.value

@@ -155,7 +155,7 @@ struct ftk_ctx {
     unsigned short* d_own_ids = nullptr;
     unsigned int* d_own_fill = nullptr;
     float* d_own_core = nullptr;
-    unsigned int* d_own_overflow = nullptr;
+    unsigned int* d_own_overflow = nullptr;   // rows that found a full list: of the step in the stream | of all steps before
     size_t own_value_floats = 0, own_fill_words = 0, own_core_total = 0;
     float* use_hot_partial = nullptr; // the partial tables of the step being enqueued: the two above, or the
     float* use_gb_partial = nullptr;  // library's static scratch array (ftk_sgd_step_noalloc)
@@ -1259,14 +1259,14 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
             have = want;
             return true;
         };
-        size_t ids_have = c->d_own_ids ? c->own_value_floats / Rs : 0, one = c->d_own_overflow ? 1 : 0, s_have = c->d_S ? (size_t)rows_total * Rs : 0;
+        size_t ids_have = c->d_own_ids ? c->own_value_floats / Rs : 0, one = c->d_own_overflow ? 2 : 0, s_have = c->d_S ? (size_t)rows_total * Rs : 0;
         const bool ok = grow(c->d_own_ids, ids_have, values / Rs) && grow(c->d_own_values, c->own_value_floats, values) &&
                         grow(c->d_own_fill, c->own_fill_words, fill) && grow(c->d_own_core, c->own_core_total, core) &&
                         grow(c->d_S, s_have, (size_t)rows_total * Rs);
         if (!ok) return;
         if (!one) {
-            if (!grow(c->d_own_overflow, one, 1)) return;
-            hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<float*>(c->d_own_overflow), 1LL);
+            if (!grow(c->d_own_overflow, one, 2)) return;
+            hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<float*>(c->d_own_overflow), 2LL);
             if (hipGetLastError() != hipSuccess) {
                 hipFree(c->d_own_overflow);
                 c->d_own_overflow = nullptr;
@@ -2307,6 +2307,23 @@ int ftk_get_table_rows(ftk_ctx* c, int32_t* K_out, int32_t* top_out) {
     for (int n = 0; n < c->order; ++n) {
         if (K_out) K_out[n] = table ? c->hot_K[n] : 0;
         if (top_out) top_out[n] = table ? c->hot_top[n] : 0;
+    }
+    return FTK_OK;
+}
+
+int ftk_get_row_owners(ftk_ctx* c, int32_t* planned, int64_t* bytes, int64_t* spilled) {
+    if (!c) return FTK_EINVAL;
+    if (planned) *planned = (c->own && c->mode == FTK_SYNC) ? 1 : 0;
+    if (bytes) {
+        const size_t rank4 = ((size_t)c->R_user + 3) & ~(size_t)3;
+        *bytes = (int64_t)(c->own_value_floats * 4 + (c->d_own_ids ? c->own_value_floats / rank4 * 2 : 0) + c->own_fill_words * 4 + c->own_core_total * 4);
+    }
+    if (spilled) {
+        if (const int rc_dev = check_device(c)) return rc_dev;
+        unsigned int total = 0;
+        FTK_HIP(c, hipStreamSynchronize(c->stream));
+        if (c->d_own_overflow) FTK_HIP(c, hipMemcpy(&total, c->d_own_overflow + 1, sizeof total, hipMemcpyDeviceToHost));
+        *spilled = (int64_t)total;
     }
     return FTK_OK;
 }

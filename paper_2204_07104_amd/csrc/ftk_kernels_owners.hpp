@@ -354,7 +354,7 @@ struct FinishArgs {
     int B_off[kMaxOrder], J[kMaxOrder];
     float* B;
     float* GB;                  // what went through atomics
-    unsigned int* overflow;
+    unsigned int* overflow;     // [2]: of this step, of all before it
     float lr_B, lambda_B, inv_M;
 };
 // B <- B - lr_B (GB / M + lambda_B B): one workgroup per mode and 64 elements, four threads per element over the buckets
@@ -386,7 +386,10 @@ __global__ void __launch_bounds__(256) finish_core_kernel(FinishArgs g, int bloc
         float* b = g.B + g.B_off[n] + jj * g.stride_B + r;
         *b = *b - g.lr_B * fmaf(total, g.inv_M, g.lambda_B * *b);
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *g.overflow = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        g.overflow[1] += g.overflow[0];
+        g.overflow[0] = 0u;
+    }
 }
 #endif
 

@@ -4,6 +4,8 @@ Bars (from the benchmark spec): sampled index sets bit-exact; after one synchron
 parameter within 1e-4 relative / 1e-6 absolute of the oracle; RMSE over 10 steps within 1e-3
 relative.  Everything goes through the C ABI (binding.FastTucker); every input is seeded.
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -648,6 +650,21 @@ def test_a_diverged_run_still_returns(kernel, J, R):
     assert not all(np.isfinite(a).all() for a in A)
 
 
+def test_a_diverged_run_by_row_owners_still_returns():
+    """The same where row owners do the step: their sums in LDS are compare-and-swap loops on bit patterns, too."""
+    dims, R, M = (6_311, 6_400, 7_001, 6_300), 8, 520_000
+    announce("diverged run by row owners")
+    idx, vals = evenly_hit_tensor(dims, 5, False)
+    with binding.FastTucker(dims, idx, vals, (8,) * 4, R, 3) as ft:
+        for t in range(4):
+            ft.ftk_sample(t, M)
+            assert ft.ftk_get_row_owners()[0]
+            ft.ftk_sgd_step(1e30, 1e30, 0.1, 0.1)
+        A, B = ft.ftk_get_factors()
+        assert not np.isfinite(ft.ftk_rmse())
+    assert not all(np.isfinite(a).all() for a in A)
+
+
 def test_repeating_a_step_reuses_psi_and_accumulators_are_clean():
     """Two steps on the same Psi equal two oracle steps on it: nothing is left over in the
     gradient accumulators between steps."""
@@ -680,27 +697,50 @@ def test_rmse_and_mae_match_oracle():
         assert ma == pytest.approx(want_ma, rel=1e-5)
 
 
+def evenly_hit_tensor(dims, seed, runs):
+    """64 entries per row of mode 0, rows of the other modes drawn uniformly: what row owners are planned for.  runs: the 64
+    entries that the tile rule draws together (see ftk_set_sampling) share their row of mode 0, so that a workgroup meets one
+    bucket 64 times in a row and its list is full long before its expected length is reached."""
+    nnz = 64 * dims[0]
+    rng = np.random.default_rng(seed)
+    idx = [rng.integers(0, d, nnz).astype(np.int32) for d in dims]
+    place = np.arange(nnz, dtype=np.int64)
+    row = place // 64 if runs else rng.permutation(place) // 64
+    a = max(1, nnz * 618034 // 1000000)
+    while a > 1 and math.gcd(a, nnz) != 1:
+        a -= 1
+    idx[0] = np.empty(nnz, dtype=np.int32)
+    idx[0][(a * place + nnz // 3) % nnz] = (row * 7919) % dims[0]
+    return idx, rng.standard_normal(nnz).astype(np.float32)
+
+
 OWNER_CASES = [
-    # order, rows per mode, J, R, stored entries, |Psi|: modes hit evenly, enough samples x modes, ranks up to 8
-    (10, (10_000,) * 10, (4,) * 10, 4, 400_000, 100_001),
-    (2, (60_013, 40_009), (9, 3), 1, 300_000, 460_001),            # one column in use out of four, a ragged last group
-    (3, (30_011, 70_001, 26_000), (16, 5, 64), 7, 500_000, 700_003),   # idle columns, one row of B per thread group of 64
-    (7, (9_001, 8_000, 12_007, 6_500, 9_999, 7_000, 8_192), (8, 3, 8, 8, 1, 8, 12), 8, 300_000, 300_007),
+    # rows per mode, J, R, |Psi|: enough samples x modes, ranks up to 8
+    ((2_600, 2_503, 2_700, 2_600, 2_555, 2_611, 2_600, 2_700, 2_600, 2_801), (4,) * 10, 4, 100_001),
+    ((2_600, 2_503, 2_700, 2_600, 2_555, 2_611, 2_600, 2_700, 2_600, 2_801), (8, 3, 8, 8, 5, 8, 8, 8, 8, 8), 8, 210_013),
+    ((13_000, 14_001), (9, 3), 1, 460_001),                         # one column in use out of four, a ragged last group
+    ((8_500, 9_001, 8_700), (16, 5, 64), 7, 700_003),               # idle columns, one row of B per thread group of 64
+    ((6_311, 6_400, 7_001, 6_300), (8, 8, 8, 8), 8, 520_000),
+    ((5_200, 5_003, 5_400, 5_111, 5_222), (4, 4, 2, 4, 4), 3, 200_019),
+    ((4_300, 4_400, 4_211, 4_500, 4_300, 4_603), (8,) * 6, 8, 350_000),
+    ((9_001, 8_000, 12_007, 6_500, 9_999, 7_000, 8_192), (8, 3, 8, 8, 1, 8, 12), 8, 300_007),
+    ((3_200, 3_211, 3_300, 3_400, 3_201, 3_500, 3_200, 3_333), (4,) * 8, 4, 130_000),
+    ((2_900, 2_911, 2_800, 3_000, 2_903, 2_900, 2_950, 2_900, 3_100), (8,) * 9, 6, 240_000),
 ]
 
 
-@pytest.mark.parametrize("order,dims,J,R,nnz,M", OWNER_CASES)
+@pytest.mark.parametrize("dims,J,R,M", OWNER_CASES)
 @pytest.mark.parametrize("tiles", [False, True])
-def test_step_by_row_owners(order, dims, J, R, nnz, M, tiles):
+def test_step_by_row_owners(dims, J, R, M, tiles):
     """Large sample sets over evenly hit modes at small ranks: the step sums R numbers per row and sample in lists and
     applies B and A per row.  Every parameter against the oracle's step, then a step on the kernel with atomics (set by
     name), which finds the accumulators as it needs them, and one on the owners again.  Under the tile
-    rule every run of 64 entries is drawn many times, so that lists fill up and rows take the fallback."""
+    rule lists fill up and rows take the fallback."""
+    order = len(dims)
     announce("row owners order=%d J=%r R=%d M=%d%s" % (order, J, R, M, ", tiles" if tiles else ""))
-    w = synth.tiny_workload(order, dims, 6_400 if tiles else nnz, J, R, M, seed=50 + order, values="normal")
+    idx, vals = evenly_hit_tensor(dims, 50 + order, tiles)
     # an element moves by many tolerances: hits x |GS| x e
-    w = synth.replace(w, lr_A=0.2 * 6_400 / M if tiles else 0.005, lr_B=0.1, lambda_A=0.05, lambda_B=0.02)
-    idx, vals = synth.make_tensor(w)
+    rates = (0.1 * dims[0] / M, 0.1, 0.05, 0.02)
     rng = np.random.default_rng(order)
     A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
     B = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
@@ -712,8 +752,12 @@ def test_step_by_row_owners(order, dims, J, R, nnz, M, tiles):
         for t, kernel in enumerate(("auto", "tiled", "auto")):
             ft.ftk_set_kernel(kernel)
             ft.ftk_sample(900 + t, M)
-            ft.ftk_sgd_step(w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
-            oracle.sgd_step_sync(dims, idx, vals, A, B, draw(900 + t, M, w.nnz), w.lr_A, w.lr_B, w.lambda_A, w.lambda_B)
+            planned, _, before = ft.ftk_get_row_owners()
+            assert planned == (kernel == "auto")
+            ft.ftk_sgd_step(*rates)
+            spilled = ft.ftk_get_row_owners()[2] - before
+            assert (spilled > M // 20) if tiles and planned else (spilled < M // 100), spilled
+            oracle.sgd_step_sync(dims, idx, vals, A, B, draw(900 + t, M, len(vals)), *rates)
             gA, gB = ft.ftk_get_factors()
             assert_params_close(gA, A, "A, step %d" % t)
             assert_params_close(gB, B, "B, step %d" % t)
@@ -756,10 +800,9 @@ def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
     import torch
-    dims, J, R, M = (60_013, 40_009), (5, 8), 8, 1_100_001
+    dims, J, R, M = (13_000, 14_001), (5, 8), 8, 1_100_001
     announce("captured step, M=%d" % M)
-    w = synth.tiny_workload(2, dims, 300_000, J, R, M, seed=3, values="normal")
-    idx, vals = synth.make_tensor(w)
+    idx, vals = evenly_hit_tensor(dims, 3, False)
     rng = np.random.default_rng(2)
     A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
     B = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
@@ -769,12 +812,16 @@ def test_a_captured_step_outlives_the_owners_lists():
         ft.ftk_set_stream(stream.cuda_stream)
         ft.ftk_sample(77, M)
         ft.ftk_sgd_step(*rates)
+        planned, held, _ = ft.ftk_get_row_owners()
+        assert planned and held > 0
         with torch.cuda.graph(graph, stream=stream):
             ft.ftk_sgd_step(*rates)
         ft.ftk_sample(78, 3 * M)
         ft.ftk_sgd_step(*rates)
+        planned, more, _ = ft.ftk_get_row_owners()
+        assert planned and more > held          # the lists that were there at the capture are gone
         ft.ftk_set_factors(A, B)
-        pos = oracle.sample_positions(77, M, w.nnz)
+        pos = oracle.sample_positions(77, M, len(vals))
         for t in range(3):
             with torch.cuda.stream(stream):
                 graph.replay()
