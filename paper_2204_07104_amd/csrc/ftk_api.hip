@@ -2112,7 +2112,10 @@ int move_params(ftk_ctx* c, F* const* A, F* const* B) {
     F* host[2 * kMaxOrder] = {};
     const ParamSegments p = param_segments(c, A, B, host);
     const long long total = p.begin[p.count];
-    if (total == 0) return FTK_OK;
+    if (total == 0) {   // nothing to move, but these calls always wait
+        FTK_HIP(c, hipStreamSynchronize(c->stream));
+        return FTK_OK;
+    }
     int threads = 1;
     if (const int rc = ring_setup(c, (size_t)total * sizeof(float), &threads)) return rc;
     const long long chunk = (long long)(c->ring_chunk / sizeof(float)), n = (total + chunk - 1) / chunk;

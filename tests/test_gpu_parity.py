@@ -834,6 +834,25 @@ def test_a_captured_step_outlives_the_owners_lists():
         ft.ftk_set_stream(None)
 
 
+def test_moving_no_factors_still_waits_for_the_stream():
+    """ftk_get_factors / ftk_set_factors wait for the context's stream also where every pointer is NULL."""
+    import torch
+    announce("no factors to move")
+    w = synth.tiny_workload(3, (3_000, 2_000, 1_000), 200_000, (32, 32, 32), 32, 2_000_000)
+    idx, vals = synth.make_tensor(w)
+    stream = torch.cuda.Stream()
+    with binding.FastTucker(w.dims, idx, vals, w.J, w.R) as ft:
+        ft.ftk_set_stream(stream.cuda_stream)
+        ft.ftk_sample(1, w.n_samples)
+        for move in (lambda: ft._check(ft._L.ftk_get_factors(ft._ctx, None, None)), lambda: ft.ftk_set_factors(None, None)):
+            for _ in range(50):
+                ft.ftk_sgd_step(0.0, 0.0, 0.0, 0.0)
+            assert not stream.query()      # there is something to wait for
+            move()
+            assert stream.query()
+        ft.ftk_set_stream(None)
+
+
 @pytest.mark.parametrize("dims,J,R", [
     ((1, 1), (1, 1), 1),
     ((4_097, 3, 259), (5, 16, 8), 9),             # one chunk of the ring, odd row lengths
