@@ -2253,50 +2253,47 @@ int ftk_set_kernel(ftk_ctx* c, const char* name) {
     if (!c) return FTK_EINVAL;
     if (!name) return fail(c, FTK_EINVAL, "name is NULL");
     if (const int rc_dev = check_device(c)) return rc_dev;
-    // the accumulators of both variants are clean between steps, so switching is always safe
-    c->auto_kernel = !strcmp(name, "auto");
-    c->own = false;
-    c->own_for_M = -1;   // planned again with the next ftk_sample
-    if (c->auto_kernel)
-        name = (c->mfma16_ok && (c->order <= 5 || !c->tiled_ok)) ? "mfma16" : c->tiled_ok ? "tiled" : c->mfma16_ok ? "mfma16" : "generic";
-    if (!strcmp(name, "rows") || !strcmp(name, "rows:tight")) {
+    // what is asked for, and whether this shape and mode have it: a refusal changes nothing
+    const bool is_auto = !strcmp(name, "auto");
+    if (is_auto) name = (c->mfma16_ok && (c->order <= 5 || !c->tiled_ok)) ? "mfma16" : c->tiled_ok ? "tiled" : c->mfma16_ok ? "mfma16" : "generic";
+    const bool tight = !strcmp(name, "rows:tight"), rows = tight || !strcmp(name, "rows");
+    int variant;
+    if (rows) {
         if (!c->rows_ok)
             return fail(c, FTK_EUNSUPPORTED, "rows needs the tiled kernel's shapes with every J_n a multiple of 4 and at most 4096 buckets of rows");
         if (c->mode != FTK_SYNC) return fail(c, FTK_EUNSUPPORTED, "the \"rows\" kernel serves the synchronous step only");
-        const int old_variant = c->variant;
-        const bool old_rows = c->rows, old_tight = c->rows_tight;
-        c->variant = V_TILED;
-        c->rows = true;
-        c->rows_tight = name[4] == ':';
-        int rc = pick_hot_rows(c, std::max<long long>(c->n_samples, 1));
-        if (rc == FTK_OK) rc = prepare_variant(c);
-        if (rc != FTK_OK) {   // back to what was in use
-            c->variant = old_variant;
-            c->rows = old_rows;
-            c->rows_tight = old_tight;
-            if (c->variant != V_GENERIC) pick_hot_rows(c, std::max<long long>(c->n_samples, 1));
-        }
-        return rc;
-    }
-    c->rows = false;
-    if (!strcmp(name, "generic")) {
+        variant = V_TILED;
+    } else if (!strcmp(name, "generic")) {
         if (c->gen_threads == 0) return fail(c, FTK_EUNSUPPORTED, "the generic kernel does not fit this shape");
-        c->variant = V_GENERIC;
-        return prepare_variant(c);
-    }
-    if (!strcmp(name, "mfma16")) {
+        variant = V_GENERIC;
+    } else if (!strcmp(name, "mfma16")) {
         if (!c->mfma16_ok) return fail(c, FTK_EUNSUPPORTED, "mfma16 needs J_n = R = 16 and order <= 6");
-        c->variant = V_MFMA16;
-        if (const int rc = pick_hot_rows(c, std::max<long long>(c->n_samples, 1))) return rc;
-        return prepare_variant(c);
+        variant = V_MFMA16;
+    } else if (!strcmp(name, "tiled")) {
+        if (!c->tiled_ok) return fail(c, FTK_EUNSUPPORTED, "tiled needs order <= 8 with J_n, R <= 64 (order 9, 10: <= 16) and padded core factors that fit LDS");
+        variant = V_TILED;
+    } else {
+        return fail(c, FTK_EUNSUPPORTED, "no kernel variant named '%s'", name);
     }
-    if (!strcmp(name, "tiled")) {
-        if (!c->tiled_ok) return fail(c, FTK_EUNSUPPORTED, "tiled needs order <= 8 with J_n, R <= 64 (order 9, 10: <= 16) and padded core factors that fit LDS twice");
-        c->variant = V_TILED;
-        if (const int rc = pick_hot_rows(c, std::max<long long>(c->n_samples, 1))) return rc;
-        return prepare_variant(c);
+    // the accumulators of all variants are clean between steps, so switching is always safe
+    const int old_variant = c->variant;
+    const bool old_rows = c->rows, old_tight = c->rows_tight, old_auto = c->auto_kernel;
+    c->variant = variant;
+    c->rows = rows;
+    c->rows_tight = tight;
+    c->auto_kernel = is_auto;
+    c->own = false;
+    c->own_for_M = -1;   // planned again with the next ftk_sample
+    int rc = variant == V_GENERIC ? FTK_OK : pick_hot_rows(c, std::max<long long>(c->n_samples, 1));
+    if (rc == FTK_OK) rc = prepare_variant(c);
+    if (rc != FTK_OK) {   // back to what was in use
+        c->variant = old_variant;
+        c->rows = old_rows;
+        c->rows_tight = old_tight;
+        c->auto_kernel = old_auto;
+        if (c->variant != V_GENERIC) pick_hot_rows(c, std::max<long long>(c->n_samples, 1));
     }
-    return fail(c, FTK_EUNSUPPORTED, "no kernel variant named '%s'", name);
+    return rc;
 }
 
 const char* ftk_kernel_name(const ftk_ctx* c) {

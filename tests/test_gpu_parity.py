@@ -796,6 +796,29 @@ def test_table_rows_of_the_callers_width(dims, zipf, J, R):
             A, B = gA, gB
 
 
+def test_a_refused_kernel_name_changes_nothing():
+    announce("refused kernel names")
+    dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_sample(1, M)
+        for name in ("no such kernel", "rows!", ""):
+            with pytest.raises(binding.FtkError):
+                ft.ftk_set_kernel(name)
+            assert ft.ftk_get_row_owners()[0] and ft.ftk_kernel_name() == "mfma16"
+            ft.ftk_sample(2, M + 1)
+            assert ft.ftk_get_row_owners()[0]      # "auto" is still in force
+            ft.ftk_sample(1, M)
+    w = synth.tiny_workload(3, (300, 200, 100), 20_000, (32, 32, 32), 32, 5_000)
+    idx, vals = synth.make_tensor(w)
+    with binding.FastTucker(w.dims, idx, vals, w.J, w.R) as ft:
+        ft.ftk_set_kernel("rows")
+        for name in ("mfma16", "no such kernel"):
+            with pytest.raises(binding.FtkError):
+                ft.ftk_set_kernel(name)
+            assert ft.ftk_kernel_name() == "rows"
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
