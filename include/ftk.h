@@ -110,7 +110,7 @@ void ftk_destroy(ftk_ctx* ctx);
  *   u = w0 | w1 << 32  for even k,   w2 | w3 << 32  for odd k
  *   p_k = floor(u * nnz / 2^64)
  * Psi stays valid until the next ftk_sample.  1 <= n_samples < 2^31.
- * A changed n_samples plans the step anew; where "auto" then takes row owners (see ftk_set_kernel) this allocates
+ * A changed n_samples plans the step anew; where "auto" then takes row owners (FTK_SYNC only, see ftk_set_kernel) this allocates
  * their lists and workspace on the device, kept for the context's life.  While the stream is being captured, or where memory is
  * short, nothing is allocated and the step runs without them.
  */

@@ -145,7 +145,7 @@ struct ftk_ctx {
     unsigned int* d_overflow = nullptr;
     // Synchronous step by row owners in the space of the projections (ftk_kernels_owners.hpp)
     bool auto_kernel = true;         // the kernel variant is the library's choice
-    bool own = false;                // for the current |Psi|
+    bool own = false;                // with a Psi of own_for_M samples, for which the rest here is planned
     long long own_for_M = -1;
     int own_buckets = 0, own_lists = 0, own_core_floats = 0;
     unsigned int own_rows_per_bucket[kMaxOrder] = {}, own_bucket0[kMaxOrder + 1] = {}, own_cap[kMaxOrder] = {}, own_place0[kMaxOrder] = {};
@@ -1277,6 +1277,9 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
     c->own = true;
 }
 
+// Whether the plan is that of the Psi and mode in force.
+bool step_is_owners(const ftk_ctx* c) { return c->own && c->own_for_M == c->n_samples && c->mode == FTK_SYNC; }
+
 template <int N, int G>
 int launch_append_ng(ftk_ctx* c, const AppendArgs& g) {
     if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(append_lists_kernel<N, G>), c->max_lds)) return rc;
@@ -1681,7 +1684,7 @@ int ftk_sample(ftk_ctx* c, uint64_t seed, int64_t n_samples) {
             return rc;
         }
     }
-    if (c->own_for_M != n_samples) {
+    if (c->mode == FTK_SYNC && c->own_for_M != n_samples) {   // (the in-place modes have no use for the owners' lists)
         c->own_for_M = n_samples;
         c->own = false;
         if (check_device(c) == FTK_OK) plan_owners(c, n_samples);
@@ -1715,7 +1718,7 @@ int ftk_sgd_step(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, float lambd
     if (c->n_samples < 1) return fail(c, FTK_ESTATE, "ftk_sgd_step before ftk_sample");
     // A captured step keeps to buffers that live as long as the context: a larger Psi replaces the owners' lists, and a graph
     // recorded before would go on using the old ones.
-    if (c->own && c->mode == FTK_SYNC && !stream_capturing(c)) return step_owners(c, lr_A, lr_B, lambda_A, lambda_B);
+    if (step_is_owners(c) && !stream_capturing(c)) return step_owners(c, lr_A, lr_B, lambda_A, lambda_B);
     c->use_hot_partial = c->d_hot_partial;
     c->use_gb_partial = c->d_gb_partial;
     return step_impl(c, lr_A, lr_B, lambda_A, lambda_B);
@@ -2313,7 +2316,7 @@ int ftk_get_table_rows(ftk_ctx* c, int32_t* K_out, int32_t* top_out) {
 
 int ftk_get_row_owners(ftk_ctx* c, int32_t* planned, int64_t* bytes, int64_t* spilled) {
     if (!c) return FTK_EINVAL;
-    if (planned) *planned = (c->own && c->mode == FTK_SYNC) ? 1 : 0;
+    if (planned) *planned = step_is_owners(c) ? 1 : 0;
     if (bytes) {
         const size_t rank4 = ((size_t)c->R_user + 3) & ~(size_t)3;
         *bytes = (int64_t)(c->own_value_floats * 4 + (c->d_own_ids ? c->own_value_floats / rank4 * 2 : 0) + c->own_fill_words * 4 + c->own_core_total * 4);

@@ -819,6 +819,33 @@ def test_a_refused_kernel_name_changes_nothing():
             assert ft.ftk_kernel_name() == "rows"
 
 
+def test_in_place_modes_hold_no_lists_for_row_owners():
+    announce("in-place modes and row owners")
+    dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        for mode in (binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE):
+            ft.ftk_set_mode(mode)
+            ft.ftk_sample(1, M)
+            ft.ftk_sgd_step(0.0, 0.0, 0.0, 0.0)
+            assert ft.ftk_get_row_owners()[:2] == (False, 0)
+        ft.ftk_set_mode(binding.FTK_SYNC)
+        ft.ftk_sample(1, M)
+        planned, held, _ = ft.ftk_get_row_owners()
+        assert planned and held > 0
+        # a Psi drawn in another mode: no plan is taken up that was made for another size
+        ft.ftk_set_mode(binding.FTK_HOGWILD)
+        ft.ftk_sample(1, 3 * M)
+        ft.ftk_set_mode(binding.FTK_SYNC)
+        assert ft.ftk_get_row_owners()[:2] == (False, held)
+        A, B = ft.ftk_get_factors()
+        ft.ftk_sgd_step(1e-3, 1e-3, 0.05, 0.02)
+        oracle.sgd_step_sync(dims, idx, vals, A, B, oracle.sample_positions(1, 3 * M, len(vals)), 1e-3, 1e-3, 0.05, 0.02)
+        gA, gB = ft.ftk_get_factors()
+        assert_params_close(gA, A, "A")
+        assert_params_close(gB, B, "B")
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
