@@ -156,7 +156,7 @@ struct ftk_ctx {
     unsigned int* d_own_fill = nullptr;
     float* d_own_core = nullptr;
     unsigned int* d_own_overflow = nullptr;   // rows that found a full list: of the step in the stream | of all steps before
-    size_t own_value_floats = 0, own_fill_words = 0, own_core_total = 0;
+    size_t own_value_floats = 0, own_ids = 0, own_fill_words = 0, own_core_total = 0;
     float* use_hot_partial = nullptr; // the partial tables of the step being enqueued: the two above, or the
     float* use_gb_partial = nullptr;  // library's static scratch array (ftk_sgd_step_noalloc)
 
@@ -1241,26 +1241,29 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
     // memory
     const size_t values = (size_t)lists * places * Rs, fill = (size_t)lists * n_buckets, core = (size_t)n_buckets * c->own_core_floats;
     // (a growth that failed half way leaves a part missing, which is made here another time)
-    if (!c->d_S || !c->d_own_ids || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
+    if (!c->d_S || values / Rs > c->own_ids || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
         if (stream_capturing(c)) return;
         size_t free_bytes = 0, all_bytes = 0;
         if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes) return;
         hipStreamSynchronize(c->stream);
+        // (by half at least, where memory allows it: a |Psi| that rises from step to step makes new lists now and then only)
         auto grow = [&](auto*& ptr, size_t& have, size_t want) {
             if (ptr && have >= want) return true;
+            size_t room = std::max(want, have + have / 2);
+            if (room * sizeof(*ptr) * 5 / 4 > free_bytes) room = want;
             if (ptr) hipFree(ptr);
             ptr = nullptr;
             have = 0;
-            if (hipMalloc((void**)&ptr, want * sizeof(*ptr)) != hipSuccess) {
+            if (hipMalloc((void**)&ptr, room * sizeof(*ptr)) != hipSuccess) {
                 (void)hipGetLastError();
                 ptr = nullptr;
                 return false;
             }
-            have = want;
+            have = room;
             return true;
         };
-        size_t ids_have = c->d_own_ids ? c->own_value_floats / Rs : 0, one = c->d_own_overflow ? 2 : 0, s_have = c->d_S ? (size_t)rows_total * Rs : 0;
-        const bool ok = grow(c->d_own_ids, ids_have, values / Rs) && grow(c->d_own_values, c->own_value_floats, values) &&
+        size_t one = c->d_own_overflow ? 2 : 0, s_have = c->d_S ? (size_t)rows_total * Rs : 0;
+        const bool ok = grow(c->d_own_ids, c->own_ids, values / Rs) && grow(c->d_own_values, c->own_value_floats, values) &&
                         grow(c->d_own_fill, c->own_fill_words, fill) && grow(c->d_own_core, c->own_core_total, core) &&
                         grow(c->d_S, s_have, (size_t)rows_total * Rs);
         if (!ok) return;
@@ -2317,10 +2320,7 @@ int ftk_get_table_rows(ftk_ctx* c, int32_t* K_out, int32_t* top_out) {
 int ftk_get_row_owners(ftk_ctx* c, int32_t* planned, int64_t* bytes, int64_t* spilled) {
     if (!c) return FTK_EINVAL;
     if (planned) *planned = step_is_owners(c) ? 1 : 0;
-    if (bytes) {
-        const size_t rank4 = ((size_t)c->R_user + 3) & ~(size_t)3;
-        *bytes = (int64_t)(c->own_value_floats * 4 + (c->d_own_ids ? c->own_value_floats / rank4 * 2 : 0) + c->own_fill_words * 4 + c->own_core_total * 4);
-    }
+    if (bytes) *bytes = (int64_t)(c->own_value_floats * 4 + c->own_ids * 2 + c->own_fill_words * 4 + c->own_core_total * 4);
     if (spilled) {
         if (const int rc_dev = check_device(c)) return rc_dev;
         unsigned int total = 0;

@@ -846,6 +846,22 @@ def test_in_place_modes_hold_no_lists_for_row_owners():
         assert_params_close(gB, B, "B")
 
 
+def test_row_owners_lists_grow_in_few_steps():
+    """|Psi| rising by a twentieth from step to step to 2.9 times its size: lists that grow by half at least are made four
+    times, lists of the exact size at every rise."""
+    announce("rising Psi and row owners")
+    dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    sizes = []
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        for t in range(22):
+            ft.ftk_sample(t, int(M * 1.05 ** t))
+            planned, held, _ = ft.ftk_get_row_owners()
+            assert planned
+            sizes.append(held)
+    assert sizes == sorted(sizes) and len(set(sizes)) <= 6, sizes
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
