@@ -147,6 +147,8 @@ struct ftk_ctx {
     bool auto_kernel = true;         // the kernel variant is the library's choice
     bool own = false;                // with a Psi of own_for_M samples, for which the rest here is planned
     long long own_for_M = -1;
+    long long own_refused_M = -1;    // |Psi| whose plan failed for a reason that passes: asked for again (see replan_owners)
+    int own_wait = 0, own_backoff = 1;
     int own_buckets = 0, own_lists = 0, own_core_floats = 0;
     unsigned int own_rows_per_bucket[kMaxOrder] = {}, own_bucket0[kMaxOrder + 1] = {}, own_cap[kMaxOrder] = {}, own_place0[kMaxOrder] = {};
     unsigned int own_places = 0;
@@ -1157,28 +1159,28 @@ bool stream_capturing(ftk_ctx* c) {
 
 // Whether the synchronous step over n_samples samples goes by row owners, with what buckets and lists, and their memory.
 // Not an error if not: the other kernels do every step.
-void plan_owners(ftk_ctx* c, long long n_samples) {
-    c->own = false;
+enum class OwnersPlan { never, not_now, ready };   // not_now: for a reason that passes (stream capture, memory short)
+OwnersPlan plan_owners(ftk_ctx* c, long long n_samples) {
     const int N = c->order, Rs = (c->R_user + 3) & ~3;
-    if (!c->auto_kernel || c->variant == V_GENERIC || N < 2 || c->R_user > kOwnersRank) return;
+    if (!c->auto_kernel || c->variant == V_GENERIC || N < 2 || c->R_user > kOwnersRank) return OwnersPlan::never;
     long long rows_total = 0;
     double cold = 0.0;
     for (int n = 0; n < N; ++n) {
-        if (c->J_user[n] > kProjectMaxRank || c->dims[n] >= (1LL << 24)) return;
+        if (c->J_user[n] > kProjectMaxRank || c->dims[n] >= (1LL << 24)) return OwnersPlan::never;
         rows_total += c->dims[n];
         double on_chip = 0.0;
         for (int r = 0; r < c->hot_K[n]; ++r) on_chip += (double)c->sorted_counts[n][r];
         cold += 1.0 - on_chip / (double)c->nnz;
     }
     const double entries = (double)n_samples * N;
-    if (cold < kOwnersCold * N || entries < (Rs <= 4 ? kOwnersEntries4 : kOwnersEntries8) || (double)rows_total > kOwnersRows * entries) return;
+    if (cold < kOwnersCold * N || entries < (Rs <= 4 ? kOwnersEntries4 : kOwnersEntries8) || (double)rows_total > kOwnersRows * entries) return OwnersPlan::never;
     // Buckets: as many as two workgroups per CU own at once, or a multiple of that, with their sums in half of a CU's LDS.  Every
     // mode has one entry per sample, so the modes get the same number of buckets, but for those whose rows need more.
     const long long most_rows = std::min<long long>(65535, ((long long)c->max_lds / 8 - c->num_cu) / (Rs + 1));
     int n_buckets = 0;
     for (int m = 1;; ++m) {
         const long long target = 2LL * c->num_cu * m;
-        if (target > kOwnersMaxBuckets) return;
+        if (target > kOwnersMaxBuckets) return OwnersPlan::never;
         long long nb[kMaxOrder], left = target;
         for (int n = 0; n < N; ++n) left -= nb[n] = (c->dims[n] + most_rows - 1) / most_rows;
         if (left < 0) continue;
@@ -1197,7 +1199,7 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
         n_buckets = 0;
         for (int n = 0; n < N; ++n) {
             const long long per = (c->dims[n] + nb[n] - 1) / nb[n];
-            if (per < kOwnersBucketRows) return;
+            if (per < kOwnersBucketRows) return OwnersPlan::never;
             c->own_rows_per_bucket[n] = (unsigned int)per;
             c->own_bucket0[n] = (unsigned int)n_buckets;
             n_buckets += (int)((c->dims[n] + per - 1) / per);
@@ -1212,12 +1214,12 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
         share[n] /= (double)c->nnz;
         fullest = std::max(fullest, share[n]);
     }
-    if (fullest * n_buckets > 1.6 * N) return;   // uneven: the owner of the fullest bucket would work on alone
+    if (fullest * n_buckets > 1.6 * N) return OwnersPlan::never;   // uneven: the owner of the fullest bucket would work on alone
     // one workgroup of the appending pass per CU, but no more than give every wave 64 samples: a bucket has a list in each
     int lists = (int)std::max<long long>(1, std::min<long long>(c->num_cu, (n_samples + kAppendThreads - 1) / kAppendThreads));
     unsigned long long places = 0;
     for (;; lists += c->num_cu) {
-        if (lists > 8 * c->num_cu) return;
+        if (lists > 8 * c->num_cu) return OwnersPlan::never;
         places = 0;
         for (int n = 0; n < N; ++n) {
             const double expect = share[n] * (double)n_samples / lists;
@@ -1240,12 +1242,14 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
     }
     // memory
     const size_t values = (size_t)lists * places * Rs, fill = (size_t)lists * n_buckets, core = (size_t)n_buckets * c->own_core_floats;
-    // (a growth that failed half way leaves a part missing, which is made here another time)
+    // (a growth that failed half way leaves a part missing, which is made here the next time)
     if (!c->d_S || values / Rs > c->own_ids || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
-        if (stream_capturing(c)) return;
+        if (stream_capturing(c)) return OwnersPlan::not_now;
         size_t free_bytes = 0, all_bytes = 0;
-        if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes) return;
-        hipStreamSynchronize(c->stream);
+        if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes || hipStreamSynchronize(c->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return OwnersPlan::not_now;
+        }
         // (by half at least, where memory allows it: a |Psi| that rises from step to step makes new lists now and then only)
         auto grow = [&](auto*& ptr, size_t& have, size_t want) {
             if (ptr && have >= want) return true;
@@ -1266,22 +1270,45 @@ void plan_owners(ftk_ctx* c, long long n_samples) {
         const bool ok = grow(c->d_own_ids, c->own_ids, values / Rs) && grow(c->d_own_values, c->own_value_floats, values) &&
                         grow(c->d_own_fill, c->own_fill_words, fill) && grow(c->d_own_core, c->own_core_total, core) &&
                         grow(c->d_S, s_have, (size_t)rows_total * Rs);
-        if (!ok) return;
+        if (!ok) return OwnersPlan::not_now;
         if (!one) {
-            if (!grow(c->d_own_overflow, one, 2)) return;
+            if (!grow(c->d_own_overflow, one, 2)) return OwnersPlan::not_now;
             hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<float*>(c->d_own_overflow), 2LL);
             if (hipGetLastError() != hipSuccess) {
                 hipFree(c->d_own_overflow);
                 c->d_own_overflow = nullptr;
-                return;
+                return OwnersPlan::not_now;
             }
         }
     }
-    c->own = true;
+    return OwnersPlan::ready;
 }
 
 // Whether the plan is that of the Psi and mode in force.
 bool step_is_owners(const ftk_ctx* c) { return c->own && c->own_for_M == c->n_samples && c->mode == FTK_SYNC; }
+
+// Plans the synchronous step over n_samples samples.  What could not be had this time is asked for again, at the next
+// ftk_sample while the stream is captured, else (memory short) after 1, 2, 4 ... up to 1 024 of them.
+void replan_owners(ftk_ctx* c, long long n_samples) {
+    c->own = false;
+    c->own_for_M = -1;
+    if (n_samples == c->own_refused_M && c->own_wait > 0) {
+        c->own_wait -= 1;
+        return;
+    }
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev != c->device) return;   // nothing is allocated on another device
+    const OwnersPlan plan = plan_owners(c, n_samples);
+    if (plan == OwnersPlan::not_now) {
+        c->own_backoff = n_samples == c->own_refused_M ? std::min(2 * c->own_backoff, 1024) : 1;
+        c->own_refused_M = n_samples;
+        c->own_wait = stream_capturing(c) ? 0 : c->own_backoff - 1;
+        return;
+    }
+    c->own = plan == OwnersPlan::ready;
+    c->own_for_M = n_samples;
+    c->own_refused_M = -1;
+}
 
 template <int N, int G>
 int launch_append_ng(ftk_ctx* c, const AppendArgs& g) {
@@ -1687,11 +1714,7 @@ int ftk_sample(ftk_ctx* c, uint64_t seed, int64_t n_samples) {
             return rc;
         }
     }
-    if (c->mode == FTK_SYNC && c->own_for_M != n_samples) {   // (the in-place modes have no use for the owners' lists)
-        c->own_for_M = n_samples;
-        c->own = false;
-        if (check_device(c) == FTK_OK) plan_owners(c, n_samples);
-    }
+    if (c->mode == FTK_SYNC && c->own_for_M != n_samples) replan_owners(c, n_samples);   // (the in-place modes have no use for lists)
     return FTK_OK;
 }
 

@@ -862,6 +862,36 @@ def test_row_owners_lists_grow_in_few_steps():
     assert sizes == sorted(sizes) and len(set(sizes)) <= 6, sizes
 
 
+def test_row_owners_are_planned_when_a_refusal_has_passed():
+    """A Psi first drawn while the stream is being captured gets no lists (nothing may be allocated then); the same size drawn
+    again afterwards does, and the graph's steps and the direct ones are the oracle's."""
+    import torch
+    announce("row owners after a capture")
+    dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    rates = (0.002, 0.1, 0.05, 0.02)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_set_stream(stream.cuda_stream)
+        A, B = ft.ftk_get_factors()
+        with torch.cuda.graph(graph, stream=stream):
+            ft.ftk_sample(5, M)
+            ft.ftk_sgd_step(*rates)
+        assert ft.ftk_get_row_owners()[:2] == (False, 0)
+        pos = oracle.sample_positions(5, M, len(vals))
+        for step in (graph.replay, lambda: (ft.ftk_sample(5, M), ft.ftk_sgd_step(*rates)), graph.replay):
+            with torch.cuda.stream(stream):
+                step()
+            oracle.sgd_step_sync(dims, idx, vals, A, B, pos, *rates)
+            gA, gB = ft.ftk_get_factors()
+            assert_params_close(gA, A, "A")
+            assert_params_close(gB, B, "B")
+            A, B = gA, gB
+        assert ft.ftk_get_row_owners()[0]
+        stream.synchronize()
+        ft.ftk_set_stream(None)
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
