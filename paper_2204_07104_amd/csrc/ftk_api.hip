@@ -1157,6 +1157,22 @@ bool stream_capturing(ftk_ctx* c) {
     return true;
 }
 
+// While one lives, this thread's allocations do not end a graph that another stream is recording (the default mode of a
+// recording forbids them to every thread).  The context's own stream is not being captured where this is used.
+class BesideCapture {
+public:
+    BesideCapture() : set_(hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess) {}
+    ~BesideCapture() {
+        if (set_) hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+    BesideCapture(const BesideCapture&) = delete;
+    BesideCapture& operator=(const BesideCapture&) = delete;
+
+private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool set_;
+};
+
 // Whether the synchronous step over n_samples samples goes by row owners, with what buckets and lists, and their memory.
 // Not an error if not: the other kernels do every step.
 enum class OwnersPlan { never, not_now, ready };   // not_now: for a reason that passes (stream capture, memory short)
@@ -1245,6 +1261,7 @@ OwnersPlan plan_owners(ftk_ctx* c, long long n_samples) {
     // (a growth that failed half way leaves a part missing, which is made here the next time)
     if (!c->d_S || values / Rs > c->own_ids || values > c->own_value_floats || fill > c->own_fill_words || core > c->own_core_total || !c->d_own_overflow) {
         if (stream_capturing(c)) return OwnersPlan::not_now;
+        const BesideCapture beside;
         size_t free_bytes = 0, all_bytes = 0;
         if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || values * 5 > free_bytes || hipStreamSynchronize(c->stream) != hipSuccess) {
             (void)hipGetLastError();

@@ -892,6 +892,38 @@ def test_row_owners_are_planned_when_a_refusal_has_passed():
         ft.ftk_set_stream(None)
 
 
+def test_planning_beside_another_streams_capture_leaves_it_alone():
+    """ftk_sample and steps on one stream while another stream records a graph: the recording ends as if nothing had happened,
+    and the steps are the oracle's."""
+    import torch
+    announce("planning beside a capture")
+    dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    mine, other, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    x = torch.ones(1024, device="cuda")
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_set_stream(mine.cuda_stream)
+        with torch.cuda.graph(graph, stream=other):
+            x += 1.0
+            ft.ftk_sample(5, M)            # makes lists
+            ft.ftk_sgd_step(1e-3, 1e-3, 0.0, 0.0)
+            ft.ftk_sample(5, 2 * M)        # makes larger ones
+            ft.ftk_sgd_step(1e-3, 1e-3, 0.0, 0.0)
+            x *= 2.0
+        for t in range(3):
+            with torch.cuda.stream(other):
+                graph.replay()
+        other.synchronize()
+        assert (x == 22.0).all()       # ((1 + 1) 2 + 1) 2 ... three times
+        assert ft.ftk_get_row_owners()[0]
+        gA, gB = ft.ftk_get_factors()
+        A, B = oracle.init_factors(1, dims, J, R)
+        for m in (M, 2 * M):
+            oracle.sgd_step_sync(dims, idx, vals, A, B, oracle.sample_positions(5, m, len(vals)), 1e-3, 1e-3, 0.0, 0.0)
+        assert max(np.abs(g - o).max() for g, o in zip(gA + gB, A + B)) < 1e-5       # two steps of one within 1e-6 + 1e-4 x
+        ft.ftk_set_stream(None)
+
+
 def test_a_captured_step_outlives_the_owners_lists():
     """A step recorded into a graph where a step called directly would take the row owners, replayed after a larger Psi has
     replaced their lists: each replay against the oracle's step."""
