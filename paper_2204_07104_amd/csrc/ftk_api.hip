@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <numeric>
 #include <cstdarg>
 #include <cstdio>
@@ -268,7 +269,9 @@ int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
     return FTK_OK;
 }
 
-// Runs work(part, parts) on `parts` threads each time step() is called; step() returns when all have.
+// Runs work(part, parts) on `parts` threads each time step() is called; step() returns when all have.  Between two steps the
+// threads look for the next one for a while (a chunk takes the bus about 130 us) and then sleep: the caller may be waiting
+// behind a long queue (200 queued steps of 0.6 ms took 1.06 s of processor time for 8 threads that went on looking).
 template <class Work>
 class CopyTeam {
 public:
@@ -281,26 +284,40 @@ public:
             }
         }
         parts_ = (int)team_.size() + 1;
-        go_.store(0, std::memory_order_release);
+        tell(0);
     }
     ~CopyTeam() {
-        go_.store(-1, std::memory_order_release);
+        tell(-1);
         for (std::thread& t : team_) t.join();
     }
     CopyTeam(const CopyTeam&) = delete;
     CopyTeam& operator=(const CopyTeam&) = delete;
     void step(long long item) {
         item_ = item;
-        go_.store(++steps_, std::memory_order_release);
+        tell(++steps_);
         work_(item, 0, parts_);
         while (finished_.load(std::memory_order_acquire) != steps_ * (long long)team_.size()) std::this_thread::yield();
     }
 
 private:
+    static constexpr int kLooks = 500;   // of half a microsecond or more each
+    void tell(long long now) {
+        {
+            std::lock_guard<std::mutex> lock(mutex_);
+            go_.store(now, std::memory_order_release);
+        }
+        told_.notify_all();
+    }
     void follow(int part) {
         for (long long seen = 0;;) {
             long long now;
-            while ((now = go_.load(std::memory_order_acquire)) == seen || now == -2) std::this_thread::yield();
+            auto news = [&] { return (now = go_.load(std::memory_order_acquire)) != seen && now != -2; };
+            int looks = 0;
+            while (!news() && ++looks < kLooks) std::this_thread::yield();
+            if (looks == kLooks) {
+                std::unique_lock<std::mutex> lock(mutex_);
+                told_.wait(lock, news);
+            }
             if (now == -1) return;
             seen = now;
             work_(item_, part, parts_);
@@ -311,6 +328,8 @@ private:
     std::vector<std::thread> team_;
     int parts_ = 1;
     long long item_ = 0, steps_ = 0;
+    std::mutex mutex_;
+    std::condition_variable told_;
     std::atomic<long long> go_{-2}, finished_{0};   // -2: the team is still being put together, -1: over
 };
 

@@ -962,6 +962,32 @@ def test_a_captured_step_outlives_the_owners_lists():
         ft.ftk_set_stream(None)
 
 
+def test_copying_threads_sleep_while_the_stream_is_busy():
+    """Factors large enough for several copying threads, moved behind a queue of steps: the wait costs about one processor
+    (the runtime's own), not one per thread."""
+    import resource
+    import time
+    announce("copying threads behind a queue")
+    w = synth.tiny_workload(3, (400_000, 200_000, 100_000), 200_000, (32, 32, 32), 32, 2_000_000)
+    idx, vals = synth.make_tensor(w)
+
+    def processor_time():
+        r = resource.getrusage(resource.RUSAGE_SELF)
+        return r.ru_utime + r.ru_stime
+
+    with binding.FastTucker(w.dims, idx, vals, w.J, w.R) as ft:
+        A, B = ft.ftk_get_factors()
+        ft.ftk_sample(1, w.n_samples)
+        for move in (lambda: ft.ftk_get_factors(), lambda: ft.ftk_set_factors(A, B)):
+            for _ in range(200):
+                ft.ftk_sgd_step(0.0, 0.0, 0.0, 0.0)
+            t0, c0 = time.perf_counter(), processor_time()
+            move()
+            wall, used = time.perf_counter() - t0, processor_time() - c0
+            assert wall > 0.05       # there was a queue
+            assert used < 3.0 * wall, (used, wall)
+
+
 def test_moving_no_factors_still_waits_for_the_stream():
     """ftk_get_factors / ftk_set_factors wait for the context's stream also where every pointer is NULL."""
     import torch
