@@ -253,6 +253,8 @@ constexpr int kCopyThreads = 8;
 int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
     size_t chunk = kRingChunkMin;
     while (chunk < kRingChunkMax && chunk * 8 < bytes) chunk *= 2;   // (a large ring takes long to pin: 0.15 ms per MB)
+    for (hipEvent_t& e : c->ring_event)
+        if (!e) FTK_HIP(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     if (c->ring_chunk < chunk) {
         FTK_HIP(c, hipStreamSynchronize(c->stream));
         if (c->h_ring) hipHostFree(c->h_ring);
@@ -261,8 +263,6 @@ int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
         FTK_HIP(c, hipHostMalloc((void**)&c->h_ring, chunk * kRingDepth, hipHostMallocDefault));
         FTK_HIP(c, hipHostGetDevicePointer((void**)&c->d_ring, c->h_ring, 0));
         c->ring_chunk = chunk;
-        for (hipEvent_t& e : c->ring_event)
-            if (!e) FTK_HIP(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     const int cpus = (int)std::thread::hardware_concurrency();
     *threads = (int)std::max<size_t>(1, std::min<size_t>(bytes >> 20, (size_t)std::min(kCopyThreads, cpus > 1 ? cpus / 2 : 1)));
