@@ -269,6 +269,16 @@ int ring_setup(ftk_ctx* c, size_t bytes, int* threads) {
     return FTK_OK;
 }
 
+// A transfer that ends early leaves kernels behind that read or write the ring (and what they were sent to): they are waited
+// for before the call returns.  One that ends well has waited itself.
+struct RingDrain {
+    ftk_ctx* c;
+    bool ended_well = false;
+    ~RingDrain() {
+        if (!ended_well) hipStreamSynchronize(c->stream);
+    }
+};
+
 // Runs work(part, parts) on `parts` threads each time step() is called; step() returns when all have.  Between two steps the
 // threads look for the next one for a while (a chunk takes the bus about 130 us) and then sleep: the caller may be waiting
 // behind a long queue (200 queued steps of 0.6 ms took 1.06 s of processor time for 8 threads that went on looking).
@@ -2031,6 +2041,7 @@ int evaluate_host(ftk_ctx* c, int64_t n_eval, const int32_t* const* idx, const f
     int threads = 1;
     const size_t entry = (size_t)(N + 1) * sizeof(uint32_t);
     if (const int rc = ring_setup(c, (size_t)n_eval * entry, &threads)) return rc;
+    RingDrain drain{c};
     HeldOutArgs p = {};
     p.order = N;
     p.words = c->rec_words;
@@ -2061,6 +2072,7 @@ int evaluate_host(ftk_ctx* c, int64_t n_eval, const int32_t* const* idx, const f
     // (entries out of range read row 0: the errors over them are taken before the count is looked at, and dropped)
     double s[2] = {0.0, 0.0};
     if (const int rc = launch_errors(c, Coo{c->d_held_out, c->rec_words}, n_eval, s)) return rc;
+    drain.ended_well = true;
     unsigned int bad[kMaxOrder] = {};
     FTK_HIP(c, hipMemcpy(bad, c->d_flag, sizeof bad, hipMemcpyDeviceToHost));
     for (int n = 0; n < N; ++n)
@@ -2183,6 +2195,7 @@ int move_params(ftk_ctx* c, F* const* A, F* const* B) {
     }
     int threads = 1;
     if (const int rc = ring_setup(c, (size_t)total * sizeof(float), &threads)) return rc;
+    RingDrain drain{c};
     const long long chunk = (long long)(c->ring_chunk / sizeof(float)), n = (total + chunk - 1) / chunk;
     auto place = [&](char* ring, long long k) { return reinterpret_cast<float*>(ring + (size_t)(k % kRingDepth) * c->ring_chunk); };
     auto copy = [&](long long k, int part, int parts) {
@@ -2200,6 +2213,7 @@ int move_params(ftk_ctx* c, F* const* A, F* const* B) {
         return fail(c, FTK_ENOMEM, "host allocation failed");
     }
     FTK_HIP(c, hipStreamSynchronize(c->stream));
+    drain.ended_well = true;
     return FTK_OK;
 }
 

@@ -56,3 +56,24 @@ for k in (1, 3):
 ft.ftk_set_factors(A, B)
 same(ft.ftk_get_factors(), (A, B))
 """)
+
+
+def test_a_transfer_that_fails_half_way_leaves_nothing_in_the_stream(tmp_path):
+    """The chunks under way are waited for before the call returns: the ring is the next call's, and a held-out set's records are
+    freed."""
+    run(tmp_path, """
+hip = C.CDLL(binding.hip_runtime_path())
+held = [rng.integers(0, d, 1_500_000).astype(np.int32) for d in dims], np.ones(1_500_000, dtype=np.float32)
+ft.ftk_set_factors(A, B)
+want = ft.ftk_evaluate(*held)
+calls = (lambda: ft.ftk_set_factors([2 * a for a in A], B), lambda: ft.ftk_get_factors(), lambda: ft.ftk_evaluate(*held))
+for call in calls:
+    for k in (1, 3, 5):      # (17 and 18 MB: five chunks of up to 4 MB each)
+        shim.hip_failures_set(0, k)
+        refused(call, binding.FTK_EDEVICE)
+        assert hip.hipStreamQuery(None) == 0
+        shim.hip_failures_set(0, 0)
+        ft.ftk_set_factors(A, B)
+        same(ft.ftk_get_factors(), (A, B))
+assert np.allclose(ft.ftk_evaluate(*held), want, rtol=1e-12)
+""")
