@@ -396,6 +396,35 @@ def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
     one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
 
 
+@pytest.mark.parametrize("J,R", [((33,) * 5, 33), ((64,) * 5, 64), ((64, 35, 40, 8, 50), 48), ((16, 12, 9, 4, 16), 40)])
+@pytest.mark.parametrize("M", [15, 3_001])
+def test_order_five_above_rank_32(J, R, M):
+    """The highest order of the general kernel's form for ranks up to 64, whose registers spill most: every parameter of every
+    mode, each of which moves by a hundred tolerances and more."""
+    dims, nnz = (61, 50, 43, 37, 29), 20_000
+    announce("order 5, J=%r R=%d M=%d" % (J, R, M))
+    rng = np.random.default_rng(R)
+    idx = [rng.integers(0, d, nnz).astype(np.int32) for d in dims]
+    vals = rng.standard_normal(nnz).astype(np.float32)
+    A0 = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B0 = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
+    A, B = [a.copy() for a in A0], [b.copy() for b in B0]
+    rates = (0.02, 1.0, 0.05, 0.02)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "tiled"
+        ft.ftk_set_factors(A0, B0)
+        ft.ftk_sample(7, M)
+        ft.ftk_sgd_step(*rates)
+        gA, gB = ft.ftk_get_factors()
+    oracle.sgd_step_sync(dims, idx, vals, A, B, oracle.sample_positions(7, M, nnz), *rates)
+    assert_params_close(gA, A, "A")
+    assert_params_close(gB, B, "B")
+    for new, old in zip(A + B, A0 + B0):
+        # (the regulariser's part of a core factor is lr lambda = 2 % of it: what is left is the gradient's)
+        moved = np.abs(new - old * (1.0 if old.shape[0] in dims else 0.98))
+        assert np.max(moved / (ATOL + RTOL * np.abs(new))) > 100
+
+
 @pytest.mark.parametrize("J,R", [((5, 9, 7), 6), ((18, 30, 9), 22), ((35, 33, 50), 40)])
 @pytest.mark.parametrize("mode", [binding.FTK_SYNC, binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE])
 def test_a_row_that_no_sample_touches_may_hold_anything(J, R, mode):
@@ -1295,7 +1324,7 @@ def test_hogwild_mode_rmse_curve(name, nnz, M, dims, lr_A, lr_B, kernel, mode):
     # the general matrix-core kernel: one, two and four blocks of 16 ranks, and orders the J_n = R = 16 kernel is not built for
     ("tiled", 3, (16, 8, 12), 8, 5e-2, 1e-2), ("tiled", 3, (32, 24, 20), 24, 3e-5, 1e-3), ("tiled", 3, (64, 48, 40), 48, 3e-7, 1e-5),
     ("tiled", 4, (32, 32, 16, 20), 32, 3e-6, 1e-3), ("tiled", 6, (32, 16, 32, 16, 32, 16), 32, 3e-7, 1e-4),
-    ("tiled", 7, (16,) * 7, 16, 1e-4, 1e-3),
+    ("tiled", 7, (16,) * 7, 16, 1e-4, 1e-3), ("tiled", 5, (40, 33, 36, 64, 48), 40, 1e-10, 1e-8),
     # ranks that are no multiples of four: rows fetched float by float
     ("tiled", 3, (6, 10, 7), 5, 5e-2, 1e-2), ("tiled", 3, (18, 30, 9), 20, 3e-4, 1e-3), ("tiled", 2, (50, 33), 40, 1e-5, 1e-5)])
 def test_modewise_in_place_step_equals_the_printed_order_when_no_row_is_shared(kernel, N, J, R, lr_A, lr_B):
