@@ -136,10 +136,11 @@ __host__ __device__ constexpr size_t tiled_rows_lds_words(int order, int waves, 
 // projections.
 // (P = 1: the fp32 values twice, in the operand order of both products, see operand_slot)
 __host__ __device__ constexpr int tiled_core_bytes(int order, int P) { return P == 1 ? order * 2048 : 3 * order * P * P * kSplitBlockBytes; }
-// per wave, in words: two parked groups, three blocks in which tiles change their layout, and (P <= 2) 4 x 16 P words
-// nobody reads (see `sink`)
+// per wave, in words: two parked groups, what tiles change their layout in (the three parts of a block; P = 1: fp32 values in
+// padded rows), and (P <= 2) 4 x 16 P words nobody reads (see `sink`)
+__host__ __device__ constexpr int tiled_turn_words(int P) { return P == 1 ? kTransposeFloats : 3 * kSplitBlockBytes / 4; }
 __host__ __device__ constexpr int tiled_wave_scratch(int order, int P) {
-    return 2 * tiled_grad_park_words(order) + 3 * kSplitBlockBytes / 4 + (P < 4 ? 64 * P : 0);
+    return 2 * tiled_grad_park_words(order) + tiled_turn_words(P) + (P < 4 ? 64 * P : 0);
 }
 __host__ __device__ constexpr size_t tiled_lds_floats(int order, int P, int waves, int H) {
     return (size_t)tiled_core_bytes(order, P) / 4 + (size_t)H * 16 * P + (size_t)waves * tiled_wave_scratch(order, P);
@@ -174,7 +175,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     const SplitConst sc = split_const();
     // Table updates are issued for every element; those of samples that take another route aim at a
     // row of their own that nobody reads (one per 16-lane group, so they never collide).
-    float* sink = wave_lds + 2 * tiled_grad_park_words(N) + 3 * kSplitBlockBytes / 4;
+    float* sink = wave_lds + 2 * tiled_grad_park_words(N) + tiled_turn_words(P);
     const unsigned int sink_addr = lds_address(sink + g4 * D), hot_addr = lds_address(hot);
     const unsigned int sink_rel = sink_addr - hot_addr;          // beyond every row of the table
     const unsigned int top_key = kRouteOneHot | ((unsigned int)c << 2);   // the route word of row c of the one-hot product

@@ -396,6 +396,21 @@ def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
     one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
 
 
+def test_table_of_the_general_kernel_up_to_rank_16_fills_the_lds():
+    """Eight waves of 2 x (2 N + 1) x 64 words of parked samples, 16 x 20 floats to transpose a tile in and 64 words that nobody
+    reads, next to two copies of the core factors: the rest of the 160 KB is table, in rows of 64 bytes."""
+    N, dims = 6, (400,) * 6
+    announce("table rows, order 6")
+    w = synth.tiny_workload(N, dims, 100_000, (16,) * N, 16, 1_000_000)
+    idx, vals = synth.make_tensor(w)
+    with binding.FastTucker(dims, idx, vals, w.J, w.R) as ft:
+        assert ft.ftk_kernel_name() == "tiled"
+        ft.ftk_sample(1, w.n_samples)
+        K, top = ft.ftk_get_table_rows()
+    room = 160 * 1024 - 1024 - 4 * (2 * N * 256 + 8 * (2 * (2 * N + 1) * 64 + 16 * 20 + 64))
+    assert room // 64 - 1 <= sum(K) <= room // 64, (sum(K), room // 64)
+
+
 @pytest.mark.parametrize("J,R", [((33,) * 5, 33), ((64,) * 5, 64), ((64, 35, 40, 8, 50), 48), ((16, 12, 9, 4, 16), 40)])
 @pytest.mark.parametrize("M", [15, 3_001])
 def test_order_five_above_rank_32(J, R, M):
