@@ -147,7 +147,9 @@ int ftk_get_samples(ftk_ctx* ctx, int64_t* pos_out);
  * Non-finite parameters: the kernels keep the sample slots behind the end of Psi and the padding of
  * short ranks out of the sums by arithmetic (their operands are zero), which holds while A and B
  * are finite.  Once a step has produced inf or NaN (a step size far too large), every later call
- * still returns normally, but which further elements turn NaN is unspecified.
+ * still returns normally, but which further elements turn NaN is unspecified.  (A row that no sample of Psi touches may hold
+ * anything: nothing else sees it.)
+ * Small parameters: above rank 16 the "tiled" kernel takes products of numbers below 2^-108 (3e-33) with fewer than 24 bits.
  */
 int ftk_sgd_step(ftk_ctx* ctx, float lr_A, float lr_B, float lambda_A, float lambda_B);
 

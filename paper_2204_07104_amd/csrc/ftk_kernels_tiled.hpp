@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
             continue;
         }
         store_block(core + ((3 * n * P + (j >> 4)) * P + (r >> 4)) * kSplitBlockBytes + split_slot(j & 15, (r & 15) >> 2),
-                    P * P * kSplitBlockBytes, split(b, sc));
+                    P * P * kSplitBlockBytes, split<true>(b, sc));
     }
     for (int q = tid; q < g.H * D; q += THREADS) hot[q] = 0.0f;
     if constexpr (LDS_TABLE)
@@ -518,7 +518,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                     bf16x8 a[KC][3];
                     if constexpr (!X4) trim_rows(n, cur[n]);
 #pragma unroll
-                    for (int kc = 0; kc < KC; ++kc) split2(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a[kc]);
+                    for (int kc = 0; kc < KC; ++kc) split2<true>(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a[kc]);
 #pragma unroll
                     for (int i = 0; i < kSteps; ++i) {
                         const int st = n * kSteps + i, next = st + kAhead, part = 2 - i / KC, kc = i % KC;
@@ -603,7 +603,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
 #pragma unroll
                     for (int kc = 0; kc < KC; ++kc) {
                         bf16x8 a[3];
-                        split2(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a);
+                        split2<true>(cur[n][2 * kc], cur[n][2 * kc + 1], sc, a);
                         aYp[2 * kc] = turn_block(a, 0);
                         aYp[2 * kc + 1] = turn_block(a, 1);
                     }

@@ -58,9 +58,14 @@ __device__ __forceinline__ bf16x2 round_pair(float x, float y) {
     typedef float floatx2 __attribute__((ext_vector_type(2)));
     return __builtin_convertvector(floatx2{x, y}, bf16x2);
 }
+// WHOLE_RANGE (parameters): what is above the largest bf16, up to the largest fp32, goes into m; a plain conversion would make it
+// inf.  (C3 and C5 50.4 and 84.8 ms per pass either way; on every operand 51.3 ms.)  At the other end the parts run out: of a value
+// below 2^-108 the lower ones fall under the smallest bf16 (J = R = 64: 1e-36 keeps 1e-7, 1e-37 keeps 3e-6 of its size).
+constexpr float kTop = 0x1.fep127f;   // the largest bf16
+template <bool WHOLE_RANGE = false>
 __device__ __forceinline__ void split_pair(float x, float y, const SplitConst& k, unsigned int& h, unsigned int& m, unsigned int& l) {
     const bf16x2 low = __builtin_bit_cast(bf16x2, k.low), high = __builtin_bit_cast(bf16x2, k.high);
-    const bf16x2 hp = round_pair(x, y);
+    const bf16x2 hp = WHOLE_RANGE ? round_pair(__builtin_amdgcn_fmed3f(x, -kTop, kTop), __builtin_amdgcn_fmed3f(y, -kTop, kTop)) : round_pair(x, y);
     const float x1 = __builtin_amdgcn_fdot2_f32_bf16(hp, low, x, false), y1 = __builtin_amdgcn_fdot2_f32_bf16(hp, high, y, false);
     const bf16x2 mp = round_pair(x1, y1);
     const float x2 = __builtin_amdgcn_fdot2_f32_bf16(mp, low, x1, false), y2 = __builtin_amdgcn_fdot2_f32_bf16(mp, high, y1, false);
@@ -71,19 +76,21 @@ __device__ __forceinline__ void split_pair(float x, float y, const SplitConst& k
 }
 typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+template <bool WHOLE_RANGE = false>
 __device__ __forceinline__ Split split(const floatx4& x, const SplitConst& k) {
     unsigned int h0, h1, m0, m1, l0, l1;
-    split_pair(x[0], x[1], k, h0, m0, l0);
-    split_pair(x[2], x[3], k, h1, m1, l1);
+    split_pair<WHOLE_RANGE>(x[0], x[1], k, h0, m0, l0);
+    split_pair<WHOLE_RANGE>(x[2], x[3], k, h1, m1, l1);
     return Split{__builtin_bit_cast(bf16x8, uintx4{m0, m1, h0, h1}), __builtin_bit_cast(shortx4, uintx2{l0, l1})};
 }
 // The parts of two neighbouring blocks side by side: part 0 h, 1 m, 2 l.
+template <bool WHOLE_RANGE = false>
 __device__ __forceinline__ void split2(const floatx4& x, const floatx4& y, const SplitConst& k, bf16x8 (&part)[3]) {
     uintx4 h, m, l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         unsigned int hi, mi, li;
-        split_pair(i < 2 ? x[2 * i] : y[2 * i - 4], i < 2 ? x[2 * i + 1] : y[2 * i - 3], k, hi, mi, li);
+        split_pair<WHOLE_RANGE>(i < 2 ? x[2 * i] : y[2 * i - 4], i < 2 ? x[2 * i + 1] : y[2 * i - 3], k, hi, mi, li);
         h[i] = hi;
         m[i] = mi;
         l[i] = li;

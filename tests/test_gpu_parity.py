@@ -440,6 +440,36 @@ def test_order_five_above_rank_32(J, R, M):
         assert np.max(moved / (ATOL + RTOL * np.abs(new))) > 100
 
 
+@pytest.mark.parametrize("size", [3.4028e38, 1e-32])
+@pytest.mark.parametrize("J,R", [(24, 20), (64, 64)])
+def test_parameters_at_the_ends_of_the_fp32_range(J, R, size):
+    """Rows of the first mode up to the largest fp32 number (above the largest bf16) or near the smallest ones, with core factors
+    that bring the projections back: the core gradients of the modes whose own parameters are of ordinary size, against 64 bits
+    (sums of 4 000 positive terms in fp32: 4 000 / 16 tiles over 2 000 waves leave a handful of roundings of 2^-24 each)."""
+    dims, nnz, M = (300, 200, 100), 20_000, 4_000
+    announce("parameters of size %g, J=%d" % (size, J))
+    rng = np.random.default_rng(3)
+    idx = [rng.integers(0, d, nnz).astype(np.int32) for d in dims]
+    vals = rng.standard_normal(nnz).astype(np.float32)
+    A = [(rng.uniform(0.5, 1.0, size=(d, J)) * s).astype(np.float32) for d, s in zip(dims, (size, 1.0, 1.0))]
+    back = (1e-30, 1e-4, 1e-4) if size > 1 else (1e32, 1.0, 1.0)
+    B = [(rng.uniform(0.5, 1.0, size=(J, R)) * s / J).astype(np.float32) for s in back]
+    with binding.FastTucker(dims, idx, vals, (J,) * 3, R, 1, flags=binding.FTK_LAYOUT_EXACT) as ft:
+        ft.ftk_set_kernel("tiled")
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(5, M)
+        ft.ftk_sgd_step(0.0, float(M), 0.0, 0.0)
+        got = ft.ftk_get_factors()[1]
+    pos = oracle.sample_positions(5, M, nnz)
+    A64, B64 = [a.astype(np.float64) for a in A], [b.astype(np.float64) for b in B]
+    rows = [i[pos] for i in idx]
+    c = [a[r] @ b for a, r, b in zip(A64, rows, B64)]
+    minus_e = ((c[0] * c[1] * c[2]).sum(1) - vals[pos])[:, None]
+    for n, (k, m) in ((1, (0, 2)), (2, (0, 1))):
+        want = A64[n][rows[n]].T @ (c[k] * c[m] * minus_e)
+        assert np.linalg.norm((B64[n] - got[n]) - want) <= 4e-7 * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("J,R", [((5, 9, 7), 6), ((18, 30, 9), 22), ((35, 33, 50), 40)])
 @pytest.mark.parametrize("mode", [binding.FTK_SYNC, binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE])
 def test_a_row_that_no_sample_touches_may_hold_anything(J, R, mode):
