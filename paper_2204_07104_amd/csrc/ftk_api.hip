@@ -1811,7 +1811,6 @@ int ftk_sgd_step_noalloc(ftk_ctx* c, float lr_A, float lr_B, float lambda_A, flo
     float* base = scratch_address(c);
     if (!base) return fail(c, FTK_EUNSUPPORTED, "no static scratch array on device %d", c->device);
     // the partial tables of this step: [grid][H][row floats], then [grid x parts][B_total]
-    const bool tiled = c->variant == V_TILED;
     // (ranks above 32: the tables of the frequent rows sit behind dA, allocated with it)
     const size_t hot_floats = wide_tables(c) ? 0 : (((size_t)c->mfma_grid * c->hot_H * table_width(c)) + 63) / 64 * 64;
     const size_t gb_floats = (size_t)c->mfma_grid * c->L.B_total;

@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
     constexpr int THREADS = WAVES * 64;
     // Rows [top, K) of a mode: summed in the workgroup's LDS table (P <= 2, where the float atomics are what bounds
     // the pass), or in the workgroup's table in global memory through the atomics every element issues anyway
-    // (P = 4, where instruction issue bounds the pass and a swap with its round trip costs more than it saves).
+    // (P = 4: one wave per SIMD, where a swap with its round trip costs more than it saves).
     constexpr bool LDS_TABLE = P < 4;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g4 = lane >> 4;
