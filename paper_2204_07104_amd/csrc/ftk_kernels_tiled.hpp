@@ -766,7 +766,8 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                             for (int k = 0; k < 4; ++k)
                                 Top[n][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(is_top[k] ? 1.0f : 0.0f, grad[k], Top[n][0], 0, 0, 0);
                         } else {
-                            const Split gp = split(whole, sc);
+                            // (with the wave's sign turned back on: these sums lean, too, see ftk_split.hpp)
+                            const Split gp = split(floatx4{turned(grad[0]), turned(grad[1]), turned(grad[2]), turned(grad[3])}, sc);
                             floatx4 part = mfma_bf16(pair_up(shortx4{0, 0, 0, 0}, onehot), pair_up(high_half(gp.mh), gp.l), floatx4{0.0f, 0.0f, 0.0f, 0.0f});
                             part = mfma_bf16(pair_up(onehot, onehot), gp.mh, part);
                             Top[n][jb] += part;
@@ -842,7 +843,7 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
             for (int jb = 0; jb < P; ++jb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    lds_float_add(hot + (size_t)(g.hot_off[n] + 4 * g4 + v) * D + 16 * jb + c, Top[n][jb][v]);
+                    lds_float_add(hot + (size_t)(g.hot_off[n] + 4 * g4 + v) * D + 16 * jb + c, turned(1.0f) * Top[n][jb][v]);
         }
     // core gradient: summed over the workgroup's waves in LDS, where the operand tables are no longer needed (the
     // waves take turns, so plain adds do), and stored as one table per workgroup (entries outside J_n x R are padding)

@@ -502,6 +502,46 @@ def test_a_row_that_no_sample_touches_may_hold_anything(J, R, mode):
         assert_params_close(gB, B, "B")
 
 
+@pytest.mark.parametrize("J,R", [(32, 32), (21, 20), (64, 64)])
+def test_most_frequent_rows_are_as_precise_as_fp32_sums(J, R):
+    """The gradients of the 16 most frequent rows of every mode (2e4 to 5e5 samples each, of both signs) against 64 bits: sums
+    of as many terms over 2 000 waves, four fp32 roundings a tile and 61 tiles a wave, 2^-25 sqrt(244) = 4.7e-7, and the waves'
+    sums after that: 6e-7.  Roundings that lean one way show as a mean of the errors."""
+    dims, nnz, M = (20_000, 3_000, 500), 1_000_000, 2_000_003
+    announce("most frequent rows J=%d R=%d" % (J, R))
+    rng = np.random.default_rng(J)
+    idx = [np.minimum(((1.0 + rng.random(nnz) * ((d + 1.0) ** -0.2 - 1.0)) ** -5.0).astype(np.int64) - 1, d - 1).astype(np.int32) for d in dims]
+    vals = rng.standard_normal(nnz).astype(np.float32)
+    A = [rng.uniform(-1, 1, size=(d, J)).astype(np.float32) for d in dims]
+    B = [(rng.uniform(-1, 1, size=(J, R)) / J).astype(np.float32) for _ in dims]
+    with binding.FastTucker(dims, idx, vals, (J,) * 3, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "tiled"
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(5, M)
+        assert min(ft.ftk_get_table_rows()[1]) == 16       # the one-hot product is in use
+        ft.ftk_sgd_step(1.0, 0.0, 0.0, 0.0)
+        got = ft.ftk_get_factors()[0]
+    pos = oracle.sample_positions(5, M, nnz)
+    B64 = [b.astype(np.float64) for b in B]
+    proj = [a.astype(np.float64) @ b for a, b in zip(A, B64)]
+    err, size = [], []
+    for n, (k, m) in enumerate(((1, 2), (0, 2), (0, 1))):
+        for row in range(16):
+            hit = pos[idx[n][pos] == row]
+            w = np.zeros(R)
+            for lo in range(0, len(hit), 1 << 16):
+                p = hit[lo:lo + (1 << 16)]
+                ck, cm = proj[k][idx[k][p]], proj[m][idx[m][p]]
+                w += ((((ck * cm) @ proj[n][row]) - vals[p])[:, None] * ck * cm).sum(0)
+            grad = B64[n] @ w
+            err.append(got[n][row] - (A[n][row] - grad))
+            size.append(grad)
+    err, size = np.concatenate(err), np.sqrt(np.mean(np.concatenate(size) ** 2))
+    print("[case] relative error %.2e, mean %.1f standard errors" % (np.sqrt(np.mean(err ** 2)) / size, err.mean() / err.std() * np.sqrt(err.size)), flush=True)
+    assert np.sqrt(np.mean(err ** 2)) <= 6e-7 * size
+    assert abs(err.mean()) <= 6 * err.std() / np.sqrt(err.size)
+
+
 @pytest.mark.parametrize("J,R", [(32, 32), (18, 25), (64, 64), (40, 48)])
 def test_core_gradient_of_a_long_psi_is_as_precise_as_fp32_sums(J, R):
     """The core gradient by itself (lr_A = 0), 1e6 samples whose contributions have both signs, against 64 bits.  With fp32
