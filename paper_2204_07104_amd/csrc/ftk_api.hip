@@ -504,12 +504,23 @@ int launch_mfma16_ntm(ftk_ctx* c, const Mfma16Args& g) {
 }
 
 template <int N, bool TILES>
+int launch_core_phase_mfma16(ftk_ctx* c, const Mfma16Args& g) {
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(core_phase_mfma16_kernel<N, TILES>), c->max_lds)) return rc;
+    if (c->prepare_only) return FTK_OK;
+    Bracket t(c, FTK_K_GRAD);
+    hipLaunchKernelGGL((core_phase_mfma16_kernel<N, TILES>), dim3(c->mfma_grid), dim3(core_phase_waves(N) * 64), core_phase_lds_bytes(N),
+                       c->stream, g);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
+
+template <int N, bool TILES>
 int launch_mfma16_nt(ftk_ctx* c, const Mfma16Args& g, int pass) {
     switch (pass) {
         case kSyncPass: return launch_mfma16_ntm<N, TILES, kSyncPass>(c, g);
         case kInPlacePass: return launch_mfma16_ntm<N, TILES, kInPlacePass>(c, g);
         case kFactorPhase: return launch_mfma16_ntm<N, TILES, kFactorPhase>(c, g);
-        default: return launch_mfma16_ntm<N, TILES, kCorePhase>(c, g);
+        default: return launch_core_phase_mfma16<N, TILES>(c, g);
     }
 }
 

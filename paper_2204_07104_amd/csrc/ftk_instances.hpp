@@ -7,10 +7,10 @@
 #include "ftk_kernels_errors.hpp"
 #include "ftk_kernels_owners.hpp"
 
-// J_n = R = 16 kernel, order N: both sampling rules x the four passes, and the evaluation pass
-#define FTK_MFMA16_INSTANCES(X, XE, N)                                                    \
-    X(N, false, ftk::kSyncPass) X(N, false, ftk::kInPlacePass) X(N, false, ftk::kFactorPhase) X(N, false, ftk::kCorePhase) \
-    X(N, true, ftk::kSyncPass) X(N, true, ftk::kInPlacePass) X(N, true, ftk::kFactorPhase) X(N, true, ftk::kCorePhase)     \
+// J_n = R = 16 kernel, order N: both sampling rules x the passes, the core phase (a kernel of its own), and the evaluation pass
+#define FTK_MFMA16_INSTANCES(X, XC, XE, N)                                                \
+    X(N, false, ftk::kSyncPass) X(N, false, ftk::kInPlacePass) X(N, false, ftk::kFactorPhase) XC(N, false) \
+    X(N, true, ftk::kSyncPass) X(N, true, ftk::kInPlacePass) X(N, true, ftk::kFactorPhase) XC(N, true)     \
     XE(N)
 // general matrix-core kernel, order N, ranks padded to 16 P (WAVES waves per workgroup): one pass and the two phases of the
 // mode-by-mode order, for ranks that are multiples of four and for any; the row-owner form for the former; the evaluation
@@ -37,16 +37,17 @@
 #define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G, false>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_ERRORS_HOT(N, G) template __global__ void ftk::errors_rows_kernel<N, G, true>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_GRAD_MFMA16(N, T, M) template __global__ void ftk::grad_mfma16_kernel<N, T, M>(ftk::Mfma16Args);
+#define FTK_CORE_MFMA16(N, T) template __global__ void ftk::core_phase_mfma16_kernel<N, T>(ftk::Mfma16Args);
 #define FTK_ERRORS_MFMA16(N) \
     template __global__ void ftk::errors_mfma16_kernel<N>(ftk::Coo, uint64_t, const float*, const float*, ftk::Layout, ftk::ModeBytes, double*);
 #define FTK_GRAD_TILED(N, P, W, X4, R, M) template __global__ void ftk::grad_tiled_kernel<N, P, W, X4, R, M>(ftk::TiledArgs);
 #define FTK_ERRORS_TILED(N, P, X4) \
     template __global__ void ftk::errors_tiled_kernel<N, P, X4>(ftk::Coo, uint64_t, const float*, const float*, ftk::Layout, ftk::TiledModeBytes, double*);
 
-#define FTK_ALL_INSTANCES(PREFIX_GM, PREFIX_EM, PREFIX_GT, PREFIX_ET)                                      \
-    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 1) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 2)           \
-    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 3) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 4)           \
-    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 5) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_EM, 6)           \
+#define FTK_ALL_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, PREFIX_GT, PREFIX_ET)                          \
+    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 1) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 2)           \
+    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 3) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 4)           \
+    FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 5) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 6)           \
     FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 1) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 2)             \
     FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 3) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 4)             \
     FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 5) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 6)             \
@@ -56,10 +57,11 @@
 #ifdef FTK_INSTANCES_EXTERN
 // the host file: every instance is defined elsewhere
 #define FTK_X_GM(N, T, M) extern FTK_GRAD_MFMA16(N, T, M)
+#define FTK_X_CM(N, T) extern FTK_CORE_MFMA16(N, T)
 #define FTK_X_EM(N) extern FTK_ERRORS_MFMA16(N)
 #define FTK_X_GT(N, P, W, X4, R, M) extern FTK_GRAD_TILED(N, P, W, X4, R, M)
 #define FTK_X_ET(N, P, X4) extern FTK_ERRORS_TILED(N, P, X4)
-FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
+FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_CM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
 #define FTK_X_ER(N, G) extern FTK_ERRORS_ROWS(N, G)
 #define FTK_X_EH(N, G) extern FTK_ERRORS_HOT(N, G)
 FTK_HOT_INSTANCES(FTK_X_EH, 1) FTK_HOT_INSTANCES(FTK_X_EH, 2) FTK_HOT_INSTANCES(FTK_X_EH, 3) FTK_HOT_INSTANCES(FTK_X_EH, 4)

@@ -183,7 +183,8 @@ __device__ __forceinline__ void gather_rows(const __amdgpu_buffer_rsrc_t (&rsrc_
 //                 projections of that mode are advanced, c^(n) += delta B^(n) (one more 16x16 product), so that the
 //                 next mode's prediction, error and GS see the row mode n has just written; rows are updated as in
 //                 kInPlacePass; no core gradient
-//   kCorePhase    Algorithm 1, lines 17-39: only the core gradient, at the rows the factor phase left
+//   kCorePhase    Algorithm 1, lines 17-39: only the core gradient, at the rows the factor phase left (on this shape a kernel
+//                 of its own: core_phase_mfma16_kernel)
 constexpr int kSyncPass = 0, kInPlacePass = 1, kFactorPhase = 2, kCorePhase = 3;
 
 template <int N, int MODE>
@@ -329,13 +330,11 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         floatx4 gs[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) gs[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (MODE != kCorePhase) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int n = 0; n < N; ++n)
-                    gs[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[n][k], st.Br[n][k], gs[n], 0, 0, 0);
-        }
+            for (int n = 0; n < N; ++n)
+                gs[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[n][k], st.Br[n][k], gs[n], 0, 0, 0);
         lds_wave_sync();
 #pragma unroll
         for (int n = 0; n < N; ++n)
@@ -364,16 +363,6 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         // The whole chip retires 20.5e9 float-atomic requests of up to 64 bytes a second, and an atomic
         // instruction takes a CU the same time whether one or all four of its 16-lane rows are in range, so the
         // lists matter: without them nearly every instruction of every (mode, quarter) would carry such a row.
-        if constexpr (MODE == kCorePhase) {
-            // core gradient only: GB[j = 4g+v'][r = c] += sum_samples a_j (-e w_r)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-#pragma unroll
-                for (int n = 0; n < N; ++n)
-                    st.GBacc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(aY[n][v], wY[n][v], st.GBacc[n], 0, 0, 0);
-            lds_wave_sync();   // the next tile overwrites the buffer
-            continue;
-        }
         if constexpr (MODE != kFactorPhase) {   // (the factor phase has staged its rows mode by mode)
 #pragma unroll
             for (int n = 0; n < N; ++n)
@@ -771,6 +760,194 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     for (int q = tid; q < N * 256; q += kMfmaThreads) gb_out[q] = gbred[q];
     float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * g.width;
     for (int q = tid; q < g.H * (g.width / 4); q += kMfmaThreads) reinterpret_cast<float4*>(hot_out)[q] = reinterpret_cast<const float4*>(hot)[q];
+}
+
+// ---------------------------------------------------------------------------------------------
+// The core phase of the mode-by-mode order (Algorithm 1, lines 17-39): only the core gradient over Psi, at the rows the
+// factor phase left.  Rows are read and never written, so nothing of the scatter is here: no lists, no table in LDS, no
+// products for the row gradients, and B in one operand layout.  That leaves registers and LDS for twice the waves, which
+// is what the phase needs: a tile is 25 matrix instructions behind three waits (rows, and two turns through LDS), and
+// with two waves per SIMD the waits stood open.
+// Waves: 16 up to order 3, then as many as the registers allow (COREWAVES).
+// ---------------------------------------------------------------------------------------------
+__host__ __device__ constexpr int core_phase_waves(int order) { return order <= 3 ? 16 : order == 4 ? 12 : 8; }
+__host__ __device__ constexpr int core_phase_wave_words(int order) {
+    // two parked groups (row offsets and values of 64 samples) | one buffer per mode to change the register layout
+    return 2 * (order + 1) * 64 + order * kTransposeFloats;
+}
+__host__ __device__ constexpr size_t core_phase_lds_bytes(int order) {
+    return 4 * ((size_t)core_phase_waves(order) * core_phase_wave_words(order) + order * 256);
+}
+
+template <int N, bool TILES>
+__global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_kernel(Mfma16Args g) {
+    extern __shared__ float lds[];
+    constexpr int W4 = (N + 1 + 3) / 4, WAVES = core_phase_waves(N), THREADS = WAVES * 64;
+    constexpr int kGroup = (N + 1) * 64;
+    constexpr int kAhead = 2;   // tiles whose rows are requested ahead of the one worked on
+    typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g4 = lane >> 4;
+    unsigned int* sbuf = reinterpret_cast<unsigned int*>(lds + wave * core_phase_wave_words(N));
+    float* tbuf = reinterpret_cast<float*>(sbuf + 2 * kGroup);
+    float* gbred = lds + WAVES * core_phase_wave_words(N);
+
+    // the wave's share: tiles [t0, t0 + tiles) of the workgroup's, dealt evenly
+    const int blk = (int)blockIdx.x;
+    const int Tb = g.tiles_each + (blk < g.tiles_more ? 1 : 0);
+    const long long b0 = (long long)blk * g.tiles_each + (blk < g.tiles_more ? blk : g.tiles_more);
+    const int tiles = Tb / WAVES + (wave < Tb % WAVES ? 1 : 0);
+    const long long s0 = (b0 + (long long)wave * (Tb / WAVES) + (wave < Tb % WAVES ? wave : Tb % WAVES)) * 16;
+    const long long s_end = s0 + tiles * 16LL < g.M ? s0 + tiles * 16LL : g.M;
+    // turns of 64 samples; in pairs that share their Philox blocks as in grad_mfma16_kernel
+    const int n_pair_turns = (!TILES && g.pair_turns != 0) ? 2 * (tiles >> 3) : 0;
+    const int rest = tiles - 4 * n_pair_turns;
+    const int n_turns = n_pair_turns + ((rest + 3) >> 2);
+    auto sample_of = [&](int t) -> long long {
+        if (t < n_pair_turns) return s0 + 128LL * (t >> 1) + 2 * lane + (t & 1);
+        return s0 + 64LL * t + lane;
+    };
+    const uint4* rec4 = reinterpret_cast<const uint4*>(g.coo.rec);
+    uint32_t odd_place = 0u;
+    auto load_record = [&](int t, uint4 (&rec)[W4]) {
+        const long long k = sample_of(t);
+        uint32_t p;
+        if constexpr (TILES) {
+            p = tile_place(g.seed, (uint64_t)k, g.rule);
+        } else if (t >= n_pair_turns) {
+            p = sample_position(g.seed, (uint64_t)k, g.rule.nnz);
+        } else if ((t & 1) == 0) {
+            const uint64_t ctr = (uint64_t)k >> 1;
+            const U4 o = philox4x32_10((uint32_t)ctr, (uint32_t)(ctr >> 32), 0u, 0u, (uint32_t)g.seed, (uint32_t)(g.seed >> 32));
+            p = (uint32_t)__umul64hi(((uint64_t)o.y << 32) | (uint64_t)o.x, g.rule.nnz);
+            odd_place = (uint32_t)__umul64hi(((uint64_t)o.w << 32) | (uint64_t)o.z, g.rule.nnz);
+        } else {
+            p = odd_place;
+        }
+        if (k >= s_end) p = 0u;
+#pragma unroll
+        for (int q = 0; q < W4; ++q) rec[q] = rec4[(size_t)p * W4 + q];
+    };
+    // row offsets and values; a slot with no sample behind it names the row past the mode's last one, which reads as zeros
+    auto park_record = [&](int t, const uint4 (&rec)[W4], unsigned int* dst) {
+        const bool act = sample_of(t) < s_end;
+        uint32_t flat[4 * W4];
+#pragma unroll
+        for (int q = 0; q < W4; ++q) {
+            flat[4 * q + 0] = rec[q].x;
+            flat[4 * q + 1] = rec[q].y;
+            flat[4 * q + 2] = rec[q].z;
+            flat[4 * q + 3] = rec[q].w;
+        }
+#pragma unroll
+        for (int n = 0; n < N; ++n) dst[n * 64 + lane] = act ? flat[n] * 64u : g.row_bytes[n];
+        dst[N * 64 + lane] = act ? flat[N] : 0u;
+    };
+
+    float Bq[N][4];
+    floatx4 GBacc[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) Bq[n][k] = g.B[g.B_off[n] + (4 * g4 + k) * 16 + c];
+        GBacc[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    uint4 rec0[W4], rec[W4];
+    if (n_turns > 0) {
+        load_record(0, rec0);
+        load_record(1, rec);
+    }
+    for (int q = tid; q < N * 256; q += THREADS) gbred[q] = 0.0f;
+    __syncthreads();
+    if (n_turns > 0) {
+        __amdgpu_buffer_rsrc_t rsrc_A[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.row_bytes[n]);
+        floatx4 ring[4][N];
+        auto gather = [&](const unsigned int* from, int t, floatx4 (&dst)[N]) {
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], (int)(from[n * 64 + t * 16 + c] + (unsigned int)(g4 * 16)), 0, 0);
+                dst[n] = floatx4{__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]), __uint_as_float(q[3])};
+            }
+        };
+        park_record(0, rec0, sbuf);
+        lds_wave_sync();
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) gather(sbuf, t, ring[t]);
+        for (int t = 0; t < n_turns; ++t) {
+            unsigned int* scur = sbuf + (t & 1) * kGroup;
+            unsigned int* snxt = sbuf + ((t & 1) ^ 1) * kGroup;
+            park_record(t + 1, rec, snxt);   // (turns past the last one hold empty slots)
+            load_record(t + 2, rec);
+            lds_wave_sync();
+            const int here = t == n_turns - 1 && (rest & 3) != 0 ? (rest & 3) : 4;   // tiles of this turn
+            const float* sval = reinterpret_cast<const float*>(scur + N * 64);
+#pragma unroll
+            for (int sub = 0; sub < 4; ++sub) {
+                if (sub > 0 && sub >= here) break;
+                gather(sub + kAhead < 4 ? scur : snxt, (sub + kAhead) & 3, ring[(sub + kAhead) & 3]);
+                const float x = sval[sub * 16 + c];
+                floatx4 s[N], w[N];
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    const floatx4 a = ring[sub][n];
+                    *reinterpret_cast<float4*>(tbuf + n * kTransposeFloats + c * 20 + 4 * g4) = make_float4(a[0], a[1], a[2], a[3]);
+                    s[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int n = 0; n < N; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(Bq[n][k], ring[sub][n][k], s[n], 0, 0, 0);
+                floatx4 run = {1.0f, 1.0f, 1.0f, 1.0f};
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    w[n] = run;
+                    run *= s[n];
+                }
+                const float part = (run[0] + run[1]) + (run[2] + run[3]);
+                const floatx4 xsum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, part, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                const float neg_e = xsum[0] - x;
+                run = floatx4{1.0f, 1.0f, 1.0f, 1.0f};
+#pragma unroll
+                for (int n = N - 1; n >= 0; --n) {
+                    w[n] *= run;
+                    run *= s[n];
+                }
+                // rows out of the buffer in layout Y, then -e w through the same buffer
+                float aY[N][4], wY[N][4];
+                lds_wave_sync();
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) aY[n][v] = tbuf[n * kTransposeFloats + (4 * g4 + v) * 20 + c];
+                lds_wave_sync();
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    w[n] *= neg_e;
+                    *reinterpret_cast<float4*>(tbuf + n * kTransposeFloats + c * 20 + 4 * g4) = make_float4(w[n][0], w[n][1], w[n][2], w[n][3]);
+                }
+                lds_wave_sync();
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) wY[n][v] = tbuf[n * kTransposeFloats + (4 * g4 + v) * 20 + c];
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int n = 0; n < N; ++n) GBacc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(aY[n][v], wY[n][v], GBacc[n], 0, 0, 0);
+                lds_wave_sync();   // the next tile overwrites the buffer
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) lds_float_add(gbred + n * 256 + (4 * g4 + v) * 16 + c, GBacc[n][v]);
+    __syncthreads();
+    float* gb_out = g.gb_partial + (size_t)blockIdx.x * (N * 256);
+    for (int q = tid; q < N * 256; q += THREADS) gb_out[q] = gbred[q];
 }
 
 // ---------------------------------------------------------------------------------------------
