@@ -1451,6 +1451,35 @@ def test_modewise_in_place_step_equals_the_printed_order_when_no_row_is_shared(k
     assert max(float(np.max(np.abs(B[n] - B_sync[n]))) for n in range(N)) > 1e-5
 
 
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("M,tiles", [(1, False), (17, False), (272, True), (4_111, False), (300_001, False)])
+def test_core_phase_of_the_mode_by_mode_order(N, M, tiles):
+    """With lr_A = 0 the factor phase moves nothing and the core phase has to give the synchronous step's core factors: one
+    sample, tiles that do not fill the waves, turns of fewer than four tiles, and (300 001) turns in pairs, at every order the
+    J = R = 16 kernels are built for."""
+    announce("core phase order=%d M=%d tiles=%d" % (N, M, tiles))
+    w = synth.tiny_workload(N, (301, 97, 50, 211, 33, 70)[:N], 50_021, (16, 7, 16, 12, 9)[:N] if 1 < N < 6 else (16,) * N, 16, M, seed=4, values="normal")
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(N)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(w.dims, w.J)]
+    B = [(rng.uniform(-1, 1, size=(j, 16)) / np.sqrt(j)).astype(np.float32) for j in w.J]
+    with binding.FastTucker(w.dims, idx, vals, w.J, w.R, 1) as ft:
+        ft.ftk_set_kernel("mfma16")
+        ft.ftk_set_mode(binding.FTK_HOGWILD_MODEWISE)
+        if tiles:
+            ft.ftk_set_sampling(binding.FTK_SAMPLE_TILES)
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(5, M)
+        ft.ftk_sgd_step(0.0, 0.3, 0.0, 0.02)
+        gA, gB = ft.ftk_get_factors()
+    draw = oracle.sample_positions_tiles if tiles else oracle.sample_positions
+    want_A, want_B = [a.copy() for a in A], [b.copy() for b in B]
+    oracle.sgd_step_sync(w.dims, idx, vals, want_A, want_B, draw(5, M, w.nnz), 0.0, 0.3, 0.0, 0.02)
+    assert all(np.array_equal(g, a) for g, a in zip(gA, A))
+    assert_params_close(gB, want_B, "B")
+    assert max(float(np.abs(x - y).max()) for x, y in zip(want_B, B)) > 1e-3
+
+
 # ------------------------------------------------------------------------------------------------
 # the training loop of the paper's experiments, end to end: decaying step sizes, held-out Gamma
 # ------------------------------------------------------------------------------------------------
