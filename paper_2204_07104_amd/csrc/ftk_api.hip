@@ -24,6 +24,7 @@
 #include "ftk_kernels_tiled.hpp"
 #include "ftk_kernels_errors.hpp"
 #include "ftk_kernels_owners.hpp"
+#include "ftk_kernels_wide.hpp"
 #define FTK_INSTANCES_EXTERN
 #include "ftk_instances.hpp"   // the matrix-core kernel instances are compiled in translation units of their own
 
@@ -606,6 +607,21 @@ int launch_tiled_npwxr(ftk_ctx* c, const TiledArgs& g) {
 inline bool tiled_modewise_ok(const ftk_ctx* c) { return c->variant == V_TILED && !c->rows; }
 inline bool modewise_on_matrix_cores(const ftk_ctx* c) { return c->variant == V_MFMA16 || tiled_modewise_ok(c); }
 
+// Ranks above 32 at orders 2 and 3, synchronous and fused in-place pass (ftk_kernels_wide.hpp): the faster one at every size
+// measured.  Whole steps, general kernel and this one, order 3, 500 000 rows, J = R = 64: 1e3 samples 85 / 43 us, 1e4 92 / 53,
+// 6e4 133 / 91, 2e5 244 / 190, 1e6 800 / 756 (in place 907 / 769); J = 40, 36, 50, R = 33, 4e5: 480 / 443; order 2, J = 64, 50,
+// 3e5: 216 / 191.  At order 4 two tiles' operands do not fit LDS.
+template <int N, bool X4>
+int launch_wide_nx(ftk_ctx* c, const TiledArgs& g) {
+    if (wide_lds_bytes(N) > (size_t)c->max_lds) return fail(c, FTK_EUNSUPPORTED, "tiled kernel: %zu bytes of LDS needed", wide_lds_bytes(N));
+    if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(grad_wide_kernel<N, X4>), c->max_lds)) return rc;
+    if (c->prepare_only) return FTK_OK;
+    Bracket t(c, FTK_K_GRAD);
+    hipLaunchKernelGGL((grad_wide_kernel<N, X4>), dim3(c->mfma_grid), dim3(kWideThreads), wide_lds_bytes(N), c->stream, g);
+    FTK_HIP(c, hipGetLastError());
+    return FTK_OK;
+}
+
 template <int N, int P, int WAVES>
 int launch_tiled_npw(ftk_ctx* c, const TiledArgs& g, int pass) {
     if (pass == kFactorPhase || pass == kCorePhase) {
@@ -623,7 +639,10 @@ int launch_tiled_npw(ftk_ctx* c, const TiledArgs& g, int pass) {
         if (const int rc = raise_lds_limit(c, reinterpret_cast<const void*>(rows_apply_kernel), 65536)) return rc;
         return launch_tiled_npwxr<N, P, WAVES, true, true>(c, g);
     }
-    return c->tiled_x4 ? launch_tiled_npwxr<N, P, WAVES, true, false>(c, g) : launch_tiled_npwxr<N, P, WAVES, false, false>(c, g);
+    if constexpr (P == 4 && N >= 2 && N <= kWideMaxOrder)
+        return c->tiled_x4 ? launch_wide_nx<N, true>(c, g) : launch_wide_nx<N, false>(c, g);
+    else
+        return c->tiled_x4 ? launch_tiled_npwxr<N, P, WAVES, true, false>(c, g) : launch_tiled_npwxr<N, P, WAVES, false, false>(c, g);
 }
 
 template <int N>

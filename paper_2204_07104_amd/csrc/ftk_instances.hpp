@@ -6,6 +6,7 @@
 #include "ftk_kernels_tiled.hpp"
 #include "ftk_kernels_errors.hpp"
 #include "ftk_kernels_owners.hpp"
+#include "ftk_kernels_wide.hpp"
 
 // J_n = R = 16 kernel, order N: both sampling rules x the passes, the core phase (a kernel of its own), and the evaluation pass
 #define FTK_MFMA16_INSTANCES(X, XC, XE, N)                                                \
@@ -17,12 +18,19 @@
 // pass with rows fetched 16 bytes per lane or float by float
 #define FTK_TILED_INSTANCES_P(X, XE, N, P, WAVES)                                                    \
     X(N, P, WAVES, true, false, ftk::kSyncPass) X(N, P, WAVES, false, false, ftk::kSyncPass)          \
+    FTK_TILED_INSTANCES_PHASES(X, XE, N, P, WAVES)
+#define FTK_TILED_INSTANCES_PHASES(X, XE, N, P, WAVES)                                               \
     X(N, P, WAVES, true, true, ftk::kSyncPass)                                                        \
     X(N, P, WAVES, true, false, ftk::kFactorPhase) X(N, P, WAVES, false, false, ftk::kFactorPhase)    \
     X(N, P, WAVES, true, false, ftk::kCorePhase) X(N, P, WAVES, false, false, ftk::kCorePhase)        \
     XE(N, P, true) XE(N, P, false)
 #define FTK_TILED_INSTANCES(X, XE, N) \
     FTK_TILED_INSTANCES_P(X, XE, N, 1, 8) FTK_TILED_INSTANCES_P(X, XE, N, 2, 8) FTK_TILED_INSTANCES_P(X, XE, N, 4, 4)
+// orders 2 and 3: above rank 32 the one pass of the synchronous and the fused in-place step has a kernel of its own
+#define FTK_TILED_INSTANCES_LOW(X, XE, N) \
+    FTK_TILED_INSTANCES_P(X, XE, N, 1, 8) FTK_TILED_INSTANCES_P(X, XE, N, 2, 8) FTK_TILED_INSTANCES_PHASES(X, XE, N, 4, 4)
+#define FTK_WIDE_INSTANCES(X, N) X(N, true) X(N, false)
+#define FTK_GRAD_WIDE(N, X4) template __global__ void ftk::grad_wide_kernel<N, X4>(ftk::TiledArgs);
 // orders 9 and 10 (the end of the paper's order sweep): ranks up to 16 only
 #define FTK_TILED_INSTANCES_HIGH(X, XE, N) FTK_TILED_INSTANCES_P(X, XE, N, 1, 8)
 
@@ -48,8 +56,8 @@
     FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 1) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 2)           \
     FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 3) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 4)           \
     FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 5) FTK_MFMA16_INSTANCES(PREFIX_GM, PREFIX_CM, PREFIX_EM, 6)           \
-    FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 1) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 2)             \
-    FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 3) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 4)             \
+    FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 1) FTK_TILED_INSTANCES_LOW(PREFIX_GT, PREFIX_ET, 2)         \
+    FTK_TILED_INSTANCES_LOW(PREFIX_GT, PREFIX_ET, 3) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 4)         \
     FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 5) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 6)             \
     FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 7) FTK_TILED_INSTANCES(PREFIX_GT, PREFIX_ET, 8)             \
     FTK_TILED_INSTANCES_HIGH(PREFIX_GT, PREFIX_ET, 9) FTK_TILED_INSTANCES_HIGH(PREFIX_GT, PREFIX_ET, 10)
@@ -62,6 +70,8 @@
 #define FTK_X_GT(N, P, W, X4, R, M) extern FTK_GRAD_TILED(N, P, W, X4, R, M)
 #define FTK_X_ET(N, P, X4) extern FTK_ERRORS_TILED(N, P, X4)
 FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_CM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
+#define FTK_X_GW(N, X4) extern FTK_GRAD_WIDE(N, X4)
+FTK_WIDE_INSTANCES(FTK_X_GW, 2) FTK_WIDE_INSTANCES(FTK_X_GW, 3)
 #define FTK_X_ER(N, G) extern FTK_ERRORS_ROWS(N, G)
 #define FTK_X_EH(N, G) extern FTK_ERRORS_HOT(N, G)
 FTK_HOT_INSTANCES(FTK_X_EH, 1) FTK_HOT_INSTANCES(FTK_X_EH, 2) FTK_HOT_INSTANCES(FTK_X_EH, 3) FTK_HOT_INSTANCES(FTK_X_EH, 4)

@@ -396,6 +396,35 @@ def test_matrix_core_kernel_at_the_edges_of_its_blocks(J, R, M):
     one_step_case(w, idx, vals, A0=A0, B0=B0, kernel="tiled", flags=binding.FTK_LAYOUT_EXACT)
 
 
+@pytest.mark.parametrize("dims,J,R", [((901, 333), (64, 33), 50), ((20_011, 401, 90), (35, 40, 33), 36), ((3_001, 700, 90), (64, 64, 64), 64)])
+@pytest.mark.parametrize("M,tiles,kernel", [(1, False, "auto"), (33, False, "auto"), (8_209, True, "auto"), (70_001, False, "noalloc"),
+                                            (147_461, False, "auto")])
+def test_above_rank_32_at_orders_two_and_three(dims, J, R, M, tiles, kernel):
+    """The kernel whose workgroups work on a tile of 32 samples together: one sample, a tile and one sample, one more sample than
+    tiles of all workgroups, samples drawn in a second batch of eight tiles (70 001) and parked where the first were (147 461),
+    under both sampling rules, with frequent rows (the one-hot sums), against the oracle's step.  A row collects n < 3e4
+    gradients |g| < 8 of a step of 1e-5: lr n 2^-24 |g| = 1e-7, a tenth of the bound."""
+    announce("wide kernel dims=%r J=%r R=%d M=%d" % (dims, J, R, M))
+    w = synth.tiny_workload(len(dims), dims, 100_003, J, R, M, seed=6, values="normal", zipf=(1.2,) + (None,) * (len(dims) - 1))
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(len(dims))
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) / np.sqrt(j)).astype(np.float32) for j in J]
+    rates = (1e-5, 0.1, 0.05, 0.02)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "tiled"
+        if tiles:
+            ft.ftk_set_sampling(binding.FTK_SAMPLE_TILES)
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(9, M)
+        (ft.ftk_sgd_step_noalloc if kernel == "noalloc" else ft.ftk_sgd_step)(*rates)
+        gA, gB = ft.ftk_get_factors()
+    draw = oracle.sample_positions_tiles if tiles else oracle.sample_positions
+    oracle.sgd_step_sync(dims, idx, vals, A, B, draw(9, M, w.nnz), *rates)
+    assert_params_close(gA, A, "A")
+    assert_params_close(gB, B, "B")
+
+
 def test_table_of_the_general_kernel_up_to_rank_16_fills_the_lds():
     """Eight waves of 2 x (2 N + 1) x 64 words of parked samples, 16 x 20 floats to transpose a tile in and 64 words that nobody
     reads, next to two copies of the core factors: the rest of the 160 KB is table, in rows of 64 bytes."""
