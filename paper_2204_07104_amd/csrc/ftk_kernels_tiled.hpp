@@ -848,62 +848,69 @@ __global__ void __launch_bounds__(WAVES * 64) grad_tiled_kernel(TiledArgs g) {
                 for (int v = 0; v < 4; ++v)
                     lds_float_add(hot + (size_t)(g.hot_off[n] + 4 * g4 + v) * D + 16 * jb + c, turned(1.0f) * Top[n][jb][v]);
         }
-    // core gradient: summed over the workgroup's waves in LDS, where the operand tables are no longer needed (the
-    // waves take turns, so plain adds do), and stored as one table per workgroup (entries outside J_n x R are padding).
-    // A turn reads a mode's sums while it writes those of the mode before: one sum at a time, each read waited for the write in
-    // front of it, and the eight turns took 14.3 us at order 4 with P = 2, of 40 us for the smallest launch; 6 us this way.
     __syncthreads();
-    float* gb_sum = lds;   // [N][D][D]
-#pragma unroll 1
-    for (int turn = 0; turn < (MODE == kFactorPhase ? 0 : WAVES); ++turn) {
-        if (wave == turn) {
-            float* mine_out = gb_sum + (4 * g4) * D + c;
-            constexpr int kRows = P < 4 ? P : 1, kParts = N * P / kRows;   // blocks of rows read at a time
-            float seen[2][kRows][P][4];
-            auto read = [&](int part, float (&x)[kRows][P][4]) {
+    if constexpr (MODE != kCorePhase) {
+        float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * D;
+        if constexpr (LDS_TABLE) {
+            for (int q = tid; q < g.H * D; q += THREADS) hot_out[q] = hot[q];
+        } else {
+            // only rows 0..15 of a mode were summed on chip; the other table rows of hot_out hold what the atomics added
 #pragma unroll
-                for (int i = 0; i < kRows; ++i)
-#pragma unroll
-                    for (int rb = 0; rb < P; ++rb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) x[i][rb][v] = mine_out[((part * kRows + i) * 16 + v) * D + 16 * rb];
-            };
-            if (turn > 0) read(0, seen[0]);
-#pragma unroll
-            for (int part = 0; part < kParts; ++part) {
-                if (turn > 0 && part + 1 < kParts) read(part + 1, seen[(part + 1) & 1]);
-#pragma unroll
-                for (int i = 0; i < kRows; ++i)
-#pragma unroll
-                    for (int rb = 0; rb < P; ++rb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int at = part * kRows + i;   // block of rows, counted over all modes
-                            const float sum = GBacc[at / P][at % P][rb][v];
-                            mine_out[(at * 16 + v) * D + 16 * rb] = turn == 0 ? sum : fmaf(turned(1.0f), sum, seen[part & 1][i][rb][v]);   // (wave 0 turns none)
-                        }
-            }
+            for (int n = 0; n < N; ++n)
+                if (g.top[n] > 0)
+                    for (int q = tid; q < 16 * D; q += THREADS) hot_out[g.hot_off[n] * D + q] = hot[g.hot_off[n] * D + q];
         }
-        __syncthreads();
     }
+    // core gradient: summed over the workgroup's waves in LDS, of which nothing else is needed now, and stored as one table per
+    // workgroup (entries outside J_n x R are padding).  Waves w, w + kAreas, ... add up in one area, in turns, so plain adds
+    // do, and the areas are added where the table is stored.  A turn reads a mode's sums while it writes those of the mode before.
+    // (Order 4 with P = 2, whole steps of 1e3 and 2.5e5 samples: eight turns in one area, each read waited for the write in
+    // front of it, 45.4 and 148.2 us; with reads ahead 37.0 and 140.0; four areas 33.5 and 137.2.)
+    constexpr int kArea = N * D * D, kLds = tiled_core_bytes(N, P) / 4 + WAVES * tiled_wave_scratch(N, P);
+    constexpr int kAreas = kLds >= 8 * kArea && WAVES >= 8 ? 8 : kLds >= 4 * kArea ? 4 : kLds >= 2 * kArea ? 2 : 1;
+    static_assert(kLds >= kArea && WAVES % kAreas == 0, "the sums lie where every launch has LDS");
     if constexpr (MODE != kFactorPhase) {
-        float* gb_out = g.gb_partial + (size_t)blockIdx.x * g.B_total;
-        for (int q = tid; q < N * D * D; q += THREADS) {
-            const int n = q / (D * D), rem = q - n * D * D, j = rem / D, r = rem - j * D;
-            if (j < g.J[n] && r < g.R) gb_out[g.B_off[n] + j * g.R + r] = gb_sum[q];
-        }
         __syncthreads();
-    }
-    if constexpr (MODE == kCorePhase) return;
-    float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * D;
-    if constexpr (LDS_TABLE) {
-        for (int q = tid; q < g.H * D; q += THREADS) hot_out[q] = hot[q];
-    } else {
-        // only rows 0..15 of a mode were summed on chip; the other table rows of hot_out hold what the atomics added
+        float* area = lds + (wave % kAreas) * kArea + (4 * g4) * D + c;
+#pragma unroll 1
+        for (int turn = 0; turn < WAVES / kAreas; ++turn) {
+            if (wave / kAreas == turn) {
+                constexpr int kRows = P < 4 ? P : 1, kParts = N * P / kRows;   // blocks of rows read at a time
+                float seen[2][kRows][P][4];
+                auto read = [&](int part, float (&x)[kRows][P][4]) {
 #pragma unroll
-        for (int n = 0; n < N; ++n)
-            if (g.top[n] > 0)
-                for (int q = tid; q < 16 * D; q += THREADS) hot_out[g.hot_off[n] * D + q] = hot[g.hot_off[n] * D + q];
+                    for (int i = 0; i < kRows; ++i)
+#pragma unroll
+                        for (int rb = 0; rb < P; ++rb)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) x[i][rb][v] = area[((part * kRows + i) * 16 + v) * D + 16 * rb];
+                };
+                if (turn > 0) read(0, seen[0]);
+#pragma unroll
+                for (int part = 0; part < kParts; ++part) {
+                    if (turn > 0 && part + 1 < kParts) read(part + 1, seen[(part + 1) & 1]);
+#pragma unroll
+                    for (int i = 0; i < kRows; ++i)
+#pragma unroll
+                        for (int rb = 0; rb < P; ++rb)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const int at = part * kRows + i;   // block of rows, counted over all modes
+                                const float sum = turned(GBacc[at / P][at % P][rb][v]);
+                                area[(at * 16 + v) * D + 16 * rb] = turn == 0 ? sum : sum + seen[part & 1][i][rb][v];
+                            }
+                }
+            }
+            __syncthreads();
+        }
+        float* gb_out = g.gb_partial + (size_t)blockIdx.x * g.B_total;
+        for (int q = tid; q < kArea; q += THREADS) {
+            const int n = q / (D * D), rem = q - n * D * D, j = rem / D, r = rem - j * D;
+            float sum = lds[q];
+#pragma unroll
+            for (int i = 1; i < kAreas; ++i) sum += lds[i * kArea + q];
+            if (j < g.J[n] && r < g.R) gb_out[g.B_off[n] + j * g.R + r] = sum;
+        }
     }
     if constexpr (ROWS) {
         for (int q = tid; q < g.n_buckets; q += THREADS)
