@@ -8,11 +8,13 @@
 #include "ftk_kernels_owners.hpp"
 #include "ftk_kernels_wide.hpp"
 
-// J_n = R = 16 kernel, order N: both sampling rules x the passes, the core phase (a kernel of its own), and the evaluation pass
-#define FTK_MFMA16_INSTANCES(X, XC, XE, N)                                                \
-    X(N, false, ftk::kSyncPass) X(N, false, ftk::kInPlacePass) X(N, false, ftk::kFactorPhase) XC(N, false) \
-    X(N, true, ftk::kSyncPass) X(N, true, ftk::kInPlacePass) X(N, true, ftk::kFactorPhase) XC(N, true)     \
-    XE(N)
+// J_n = R = 16 kernel, order N: both sampling rules x the passes, the core phase (a kernel of its own), and the evaluation pass;
+// orders 2 to 5 also with two samples of ranks up to 8 side by side
+#define FTK_MFMA16_INSTANCES_P(X, XC, N, P)                                               \
+    X(N, false, ftk::kSyncPass, P) X(N, false, ftk::kInPlacePass, P) X(N, false, ftk::kFactorPhase, P) XC(N, false, P) \
+    X(N, true, ftk::kSyncPass, P) X(N, true, ftk::kInPlacePass, P) X(N, true, ftk::kFactorPhase, P) XC(N, true, P)
+#define FTK_MFMA16_INSTANCES(X, XC, XE, N) FTK_MFMA16_INSTANCES_P(X, XC, N, 1) XE(N)
+#define FTK_PAIR8_INSTANCES(X, XC, N) FTK_MFMA16_INSTANCES_P(X, XC, N, 2)
 // general matrix-core kernel, order N, ranks padded to 16 P (WAVES waves per workgroup): one pass and the two phases of the
 // mode-by-mode order, for ranks that are multiples of four and for any; the row-owner form for the former; the evaluation
 // pass with rows fetched 16 bytes per lane or float by float
@@ -40,8 +42,8 @@
 #define FTK_APPEND(N, G) template __global__ void ftk::append_lists_kernel<N, G>(ftk::AppendArgs);
 #define FTK_ERRORS_ROWS(N, G) template __global__ void ftk::errors_rows_kernel<N, G, false>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
 #define FTK_ERRORS_HOT(N, G) template __global__ void ftk::errors_rows_kernel<N, G, true>(ftk::Coo, uint64_t, ftk::ErrorRows, double*);
-#define FTK_GRAD_MFMA16(N, T, M) template __global__ void ftk::grad_mfma16_kernel<N, T, M>(ftk::Mfma16Args);
-#define FTK_CORE_MFMA16(N, T) template __global__ void ftk::core_phase_mfma16_kernel<N, T>(ftk::Mfma16Args);
+#define FTK_GRAD_MFMA16(N, T, M, P) template __global__ void ftk::grad_mfma16_kernel<N, T, M, P>(ftk::Mfma16Args);
+#define FTK_CORE_MFMA16(N, T, P) template __global__ void ftk::core_phase_mfma16_kernel<N, T, P>(ftk::Mfma16Args);
 #define FTK_ERRORS_MFMA16(N) \
     template __global__ void ftk::errors_mfma16_kernel<N>(ftk::Coo, uint64_t, const float*, const float*, ftk::Layout, ftk::ModeBytes, double*);
 #define FTK_GRAD_TILED(N, P, W, X4, R, M) template __global__ void ftk::grad_tiled_kernel<N, P, W, X4, R, M>(ftk::TiledArgs);
@@ -60,12 +62,14 @@
 
 #ifdef FTK_INSTANCES_EXTERN
 // the host file: every instance is defined elsewhere
-#define FTK_X_GM(N, T, M) extern FTK_GRAD_MFMA16(N, T, M)
-#define FTK_X_CM(N, T) extern FTK_CORE_MFMA16(N, T)
+#define FTK_X_GM(N, T, M, P) extern FTK_GRAD_MFMA16(N, T, M, P)
+#define FTK_X_CM(N, T, P) extern FTK_CORE_MFMA16(N, T, P)
 #define FTK_X_EM(N) extern FTK_ERRORS_MFMA16(N)
 #define FTK_X_GT(N, P, W, X4, R, M) extern FTK_GRAD_TILED(N, P, W, X4, R, M)
 #define FTK_X_ET(N, P, X4) extern FTK_ERRORS_TILED(N, P, X4)
 FTK_ALL_INSTANCES(FTK_X_GM, FTK_X_CM, FTK_X_EM, FTK_X_GT, FTK_X_ET)
+FTK_PAIR8_INSTANCES(FTK_X_GM, FTK_X_CM, 2) FTK_PAIR8_INSTANCES(FTK_X_GM, FTK_X_CM, 3)
+FTK_PAIR8_INSTANCES(FTK_X_GM, FTK_X_CM, 4) FTK_PAIR8_INSTANCES(FTK_X_GM, FTK_X_CM, 5)
 #define FTK_X_GW(N, X4) extern FTK_GRAD_WIDE(N, X4)
 FTK_WIDE_INSTANCES(FTK_X_GW, 2) FTK_WIDE_INSTANCES(FTK_X_GW, 3)
 #define FTK_X_ER(N, G) extern FTK_ERRORS_ROWS(N, G)

@@ -1,4 +1,4 @@
-// Fused sampling + gradient pass for J_n = R = 16 (order N <= 6), built on the fp32 matrix cores.
+// Fused sampling + gradient pass for J_n = R = 16 (order N <= 6) and for ranks up to 8 (orders 2 to 5), built on the fp32 matrix cores.
 //
 // One wavefront draws 64 positions of Psi at a time (one Philox position and one random record
 // read per lane), parks the 64 records in a private LDS buffer, and then works through them as
@@ -50,31 +50,65 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaWaves = 8;                  // waves per workgroup (one workgroup per CU)
 constexpr int kMfmaThreads = kMfmaWaves * 64;
 constexpr int kTransposeFloats = 16 * 20;      // 16x16 tile, rows padded to 20 floats
+
+// Ranks up to 8 (PACK = 2): two samples side by side in a 16x16 product.  A product's 16 components are the 8 of sample s
+// and the 8 of sample s + 16 of a tile of 32, and B^(n) stands twice on the diagonal of the 16x16 operand, so that every
+// instruction of the tile -- products, transposes, the arithmetic between them -- does the work of two samples where ranks
+// padded to 16 spend three quarters of a product on zeros.  What it changes is which lane holds what:
+//   X: lane (c, g) holds components 4 (g % 2) .. + 3 of sample 16 (g / 2) + c
+//   Y: lane (c, g) holds component c % 8 of samples 16 (c / 8) + 4g .. + 3   (8 lanes cover the 32 bytes of one row)
+// Of the accumulated 16x16 sums over samples (core gradient, one-hot rows) the two 8x8 blocks on the diagonal count, the
+// others mix two samples and are dropped at the end of the launch.
+// Whole steps, one sample at a time -> two side by side, order 3, J = R = 8: 1e4 samples of 2 400 rows 15.3 -> 13.3 us, 1e5 29.7 ->
+// 24.8; 1e6 over 500 000 rows by power laws 111.5 -> 84.1, in place 118 -> 93, mode by mode 169 -> 133; evenly hit rows that all leave as
+// atomics, which bound them, 53.2 -> 53.1 (order 4 64.4 -> 62.6, order 5 78.4 -> 77.7).
+template <int PACK>
+struct Packing {
+    static_assert(PACK == 1 || PACK == 2, "one sample or two side by side");
+    static constexpr int kWidth = 16 / PACK;         // components of a row that are worked on
+    static constexpr int kTile = 16 * PACK;          // samples of a tile
+    static constexpr int kTiles = 64 / kTile;        // tiles of a parked group
+    static constexpr int kAhead = PACK == 1 ? 3 : 2; // tiles whose rows are on their way while one is worked on
+    static constexpr int kRing = PACK == 1 ? 4 : 2;  // register tiles they arrive in
+    // A list entry names the staged gradient row by its slot: 16 n + s, or for two samples side by side its place in the
+    // buffer in units of 16 bytes.
+    static constexpr int kSlotBits = PACK == 1 ? 7 : 9;
+    static constexpr int kSlotWords = PACK == 1 ? 20 : 4;
+    static __device__ __forceinline__ unsigned int slot(int n, int s) {
+        return PACK == 1 ? (unsigned int)(n * 16 + s) : (unsigned int)(n * (kTransposeFloats / 4) + (s & 15) * 5 + (s >> 4) * 2);
+    }
+    static constexpr unsigned int kSlotMask = (1u << kSlotBits) - 1u;
+    static constexpr unsigned int kNoAtomic = ~kSlotMask;   // slot 0, row far past the end
+};
 // One parked group of 64 samples, per wave, in 32-bit words:
 //   [N][64] row words | [64] values | [4][4][4N] atomic list | [4][4][4N] table list | [8] list lengths (+8 unused)
 // The lists are per tile and hold, compacted, the (sample, mode) pairs of the tile whose gradient
 // row goes to a global atomic resp. to the workgroup's LDS table; list position p sits at
 // [p % 4][p / 4], so that the 16 lanes of quarter g = p % 4 find their entries side by side.
+// (Two samples side by side: two tiles, lists of [2][8][4N], eight lanes to a row and position p at [p % 8][p / 8].)
 __host__ __device__ constexpr int mfma16_list_words(int order) { return 4 * 16 * order; }   // 16 N positions per tile
-__host__ __device__ constexpr int mfma16_group_words(int order) {
-    return (order + 1) * 64 + 2 * mfma16_list_words(order) + 16;
+// Two samples side by side: the lists are made from the row words when the group's turn comes, so a wave has one copy of them
+// for its two groups and a sixth of its LDS is left to the table (order 3, J = R = 8, 3e5 samples: over 6 000 rows 44.4 -> 37.2 us per
+// step, 2 816 -> 3 208 table rows; 500 000 rows with power laws, 1e6 samples 86.3 -> 84.1, in place 106 -> 93).
+__host__ __device__ constexpr int mfma16_lists_words(int order) { return 2 * mfma16_list_words(order) + 16; }
+__host__ __device__ constexpr int mfma16_group_words(int order, int pack) {
+    return (order + 1) * 64 + (pack == 1 ? mfma16_lists_words(order) : 0);
 }
-__host__ __device__ constexpr int mfma16_wave_scratch(int order) {
-    // floats per wave: two parked groups | one transpose buffer per mode
-    return 2 * mfma16_group_words(order) + order * kTransposeFloats;
+__host__ __device__ constexpr int mfma16_wave_scratch(int order, int pack) {
+    // floats per wave: two parked groups | (lists) | one transpose buffer per mode
+    return 2 * mfma16_group_words(order, pack) + (pack == 1 ? 0 : mfma16_lists_words(order)) + order * kTransposeFloats;
 }
 constexpr int kSinkRows = 4;   // rows of +inf behind the LDS table (see the scatter stage)
 
 // A row word describes one (sample, mode):
-//   bits 0..29  row * 64, the byte offset of the row inside its mode (rows < 2^24)
+//   bits 0..29  row * 64, the byte offset of the row inside its mode (rows < 2^24, PACK = 2: < 2^23)
 //   bits 30..31 route of its gradient: 0 global atomic, 1 LDS table, 2 one of the 16 most frequent rows
 constexpr unsigned int kRouteShift = 30;
 constexpr unsigned int kRowMask = (1u << kRouteShift) - 1u;
-// An atomic-list entry is (row number counted over the whole packed parameter array) << 7 | slot,
-// a table-list entry is slot << 20 | byte offset of the row's cell in the LDS table; slot = 16 n + s
-// names the tile's staged gradient row of mode n, sample s.  An unused atomic entry names a row far
+// An atomic-list entry is (row number counted over the whole packed parameter array) << kSlotBits | slot,
+// a table-list entry is slot << 20 | byte offset of the row's cell in the LDS table; the slot
+// names the tile's staged gradient row of mode n, sample s (Packing).  An unused atomic entry names a row far
 // past the end of the array.
-constexpr unsigned int kNoAtomic = 0xffffff80u;   // slot 0, row far past the end
 
 constexpr int kMfma16MaxOrder = 6;   // orders this kernel is instantiated for
 struct Mfma16Args {
@@ -93,14 +127,14 @@ struct Mfma16Args {
     int H;                    // rows in the LDS table (>= sum K[n])
     int width;                // floats in a row of the table: 4, 8 or 16, no fewer than the caller's J_n (see table_width)
     float* hot_partial;       // [gridDim.x][H][width]
-    float* gb_partial;        // [gridDim.x][N * 256]
+    float* gb_partial;        // [gridDim.x][floats of B]
     unsigned int row_bytes[kMfma16MaxOrder];   // I_n * 64: size of mode n's rows in A and dA
-    unsigned int all_bytes;              // size of the whole packed A (and dA), below 2^31 - 64
+    unsigned int all_bytes;              // size of the whole packed A (and dA), below 2^31 - 64 (PACK = 2: 2^29 - 64)
     unsigned int first_row[kMfma16MaxOrder];   // A_off[n] / 16: number of mode n's row 0 counted over the packed array
     float lambda_A;
     float scale;              // 1 (synchronous: the update pass applies -lr_A) or -lr_A (in-place mode)
     int pair_turns;           // entry-sampling rule: a wave's turns come in pairs that share their Philox blocks (see the kernel)
-    int tiles_each, tiles_more;   // ceil(M / 16) tiles over the launch's workgroups: each gets tiles_each, the first tiles_more one more
+    int tiles_each, tiles_more;   // the tiles of Psi over the launch's workgroups: each gets tiles_each, the first tiles_more one more
 };
 
 __device__ __forceinline__ void lds_wave_sync() {
@@ -138,13 +172,63 @@ __device__ __forceinline__ unsigned int lds_cas(unsigned int addr, unsigned int 
 }
 
 // Everything a wave keeps across tiles.
-template <int N>
+template <int N, int PACK>
 struct WaveState {
     float Bq[N][4], Br[N][4];   // B^(n) in the two operand layouts: Bq[n][k] = B[4g+k][c], Br[n][k] = B[c][4g+k]
     floatx4 GBacc[N];           // core gradient, D layout: GB[j = 4g+v][r = c]
-    floatx4 Top[N];             // gradient sums of rows 0..15 of each mode, D layout: [row 4g+v][j = c]
-    floatx4 ring[4][N];         // rows in flight, layout X: slot t % 4 holds tile t (components 4g..4g+3 of sample c)
+    floatx4 Top[N][PACK];       // gradient sums of rows 0..15 of each mode, D layout: [row 4g+v][j = c] (PACK = 2: [row 8u + 4(g%2) + v][j = c % 8])
+    floatx4 ring[Packing<PACK>::kRing][N];   // rows in flight, layout X: slot t % kRing holds tile t (components 4g..4g+3 of sample c)
 };
+
+// Element [j][r] of the 16x16 operand that stands for B^(n): the core factor itself, or twice on the diagonal.
+template <int PACK>
+__device__ __forceinline__ float core_operand(const float* Bn, int j, int r) {
+    constexpr int W = Packing<PACK>::kWidth;
+    const float b = Bn[(j % W) * W + (r % W)];
+    return PACK == 1 || j / W == r / W ? b : 0.0f;
+}
+
+// Sums that every wave of a workgroup holds a part of, at the end of a launch: each wave stores its accumulators in its own
+// part of LDS, and behind a barrier a thread adds the waves' values of an element in a fixed order.
+// (Adds by compare-and-swap into one place for all waves, which came before: the waves queue on the same words, and two samples
+// side by side make them 16 in a queue instead of eight: 1e4 samples of order 3, J = R = 8 18.8 us per step instead of 14.9, J = R = 16
+// 15.4 instead of 14.1.)
+// Of the accumulator tile only the blocks on the diagonal are kept: element (i, j) of block h lies at ((h W/4 + i/4) W + j) 4 + i%4.
+template <int PACK>
+__device__ __forceinline__ void store_sums(float* dst, const floatx4& v, int c, int g4) {
+    constexpr int W = Packing<PACK>::kWidth;
+    if (PACK == 1 || c / W == 4 * g4 / W) *reinterpret_cast<float4*>(dst + (g4 * W + c % W) * 4) = make_float4(v[0], v[1], v[2], v[3]);
+}
+template <int PACK>
+__host__ __device__ constexpr int sums_words() { return 256 / PACK; }
+template <int PACK, int WAVES>
+__device__ __forceinline__ float add_sums(const float* first_wave, int wave_words, int i, int j) {
+    constexpr int W = Packing<PACK>::kWidth;
+    const float* p = first_wave + (i / 4 * W + j) * 4 + i % 4;
+    float part[WAVES * PACK];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w)
+#pragma unroll
+        for (int h = 0; h < PACK; ++h) part[w * PACK + h] = p[w * wave_words + h * (W * W)];
+#pragma unroll
+    for (int k = 1; k < WAVES * PACK; k *= 2)
+#pragma unroll
+        for (int w = 0; w + k < WAVES * PACK; w += 2 * k) part[w] += part[w + k];
+    return part[0];
+}
+
+// The workgroup's table of the core gradient from the waves' sums (of mode n at first_wave + n sums_words).  B^(n) has
+// 16 rows, as a row of A^(n) has 16 floats (PACK = 2: 16 x 8, and zeros behind the eight that are multiplied).
+template <int PACK, int N, int WAVES>
+__device__ __forceinline__ void store_core(const Mfma16Args& g, const float* first_wave, int wave_words, int tid) {
+    constexpr int W = Packing<PACK>::kWidth;
+    constexpr int kTotal = N * 16 * W;
+    float* out = g.gb_partial + (size_t)blockIdx.x * kTotal;
+    for (int q = tid; q < kTotal; q += WAVES * 64) {
+        const int i = q / W % 16, n = q / (16 * W);
+        out[q] = i < W ? add_sums<PACK, WAVES>(first_wave + n * sums_words<PACK>(), wave_words, i, q % W) : 0.0f;
+    }
+}
 
 // Buffer resource over `bytes` bytes at p (raw buffer, 32-bit data).  Accesses at offsets past
 // `bytes` are dropped by the hardware: loads return 0 and atomics do nothing.
@@ -152,24 +236,25 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsig
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
-// Issue the row gather of tile `t` (0..3) of the group parked at `sbuf` into a ring slot:
+// Issue the row gather of tile `t` of the group parked at `sbuf` into a ring slot:
 // layout X, lane (c, g) reads bytes [16g, 16g + 16) of sample c's row.
-template <int N>
+template <int N, int PACK>
 __device__ __forceinline__ void gather_rows(const __amdgpu_buffer_rsrc_t (&rsrc_A)[N], const unsigned int* sbuf, int t,
                                             int c, int g4, floatx4 (&dst)[N]) {
     typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        const unsigned int word = sbuf[n * 64 + t * 16 + c];
-        const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], (int)((word & kRowMask) | (unsigned int)(g4 * 16)), 0, 0);
+        const unsigned int word = sbuf[n * 64 + t * Packing<PACK>::kTile + (g4 * PACK / 4) * 16 + c];
+        const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], (int)((word & kRowMask) | (unsigned int)(g4 % (4 / PACK) * 16)), 0, 0);
         dst[n] = floatx4{__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]), __uint_as_float(q[3])};
     }
 }
 
 // One group of 64 samples parked at `scur` (row words, values, scatter lists): four tiles of 16 (the
-// first n_tiles of them in the last group of a wave's share).
+// first n_tiles of them in the last group of a wave's share), or two of 32.
 // While tile t is computed, the rows of tile t + 3 are requested: tile 3 of this group during
-// tile 0, then tiles 0..2 of the wave's next group (parked at `snxt`).  The requests are
+// tile 0, then tiles 0..2 of the wave's next group (parked at `snxt`).  (Tiles of 32: two ahead, both of the next group, into
+// the registers that the projections have just read.)  The requests are
 // unconditional, so that the compiler's count of outstanding memory operations is exact.
 // A sample slot with no sample behind it (the ragged end of Psi, or a whole group past it) is
 // parked as value 0 and, in every mode, as the row just past the mode's last one: the buffer
@@ -187,30 +272,34 @@ __device__ __forceinline__ void gather_rows(const __amdgpu_buffer_rsrc_t (&rsrc_
 //                 of its own: core_phase_mfma16_kernel)
 constexpr int kSyncPass = 0, kInPlacePass = 1, kFactorPhase = 2, kCorePhase = 3;
 
-template <int N, int MODE>
-__device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>& st, unsigned int cell_base, unsigned int cell_mask,
-                                              unsigned int top_key, const unsigned int* scur, const unsigned int* snxt,
+template <int N, int MODE, int PACK>
+__device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, PACK>& st, unsigned int cell_base, unsigned int cell_mask,
+                                              unsigned int top_key, const unsigned int* scur, const unsigned int* snxt, const unsigned int* lists,
                                               float* tbuf, int c, int g4, int n_tiles) {
+    typedef Packing<PACK> P;
+    constexpr int kTile = P::kTile, kQuads = 4 * PACK;   // kQuads: rows of an instruction of the scatter
+    // this lane in the scatter: component j of the row that its `q8`-th share of the lanes works on
+    const int j = PACK == 1 ? c : c & 7, q8 = PACK == 1 ? g4 : g4 * 2 + (c >> 3);
     __amdgpu_buffer_rsrc_t rsrc_A[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.row_bytes[n]);
     const __amdgpu_buffer_rsrc_t rsrc_dA = make_rsrc(g.dA, g.all_bytes);
     const float* sval = reinterpret_cast<const float*>(scur + N * 64);
-    const unsigned int* atomic_list = scur + (N + 1) * 64;
+    const unsigned int* atomic_list = lists;
     const unsigned int* table_list = atomic_list + mfma16_list_words(N);
     const unsigned int* list_len = table_list + mfma16_list_words(N);
-    const unsigned int c4 = (unsigned int)c * 4u;
+    const unsigned int c4 = (unsigned int)j * 4u;
 
 #pragma unroll
-    for (int sub = 0; sub < 4; ++sub) {
-        // (wave-uniform) only the last group of a wave's share holds fewer than four tiles (n_tiles >= 1)
+    for (int sub = 0; sub < P::kTiles; ++sub) {
+        // (wave-uniform) only the last group of a wave's share holds fewer than all tiles (n_tiles >= 1)
         if (sub > 0 && sub >= n_tiles) break;
         // The tile's scatter lists were written when the group was parked: their first batches and
         // lengths are asked for now, long before they are used.
         // (Up to order 3, where the registers allow it; above, everything is read where it is used.)
         constexpr bool AHEAD = N <= 3;
-        const unsigned int* alist = atomic_list + sub * (16 * N) + g4 * (4 * N);
-        const unsigned int* tlist = table_list + sub * (16 * N) + g4 * (4 * N);
+        const unsigned int* alist = atomic_list + sub * (kTile * N) + q8 * (4 * N);
+        const unsigned int* tlist = table_list + sub * (kTile * N) + q8 * (4 * N);
         uint4 a_first = {0u, 0u, 0u, 0u}, a_second = {0u, 0u, 0u, 0u}, t_first = {0u, 0u, 0u, 0u};
         unsigned int len_atomic = 0u, len_table = 0u;
         if constexpr (AHEAD) {
@@ -221,15 +310,17 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             len_table = list_len[4 + sub];
         }
 
-        if (sub == 0)
-            gather_rows<N>(rsrc_A, scur, 3, c, g4, st.ring[3]);
-        else
-            gather_rows<N>(rsrc_A, snxt, sub - 1, c, g4, st.ring[sub - 1]);
+        if constexpr (PACK == 1) {
+            if (sub == 0)
+                gather_rows<N, PACK>(rsrc_A, scur, 3, c, g4, st.ring[3]);
+            else
+                gather_rows<N, PACK>(rsrc_A, snxt, sub - 1, c, g4, st.ring[sub - 1]);
+        }
 
         floatx4 aX[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) aX[n] = st.ring[sub][n];
-        const float x = sval[sub * 16 + c];
+        const float x = sval[sub * kTile + (g4 * PACK / 4) * 16 + c];
 
         // rows of all modes: layout X -> LDS -> layout Y (read back further down)
 #pragma unroll
@@ -249,6 +340,9 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         for (int n = 0; n < N; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(st.Bq[n][2], aX[n][2], s[n], 0, 0, 0);
 #pragma unroll
         for (int n = 0; n < N; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(st.Bq[n][3], aX[n][3], s[n], 0, 0, 0);
+        if constexpr (PACK == 2) gather_rows<N, PACK>(rsrc_A, snxt, sub, c, g4, st.ring[sub]);
+        // first operand of the product that adds a sample's components across the lane groups that hold them
+        const float ones = PACK == 1 || c / P::kWidth == g4 * 4 / P::kWidth ? 1.0f : 0.0f;
 
         float aY[N][4], wY[N][4], grad[N][4];
         if constexpr (MODE == kFactorPhase) {
@@ -268,7 +362,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
                     if (k != n) wn *= s[k];
                 const floatx4 full = wn * s[n];
                 const float part_n = (full[0] + full[1]) + (full[2] + full[3]);
-                const floatx4 xsum_n = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, part_n, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                const floatx4 xsum_n = __builtin_amdgcn_mfma_f32_16x16x4f32(ones, part_n, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
                 wn *= xsum_n[0] - x;   // -e w^(n)
                 floatx4 gsn = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -302,7 +396,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         // other three g.  A product with an all-ones matrix adds across g and leaves the sum in
         // every lane of column c, without a trip through LDS.
         const float part = (run[0] + run[1]) + (run[2] + run[3]);
-        const floatx4 xsum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, part, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+        const floatx4 xsum = __builtin_amdgcn_mfma_f32_16x16x4f32(ones, part, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
         const float neg_e = xsum[0] - x;
         run = floatx4{1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
@@ -371,15 +465,18 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
         }
         lds_wave_sync();
 
+        auto atomic_offset = [&](unsigned int e) -> int {   // row number x 64 + this lane's component
+            return (int)(((e >> (P::kSlotBits - 6)) & ~63u) | c4);
+        };
         auto atomics4 = [&](int first) {
             const uint4 e4 = *reinterpret_cast<const uint4*>(alist + first);
             const unsigned int e[4] = {e4.x, e4.y, e4.z, e4.w};
             float val[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) val[i] = tbuf[(e[i] & 127u) * 20u + (unsigned int)c];
+            for (int i = 0; i < 4; ++i) val[i] = tbuf[(e[i] & P::kSlotMask) * P::kSlotWords + (unsigned int)j];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(val[i], rsrc_dA, (int)(((e[i] >> 1) & ~63u) | c4), 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(val[i], rsrc_dA, atomic_offset(e[i]), 0, 0);
         };
         // LDS table, four list positions (16 rows) per batch.  Entries past the end of the list aim
         // at a row of +inf, which absorbs any finite addend: their swaps succeed and change nothing.
@@ -398,7 +495,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             if (__builtin_amdgcn_ballot_w64(lost) != 0) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    bool again = got[i] != sn[i] && (first + i) * 4 + g4 < n_table;
+                    bool again = got[i] != sn[i] && (first + i) * kQuads + q8 < n_table;
                     while (again) {
                         const unsigned int expect = got[i];
                         got[i] = lds_cas(cl[i], expect, __float_as_uint(__uint_as_float(expect) + val[i]));
@@ -414,7 +511,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             unsigned int cl[4], sn[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                val[i] = tbuf[(e[i] >> 20) * 20u + (unsigned int)c];
+                val[i] = tbuf[(e[i] >> 20) * P::kSlotWords + (unsigned int)j];
                 cl[i] = cell_base + (e[i] & cell_mask);
                 sn[i] = *(lds_u32*)(uintptr_t)cl[i];
             }
@@ -438,19 +535,23 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             float aval[8], tval[4];
             unsigned int cell[4], seen[4];
 #pragma unroll
-            for (int i = 0; i < (N > 1 ? 8 : 4); ++i) aval[i] = tbuf[(ea[i] & 127u) * 20u + (unsigned int)c];
+            for (int i = 0; i < (N > 1 ? 8 : 4); ++i) aval[i] = tbuf[(ea[i] & P::kSlotMask) * P::kSlotWords + (unsigned int)j];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) tval[i] = tbuf[(et[i] >> 20) * 20u + (unsigned int)c];
+            for (int i = 0; i < 4; ++i) tval[i] = tbuf[(et[i] >> 20) * P::kSlotWords + (unsigned int)j];
             // one-hot operands of the 16 most frequent rows: all compares first, then the products
-            float onehot[N][4];
+            float onehot[N][PACK][4];
 #pragma unroll
             for (int n = 0; n < N; ++n)
                 if (g.top[n] > 0) {
-                    const uint4 r = *reinterpret_cast<const uint4*>(scur + n * 64 + sub * 16 + 4 * g4);
-                    onehot[n][0] = r.x == top_key ? 1.0f : 0.0f;
-                    onehot[n][1] = r.y == top_key ? 1.0f : 0.0f;
-                    onehot[n][2] = r.z == top_key ? 1.0f : 0.0f;
-                    onehot[n][3] = r.w == top_key ? 1.0f : 0.0f;
+                    const uint4 r = *reinterpret_cast<const uint4*>(scur + n * 64 + sub * kTile + (c / P::kWidth) * 16 + 4 * g4);
+#pragma unroll
+                    for (int u = 0; u < PACK; ++u) {
+                        const unsigned int key = top_key + u * (8 * 64u);
+                        onehot[n][u][0] = r.x == key ? 1.0f : 0.0f;
+                        onehot[n][u][1] = r.y == key ? 1.0f : 0.0f;
+                        onehot[n][u][2] = r.z == key ? 1.0f : 0.0f;
+                        onehot[n][u][3] = r.w == key ? 1.0f : 0.0f;
+                    }
                 }
             const int n_atomic = __builtin_amdgcn_readfirstlane((int)len_atomic);
             n_table = __builtin_amdgcn_readfirstlane((int)len_table);
@@ -460,7 +561,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             // compiler wait for prefetched rows without waiting for atomics issued after them.
 #pragma unroll
             for (int i = 0; i < (N > 1 ? 8 : 4); ++i)
-                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(aval[i], rsrc_dA, (int)(((ea[i] >> 1) & ~63u) | c4), 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(aval[i], rsrc_dA, atomic_offset(ea[i]), 0, 0);
             // the table cells of the first batch are read while the matrix core is busy below
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -469,31 +570,35 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             }
 #pragma unroll
             for (int b = 2; b < N; ++b)
-                if (n_atomic > 16 * b) atomics4(4 * b);
+                if (n_atomic > kTile * b) atomics4(4 * b);
 #pragma unroll
             for (int n = 0; n < N; ++n)
                 if (g.top[n] > 0) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
-                        st.Top[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(onehot[n][k], grad[n][k], st.Top[n], 0, 0, 0);
+#pragma unroll
+                        for (int u = 0; u < PACK; ++u)
+                            st.Top[n][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(onehot[n][u][k], grad[n][k], st.Top[n][u], 0, 0, 0);
                 }
             core_gradient();
             if (n_table > 0) swap4(0, tval, cell, seen);
 #pragma unroll
             for (int b = 1; b < N; ++b)
-                if (n_table > 16 * b) table4(4 * b);
+                if (n_table > kTile * b) table4(4 * b);
         } else {
             // the same steps with everything read where it is used (fewer values alive at once)
 #pragma unroll
             for (int n = 0; n < N; ++n)
                 if (g.top[n] > 0) {
-                    const uint4 r = *reinterpret_cast<const uint4*>(scur + n * 64 + sub * 16 + 4 * g4);
+                    const uint4 r = *reinterpret_cast<const uint4*>(scur + n * 64 + sub * kTile + (c / P::kWidth) * 16 + 4 * g4);
                     const unsigned int rw[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float onehot = rw[k] == top_key ? 1.0f : 0.0f;
-                        st.Top[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(onehot, grad[n][k], st.Top[n], 0, 0, 0);
-                    }
+                    for (int k = 0; k < 4; ++k)
+#pragma unroll
+                        for (int u = 0; u < PACK; ++u) {
+                            const float onehot = rw[k] == top_key + u * (8 * 64u) ? 1.0f : 0.0f;
+                            st.Top[n][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(onehot, grad[n][k], st.Top[n][u], 0, 0, 0);
+                        }
                 }
             const int n_atomic = __builtin_amdgcn_readfirstlane((int)list_len[sub]);
             n_table = __builtin_amdgcn_readfirstlane((int)list_len[4 + sub]);
@@ -501,11 +606,11 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
             if (N > 1) atomics4(4);
 #pragma unroll
             for (int b = 2; b < N; ++b)
-                if (n_atomic > 16 * b) atomics4(4 * b);
+                if (n_atomic > kTile * b) atomics4(4 * b);
             core_gradient();
 #pragma unroll
             for (int b = 0; b < N; ++b)
-                if (n_table > 16 * b) table4(4 * b);
+                if (n_table > kTile * b) table4(4 * b);
         }
         lds_wave_sync();   // the next tile overwrites the staged rows
     }
@@ -513,33 +618,39 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N>&
 
 // TILES: Psi is drawn by the tile-sampling rule (runs of 64 neighbouring records) instead of entry
 // by entry.  MODE: see process_group (in the synchronous pass g.scale is 1 and not looked at).
-template <int N, bool TILES, int MODE>
+// PACK: samples side by side in a product (1: J_n = R = 16; 2: J_n, R <= 8, in rows of 16 floats all the same).
+template <int N, bool TILES, int MODE, int PACK>
 __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g) {
+    typedef Packing<PACK> P;
+    constexpr int kWidth = P::kWidth, kTile = P::kTile, kTiles = P::kTiles;
     extern __shared__ float lds[];
     constexpr int W4 = (N + 1 + 3) / 4;   // 16-byte words per record
-    constexpr int kGroupWords = mfma16_group_words(N);
+    constexpr int kGroupWords = mfma16_group_words(N, PACK), kScratch = mfma16_wave_scratch(N, PACK);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
     const int c = lane & 15, g4 = lane >> 4;
     float* hot = lds;
-    float* wave_lds = lds + (size_t)(g.H * g.width + kSinkRows * 16) + wave * mfma16_wave_scratch(N);
+    float* wave_lds = lds + (size_t)(g.H * g.width + kSinkRows * 16) + wave * kScratch;
     unsigned int* sbuf = reinterpret_cast<unsigned int*>(wave_lds);   // two parked groups
-    float* tbuf = wave_lds + 2 * kGroupWords;                          // [N][16][20]
-    float* gbred = lds + (size_t)(g.H * g.width + kSinkRows * 16) + kMfmaWaves * mfma16_wave_scratch(N);
+    unsigned int* own_lists = sbuf + 2 * kGroupWords;                  // PACK = 2
+    float* tbuf = wave_lds + kScratch - N * kTransposeFloats;          // [N][16][20]
 
-    WaveState<N> st;
+    const int j = c % kWidth;   // this lane's component of a row in the scatter
+
+    WaveState<N, PACK> st;
 #pragma unroll
     for (int n = 0; n < N; ++n) {
         const float* Bn = g.B + g.B_off[n];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            st.Bq[n][k] = Bn[(4 * g4 + k) * 16 + c];
-            st.Br[n][k] = Bn[c * 16 + 4 * g4 + k];
+            st.Bq[n][k] = core_operand<PACK>(Bn, 4 * g4 + k, c);
+            st.Br[n][k] = core_operand<PACK>(Bn, c, 4 * g4 + k);
         }
         st.GBacc[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        st.Top[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) st.ring[t][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int u = 0; u < PACK; ++u) st.Top[n][u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int t = 0; t < P::kRing; ++t) st.ring[t][n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
     const long long M = g.M;
@@ -547,10 +658,10 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     const unsigned int hot_addr = lds_address(hot);
     // Where this lane's column of a listed table row lies: cell_base + (entry & cell_mask).  A table row holds g.width
     // floats; lanes of the columns behind them carry zeros and aim at the quarter's row of +inf, whatever the entry.
-    const unsigned int sink_addr = hot_addr + (unsigned int)(g.H * g.width) * 4u, cell_mask = c < g.width ? 0xfffffu : 0u;
-    const unsigned int cell_base = (c < g.width ? hot_addr : sink_addr + (unsigned int)g4 * 64u) + (unsigned int)c * 4u;
-    // row word of "row c, one of the 16 most frequent" (kept opaque so that the match below is one compare)
-    unsigned int top_key = (2u << kRouteShift) + (unsigned int)c * 64u;
+    const unsigned int sink_addr = hot_addr + (unsigned int)(g.H * g.width) * 4u, cell_mask = j < g.width ? 0xfffffu : 0u;
+    const unsigned int cell_base = (j < g.width ? hot_addr : sink_addr + (unsigned int)(lane / kWidth) * (4u * kWidth)) + (unsigned int)j * 4u;
+    // row word of "row j, one of the 16 most frequent" (PACK = 2: row j and row 8 + j) (kept opaque so that the match below is one compare)
+    unsigned int top_key = (2u << kRouteShift) + (unsigned int)j * 64u;
     asm volatile("" : "+v"(top_key));
 
     // Which samples a wave takes: a share [s0, s_end) of Psi made of whole tiles of 16 samples.  The kernel lasts as long
@@ -579,21 +690,21 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         const int pr = wave & 3;
         const int Tp = (Tb >> 2) + (pr < (Tb & 3) ? 1 : 0);                    // the pair's tiles, from tile p0 on
         const long long p0 = b0 + pr * (Tb >> 2) + (pr < (Tb & 3) ? pr : (Tb & 3));
-        const int older = Tp >= 16 ? (9 * Tp + 15) >> 4 : (Tp + 1) >> 1;
+        const int older = Tp >= 16 ? (9 * Tp + (PACK == 1 ? 15 : 8)) >> 4 : (Tp + 1) >> 1;
         const int tiles = wave < 4 ? older : Tp - older;
-        s0 = (wave < 4 ? p0 : p0 + older) * 16;
-        s_end = s0 + tiles * 16 < M ? s0 + tiles * 16 : M;
-        n_pair_turns = paired ? 2 * (tiles >> 3) : 0;
-        const int rest = tiles - 4 * n_pair_turns;                // tiles of the turns that are not paired
-        n_turns = n_pair_turns + ((rest + 3) >> 2);
-        last_tiles = (rest & 3) == 0 ? 4 : (rest & 3);
+        s0 = (wave < 4 ? p0 : p0 + older) * kTile;
+        s_end = s0 + (long long)tiles * kTile < M ? s0 + (long long)tiles * kTile : M;
+        n_pair_turns = paired ? 2 * (tiles / (2 * kTiles)) : 0;
+        const int rest = tiles - kTiles * n_pair_turns;           // tiles of the turns that are not paired
+        n_turns = n_pair_turns + (rest + kTiles - 1) / kTiles;
+        last_tiles = rest % kTiles == 0 ? kTiles : rest % kTiles;
     }
     auto sample_of = [&](long long t) -> long long {   // this lane's sample number in turn t
         if (t < n_pair_turns) return s0 + 128 * (t >> 1) + 2 * lane + (t & 1);
         return s0 + 64 * t + lane;
     };
     auto turn_exists = [&](long long t) -> bool { return t < n_turns; };   // wave-uniform
-    auto tiles_of = [&](long long t) -> int { return t == n_turns - 1 ? last_tiles : 4; };
+    auto tiles_of = [&](long long t) -> int { return t == n_turns - 1 ? last_tiles : kTiles; };
     uint32_t odd_place = 0u;   // entry rule: where the odd turn's sample is read, kept from the even turn
 
     // record of this lane's sample in turn t: N row numbers and the value's bits.  A slot with no
@@ -619,9 +730,10 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
 #pragma unroll
         for (int q = 0; q < W4; ++q) rec[q] = rec4[(size_t)p * W4 + q];
     };
-    // Park a group (lane = sample): row words, values, and the two compacted lists of each tile.
-    const int my_tile = lane >> 4, my_s = lane & 15;
-    const unsigned long long tile_lanes = 0xffffull << (16 * my_tile);
+    // Park a group (lane = sample): row words and values.
+    constexpr int kQuads = 64 / kWidth;   // rows of an instruction of the scatter
+    const int my_tile = lane / kTile, my_s = lane % kTile;
+    const unsigned long long tile_lanes = (PACK == 1 ? 0xffffull : 0xffffffffull) << (kTile * my_tile);
     const unsigned long long lanes_below = tile_lanes & ((1ull << lane) - 1ull);   // of my tile
     auto park_record = [&](long long t, const uint4 (&rec)[W4], unsigned int* dst) {
         const bool act = sample_of(t) < s_end;
@@ -633,15 +745,26 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             flat[4 * q + 2] = rec[q].z;
             flat[4 * q + 3] = rec[q].w;
         }
-        unsigned int* atomic_list = dst + (N + 1) * 64 + my_tile * (16 * N);
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            // an empty slot: the row just past the mode's last one (reads as zeros), on no list
+            const int row = act ? (int)flat[n] : (int)(g.row_bytes[n] >> 6);
+            const unsigned int route = !act || row >= g.K[n] ? 0u : row >= g.top[n] ? 1u : 2u;
+            dst[n * 64 + lane] = (unsigned int)row * 64u + (route << kRouteShift);
+        }
+        dst[N * 64 + lane] = act ? flat[N] : 0u;
+    };
+    // The two compacted lists of each tile, from the row words of a parked group.
+    auto make_lists = [&](const unsigned int* group, unsigned int* lists) {
+        unsigned int* atomic_list = lists + my_tile * (kTile * N);
         unsigned int* table_list = atomic_list + mfma16_list_words(N);
         // every list position starts out unused: lane (tile, quarter q, j) clears positions [q][j], [q][j+4], ...
         {
-            const int q = (lane >> 2) & 3, j = lane & 3;
-            const unsigned int unused_cell = (unsigned int)(g.H * g.width + q * 16) * 4u;   // a row of +inf, one per quarter
+            const int q = (lane >> 2) % kQuads, j = lane & 3;
+            const unsigned int unused_cell = (unsigned int)(g.H * g.width + q * kWidth) * 4u;   // a row of +inf, one per quarter
 #pragma unroll
             for (int i = 0; i < 4 * N; i += 4) {
-                atomic_list[q * (4 * N) + j + i] = kNoAtomic;
+                atomic_list[q * (4 * N) + j + i] = P::kNoAtomic;
                 table_list[q * (4 * N) + j + i] = unused_cell;
             }
         }
@@ -649,30 +772,25 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         int n_atomic = 0, n_table = 0;   // entries of my tile's lists so far
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            // an empty slot: the row just past the mode's last one (reads as zeros), on no list
-            const int row = act ? (int)flat[n] : (int)(g.row_bytes[n] >> 6);
-            const bool to_table = act && row >= g.top[n] && row < g.K[n];
-            const bool to_atomic = act && row >= g.K[n];
-            const unsigned int route = (to_atomic || !act) ? 0u : to_table ? 1u : 2u;
-            dst[n * 64 + lane] = (unsigned int)row * 64u + (route << kRouteShift);
+            const unsigned int word = group[n * 64 + lane], row = (word & kRowMask) >> 6;
+            const bool to_table = word >> kRouteShift == 1u, to_atomic = word < g.row_bytes[n];   // (an empty slot's word is row_bytes)
             const unsigned long long atomic_lanes = __builtin_amdgcn_ballot_w64(to_atomic);
             const unsigned long long table_lanes = __builtin_amdgcn_ballot_w64(to_table);
-            const unsigned int slot = (unsigned int)(n * 16 + my_s);
+            const unsigned int slot = P::slot(n, my_s);
             if (to_atomic) {
-                const int p = n_atomic + __popcll(atomic_lanes & lanes_below);
-                atomic_list[(p & 3) * (4 * N) + (p >> 2)] = ((g.first_row[n] + (unsigned int)row) << 7) | slot;
+                const unsigned int p = n_atomic + __popcll(atomic_lanes & lanes_below);
+                atomic_list[(p % kQuads) * (4 * N) + p / kQuads] = ((g.first_row[n] + row) << P::kSlotBits) | slot;
             }
             if (to_table) {
-                const int p = n_table + __popcll(table_lanes & lanes_below);
-                table_list[(p & 3) * (4 * N) + (p >> 2)] = (slot << 20) | ((unsigned int)((g.hot_off[n] + row) * g.width) * 4u);
+                const unsigned int p = n_table + __popcll(table_lanes & lanes_below);
+                table_list[(p % kQuads) * (4 * N) + p / kQuads] = (slot << 20) | (((unsigned int)g.hot_off[n] + row) * (unsigned int)g.width * 4u);
             }
             n_atomic += __popcll(atomic_lanes & tile_lanes);
             n_table += __popcll(table_lanes & tile_lanes);
         }
-        dst[N * 64 + lane] = act ? flat[N] : 0u;
         if (my_s == 0) {
-            dst[(N + 1) * 64 + 2 * mfma16_list_words(N) + my_tile] = (unsigned int)n_atomic;
-            dst[(N + 1) * 64 + 2 * mfma16_list_words(N) + 4 + my_tile] = (unsigned int)n_table;
+            lists[2 * mfma16_list_words(N) + my_tile] = (unsigned int)n_atomic;
+            lists[2 * mfma16_list_words(N) + 4 + my_tile] = (unsigned int)n_table;
         }
     };
 
@@ -685,18 +803,18 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
     }
     for (int q = tid; q < g.H * (g.width / 4); q += kMfmaThreads) reinterpret_cast<float4*>(hot)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int q = tid; q < kSinkRows * 16; q += kMfmaThreads) hot[g.H * g.width + q] = __uint_as_float(0x7f800000u);
-    for (int q = tid; q < N * 256; q += kMfmaThreads) gbred[q] = 0.0f;
     __syncthreads();
     if (has_turns) {
         __amdgpu_buffer_rsrc_t rsrc_A[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.row_bytes[n]);
 
-        // ... then the rows of the first three tiles
+        // ... then the rows of the first tiles
         park_record(0, rec0, sbuf);
         lds_wave_sync();
+        if constexpr (PACK == 1) make_lists(sbuf, sbuf + (N + 1) * 64);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) gather_rows<N>(rsrc_A, sbuf, t, c, g4, st.ring[t]);
+        for (int t = 0; t < P::kAhead; ++t) gather_rows<N, PACK>(rsrc_A, sbuf, t, c, g4, st.ring[t]);
 
         // One turn: park the next turn's records (requested a whole turn ago), request the
         // records of the turn after it, then the four tiles.  Turns past the wave's last one hold
@@ -707,7 +825,13 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             park_record(t + 1, rec, snxt);
             load_record(t + 2, rec);
             lds_wave_sync();
-            process_group<N, MODE>(g, st, cell_base, cell_mask, top_key, scur, snxt, tbuf, c, g4, tiles_of(t));
+            if constexpr (PACK == 1)
+                make_lists(snxt, snxt + (N + 1) * 64);
+            else
+                make_lists(scur, own_lists);
+            lds_wave_sync();
+            process_group<N, MODE, PACK>(g, st, cell_base, cell_mask, top_key, scur, snxt, PACK == 1 ? scur + (N + 1) * 64 : own_lists, tbuf, c, g4,
+                                         tiles_of(t));
         };
         // From order 4 on the first turn is peeled off the loop: the loop proper is then entered with the same sequence
         // of outstanding memory operations as its own back edge, and the compiler's wait counts in the steady state
@@ -724,40 +848,32 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         for (; turn_exists(t); ++t, parity ^= 1) one_turn(t, parity);
     }
 
-    // rows 0..15 of each mode: from the wave's accumulators into the workgroup's LDS table (a mode whose table
-    // holds fewer than 16 rows never used its accumulator: its zeros aim at the rows of +inf), and the workgroup
-    // reduction of the core gradient.  All cells are read, then all swaps issued, then the lost ones repeated, so that
-    // the round trips of a wave overlap.  Then one table of plain stores per workgroup.
-    {
-        unsigned int cell[8 * N], seen[8 * N], got[8 * N];
-        float val[8 * N];
+    // Core gradient and the sums of rows 0..15 of each mode: the waves' accumulators added up, the rows' sums into their rows
+    // of the LDS table (which no swap has touched).  Then one table of plain stores per workgroup.
+    constexpr int kSums = sums_words<PACK>();
+    static_assert((1 + PACK) * N * kSums <= kScratch, "a wave's sums fit its scratch");
+    lds_wave_sync();
 #pragma unroll
-        for (int n = 0; n < N; ++n)
+    for (int n = 0; n < N; ++n) {
+        store_sums<PACK>(wave_lds + n * kSums, st.GBacc[n], c, g4);
+        if (g.top[n] > 0) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                cell[8 * n + v] = g.top[n] > 0 && c < g.width ? hot_addr + (unsigned int)((g.hot_off[n] + 4 * g4 + v) * g.width + c) * 4u
-                                                              : sink_addr + (unsigned int)(v * 16 + c) * 4u;
-                val[8 * n + v] = st.Top[n][v];
-                cell[8 * n + 4 + v] = lds_address(gbred + n * 256 + (4 * g4 + v) * 16 + c);
-                val[8 * n + 4 + v] = st.GBacc[n][v];
-            }
-#pragma unroll
-        for (int i = 0; i < 8 * N; ++i) seen[i] = *(lds_u32*)(uintptr_t)cell[i];
-#pragma unroll
-        for (int i = 0; i < 8 * N; ++i) got[i] = lds_cas(cell[i], seen[i], __float_as_uint(__uint_as_float(seen[i]) + val[i]));
-#pragma unroll
-        for (int i = 0; i < 8 * N; ++i) {
-            bool again = got[i] != seen[i];
-            while (again) {
-                const unsigned int expect = got[i];
-                got[i] = lds_cas(cell[i], expect, __float_as_uint(__uint_as_float(expect) + val[i]));
-                again = got[i] != expect;
-            }
+            for (int u = 0; u < PACK; ++u) store_sums<PACK>(wave_lds + (N + n * PACK + u) * kSums, st.Top[n][u], c, g4);
         }
     }
     __syncthreads();
-    float* gb_out = g.gb_partial + (size_t)blockIdx.x * (N * 256);
-    for (int q = tid; q < N * 256; q += kMfmaThreads) gb_out[q] = gbred[q];
+    const float* all_sums = lds + (size_t)(g.H * g.width + kSinkRows * 16);
+    store_core<PACK, N, kMfmaWaves>(g, all_sums, kScratch, tid);
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+        if (g.top[n] > 0)
+            for (int q = tid; q < 16 * kWidth; q += kMfmaThreads) {
+                const int i = q / kWidth, r = q % kWidth;
+                if (r < g.width)
+                    hot[(g.hot_off[n] + i) * g.width + r] =
+                        add_sums<PACK, kMfmaWaves>(all_sums + (N + n * PACK + i / kWidth) * kSums, kScratch, i % kWidth, r);
+            }
+    __syncthreads();
     float* hot_out = g.hot_partial + (size_t)blockIdx.x * g.H * g.width;
     for (int q = tid; q < g.H * (g.width / 4); q += kMfmaThreads) reinterpret_cast<float4*>(hot_out)[q] = reinterpret_cast<const float4*>(hot)[q];
 }
@@ -779,13 +895,15 @@ __host__ __device__ constexpr int core_phase_wave_words(int order) {
     return 2 * (order + 1) * 64 + order * kTransposeFloats;
 }
 __host__ __device__ constexpr size_t core_phase_lds_bytes(int order) {
-    return 4 * ((size_t)core_phase_waves(order) * core_phase_wave_words(order) + order * 256);
+    return 4 * (size_t)core_phase_waves(order) * core_phase_wave_words(order);
 }
 
-template <int N, bool TILES>
+template <int N, bool TILES, int PACK>
 __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_kernel(Mfma16Args g) {
+    typedef Packing<PACK> P;
+    constexpr int kWidth = P::kWidth, kTile = P::kTile, kTiles = P::kTiles;
     extern __shared__ float lds[];
-    constexpr int W4 = (N + 1 + 3) / 4, WAVES = core_phase_waves(N), THREADS = WAVES * 64;
+    constexpr int W4 = (N + 1 + 3) / 4, WAVES = core_phase_waves(N);
     constexpr int kGroup = (N + 1) * 64;
     constexpr int kAhead = 2;   // tiles whose rows are requested ahead of the one worked on
     typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
@@ -794,19 +912,18 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
     const int c = lane & 15, g4 = lane >> 4;
     unsigned int* sbuf = reinterpret_cast<unsigned int*>(lds + wave * core_phase_wave_words(N));
     float* tbuf = reinterpret_cast<float*>(sbuf + 2 * kGroup);
-    float* gbred = lds + WAVES * core_phase_wave_words(N);
 
     // the wave's share: tiles [t0, t0 + tiles) of the workgroup's, dealt evenly
     const int blk = (int)blockIdx.x;
     const int Tb = g.tiles_each + (blk < g.tiles_more ? 1 : 0);
     const long long b0 = (long long)blk * g.tiles_each + (blk < g.tiles_more ? blk : g.tiles_more);
     const int tiles = Tb / WAVES + (wave < Tb % WAVES ? 1 : 0);
-    const long long s0 = (b0 + (long long)wave * (Tb / WAVES) + (wave < Tb % WAVES ? wave : Tb % WAVES)) * 16;
-    const long long s_end = s0 + tiles * 16LL < g.M ? s0 + tiles * 16LL : g.M;
+    const long long s0 = (b0 + (long long)wave * (Tb / WAVES) + (wave < Tb % WAVES ? wave : Tb % WAVES)) * kTile;
+    const long long s_end = s0 + (long long)tiles * kTile < g.M ? s0 + (long long)tiles * kTile : g.M;
     // turns of 64 samples; in pairs that share their Philox blocks as in grad_mfma16_kernel
-    const int n_pair_turns = (!TILES && g.pair_turns != 0) ? 2 * (tiles >> 3) : 0;
-    const int rest = tiles - 4 * n_pair_turns;
-    const int n_turns = n_pair_turns + ((rest + 3) >> 2);
+    const int n_pair_turns = (!TILES && g.pair_turns != 0) ? 2 * (tiles / (2 * kTiles)) : 0;
+    const int rest = tiles - kTiles * n_pair_turns;
+    const int n_turns = n_pair_turns + (rest + kTiles - 1) / kTiles;
     auto sample_of = [&](int t) -> long long {
         if (t < n_pair_turns) return s0 + 128LL * (t >> 1) + 2 * lane + (t & 1);
         return s0 + 64LL * t + lane;
@@ -853,7 +970,7 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
 #pragma unroll
     for (int n = 0; n < N; ++n) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) Bq[n][k] = g.B[g.B_off[n] + (4 * g4 + k) * 16 + c];
+        for (int k = 0; k < 4; ++k) Bq[n][k] = core_operand<PACK>(g.B + g.B_off[n], 4 * g4 + k, c);
         GBacc[n] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     }
     uint4 rec0[W4], rec[W4];
@@ -861,17 +978,16 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
         load_record(0, rec0);
         load_record(1, rec);
     }
-    for (int q = tid; q < N * 256; q += THREADS) gbred[q] = 0.0f;
-    __syncthreads();
     if (n_turns > 0) {
         __amdgpu_buffer_rsrc_t rsrc_A[N];
 #pragma unroll
         for (int n = 0; n < N; ++n) rsrc_A[n] = make_rsrc(g.A + g.A_off[n], g.row_bytes[n]);
-        floatx4 ring[4][N];
+        floatx4 ring[P::kRing][N];
+        const float ones = PACK == 1 || c / kWidth == 4 * g4 / kWidth ? 1.0f : 0.0f;
         auto gather = [&](const unsigned int* from, int t, floatx4 (&dst)[N]) {
 #pragma unroll
             for (int n = 0; n < N; ++n) {
-                const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], (int)(from[n * 64 + t * 16 + c] + (unsigned int)(g4 * 16)), 0, 0);
+                const uintx4 q = __builtin_amdgcn_raw_buffer_load_b128(rsrc_A[n], (int)(from[n * 64 + t * kTile + (g4 * PACK / 4) * 16 + c] + (unsigned int)(g4 % (4 / PACK) * 16)), 0, 0);
                 dst[n] = floatx4{__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]), __uint_as_float(q[3])};
             }
         };
@@ -885,13 +1001,13 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
             park_record(t + 1, rec, snxt);   // (turns past the last one hold empty slots)
             load_record(t + 2, rec);
             lds_wave_sync();
-            const int here = t == n_turns - 1 && (rest & 3) != 0 ? (rest & 3) : 4;   // tiles of this turn
+            const int here = t == n_turns - 1 && rest % kTiles != 0 ? rest % kTiles : kTiles;   // tiles of this turn
             const float* sval = reinterpret_cast<const float*>(scur + N * 64);
 #pragma unroll
-            for (int sub = 0; sub < 4; ++sub) {
+            for (int sub = 0; sub < kTiles; ++sub) {
                 if (sub > 0 && sub >= here) break;
-                gather(sub + kAhead < 4 ? scur : snxt, (sub + kAhead) & 3, ring[(sub + kAhead) & 3]);
-                const float x = sval[sub * 16 + c];
+                if constexpr (PACK == 1) gather(sub + kAhead < 4 ? scur : snxt, (sub + kAhead) & 3, ring[(sub + kAhead) & 3]);
+                const float x = sval[sub * kTile + (g4 * PACK / 4) * 16 + c];
                 floatx4 s[N], w[N];
 #pragma unroll
                 for (int n = 0; n < N; ++n) {
@@ -903,6 +1019,7 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
                 for (int k = 0; k < 4; ++k)
 #pragma unroll
                     for (int n = 0; n < N; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(Bq[n][k], ring[sub][n][k], s[n], 0, 0, 0);
+                if constexpr (PACK == 2) gather(snxt, sub, ring[sub]);   // into the registers that the projections have read
                 floatx4 run = {1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
                 for (int n = 0; n < N; ++n) {
@@ -910,7 +1027,7 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
                     run *= s[n];
                 }
                 const float part = (run[0] + run[1]) + (run[2] + run[3]);
-                const floatx4 xsum = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, part, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                const floatx4 xsum = __builtin_amdgcn_mfma_f32_16x16x4f32(ones, part, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
                 const float neg_e = xsum[0] - x;
                 run = floatx4{1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
@@ -944,13 +1061,13 @@ __global__ void __launch_bounds__(core_phase_waves(N) * 64) core_phase_mfma16_ke
             }
         }
     }
+    constexpr int kSums = sums_words<PACK>();
+    static_assert(N * kSums <= core_phase_wave_words(N), "a wave's sums fit its scratch");
+    lds_wave_sync();
 #pragma unroll
-    for (int n = 0; n < N; ++n)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) lds_float_add(gbred + n * 256 + (4 * g4 + v) * 16 + c, GBacc[n][v]);
+    for (int n = 0; n < N; ++n) store_sums<PACK>(lds + wave * core_phase_wave_words(N) + n * kSums, GBacc[n], c, g4);
     __syncthreads();
-    float* gb_out = g.gb_partial + (size_t)blockIdx.x * (N * 256);
-    for (int q = tid; q < N * 256; q += THREADS) gb_out[q] = gbred[q];
+    store_core<PACK, N, WAVES>(g, lds, core_phase_wave_words(N), tid);
 }
 
 // ---------------------------------------------------------------------------------------------

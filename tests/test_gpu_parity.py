@@ -1587,6 +1587,64 @@ def test_core_phase_of_the_mode_by_mode_order(N, M, tiles):
     assert max(float(np.abs(x - y).max()) for x, y in zip(want_B, B)) > 1e-3
 
 
+# Ranks up to 8 go two samples side by side through the products of the J = R = 16 kernel: tiles of 32 samples whose halves take
+# different lanes, two tiles to a group, rows of the scatter eight to an instruction.
+SIDE_BY_SIDE = [(2, (8, 5), 7), (3, (8, 8, 8), 8), (3, (3, 8, 1), 4), (4, (4, 8, 6, 8), 8), (5, (8, 7, 8, 2, 8), 6)]
+
+
+@pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
+@pytest.mark.parametrize("M,tiles", [(1, False), (16, False), (17, True), (32, False), (33, False), (64, True), (97, False), (8_209, True),
+                                     (8_225, False), (300_001, False)])
+def test_two_samples_side_by_side(N, J, R, M, tiles):
+    """Half-filled tiles, one tile of two, turns in pairs (300 001 samples: five tiles a wave), rows that take each of the three
+    ways out; every parameter of the synchronous step, then the core phase of the printed order (which with lr_A = 0 gives the
+    synchronous step's core factors).  The most frequent row collects n < 6e4 gradients of size |g| < 8: the error of its sum
+    grows as sqrt(n) 2^-24 times its size, lr n |g| 2^-24 = 9e-7 if all of it had one sign, inside the bound's 1e-6."""
+    announce("two samples side by side order=%d J=%r M=%d tiles=%d" % (N, J, M, tiles))
+    w = synth.tiny_workload(N, (3_001, 701, 90, 211, 33)[:N], 200_003, J, R, M, seed=5, values="normal", zipf=(None, 1.2, None, 1.1, None)[:N])
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(10 * N + R)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(w.dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) / np.sqrt(j)).astype(np.float32) for j in J]
+    pos = (oracle.sample_positions_tiles if tiles else oracle.sample_positions)(7, M, w.nnz)
+    with binding.FastTucker(w.dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "mfma16"
+        if tiles:
+            ft.ftk_set_sampling(binding.FTK_SAMPLE_TILES)
+        for mode, rates in ((binding.FTK_SYNC, (3e-5, 0.3, 0.05, 0.02)), (binding.FTK_HOGWILD_MODEWISE, (0.0, 0.3, 0.0, 0.02))):
+            ft.ftk_set_mode(mode)
+            ft.ftk_set_factors(A, B)
+            ft.ftk_sample(7, M)
+            assert not ft.ftk_get_row_owners()[0]
+            ft.ftk_sgd_step(*rates)
+            gA, gB = ft.ftk_get_factors()
+            want_A, want_B = [a.copy() for a in A], [b.copy() for b in B]
+            oracle.sgd_step_sync(w.dims, idx, vals, want_A, want_B, pos, *rates)
+            assert_params_close(gA, want_A, "A")
+            assert_params_close(gB, want_B, "B")
+            assert max(float(np.abs(x - y).max()) for x, y in zip(want_B, B)) > 1e-3
+
+
+@pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
+def test_two_samples_side_by_side_in_place(N, J, R):
+    """No row is shared by two samples: the mode-by-mode step is Algorithm 1's, and the fused in-place one the synchronous step."""
+    test_modewise_in_place_step_equals_the_printed_order_when_no_row_is_shared("mfma16", N, J, R, 5e-2, 1e-2)
+    rng = np.random.default_rng(12)
+    nnz, M = 6_000, 60
+    idx = [rng.permutation(nnz).astype(np.int32) for _ in range(N)]
+    vals = rng.uniform(1.0, 5.0, nnz).astype(np.float32)
+    seed = next(s for s in range(1_000) if len(set(oracle.sample_positions(s, M, nnz).tolist())) == M)
+    A, B = oracle.init_factors(3, (nnz,) * N, J, R)
+    with binding.FastTucker((nnz,) * N, idx, vals, J, R, 3) as ft:
+        ft.ftk_set_mode(binding.FTK_HOGWILD)
+        ft.ftk_sample(seed, M)
+        ft.ftk_sgd_step(5e-2, 1e-2, 1e-2, 1e-2)
+        gA, gB = ft.ftk_get_factors()
+    oracle.sgd_step_sync((nnz,) * N, idx, vals, A, B, oracle.sample_positions(seed, M, nnz), 5e-2, 1e-2, 1e-2, 1e-2)
+    assert_params_close(gA, A, "A")
+    assert_params_close(gB, B, "B")
+
+
 # ------------------------------------------------------------------------------------------------
 # the training loop of the paper's experiments, end to end: decaying step sizes, held-out Gamma
 # ------------------------------------------------------------------------------------------------
