@@ -13,8 +13,8 @@
 // the row's number, with plain stores; a workgroup of the second owns a bucket, sums its lists in LDS and updates its rows.
 // A list that is full sends its row to the accumulator of the atomic kernels instead, which the owner folds in.
 //
-// Order 10, J = R = 4, 1e6 samples: 537 us per step with atomics, 244 us this way: 157 us for the appending pass, where 10e6
-// entries of 16 bytes at the rate of scattered stores take 110 us, and 92 us for the owners, which read 200 MB (40 us).
+// Order 10, J = R = 4, 1e6 samples: 537 us per step with atomics, 211 us this way: 118 us for the appending pass and 85 us for
+// the owners, which read 200 MB (40 us).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -55,119 +55,194 @@ struct AppendArgs {
     unsigned int* overflow;
 };
 
-// G lanes per sample (four columns each), 64 / G samples per wave at a time.  LDS: cursors [n_buckets] | row numbers [places].
-// A workgroup takes one share of Psi; what bounds it is the scattered stores of the entries (one request of 16 G bytes each)
-// and the gathering of the rows.
+// A meeting of the workgroup's waves over what they have in LDS.  Unlike __syncthreads it waits for LDS only, so that records and
+// rows asked for and entries on their way out stay under way.
+__device__ __forceinline__ void lds_meet() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Words of LDS: [4][n_buckets] counts of the round, filled places, place of a bucket in the round, the same against its list |
+// for every thread and mode the staged entry (four floats) and, per sample and mode, the entry's bucket and row.
+__host__ __device__ inline int append_bucket_words(int n_buckets) { return 4 * ((n_buckets + 3) / 4 * 4); }
+// samples a thread takes in a round: at low orders a round of one each holds too few entries of a bucket to leave side by side
+// (order 2, R = 8, 2e6 samples: 224 us per step with one, 180 with four; order 3, 1e6: 153 with one, 157 with three)
+__host__ __device__ constexpr int append_samples(int order) { return order <= 2 ? 4 : order <= 4 ? 2 : 1; }
+__host__ __device__ constexpr int append_wave_words(int order, int G) { return append_samples(order) * order * (64 * 4 + 64 / G); }
+// from order 8 on a wave needs more than the 128 registers that 16 waves leave it, and LDS has no room for more than 14
+__host__ __device__ constexpr int append_max_waves(int order) { return order < 8 ? kAppendThreads / 64 : 12; }
+
+// A workgroup takes one share of Psi in rounds of append_samples(N) samples per G threads (four columns each).  The entries of a round are put in
+// the order of their buckets in LDS first: an entry's place is counted by an atomic that returns it, one wave per mode adds the
+// counts up, and entries of one list then leave side by side (order 10, J = R = 4: some 15 of 16 bytes), in far fewer requests
+// than when each is stored where it belongs, which bound the launch before.  What bounds it now is the gathering of the rows (10e6 of
+// 16 bytes, 40 us at 1 ns a row and CU), the records, and what a round does in turn between its three meetings.
+// Launch for 1e6 samples of order 10, J = R = 4: 152 -> 118 us.  Whole steps of 1e6 samples: order 10 R = 4 247 -> 211, R = 8 371 -> 346; order 7 R = 8
+// 277 -> 258; order 6 R = 4 193 -> 150; order 4 R = 4 168 -> 127; order 3 R = 8 165 -> 153; order 2 R = 8 135 -> 113.
 template <int N, int G>
-__global__ void __launch_bounds__(kAppendThreads) append_lists_kernel(AppendArgs g) {
-    extern __shared__ unsigned int append_lds[];
-    constexpr int W4 = (N + 1 + 3) / 4, E = 64 / G, WAVES = kAppendThreads / 64;
-    unsigned int* cursor = append_lds;
-    unsigned short* id_lds = reinterpret_cast<unsigned short*>(append_lds + g.n_buckets);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = lane % G, who = lane / G;
-    for (int q = tid; q < g.n_buckets; q += kAppendThreads) cursor[q] = 0u;
-    __syncthreads();
+__global__ void __launch_bounds__(append_max_waves(N) * 64) append_lists_kernel(AppendArgs g) {
+    extern __shared__ __align__(16) unsigned int append_lds[];
+    constexpr int W4 = (N + 1 + 3) / 4, U = append_samples(N);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), sub = tid % G, who = tid / G;
+    const int threads = (int)blockDim.x, waves = threads >> 6, turn = threads / G, S = turn * U;   // S: samples of a round
+    const int nb4 = append_bucket_words(g.n_buckets) / 4;
+    unsigned int* count = append_lds;
+    unsigned int* filled = count + nb4;
+    unsigned int* base = filled + nb4;     // first staged entry of the bucket in this round
+    unsigned int* start = base + nb4;      // place in the bucket's list = start + staged place
+    float4* staged = reinterpret_cast<float4*>(append_lds + 4 * nb4);                          // [N][S][G]
+    unsigned int* tag = reinterpret_cast<unsigned int*>(staged + (size_t)N * U * threads);         // [N][S]: bucket << 16 | row in it
+    for (int q = tid; q < 2 * nb4; q += threads) append_lds[q] = 0u;   // counts and filled places
     const bool column = 4 * sub < g.Rs;
     const int col = column ? 4 * sub : 0;
     const uint4* rec4 = reinterpret_cast<const uint4*>(g.coo.rec);
-    // A wave takes 64 samples in G turns of E.  Lane l draws the position of the l-th of them, once for all turns.
-    const long long groups = (g.M + 63) / 64;
-    const long long stride = (long long)gridDim.x * WAVES;
     float* values = g.values + (size_t)blockIdx.x * g.places * g.Rs;
-    long long group = (long long)wave * gridDim.x + blockIdx.x;
-    uint4 rec[W4];
-    uint32_t position = 0u;
-    auto draw = [&](long long grp) {
-        const long long k = grp * 64 + lane;
-        position = k < g.M ? sample_place(g.seed, (uint64_t)k, g.rule) : 0u;
-    };
-    auto load = [&](int turn) {
-        const uint32_t p = G == 1 ? position : (uint32_t)__shfl((int)position, turn * E + who);
+    unsigned short* ids = g.ids + (size_t)blockIdx.x * g.places;
+    // the workgroup's share: groups of 64 samples, dealt evenly
+    const long long groups = (g.M + 63) / 64, each = groups / gridDim.x, more = groups % gridDim.x, b0 = blockIdx.x;
+    const long long first = 64 * (b0 * each + (b0 < more ? b0 : more));
+    const long long end = min(g.M, first + 64 * (each + (b0 < more ? 1 : 0)));
+    uint4 rec[U][W4];
+    auto load = [&](long long from) {   // records of this thread's samples of the round that starts at `from`
 #pragma unroll
-        for (int q = 0; q < W4; ++q) rec[q] = rec4[(size_t)p * W4 + q];
-    };
-    if (group < groups) {
-        draw(group);
-        load(0);
-    }
-    int turn = 0;
-    while (group < groups) {
-        const bool act = group * 64 + turn * E + who < g.M;
-        uint32_t flat[4 * W4];
+        for (int u = 0; u < U; ++u) {
+            const long long k = from + u * turn + who;
+            const uint32_t p = k < end ? sample_place(g.seed, (uint64_t)k, g.rule) : 0u;
 #pragma unroll
-        for (int q = 0; q < W4; ++q) {
-            flat[4 * q + 0] = rec[q].x;
-            flat[4 * q + 1] = rec[q].y;
-            flat[4 * q + 2] = rec[q].z;
-            flat[4 * q + 3] = rec[q].w;
+            for (int q = 0; q < W4; ++q) rec[u][q] = rec4[(size_t)p * W4 + q];
         }
-        float4 c[N];
+    };
+    uint32_t flat[U][4 * W4];
+    float4 c[U][N];
+    auto gather = [&]() {
 #pragma unroll
-        for (int n = 0; n < N; ++n) c[n] = *reinterpret_cast<const float4*>(g.S[n] + (uint64_t)flat[n] * (uint32_t)g.Rs + col);
-        // the places in the lists while the rows are on their way
-        unsigned int place[N], in_bucket[N];
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int q = 0; q < W4; ++q) {
+                flat[u][4 * q + 0] = rec[u][q].x;
+                flat[u][4 * q + 1] = rec[u][q].y;
+                flat[u][4 * q + 2] = rec[u][q].z;
+                flat[u][4 * q + 3] = rec[u][q].w;
+            }
+#pragma unroll
+            for (int n = 0; n < N; ++n) c[u][n] = *reinterpret_cast<const float4*>(g.S[n] + (uint64_t)flat[u][n] * (uint32_t)g.Rs + col);
+        }
+    };
+    if (first < end) {
+        load(first);
+        gather();
+    }
+    __syncthreads();
+    for (long long s0 = first; s0 < end; s0 += S) {
+        const int here = (int)min((long long)S, end - s0);   // samples of this round
+        auto act = [&](int u) { return u * turn + who < here; };
+        // the entries' places in their buckets while the rows are on their way
+        unsigned int place[U][N], where[U][N];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             // row / rows_per_bucket: rows stay below 2^24, where the float quotient is off by one at most
-            const unsigned int row = flat[n];
+            const unsigned int row = flat[u][n];
             unsigned int b = (unsigned int)((float)row * g.inv_rows_per_bucket[n]);
             unsigned int rest = row - b * g.rows_per_bucket[n];
             if ((int)rest < 0) { b -= 1u; rest += g.rows_per_bucket[n]; }
             if (rest >= g.rows_per_bucket[n]) { b += 1u; rest -= g.rows_per_bucket[n]; }
-            in_bucket[n] = rest;
+            b += g.bucket0[n];
+            where[u][n] = b << 16 | rest;
             unsigned int p = 0u;
-            if (act && sub == 0) p = atomicAdd(cursor + g.bucket0[n] + b, 1u);
+            if (act(u) && sub == 0) p = atomicAdd(count + b, 1u);
             if constexpr (G == 2) p = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)p, 0xA0, 0xf, 0xf, true);   // lanes 0, 0, 2, 2 of a quad
-            place[n] = p < g.cap[n] ? g.place0[n] + b * g.cap[n] + p : 0xffffffffu;
+            place[u][n] = p;
         }
-        // the next turn's records
-        turn += 1;
-        if (turn == G) {
-            turn = 0;
-            group += stride;
-            if (group < groups) draw(group);
-        }
-        if (group < groups) load(turn);
-        const float x = __uint_as_float(flat[N]);
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = __uint_as_float(flat[u][N]);
+        load(s0 + S);   // the next round's records
         // leave-one-out products by a prefix and a suffix sweep
-        float4 w[N], run = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+        float4 w[U][N];
         auto times = [](float4 a, const float4& b) { return make_float4(a.x * b.x, a.y * b.y, a.z * b.z, a.w * b.w); };
 #pragma unroll
-        for (int n = 0; n < N; ++n) {
-            w[n] = run;
-            run = times(run, c[n]);
-        }
-        const float minus_e = group_sum<G>(column ? (run.x + run.y) + (run.z + run.w) : 0.0f) - x;
-        run = make_float4(minus_e, minus_e, minus_e, minus_e);
+        for (int u = 0; u < U; ++u) {
+            float4 run = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
 #pragma unroll
-        for (int n = N - 1; n >= 0; --n) {
-            w[n] = times(w[n], run);
-            run = times(run, c[n]);
-        }
-        bool full = false;
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const bool fits = act && place[n] != 0xffffffffu;
-            full = full || (act && !fits);
-            if (fits && column) *reinterpret_cast<float4*>(values + (size_t)place[n] * g.Rs + col) = w[n];
-            if (fits && sub == 0) id_lds[place[n]] = (unsigned short)in_bucket[n];
-        }
-        if (full) {   // rare: this row's share of the step goes through atomics
-#pragma unroll 1
             for (int n = 0; n < N; ++n) {
-                if (place[n] != 0xffffffffu) continue;
-                if (sub == 0) atomicAdd(g.overflow, 1u);
-                float4 v = w[0];
-                uint32_t row = flat[0];
+                w[u][n] = run;
+                run = times(run, c[u][n]);
+            }
+            const float minus_e = group_sum<G>(column ? (run.x + run.y) + (run.z + run.w) : 0.0f) - x[u];
+            run = make_float4(minus_e, minus_e, minus_e, minus_e);
 #pragma unroll
-                for (int m = 1; m < N; ++m)
-                    if (m == n) {
-                        v = w[m];
-                        row = flat[m];
-                    }
+            for (int n = N - 1; n >= 0; --n) {
+                w[u][n] = times(w[u][n], run);
+                run = times(run, c[u][n]);
+            }
+        }
+        lds_meet();   // all counted; the round before has left
+        // a wave per mode: where its buckets' entries start in the round (a mode has `here` of them)
+        for (int n = wave; n < N; n += waves) {
+            const unsigned int last = n + 1 < N ? g.bucket0[n + 1 < N ? n + 1 : n] : (unsigned int)g.n_buckets;
+            unsigned int before = (unsigned int)(n * S);
+            for (unsigned int b = g.bucket0[n]; b < last; b += 64) {
+                const bool mine = b + lane < last;
+                const unsigned int cnt = mine ? count[b + lane] : 0u;
+                unsigned int sum = cnt;
+#pragma unroll
+                for (int d = 1; d < 64; d *= 2) {
+                    const unsigned int up = (unsigned int)__shfl_up((int)sum, d);
+                    sum += lane >= d ? up : 0u;
+                }
+                if (mine) {
+                    const unsigned int f = filled[b + lane], at = before + sum - cnt;
+                    base[b + lane] = at;
+                    start[b + lane] = f - at;
+                    filled[b + lane] = f + cnt;
+                    count[b + lane] = 0u;
+                }
+                before += (unsigned int)__builtin_amdgcn_readlane((int)sum, 63);
+            }
+        }
+        lds_meet();
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (act(u)) {
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    const unsigned int at = base[where[u][n] >> 16] + place[u][n];
+                    staged[at * G + sub] = w[u][n];
+                    if (sub == 0) tag[at] = where[u][n];
+                }
+            }
+        gather();   // the next round's rows
+        lds_meet();
+        // out: a thread takes the staged entries `who`, `who` + turn ... of every mode
+        unsigned int full = 0u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!act(u)) continue;
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const unsigned int at = (unsigned int)(n * S + u * turn + who), t = tag[at], p = start[t >> 16] + at;
+                if (p < g.cap[n]) {
+                    const size_t to = g.place0[n] + ((t >> 16) - g.bucket0[n]) * g.cap[n] + p;
+                    if (column) *reinterpret_cast<float4*>(values + to * g.Rs + col) = staged[at * G + sub];
+                    if (sub == 0) ids[to] = (unsigned short)t;
+                } else {
+                    full |= 1u << (u * N + n);
+                }
+            }
+        }
+        if (full != 0u) {   // rare: no room in the list, this row's share of the step goes through atomics
+#pragma unroll 1
+            for (int un = 0; un < U * N; ++un) {
+                if (!(full >> un & 1u)) continue;
+                const int n = un % N;
+                const unsigned int at = (unsigned int)(n * S + un / N * turn + who), t = tag[at];
+                const long long row = (long long)((t >> 16) - g.bucket0[n]) * g.rows_per_bucket[n] + (t & 0xffffu);
+                if (sub == 0) atomicAdd(g.overflow, 1u);
+                const float4 v = staged[at * G + sub];
                 const float vr[4] = {v.x, v.y, v.z, v.w};
-                const float* a = g.A + g.A_off[n] + (long long)row * g.J[n];
-                float* d = g.dA + g.A_off[n] + (long long)row * g.J[n];
+                const float* a = g.A + g.A_off[n] + row * g.J[n];
+                float* d = g.dA + g.A_off[n] + row * g.J[n];
                 for (int j = 0; j < g.J[n]; ++j) {
                     float sum = sub == 0 ? g.lambda_A * a[j] : 0.0f;
                     for (int i = 0; i < 4; ++i)
@@ -181,14 +256,11 @@ __global__ void __launch_bounds__(kAppendThreads) append_lists_kernel(AppendArgs
         }
     }
     __syncthreads();
-    unsigned short* ids = g.ids + (size_t)blockIdx.x * g.places;
-    for (unsigned int q = tid; q < g.places / 2; q += kAppendThreads)   // (places is even)
-        reinterpret_cast<unsigned int*>(ids)[q] = reinterpret_cast<const unsigned int*>(id_lds)[q];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        const unsigned int end = n + 1 < N ? g.bucket0[n + 1 < N ? n + 1 : n] : (unsigned int)g.n_buckets;
-        for (unsigned int b = g.bucket0[n] + tid; b < end; b += kAppendThreads)
-            g.fill[(size_t)b * gridDim.x + blockIdx.x] = min(cursor[b], g.cap[n]);
+        const unsigned int last = n + 1 < N ? g.bucket0[n + 1 < N ? n + 1 : n] : (unsigned int)g.n_buckets;
+        for (unsigned int b = g.bucket0[n] + tid; b < last; b += threads)
+            g.fill[(size_t)b * gridDim.x + blockIdx.x] = min(filled[b], g.cap[n]);
     }
 }
 

@@ -1015,6 +1015,16 @@ def test_table_rows_of_the_callers_width(dims, zipf, J, R):
             A, B = gA, gB
 
 
+@pytest.mark.parametrize("dims,J,R,M", [
+    ((13_000, 14_001), (4, 4), 4, 524_288),              # whole rounds of whole workgroups
+    ((13_000, 14_001), (8, 7), 8, 1_048_577 + 64 * 100),   # a round more in some of them, and one sample in it
+    ((5_200, 5_003, 5_400, 5_111, 5_222, 5_001, 5_100, 5_200, 5_003, 5_050), (4,) * 10, 4, 90_113),   # fewer workgroups than CUs
+])
+def test_rounds_of_the_appending_pass(dims, J, R, M):
+    """Row owners where the rounds that entries are put in order in are full, nearly empty, or one."""
+    test_step_by_row_owners(dims, J, R, M, False)
+
+
 def test_a_refused_kernel_name_changes_nothing():
     announce("refused kernel names")
     dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
