@@ -13,7 +13,7 @@
 // the row's number, with plain stores; a workgroup of the second owns a bucket, sums its lists in LDS and updates its rows.
 // A list that is full sends its row to the accumulator of the atomic kernels instead, which the owner folds in.
 //
-// Order 10, J = R = 4, 1e6 samples: 537 us per step with atomics, 211 us this way: 118 us for the appending pass and 85 us for
+// Order 10, J = R = 4, 1e6 samples: 537 us per step with atomics, 186 us this way: 118 us for the appending pass and 58 us for
 // the owners, which read 200 MB (40 us).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -281,10 +281,17 @@ struct OwnArgs {
     float lr_A, lambda_A;
 };
 
-// One workgroup per bucket.  LDS: D [rows][Rs] | h [rows] (as counters) | fill [lists]; core gradient sums [threads][Rs] in the
-// place of D at the end.  Entries are added by compare-and-swap on pairs of floats (the native LDS float add takes 3 clocks
-// per lane).
-template <int G>
+// One workgroup per bucket.  LDS: D [rows][Rs] | (a chunk's entries) | h [rows] (as counters) | (counts and places of the chunk
+// [2][rows]) | fill [lists]; core gradient sums [threads][Rs] in the place of D at the end.
+// How entries are added: where a bucket has many rows, by compare-and-swap on pairs of floats (the native LDS float add takes 3 clocks
+// per lane).  Where it has few (SORT), the lanes of a wave meet on them and repeat their swaps: there a chunk of entries is put in the order of
+// its rows in LDS, by an atomic that counts an entry's place in its row, and threads that own a row add its entries up in
+// registers.  Order 10, J = R = 4, 1e6 samples, 196 rows a bucket: 85 -> 58 us.  Whole steps by rows in a bucket, swaps -> order: 98 (order
+// 5, 1.5e5) 51.5 -> 48.7 us; 137 (order 7, R = 8, 1e6) 258 -> 238; 196 211 -> 186; 235 (order 4) 64.8 -> 65.4, R = 8 119 -> 122; 293 58.0 -> 61.1;
+// 469 (order 8, R = 8) 166 -> 197: hence the line.
+constexpr int kOwnSortRows = 200, kOwnSortPieces = 6;   // most rows of a bucket; pieces of 64 / G entries a wave brings to a chunk
+__host__ __device__ constexpr int own_sort_floats() { return kOwnSortPieces * kOwnThreads * 4; }
+template <int G, bool SORT>
 __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g);
 
 #ifndef FTK_TEMPLATE_KERNELS_ONLY
@@ -308,7 +315,7 @@ __device__ __forceinline__ void add_four(float* cell, const float4& x) {
     } while (again0 || again1);
 }
 
-template <int G>
+template <int G, bool SORT>
 __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
     extern __shared__ float own_lds[];
     constexpr int E = 64 / G, WAVES = kOwnThreads / 64;
@@ -320,10 +327,16 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
     const long long row0 = (long long)in_mode * g.rows_per_bucket[n];
     const int rows = (int)min((long long)g.rows_per_bucket[n], g.rows[n] - row0), Rs = g.Rs;
     float* D = own_lds;
-    unsigned int* hits = reinterpret_cast<unsigned int*>(own_lds + (size_t)g.rows_per_bucket[n] * Rs);
-    unsigned int* fill = hits + g.rows_per_bucket[n];
+    float4* staged = reinterpret_cast<float4*>(own_lds + (size_t)g.rows_per_bucket[n] * Rs);
+    unsigned int* hits = reinterpret_cast<unsigned int*>(own_lds + (size_t)g.rows_per_bucket[n] * Rs + (SORT ? own_sort_floats() : 0));
+    unsigned int* count = hits + g.rows_per_bucket[n];    // SORT: entries of the chunk per row
+    unsigned int* base = count + g.rows_per_bucket[n];    // SORT: the first of them
+    unsigned int* fill = SORT ? base + g.rows_per_bucket[n] : count;
     for (int q = tid; q < rows * Rs; q += kOwnThreads) D[q] = 0.0f;
-    for (int q = tid; q < rows; q += kOwnThreads) hits[q] = 0u;
+    for (int q = tid; q < rows; q += kOwnThreads) {
+        hits[q] = 0u;
+        if constexpr (SORT) count[q] = 0u;
+    }
     for (int q = tid; q < g.lists; q += kOwnThreads) fill[q] = g.fill[(size_t)b * g.lists + q];
     __syncthreads();
     const bool column = 4 * sub < Rs;
@@ -331,7 +344,7 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
     const size_t first = g.place0[n] + (size_t)in_mode * g.cap[n];
     // Work items: the pieces of E places of every list, dealt to the waves list by list; the next kAhead of them are on
     // their way while the last ones are added.
-    constexpr int kAhead = 4;
+    constexpr int kAhead = SORT ? kOwnSortPieces : 4;
     const int pieces = ((int)g.cap[n] + E - 1) / E, items = g.lists * pieces;
     const float per_list = 1.0f / (float)pieces;
     float4 x[kAhead];
@@ -349,21 +362,100 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
         }
     };
     ask(wave);
-    for (int item0 = wave; item0 < items; item0 += kAhead * WAVES) {
-        float4 y[kAhead];
-        unsigned int to[kAhead];
+    if constexpr (SORT) {
+        // `team` threads per row and column piece, next to each other: row tid / (team G)
+        int team = 1;
+        while (2 * team * G * rows <= kOwnThreads && 2 * team * G <= 64) team *= 2;
+        const int width = team * G, at_once = kOwnThreads / width, my_part = tid % width / G;
+        constexpr int kRowsOfThread = (kOwnSortRows * G + kOwnThreads - 1) / kOwnThreads;
+        float4 acc[kRowsOfThread];
+        unsigned int my_hits[kRowsOfThread];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            y[u] = x[u];
-            to[u] = row[u];
+        for (int v = 0; v < kRowsOfThread; ++v) {
+            acc[v] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            my_hits[v] = 0u;
         }
-        ask(item0 + kAhead * WAVES);
+        for (int chunk = 0; chunk < items; chunk += kAhead * WAVES) {   // the same number of chunks for every wave
+            float4 y[kAhead];
+            unsigned int to[kAhead], rank[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u)
-            if (to[u] != 0xffffffffu) {
-                if (column) add_four(D + (size_t)to[u] * Rs + col, y[u]);
-                if (sub == 0) atomicAdd(hits + to[u], 1u);
+            for (int u = 0; u < kAhead; ++u) {
+                y[u] = x[u];
+                to[u] = row[u];
+                unsigned int r = 0u;
+                if (to[u] != 0xffffffffu && sub == 0) r = atomicAdd(count + to[u], 1u);
+                if constexpr (G == 2) r = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)r, 0xA0, 0xf, 0xf, true);   // lanes 0, 0, 2, 2 of a quad
+                rank[u] = r;
             }
+            ask(chunk + kAhead * WAVES + wave);
+            lds_meet();   // all counted
+            if (wave == 0) {
+                unsigned int before = 0u;
+                for (int r0 = 0; r0 < rows; r0 += 64) {
+                    const bool mine = r0 + lane < rows;
+                    const unsigned int cnt = mine ? count[r0 + lane] : 0u;
+                    unsigned int sum = cnt;
+#pragma unroll
+                    for (int d = 1; d < 64; d *= 2) {
+                        const unsigned int up = (unsigned int)__shfl_up((int)sum, d);
+                        sum += lane >= d ? up : 0u;
+                    }
+                    if (mine) base[r0 + lane] = before + sum - cnt;
+                    before += (unsigned int)__builtin_amdgcn_readlane((int)sum, 63);
+                }
+            }
+            lds_meet();
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (to[u] != 0xffffffffu) staged[(base[to[u]] + rank[u]) * G + sub] = y[u];
+            lds_meet();
+#pragma unroll
+            for (int v = 0; v < kRowsOfThread; ++v) {
+                const int i = v * at_once + tid / width;
+                if (i < rows) {
+                    const unsigned int cnt = count[i], b0 = base[i];
+                    for (unsigned int k = my_part; k < cnt; k += team) {
+                        const float4 t = staged[(b0 + k) * G + sub];
+                        acc[v] = make_float4(acc[v].x + t.x, acc[v].y + t.y, acc[v].z + t.z, acc[v].w + t.w);
+                    }
+                    my_hits[v] += cnt;
+                    if (tid % width == 0) count[i] = 0u;   // (the threads of a row are one wave's: they have read it)
+                }
+            }
+            lds_meet();   // the next chunk may be counted and staged
+        }
+#pragma unroll
+        for (int v = 0; v < kRowsOfThread; ++v) {
+            for (int d = G; d < width; d *= 2) {
+                acc[v].x += __shfl_xor(acc[v].x, d);
+                acc[v].y += __shfl_xor(acc[v].y, d);
+                acc[v].z += __shfl_xor(acc[v].z, d);
+                acc[v].w += __shfl_xor(acc[v].w, d);
+            }
+            const int i = v * at_once + tid / width;
+            if (i < rows && my_part == 0) {
+                if (column) *reinterpret_cast<float4*>(D + (size_t)i * Rs + col) = acc[v];
+                if (sub == 0) hits[i] = my_hits[v];
+            }
+        }
+    } else {
+        ask(wave);
+        for (int item0 = wave; item0 < items; item0 += kAhead * WAVES) {
+            float4 y[kAhead];
+            unsigned int to[kAhead];
+    #pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                y[u] = x[u];
+                to[u] = row[u];
+            }
+            ask(item0 + kAhead * WAVES);
+    #pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (to[u] != 0xffffffffu) {
+                    if (column) add_four(D + (size_t)to[u] * Rs + col, y[u]);
+                    if (sub == 0) atomicAdd(hits + to[u], 1u);
+                }
+        }
     }
     __syncthreads();
     // rows: thread (group of rows, j) holds row j of B and its sums of the core gradient

@@ -1019,6 +1019,8 @@ def test_table_rows_of_the_callers_width(dims, zipf, J, R):
     ((13_000, 14_001), (4, 4), 4, 524_288),              # whole rounds of whole workgroups
     ((13_000, 14_001), (8, 7), 8, 1_048_577 + 64 * 100),   # a round more in some of them, and one sample in it
     ((5_200, 5_003, 5_400, 5_111, 5_222, 5_001, 5_100, 5_200, 5_003, 5_050), (4,) * 10, 4, 90_113),   # fewer workgroups than CUs
+    ((60_000, 61_003), (4, 3), 4, 524_289),                    # buckets of more than 200 rows: owners add by swaps
+    ((40_000, 41_000, 39_005), (8, 8, 5), 8, 520_001),
 ])
 def test_rounds_of_the_appending_pass(dims, J, R, M):
     """Row owners where the rounds that entries are put in order in are full, nearly empty, or one."""
