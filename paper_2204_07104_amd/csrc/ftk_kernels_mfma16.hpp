@@ -730,6 +730,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
 #pragma unroll
         for (int q = 0; q < W4; ++q) rec[q] = rec4[(size_t)p * W4 + q];
     };
+    unsigned int words[N];   // this lane's row words of the group parked last
     // Park a group (lane = sample): row words and values.
     constexpr int kQuads = 64 / kWidth;   // rows of an instruction of the scatter
     const int my_tile = lane / kTile, my_s = lane % kTile;
@@ -750,12 +751,13 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             // an empty slot: the row just past the mode's last one (reads as zeros), on no list
             const int row = act ? (int)flat[n] : (int)(g.row_bytes[n] >> 6);
             const unsigned int route = !act || row >= g.K[n] ? 0u : row >= g.top[n] ? 1u : 2u;
-            dst[n * 64 + lane] = (unsigned int)row * 64u + (route << kRouteShift);
+            words[n] = (unsigned int)row * 64u + (route << kRouteShift);
+            dst[n * 64 + lane] = words[n];
         }
         dst[N * 64 + lane] = act ? flat[N] : 0u;
     };
     // The two compacted lists of each tile, from the row words of a parked group.
-    auto make_lists = [&](const unsigned int* group, unsigned int* lists) {
+    auto make_lists = [&](const unsigned int (&words)[N], unsigned int* lists) {
         unsigned int* atomic_list = lists + my_tile * (kTile * N);
         unsigned int* table_list = atomic_list + mfma16_list_words(N);
         // every list position starts out unused: lane (tile, quarter q, j) clears positions [q][j], [q][j+4], ...
@@ -772,7 +774,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         int n_atomic = 0, n_table = 0;   // entries of my tile's lists so far
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            const unsigned int word = group[n * 64 + lane], row = (word & kRowMask) >> 6;
+            const unsigned int word = words[n], row = (word & kRowMask) >> 6;
             const bool to_table = word >> kRouteShift == 1u, to_atomic = word < g.row_bytes[n];   // (an empty slot's word is row_bytes)
             const unsigned long long atomic_lanes = __builtin_amdgcn_ballot_w64(to_atomic);
             const unsigned long long table_lanes = __builtin_amdgcn_ballot_w64(to_table);
@@ -812,7 +814,7 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
         // ... then the rows of the first tiles
         park_record(0, rec0, sbuf);
         lds_wave_sync();
-        if constexpr (PACK == 1) make_lists(sbuf, sbuf + (N + 1) * 64);
+        if constexpr (PACK == 1) make_lists(words, sbuf + (N + 1) * 64);
 #pragma unroll
         for (int t = 0; t < P::kAhead; ++t) gather_rows<N, PACK>(rsrc_A, sbuf, t, c, g4, st.ring[t]);
 
@@ -823,12 +825,15 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
             unsigned int* scur = sbuf + parity * kGroupWords;
             unsigned int* snxt = sbuf + (parity ^ 1) * kGroupWords;
             park_record(t + 1, rec, snxt);
+            if constexpr (PACK == 1) make_lists(words, snxt + (N + 1) * 64);
             load_record(t + 2, rec);
             lds_wave_sync();
-            if constexpr (PACK == 1)
-                make_lists(snxt, snxt + (N + 1) * 64);
-            else
-                make_lists(scur, own_lists);
+            if constexpr (PACK == 2) {
+                unsigned int now[N];
+#pragma unroll
+                for (int n = 0; n < N; ++n) now[n] = scur[n * 64 + lane];
+                make_lists(now, own_lists);
+            }
             lds_wave_sync();
             process_group<N, MODE, PACK>(g, st, cell_base, cell_mask, top_key, scur, snxt, PACK == 1 ? scur + (N + 1) * 64 : own_lists, tbuf, c, g4,
                                          tiles_of(t));
