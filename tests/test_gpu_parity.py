@@ -1657,6 +1657,46 @@ def test_two_samples_side_by_side_in_place(N, J, R):
     assert_params_close(gB, B, "B")
 
 
+@pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
+@pytest.mark.parametrize("mode", [binding.FTK_SYNC, binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE])
+@pytest.mark.parametrize("what", ["value", "row", "prediction"])
+def test_what_is_not_finite_stays_with_its_sample(N, J, R, mode, what):
+    """One sample of sixty has a stored value of inf, a row with an inf in it, or rows whose product overflows, and no row is
+    shared by two samples: the rows of all others, those of the sample beside it in a product among them, are the oracle's."""
+    announce("not finite, one sample order=%d mode=%d %s" % (N, mode, what))
+    rng = np.random.default_rng(12)
+    nnz, M = 6_000, 60
+    dims = (nnz,) * N
+    idx = [rng.permutation(nnz).astype(np.int32) for _ in range(N)]
+    vals = rng.uniform(1.0, 5.0, nnz).astype(np.float32)
+    seed = next(s for s in range(1_000) if len(set(oracle.sample_positions(s, M, nnz).tolist())) == M)
+    pos = oracle.sample_positions(seed, M, nnz)
+    A, B = oracle.init_factors(3, dims, J, R)
+    rates = (5e-2, 1e-2, 1e-2, 1e-2)
+    for bad in (37, 3, 18):      # the first of a pair in the second tile, the first and the second of a pair in the first
+        a, b, x = [m.copy() for m in A], [m.copy() for m in B], vals.copy()
+        rows = [int(i[pos[bad]]) for i in idx]
+        if what == "value":
+            x[pos[bad]] = np.inf
+        elif what == "row":
+            a[-1][rows[-1], 0] = np.inf
+        else:
+            a[0][rows[0]], a[-1][rows[-1]] = 1e30, 1e30
+        with binding.FastTucker(dims, idx, x, J, R, 3) as ft:
+            assert ft.ftk_kernel_name() == "mfma16"
+            ft.ftk_set_mode(mode)
+            ft.ftk_set_factors(a, b)
+            ft.ftk_sample(seed, M)
+            ft.ftk_sgd_step(*rates)
+            gA, gB = ft.ftk_get_factors()
+        with np.errstate(all="ignore"):
+            (oracle.sgd_step_hogwild if mode == binding.FTK_HOGWILD_MODEWISE else oracle.sgd_step_sync)(dims, idx, x, a, b, pos, *rates)
+        others = [np.arange(nnz) != r for r in rows]
+        assert_params_close([g[o] for g, o in zip(gA, others)], [m[o] for m, o in zip(a, others)], "A")
+        assert any(not np.isfinite(g[r]).all() for g, r in zip(gA, rows))
+        assert not any(np.isfinite(m).any() for m in gB)
+
+
 # ------------------------------------------------------------------------------------------------
 # the training loop of the paper's experiments, end to end: decaying step sizes, held-out Gamma
 # ------------------------------------------------------------------------------------------------
