@@ -1638,6 +1638,25 @@ def test_two_samples_side_by_side(N, J, R, M, tiles):
 
 
 @pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
+@pytest.mark.parametrize("n_eval", [64, 4_099])
+def test_errors_of_a_set_small_against_the_factors(N, J, R, n_eval):
+    """Ranks up to 8 where projecting the rows first would not pay: evaluation through the products of the J = R = 16 kernel, whose
+    core factors have 8 columns here (bound: see test_errors_over_projected_rows)."""
+    announce("errors of a small set order=%d J=%r R=%d n=%d" % (N, J, R, n_eval))
+    w = synth.tiny_workload(N, (3_001, 701, 90, 211, 33)[:N], n_eval, J, R, 16, seed=5, values="normal")
+    assert n_eval * N < 24 * sum(w.dims)
+    idx, vals = synth.make_tensor(w)
+    rng = np.random.default_rng(N)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(w.dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) / np.sqrt(j)).astype(np.float32) for j in J]
+    with binding.FastTucker(w.dims, idx, vals, J, R, 1) as ft:
+        ft.ftk_set_factors(A, B)
+        got = (ft.ftk_rmse(), ft.ftk_mae())
+    assert got[0] == pytest.approx(oracle.rmse(w.dims, idx, vals, A, B), rel=5e-6)
+    assert got[1] == pytest.approx(oracle.errors(w.dims, idx, vals, A, B)[1], rel=5e-6)
+
+
+@pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
 def test_two_samples_side_by_side_in_place(N, J, R):
     """No row is shared by two samples: the mode-by-mode step is Algorithm 1's, and the fused in-place one the synchronous step."""
     test_modewise_in_place_step_equals_the_printed_order_when_no_row_is_shared("mfma16", N, J, R, 5e-2, 1e-2)
