@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             const int item = item0 + u * WAVES;
-            const int list = (int)(((float)item + 0.5f) * per_list);   // item / pieces: both stay far below 2^20
+            const int list = (int)(((float)item + 0.5f) * per_list);   // item / pieces: exact below 2^21 items, of which the plan leaves 2^18
             const int e = (item - list * pieces) * E + who;
             const bool there = item < items && e < (int)fill[list < g.lists ? list : 0];
             const size_t at = (size_t)list * g.places + first + e;

@@ -1027,6 +1027,46 @@ def test_rounds_of_the_appending_pass(dims, J, R, M):
     test_step_by_row_owners(dims, J, R, M, False)
 
 
+def test_row_owners_of_a_very_large_sample_set_are_refused():
+    """Lists of row owners take 36 GB at the most; beyond, the step needs no memory of its own."""
+    announce("very large sample sets and row owners")
+    dims, J, R, _ = OWNER_CASES[0]
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        for M, planned in ((400_000_000, False), (100_001, True), (20_000_000, True), (400_000_000, False), (100_001, True)):
+            ft.ftk_sample(1, M)
+            assert ft.ftk_get_row_owners()[0] == planned, M
+        assert 3 << 30 < ft.ftk_get_row_owners()[1] < 5 << 30
+
+
+@pytest.mark.parametrize("dims,J,R,M,lr", [OWNER_CASES[0][:3] + (20_000_001, 1.0), ((60_000, 61_003), (8, 7), 8, 60_000_001, 0.05)])
+def test_row_owners_over_a_large_sample_set(dims, J, R, M, lr):
+    """1.2e8 and 2e8 row updates, beside the step of the kernels that add with atomics (which the other tests hold to the oracle).
+    A row is hit n = M / dims[0] times with lr / n each, by 64 entries over and over, so that its sum grows to n |g| where their mean
+    gradient g is (order 2: 1 on the average, 5 for a few rows); each of n roundings on the way is 2^-24 of it at most, of either
+    sign: lr |g| sqrt(n) 2^-24 = 0.05 5 32 6e-8 = 5e-7 (order 10: |g| < 0.1, 1e-7 x 5), half the bound's 1e-6.  (No regulariser: nothing but
+    the samples moves the rows.)"""
+    announce("a large sample set and row owners order=%d" % len(dims))
+    idx, vals = evenly_hit_tensor(dims, 3, False)
+    rng = np.random.default_rng(2)
+    A = [rng.uniform(-1, 1, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(-1, 1, size=(j, R)) * np.sqrt(3.0 / j)).astype(np.float32) for j in J]
+    rates = (lr * dims[0] / M, 0.1, 0.0, 0.02)
+    steps = []
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        for kernel in ("auto", "tiled"):
+            ft.ftk_set_kernel(kernel)
+            ft.ftk_set_factors(A, B)
+            ft.ftk_sample(9, M)
+            assert ft.ftk_get_row_owners()[0] == (kernel == "auto")
+            ft.ftk_sgd_step(*rates)
+            steps.append(ft.ftk_get_factors())
+    (gA, gB), (tA, tB) = steps
+    assert_params_close(gA, tA, "A")
+    assert_params_close(gB, tB, "B")
+    assert max(float(np.abs(x - y).max()) for x, y in zip(gA, A)) > 1e-3
+
+
 def test_a_refused_kernel_name_changes_nothing():
     announce("refused kernel names")
     dims, J, R, M = (13_000, 14_001), (9, 3), 1, 460_001
