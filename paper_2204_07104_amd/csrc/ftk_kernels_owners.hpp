@@ -332,10 +332,11 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
     unsigned int* count = hits + g.rows_per_bucket[n];    // SORT: entries of the chunk per row
     unsigned int* base = count + g.rows_per_bucket[n];    // SORT: the first of them
     unsigned int* fill = SORT ? base + g.rows_per_bucket[n] : count;
-    for (int q = tid; q < rows * Rs; q += kOwnThreads) D[q] = 0.0f;
-    for (int q = tid; q < rows; q += kOwnThreads) {
-        hits[q] = 0u;
-        if constexpr (SORT) count[q] = 0u;
+    if constexpr (SORT) {   // (D and h are stored once all entries are in)
+        for (int q = tid; q < rows; q += kOwnThreads) count[q] = 0u;
+    } else {
+        for (int q = tid; q < rows * Rs; q += kOwnThreads) D[q] = 0.0f;
+        for (int q = tid; q < rows; q += kOwnThreads) hits[q] = 0u;
     }
     for (int q = tid; q < g.lists; q += kOwnThreads) fill[q] = g.fill[(size_t)b * g.lists + q];
     __syncthreads();
@@ -439,17 +440,16 @@ __global__ void __launch_bounds__(kOwnThreads) own_rows_kernel(OwnArgs g) {
             }
         }
     } else {
-        ask(wave);
         for (int item0 = wave; item0 < items; item0 += kAhead * WAVES) {
             float4 y[kAhead];
             unsigned int to[kAhead];
-    #pragma unroll
+#pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 y[u] = x[u];
                 to[u] = row[u];
             }
             ask(item0 + kAhead * WAVES);
-    #pragma unroll
+#pragma unroll
             for (int u = 0; u < kAhead; ++u)
                 if (to[u] != 0xffffffffu) {
                     if (column) add_four(D + (size_t)to[u] * Rs + col, y[u]);
