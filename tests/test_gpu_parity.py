@@ -988,6 +988,13 @@ def test_step_by_row_owners(dims, J, R, M, tiles):
     ((5_003, 640), (1.1, None), (8, 5), 6),                                    # of 8
     ((410, 301, 205, 97, 2_503), (None, None, None, 1.1, None), (2, 8, 7, 3, 8), 8),   # of 8, the form without values read ahead
     ((3_001, 701, 90), (None, 1.2, None), (9, 3, 1), 4),                        # of 16
+    # ranks R above 8: one sample at a time, with rows of 4 and of 8
+    ((5_003, 640), (1.1, None), (4, 3), 9),
+    ((3_001, 701, 90), (None, 1.2, None), (4, 4, 2), 16),
+    ((410, 301, 205, 97, 2_503), (None, None, None, 1.1, None), (2, 4, 4, 3, 1), 11),
+    ((5_003, 640), (1.1, None), (8, 5), 16),
+    ((3_001, 701, 90), (None, 1.2, None), (7, 8, 5), 9),
+    ((410, 301, 205, 97, 2_503), (None, None, None, 1.1, None), (2, 8, 7, 3, 8), 13),
 ])
 def test_table_rows_of_the_callers_width(dims, zipf, J, R):
     """The J = R = 16 kernel on padded ranks: its tables hold rows of 4, 8 or 16 floats.  Every parameter against the oracle's
@@ -1015,9 +1022,13 @@ def test_table_rows_of_the_callers_width(dims, zipf, J, R):
             A, B = gA, gB
 
 
+# A workgroup of the appending pass takes a share of Psi in groups of 64 samples, dealt evenly to 256 of them.  At order 2 a round
+# holds 3 840 samples for R <= 4 (15 waves of 64 threads, four samples each) and 2 048 above (16 waves, two threads a sample).
 @pytest.mark.parametrize("dims,J,R,M", [
-    ((13_000, 14_001), (4, 4), 4, 524_288),              # whole rounds of whole workgroups
-    ((13_000, 14_001), (8, 7), 8, 1_048_577 + 64 * 100),   # a round more in some of them, and one sample in it
+    ((13_000, 14_001), (4, 4), 4, 256 * 3_840),                  # one full round each
+    ((13_000, 14_001), (4, 4), 4, 256 * (3_840 + 64) - 63),      # a second round of 64 samples, in the last workgroup of one
+    ((13_000, 14_001), (8, 7), 8, 256 * (2 * 2_048 + 64) - 63),  # a third such round
+    ((13_000, 14_001), (4, 4), 4, 524_288),                      # one round, half full
     ((5_200, 5_003, 5_400, 5_111, 5_222, 5_001, 5_100, 5_200, 5_003, 5_050), (4,) * 10, 4, 90_113),   # fewer workgroups than CUs
     ((60_000, 61_003), (4, 3), 4, 524_289),                    # buckets of more than 200 rows: owners add by swaps
     ((40_000, 41_000, 39_005), (8, 8, 5), 8, 520_001),
@@ -1257,6 +1268,31 @@ def test_copying_threads_sleep_while_the_stream_is_busy():
             wall, used = time.perf_counter() - t0, processor_time() - c0
             assert wall > 0.05       # there was a queue
             assert used < 3.0 * wall, (used, wall)
+
+
+def test_factors_out_into_arrays_anywhere_in_memory():
+    """Factors taken out behind a queue of steps, when the pages of large arrays are made ahead: into arrays that start and end inside
+    a page, of which a part has been written before.  Every float arrives, and nothing beside them changes."""
+    import ctypes as C
+    announce("factors out into arrays anywhere")
+    w = synth.tiny_workload(3, (100_003, 70_001, 40_007), 200_000, (32, 31, 32), 32, 2_000_000)
+    idx, vals = synth.make_tensor(w)
+    with binding.FastTucker(w.dims, idx, vals, w.J, w.R) as ft:
+        A, B = ft.ftk_get_factors()
+        ft.ftk_sample(1, w.n_samples)
+        for first, written in ((1, 0.0), (1_023, 0.3), (517, 1.0)):      # floats into the memory; share of it written before
+            memory = [np.empty(a.size + 4_096, dtype=np.float32) for a in A]      # (4.9 MB and more: fresh pages)
+            for m, a in zip(memory, A):
+                m[first - 1], m[first + a.size] = 7.0, 9.0
+                m[first:first + int(written * a.size)] = -1.0
+            out = [m[first:first + a.size] for m, a in zip(memory, A)]
+            pointers = (C.c_void_p * 3)(*[o.ctypes.data for o in out])
+            for _ in range(50):
+                ft.ftk_sgd_step(0.0, 0.0, 0.0, 0.0)
+            ft._check(ft._L.ftk_get_factors(ft._ctx, C.cast(pointers, C.c_void_p), None))
+            for m, o, a in zip(memory, out, A):
+                assert np.array_equal(o.reshape(a.shape), a)
+                assert m[first - 1] == 7.0 and m[first + a.size] == 9.0
 
 
 def test_moving_no_factors_still_waits_for_the_stream():
@@ -1677,6 +1713,44 @@ def test_two_samples_side_by_side(N, J, R, M, tiles):
             assert max(float(np.abs(x - y).max()) for x, y in zip(want_B, B)) > 1e-3
 
 
+@pytest.mark.parametrize("rows,side_by_side", [(8_388_000, True), (8_388_600, False)])
+@pytest.mark.parametrize("mode", [binding.FTK_SYNC, binding.FTK_HOGWILD])
+def test_rows_at_the_line_of_two_samples_side_by_side(rows, side_by_side, mode):
+    """Packed rows of just under and just over 512 MB: above, the entries of the scatter's lists have no bits for two samples
+    side by side, and below they use all 32.  Every row is stored once, few are sampled, none twice: the synchronous step is the
+    oracle's, in place too."""
+    announce("rows at the line of two samples side by side, %d rows, mode %d" % (rows, mode))
+    dims, J, R, M = (100, rows), (3, 2), 5, 3_000
+    assert side_by_side == (64 * (sum(dims) + 10) < (1 << 29) - (1 << 14))
+    rng = np.random.default_rng(5)
+    idx = [rng.integers(0, 100, rows).astype(np.int32), rng.permutation(rows).astype(np.int32)]
+    vals = rng.standard_normal(rows).astype(np.float32)
+    pos = oracle.sample_positions(4, M, rows)
+    rates = (1e-4, 0.1, 0.05, 0.02)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "mfma16"
+        A, B = ft.ftk_get_factors()
+        B = [2.0 * b for b in B]
+        ft.ftk_set_factors(None, B)
+        ft.ftk_set_mode(mode)
+        ft.ftk_sample(4, M)
+        ft.ftk_sgd_step(*rates)
+        gA, gB = ft.ftk_get_factors()
+    start = [a.copy() for a in A]
+    oracle.sgd_step_sync(dims, idx, vals, A, B, pos, *rates)
+    hit = np.unique(idx[1][pos])
+    assert len(hit) > M - 10 and hit.max() > rows - 100_000
+    moved = np.any(gA[1] != start[1], axis=1)
+    assert np.array_equal(np.flatnonzero(moved), hit)      # those rows and no others
+    if mode == binding.FTK_SYNC:
+        assert_params_close(gA, A, "A")
+        assert_params_close(gB, B, "B")
+    once = hit[np.bincount(np.searchsorted(hit, idx[1][pos])) == 1]
+    step, want = gA[1][once] - start[1][once], A[1][once] - start[1][once]
+    # (float32 rows near 1: a step of 1e-4 is known to 2^-24 / 1e-4; in place, the rows of mode 0 have moved by 30 steps meanwhile)
+    assert np.linalg.norm(step - want) < (2e-3 if mode == binding.FTK_SYNC else 2e-2) * np.linalg.norm(want)
+
+
 @pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
 @pytest.mark.parametrize("n_eval", [64, 4_099])
 def test_errors_of_a_set_small_against_the_factors(N, J, R, n_eval):
@@ -1714,6 +1788,49 @@ def test_two_samples_side_by_side_in_place(N, J, R):
     oracle.sgd_step_sync((nnz,) * N, idx, vals, A, B, oracle.sample_positions(seed, M, nnz), 5e-2, 1e-2, 1e-2, 1e-2)
     assert_params_close(gA, A, "A")
     assert_params_close(gB, B, "B")
+
+
+@pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
+@pytest.mark.parametrize("mode", [binding.FTK_HOGWILD, binding.FTK_HOGWILD_MODEWISE])
+@pytest.mark.parametrize("tiles", [False, True])
+def test_two_samples_side_by_side_in_place_on_shared_rows(N, J, R, mode, tiles):
+    """300 001 samples (turns in pairs) whose rows take each of the three ways out, in place: sixteen rows of a mode have half
+    of its hits.  The step is so small that a row moves by less than three hundredths on the way, so every row's step is the synchronous
+    one within a few hundredths, where a lost half or quarter of its gradients would show; rounding (an atomic add to a row near 1 loses up to
+    2^-25) is allowed for beside it."""
+    announce("two samples side by side in place, shared rows, order=%d mode=%d tiles=%d" % (N, mode, tiles))
+    dims, nnz, M = (6_007, 701, 397, 211, 333)[:N], 200_003, 300_001
+    rng = np.random.default_rng(20 + N)
+    idx = [np.where(rng.random(nnz) < (0.0 if n == 0 else 0.5), rng.integers(0, 16, nnz) * (d // 16), rng.integers(0, d, nnz)).astype(np.int32)
+           for n, d in enumerate(dims)]
+    A = [rng.uniform(0.5, 1.0, size=(d, j)).astype(np.float32) for d, j in zip(dims, J)]
+    B = [(rng.uniform(0.5, 1.0, size=(j, R)) / j).astype(np.float32) for j in J]
+    x = sum(np.prod([A[n][idx[n]] @ B[n] for n in range(N)], axis=0).T)
+    vals = (x + rng.uniform(0.5, 1.5, nnz)).astype(np.float32)      # residuals of one sign: no row's gradients cancel
+    pos = (oracle.sample_positions_tiles if tiles else oracle.sample_positions)(7, M, nnz)
+    want_A, want_B = [a.copy() for a in A], [b.copy() for b in B]
+    most = max(int(np.bincount(i[pos]).max()) for i in idx)
+    rates = (2e-2 / most, 1e-3, 0.0, 0.0)
+    oracle.sgd_step_sync(dims, idx, vals, want_A, want_B, pos, *rates)
+    with binding.FastTucker(dims, idx, vals, J, R, 1) as ft:
+        assert ft.ftk_kernel_name() == "mfma16"
+        if tiles:
+            ft.ftk_set_sampling(binding.FTK_SAMPLE_TILES)
+        ft.ftk_set_mode(mode)
+        ft.ftk_set_factors(A, B)
+        ft.ftk_sample(7, M)
+        K, top = ft.ftk_get_table_rows()
+        assert max(top) == 16 and sum(K) > 64 and K[0] < dims[0]
+        ft.ftk_sgd_step(*rates)
+        gA, gB = ft.ftk_get_factors()
+    for n in range(N):
+        hits = np.bincount(idx[n][pos], minlength=dims[n])
+        step, want = (m[n].astype(np.float64) - A[n] for m in (gA, want_A))
+        assert np.linalg.norm(want[hits > 0], axis=1).min() > 0
+        off = np.linalg.norm(step - want, axis=1) - 0.05 * np.linalg.norm(want, axis=1) - 2.0 ** -25 * np.sqrt(J[n] * (1.0 + hits)) * 4
+        assert off.max() < 0, (n, off.max(), int(off.argmax()), int(hits[off.argmax()]))
+        step, want = (m[n].astype(np.float64) - B[n] for m in (gB, want_B))
+        assert np.linalg.norm(step - want) < 0.05 * np.linalg.norm(want)
 
 
 @pytest.mark.parametrize("N,J,R", SIDE_BY_SIDE)
