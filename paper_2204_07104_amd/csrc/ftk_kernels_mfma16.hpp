@@ -276,8 +276,10 @@ constexpr int kSyncPass = 0, kInPlacePass = 1, kFactorPhase = 2, kCorePhase = 3;
 // NaN.  So where a tile's gradients are not all finite they are worked out once more by this function, every product in two
 // passes over one sample of each pair, with the other's numbers replaced by zeros: a row, projection or prediction that is not
 // finite reaches the rows of its own sample only, as with one sample at a time.  (The core factors are lost either way: a
-// prediction that is not finite takes all of a core gradient with it.)  The look at a tile's gradients costs a step 0.6 to 0.9 %
-// (order 3, J = R = 8, 1e6 samples 83.8 -> 84.3 us, order 2 59.9 -> 60.4, order 5, J = R = 4, 75.4 -> 76.0).
+// prediction that is not finite takes all of a core gradient with it.)  The look at a tile's gradients costs a step 0 to 1 %
+// (order 3, J = R = 8, 1e6 samples 84.3 -> 84.4 us, 3e5 over 6 000 rows 37.1 -> 37.5, 1e4 12.7 and 12.7, order 2 60.0 -> 60.4, order 5, J = R = 4,
+// 76.1 -> 76.0).  This function is kept out of the way of the tile's other instructions, which with it among them took 0.35 us longer for
+// the first tile of a launch (1e4 samples 13.1).
 // The rows are read from the registers `aY`; the gradients are left in `grad` and, in the factor phase, staged as well.
 template <int N, int MODE>
 __device__ __forceinline__ void gradients_apart(const Mfma16Args& g, const WaveState<N, 2>& st, float x, float ones, const float (&aY)[N][4],
@@ -361,8 +363,8 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
     for (int sub = 0; sub < P::kTiles; ++sub) {
         // (wave-uniform) only the last group of a wave's share holds fewer than all tiles (n_tiles >= 1)
         if (sub > 0 && sub >= n_tiles) break;
-        // The tile's scatter lists were written when the group was parked: their first batches and
-        // lengths are asked for now, long before they are used.
+        // The tile's scatter lists were written when the group was parked (two samples side by side: when its turn came): their
+        // first batches and lengths are asked for now, long before they are used.
         // (Up to order 3, where the registers allow it; above, everything is read where it is used.)
         constexpr bool AHEAD = N <= 3;
         const unsigned int* alist = atomic_list + sub * (kTile * N) + q8 * (4 * N);
@@ -515,14 +517,14 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
         }
         }   // MODE != kFactorPhase
         if constexpr (PACK == 2) {
-            float most = 0.0f;   // (NaN if any of them is)
+            float most = 0.0f;   // (NaN if any of them is; the branch is marked unlikely for the order of the code)
 #pragma unroll
             for (int n = 0; n < N; ++n)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) most = __builtin_elementwise_maximum(most, fabsf(grad[n][v]));
-            if (__builtin_amdgcn_ballot_w64(!(most < __builtin_inff())) != 0) gradients_apart<N, MODE>(g, st, x, ones, aY, tbuf, c, g4, grad);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(most < __builtin_inff())) != 0, 0)) gradients_apart<N, MODE>(g, st, x, ones, aY, tbuf, c, g4, grad);
         }
-        // Where each row goes was decided when the group was parked:
+        // Where each row goes was decided when the group was parked (its row words say so):
         //   the 16 most frequent rows of a mode: summed over the tile by the matrix core against a
         //     one-hot operand, straight from the registers
         //   every other row: staged in the wave's LDS buffer (the -e w reads above are done), then
@@ -967,7 +969,8 @@ __global__ void __launch_bounds__(kMfmaThreads) grad_mfma16_kernel(Mfma16Args g)
 // clocks, which is 38 us of it on 1024 SIMDs, and vector instructions do not run beside them.  Small sets gain by what it does not
 // set up, store and clear: whole steps of 100 / 1e4 / 1e5 samples, order 3, 24.3 / 29.4 / 45.4 us as a pass of grad_mfma16_kernel,
 // 21.4 / 26.1 / 41.9 (order 1 15.9 / 20.6 / 28.0 and 15.4 / 20.0 / 27.5, order 6 37.4 / 43.9 / 81.9 and 31.8 / 37.7 / 76.6), the sums of
-// the waves at its end, which meet on the same words of LDS, among them.
+// the waves at its end, which then met on the same words of LDS, among them (they are stored side by side and added in order now:
+// see store_sums).
 // ---------------------------------------------------------------------------------------------
 __host__ __device__ constexpr int core_phase_waves(int order) { return order <= 3 ? 16 : order == 4 ? 12 : 8; }
 __host__ __device__ constexpr int core_phase_wave_words(int order) {
