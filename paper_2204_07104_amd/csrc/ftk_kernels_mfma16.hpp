@@ -273,13 +273,13 @@ __device__ __forceinline__ void gather_rows(const __amdgpu_buffer_rsrc_t (&rsrc_
 constexpr int kSyncPass = 0, kInPlacePass = 1, kFactorPhase = 2, kCorePhase = 3;
 
 // Two samples side by side: the zeros off the diagonal of an operand meet the other sample's numbers, and 0 x inf and 0 x NaN are
-// NaN.  So where a tile's gradients are not all finite they are worked out once more by this function, every product in two
+// NaN.  So where a tile's -e w are not all finite its gradients are worked out once more by this function, every product in two
 // passes over one sample of each pair, with the other's numbers replaced by zeros: a row, projection or prediction that is not
-// finite reaches the rows of its own sample only, as with one sample at a time.  (The core factors are lost either way: a
-// prediction that is not finite takes all of a core gradient with it.)  The look at a tile's gradients costs a step 0 to 1 %
-// (order 3, J = R = 8, 1e6 samples 84.3 -> 84.4 us, 3e5 over 6 000 rows 37.1 -> 37.5, 1e4 12.7 and 12.7, order 2 60.0 -> 60.4, order 5, J = R = 4,
-// 76.1 -> 76.0).  This function is kept out of the way of the tile's other instructions, which with it among them took 0.35 us longer for
-// the first tile of a launch (1e4 samples 13.1).
+// finite reaches the rows of its own sample only, as with one sample at a time.  (Each of the three shows in -e w: it makes the
+// prediction's sum, and with it e, not finite.  The core factors are lost either way, as e takes all of a core gradient with it.)
+// The look at -e w costs a step 0 to 1 %: order 3, J = R = 8, 1e6 samples 84.0 -> 84.5 us, 3e5 over 6 000 rows 37.2 -> 37.6, 1e4 12.6 ->
+// 12.7, order 2 59.8 -> 60.2, order 5, J = R = 4, 75.9 -> 75.2.  This function is kept out of the way of the tile's other instructions:
+// among them the first tile of a launch took 0.35 us longer.
 // The rows are read from the registers `aY`; the gradients are left in `grad` and, in the factor phase, staged as well.
 template <int N, int MODE>
 __device__ __forceinline__ void gradients_apart(const Mfma16Args& g, const WaveState<N, 2>& st, float x, float ones, const float (&aY)[N][4],
@@ -414,6 +414,12 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
         const float ones = PACK == 1 || c / P::kWidth == g4 * 4 / P::kWidth ? 1.0f : 0.0f;
 
         float aY[N][4], wY[N][4], grad[N][4];
+        // two samples side by side: the largest |-e w| here, NaN if one is (where all are finite, so is what the samples share)
+        float most = 0.0f;
+        auto look = [&](const floatx4& w) {
+            const float a = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(w[0]), fabsf(w[1])), fabsf(w[2]));
+            most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(most, a), fabsf(w[3]));
+        };
         if constexpr (MODE == kFactorPhase) {
             // rows in layout Y (for the regulariser term), out of the buffer before the gradients go into it
             lds_wave_sync();
@@ -433,6 +439,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
                 const float part_n = (full[0] + full[1]) + (full[2] + full[3]);
                 const floatx4 xsum_n = __builtin_amdgcn_mfma_f32_16x16x4f32(ones, part_n, floatx4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
                 wn *= xsum_n[0] - x;   // -e w^(n)
+                if constexpr (PACK == 2) look(wn);
                 floatx4 gsn = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int k = 0; k < 4; ++k) gsn = __builtin_amdgcn_mfma_f32_16x16x4f32(wn[k], st.Br[n][k], gsn, 0, 0, 0);
@@ -486,6 +493,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             w[n] *= neg_e;
+            if constexpr (PACK == 2) look(w[n]);
             *reinterpret_cast<float4*>(tbuf + n * kTransposeFloats + c * 20 + 4 * g4) =
                 make_float4(w[n][0], w[n][1], w[n][2], w[n][3]);
         }
@@ -517,11 +525,7 @@ __device__ __forceinline__ void process_group(const Mfma16Args& g, WaveState<N, 
         }
         }   // MODE != kFactorPhase
         if constexpr (PACK == 2) {
-            float most = 0.0f;   // (NaN if any of them is; the branch is marked unlikely for the order of the code)
-#pragma unroll
-            for (int n = 0; n < N; ++n)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) most = __builtin_elementwise_maximum(most, fabsf(grad[n][v]));
+            // (marked unlikely for the order of the code)
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(most < __builtin_inff())) != 0, 0)) gradients_apart<N, MODE>(g, st, x, ones, aY, tbuf, c, g4, grad);
         }
         // Where each row goes was decided when the group was parked (its row words say so):
