@@ -64,11 +64,14 @@ __device__ __forceinline__ void lds_meet() {
 // Words of LDS: [4][n_buckets] counts of the round, filled places, place of a bucket in the round, the same against its list |
 // for every thread and mode the staged entry (four floats) and, per sample and mode, the entry's bucket and row.
 __host__ __device__ inline int append_bucket_words(int n_buckets) { return 4 * ((n_buckets + 3) / 4 * 4); }
-// samples a thread takes in a round: at low orders a round of one each holds too few entries of a bucket to leave side by side
-// (order 2, R = 8, 2e6 samples: 224 us per step with one, 180 with four; order 3, 1e6: 153 with one, 157 with three)
+// Samples a thread takes in a round: at low orders a round of one each holds too few entries of a bucket to leave side by side.
+// Whole steps with one -> four, order 2, R = 8, 2e6 samples 224 -> 180 us; with one -> two, 1e6 samples: order 3, 60 000 rows a mode R = 4
+// 109 -> 98, R = 8 153 -> 134 (180 000 rows 134 -> 123, 183 -> 167); order 4, 40 000 rows 133 -> 123, 174 -> 172, 10 000 rows 115 -> 107, but R = 8
+// 155 -> 160; 3e5 samples the same either way.  (Order 3 with three: R = 8 157.)
 __host__ __device__ constexpr int append_samples(int order) { return order <= 2 ? 4 : order <= 4 ? 2 : 1; }
 __host__ __device__ constexpr int append_wave_words(int order, int G) { return append_samples(order) * order * (64 * 4 + 64 / G); }
-// from order 8 on a wave needs more than the 128 registers that 16 waves leave it, and LDS has no room for more than 14
+// from order 8 on a wave needs more than the 128 registers that 16 waves leave it: 161 at order 8, R <= 8, 157 and 168 (16 more spilled) at
+// order 10, where 12 waves leave 168.  (Order 8, R <= 4 gets by with 127.)
 __host__ __device__ constexpr int append_max_waves(int order) { return order < 8 ? kAppendThreads / 64 : 12; }
 
 // A workgroup takes one share of Psi in rounds of append_samples(N) samples per G threads (four columns each).  The entries of a round are put in
@@ -286,9 +289,14 @@ struct OwnArgs {
 // How entries are added: where a bucket has many rows, by compare-and-swap on pairs of floats (the native LDS float add takes 3 clocks
 // per lane).  Where it has few (SORT), the lanes of a wave meet on them and repeat their swaps: there a chunk of entries is put in the order of
 // its rows in LDS, by an atomic that counts an entry's place in its row, and threads that own a row add its entries up in
-// registers.  Order 10, J = R = 4, 1e6 samples, 196 rows a bucket: 85 -> 58 us.  Whole steps by rows in a bucket, swaps -> order: 98 (order
-// 5, 1.5e5) 51.5 -> 48.7 us; 137 (order 7, R = 8, 1e6) 258 -> 238; 196 211 -> 186; 235 (order 4) 64.8 -> 65.4, R = 8 119 -> 122; 293 58.0 -> 61.1;
-// 469 (order 8, R = 8) 166 -> 197: hence the line.
+// registers.  Order 10, J = R = 4, 1e6 samples, 196 rows a bucket: 85 -> 58 us.  Whole steps with 100 / 150 / 200 / 235 / 300 / 400 rows in a bucket:
+//   order 5, R = 4, 5e5      swaps 85 / 83 / 83 / 83 / 83 / 84        order 72 / 75 / 79 / 79 / 82 / 88
+//   order 4, R = 4, 1e6            126 / 123 / 122 / 122 / 122 / 125        107 / 112 / 116 / 118 / 123 / 133
+//   order 10, R = 4, 5e5           132 / 128 / 128 / 127 / 129 / 129        110 / 115 / 120 / 119 / 126 / 136
+//   order 7, R = 8, 5e5            137 / 136 / 135 / 136 / 137 / 143        123 / 131 / 133 / 134 / 142 / 154
+//   order 3, R = 8, 1e6            126 / 127 / 127 / 128 / 131 / 136        115 / 122 / 127 / 128 / 137 / 150
+//   order 4, R = 8, 1e6            162 / 164 / 168 / 170 / 172 / 179        156 / 167 / 175 / 177 / 187 / 203
+// The two meet at 300 rows for R <= 4 and between 120 and 250 for R <= 8; the line lies at 200 for both.
 constexpr int kOwnSortRows = 200, kOwnSortPieces = 6;   // most rows of a bucket; pieces of 64 / G entries a wave brings to a chunk
 __host__ __device__ constexpr int own_sort_floats() { return kOwnSortPieces * kOwnThreads * 4; }
 template <int G, bool SORT>

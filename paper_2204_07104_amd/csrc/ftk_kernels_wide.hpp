@@ -14,7 +14,8 @@
 // blocks of their parts, for two tiles: 147 KB at order 3, which is what limits it to one workgroup per CU and to order 3.
 // A contraction over a tile's samples fills the instruction's 32 slots, so no part is taken twice.
 //
-// What bounds it, J = R = 64, 1e6 samples (706 us a launch, where the general kernel takes 765): products (3 900 clocks of a
+// What bounds it, J = R = 64, 1e6 samples (649 us a launch with 40 + 47 table rows, modes by power laws; with 16 + 16, as for the
+// variants that follow, 706, where the general kernel took 765): products (3 900 clocks of a
 // SIMD per tile), vector instructions (3 600) and LDS (4 600 of the CU) that come one after the other more than side by side,
 // because a SIMD has one wave of each team and the teams meet three times a tile.  Without atomics 666 us, without rows
 // from memory either 568.  Core gradients dealt to both teams: 708 us.  Rows asked for two tiles ahead, and all core gradients with
@@ -139,7 +140,7 @@ __global__ void __launch_bounds__(kWideThreads) grad_wide_kernel(TiledArgs g) {
             }
     };
     // LDS reads stay in front of the products of the step before theirs: all waves come from a barrier, and would else read
-    // together and multiply together (706 us against 718)
+    // together and multiply together (with 16 + 16 table rows 706 us against 718)
     auto hold_reads = [&]() { __builtin_amdgcn_sched_barrier(0x6); };
 
     if (wave < 4) {
